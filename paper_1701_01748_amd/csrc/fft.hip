@@ -1,217 +1,436 @@
 // Oversampled 2D FFT of the measurement operator (Sec. 2: F Z and
-// Z^H F^H), complex float32, entirely in LDS.
+// Z^H F^H), complex float32, one row or column per group of threads with the
+// sequence in registers.
 //
-// Forward: each image row is deapodised and zero-padded into its wrapped
-// position of a length-Kx sequence and transformed (rows that are all zero
-// in the 2x oversampled grid are never touched), then every grid column is
-// transformed from its ny non-zero entries.  Adjoint: full column inverse
-// transforms keep only the ny rows the image needs, then row inverse
-// transforms keep the nx wanted entries, undo the deapodisation and keep the
-// real part -- optionally fused with the primal update of Algorithm 3.
+// The image is real, so its spectrum is Hermitian and only the grid columns
+// c = 0 .. Kx/2 are transformed (half the transforms and half the bytes of a
+// complex transform).  Forward: two image rows, deapodised and zero-padded
+// into their wrapped position, are the real and imaginary part of one
+// sequence of length Kx; the two spectra are separated and the columns
+// c < Kx/2 stored.  Columns 0 and Kx/2 of a real row are real, so they share
+// one stored column (real part: column 0, imaginary part: column Kx/2).
+// Every stored column is then transformed from its ny non-zero entries; the
+// grid keeps 8 more columns on either side (see GRID_PAD), copies of their
+// mirror images.  Adjoint: the mirrored columns are added back as the columns
+// are loaded, full inverse column transforms keep the ny rows the image
+// needs, then two rows at a time are transformed back, the deapodisation
+// undone and the real part kept -- in iterations fused with the primal update
+// of Algorithm 3 and the next forward row pass.
 //
-// In-LDS transform: iterative decimation in time on bit-reversed input,
-// two radix-2 stages per LDS round trip (a radix-4 butterfly), one leading
-// radix-2 stage when log2 L is odd.  LDS index i is padded by i/32 (+1 per
-// sequence) against bank conflicts.  Twiddles exp(-2 pi i k / L), k < L/2,
-// are computed in float64 on the host and staged in LDS.
+// A transform of length L runs on P = L / E threads with E elements each:
+// thread t holds elements t + P n.  A DFT over n in registers, twiddles, an
+// exchange through LDS, and more such stages leave thread t with outputs
+// t + P m: the input's distribution, so global accesses of consecutive threads
+// are consecutive on both sides and an inverse transform is followed by a
+// forward one without another exchange.  The padding half of an input or
+// output is never computed: it is a fixed set of a thread's elements.
+// Twiddles are computed in float64 on the host, in the order the threads read
+// them (fft_twiddles).
+//
+// What bounds the passes is the latency of their load - exchange - store chain
+// at small sizes and HBM, beside the SARA launches, at large ones.  Measured in
+// the iteration against the earlier radix-2 pairs in LDS over the full complex
+// grid (rocprofv3, median us per launch; rows: inverse, primal update and
+// forward): 64^2 columns 4.7 -> 3.6 and 5.4 -> 3.0, rows 6.9 -> 4.2; 512^2
+// columns 9.0 -> 4.8 and 8.7 -> 4.8, rows 9.8 -> 6.8; 2048^2 columns
+// 343 -> 151 and 160 -> 103, rows 92 -> 40.
 #include "ppd_internal.h"
 
 namespace ppd {
 namespace {
-
-// Elements per thread of a staging pass: every launch below has at most
-// 4 * blockDim.x of them (checked on the host).
-constexpr int FFT_PER = 4;
-// Columns per workgroup of the column passes (at most 4096 / L).
-#ifndef PPD_FFT_COLS
-#define PPD_FFT_COLS 16
-#endif
-
-__device__ __forceinline__ int padi(int i) { return i + (i >> 5); }
-__host__ __device__ inline int padded_len(int L) { return L + (L >> 5) + 1; }
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ int bitrev(int n, int log2L) { return int(__brev(unsigned(n)) >> (32 - log2L)); }
+__device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.y); }
+// a times W_4 = -i (forward) or +i (inverse)
+template <bool INV>
+__device__ __forceinline__ float2 rot4(float2 a) {
+  return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
+}
+template <bool INV>
+__device__ __forceinline__ float2 twmul(float2 a, float2 w) {
+  return cmul(a, INV ? conjf2(w) : w);
+}
 
 template <bool INV>
-__device__ void lds_fft(float2* s, int log2L, int nseq, int sstride, const float2* tw) {
-  const int L = 1 << log2L;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  int log2h = 0;
-  if (log2L & 1) {
-    const int half = L >> 1;
-    for (int g = tid; g < nseq * half; g += nth) {
-      const int sq = g >> (log2L - 1), k = g & (half - 1);
-      float2* b = s + sq * sstride;
-      const int i0 = padi(2 * k), i1 = padi(2 * k + 1);
-      const float2 a = b[i0], c = b[i1];
-      b[i0] = cadd(a, c);
-      b[i1] = csub(a, c);
-    }
-    log2h = 1;
-    __syncthreads();
-  }
-  for (; log2h < log2L; log2h += 2) {
-    const int h = 1 << log2h;
-    const int quarter = L >> 2;
-    for (int g = tid; g < nseq * quarter; g += nth) {
-      const int sq = g >> (log2L - 2), r = g & (quarter - 1);
-      const int j = r & (h - 1), blk = r >> log2h;
-      const int base = (blk << (log2h + 2)) + j;
-      float2* b = s + sq * sstride;
-      const int i0 = padi(base), i1 = padi(base + h), i2 = padi(base + 2 * h), i3 = padi(base + 3 * h);
-      const float2 a0 = b[i0], a1 = b[i1], a2 = b[i2], a3 = b[i3];
-      float2 w1 = tw[j << (log2L - log2h - 1)];   // W_{2h}^j
-      float2 w2 = tw[j << (log2L - log2h - 2)];   // W_{4h}^j
-      if (INV) {
-        w1.y = -w1.y;
-        w2.y = -w2.y;
+__device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
+  const float2 s0 = cadd(a0, a2), s1 = csub(a0, a2), s2 = cadd(a1, a3), s3 = rot4<INV>(csub(a1, a3));
+  a0 = cadd(s0, s2);
+  a1 = cadd(s1, s3);
+  a2 = csub(s0, s2);
+  a3 = csub(s1, s3);
+}
+
+// W_16^k for the k = j s that occur (j, s <= 3)
+template <int K>
+__device__ __forceinline__ float2 w16() {
+  constexpr float C1 = 0.92387953251128675613f, S1 = 0.38268343236508977173f, H = 0.70710678118654752440f;
+  if constexpr (K == 0) return make_float2(1.f, 0.f);
+  else if constexpr (K == 1) return make_float2(C1, -S1);
+  else if constexpr (K == 2) return make_float2(H, -H);
+  else if constexpr (K == 3) return make_float2(S1, -C1);
+  else if constexpr (K == 4) return make_float2(0.f, -1.f);
+  else if constexpr (K == 6) return make_float2(-H, -H);
+  else return make_float2(-C1, S1);   // 9
+}
+
+// DFT of N = 2, 4, 8 or 16 registers, natural order in and out.  HALF: the
+// middle half of the input (indices N/4 .. 3N/4) is zero and not read.
+template <int N, bool INV, bool HALF>
+__device__ __forceinline__ void dft(float2* x) {
+  if constexpr (N == 2) {
+    const float2 a = x[0], b = x[1];
+    x[0] = cadd(a, b);
+    x[1] = csub(a, b);
+  } else if constexpr (N == 4 && !HALF) {
+    dft4<INV>(x[0], x[1], x[2], x[3]);
+  } else {
+    // x[j + R s] -> X[s' + 4 j']: 4-point DFTs over s, twiddles, R-point DFTs over j
+    constexpr int R = N / 4;
+    float2 y[4][R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if constexpr (HALF) {
+        const float2 a = x[j], b = rot4<INV>(x[j + 3 * R]);   // the two others are zero
+        y[0][j] = cadd(x[j], x[j + 3 * R]);
+        y[1][j] = csub(a, b);
+        y[2][j] = csub(x[j], x[j + 3 * R]);
+        y[3][j] = cadd(a, b);
+      } else {
+        float2 a0 = x[j], a1 = x[j + R], a2 = x[j + 2 * R], a3 = x[j + 3 * R];
+        dft4<INV>(a0, a1, a2, a3);
+        y[0][j] = a0;
+        y[1][j] = a1;
+        y[2][j] = a2;
+        y[3][j] = a3;
       }
-      const float2 t1 = cmul(w1, a1), t3 = cmul(w1, a3);
-      const float2 b0 = cadd(a0, t1), b1 = csub(a0, t1), b2 = cadd(a2, t3), b3 = csub(a2, t3);
-      const float2 u2 = cmul(w2, b2);
-      float2 u3 = cmul(w2, b3);   // times W_{4h}^h = -i (forward) or +i (inverse)
-      u3 = INV ? make_float2(-u3.y, u3.x) : make_float2(u3.y, -u3.x);
-      b[i0] = cadd(b0, u2);
-      b[i2] = csub(b0, u2);
-      b[i1] = cadd(b1, u3);
-      b[i3] = csub(b1, u3);
+    }
+    if constexpr (R == 2) {
+      y[1][1] = twmul<INV>(y[1][1], w16<2>());
+      y[2][1] = rot4<INV>(y[2][1]);
+      y[3][1] = twmul<INV>(y[3][1], w16<6>());
+    } else if constexpr (R == 4) {
+      y[1][1] = twmul<INV>(y[1][1], w16<1>());
+      y[1][2] = twmul<INV>(y[1][2], w16<2>());
+      y[1][3] = twmul<INV>(y[1][3], w16<3>());
+      y[2][1] = twmul<INV>(y[2][1], w16<2>());
+      y[2][2] = rot4<INV>(y[2][2]);
+      y[2][3] = twmul<INV>(y[2][3], w16<6>());
+      y[3][1] = twmul<INV>(y[3][1], w16<3>());
+      y[3][2] = twmul<INV>(y[3][2], w16<6>());
+      y[3][3] = twmul<INV>(y[3][3], w16<9>());
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if constexpr (R > 1) dft<R, INV, false>(y[s]);
+#pragma unroll
+      for (int j = 0; j < R; ++j) x[s + 4 * j] = y[s][j];
+    }
+  }
+}
+
+// A transform of length L with E elements per thread and S sequences
+// interleaved element by element in LDS (columns; 1 for rows).  Stage i turns
+// A[k][n], k < K, n < M (K M = L), into A[k + K k1][n2]: DFTs of radix R over
+// n1, n = n2 + (M / R) n1, times exp(-2 pi i n2 k1 / M).  All radices are E but
+// the last, L's remainder.  Thread t takes the DFTs (k, n2) numbered t + P a
+// with n2 fastest, so its first inputs and last outputs are elements t + P m.
+template <int L, int E_, int S>
+struct Fft {
+  static constexpr int E = E_, P = L / E;
+  static constexpr int radix(int M) { return M > E ? E : M; }
+  // Exchange before the stage at (K, M): A[k][n] at k (M + pad) + n, before the
+  // last stage at n (K + pad) + k; the padding (elements) spreads the strided
+  // side over the 16 8-byte words a cycle of LDS serves.
+  static constexpr bool last(int M) { return M <= E; }
+  static constexpr int pad(int M) {
+    if (last(M)) return M * S < 16 ? 16 / (M * S) : 1;
+    const int run = M / radix(M);   // consecutive elements a stage's threads read
+    return run * S < 16 ? run : 0;
+  }
+  static constexpr int stride(int M) { return last(M) ? L / M + pad(M) : M + pad(M); }
+  static constexpr int lds_from(int M) {   // largest exchange from the one before the stage at M on
+    const int n = last(M) ? M * stride(M) : (L / M) * stride(M);
+    const int rest = last(M) ? 0 : lds_from(M / radix(M));
+    return n > rest ? n : rest;
+  }
+  static constexpr int ONE = lds_from(L / E);
+  // Two buffers in turn save the barrier between an exchange's reads and the
+  // next one's writes, where they leave room for a second workgroup.
+  static constexpr bool TWO = !last(L / E) && 2 * ONE * S * int(sizeof(float2)) <= FFT_TWO_LDS;
+  static constexpr int LDS = (TWO ? 2 : 1) * ONE;   // elements per sequence
+  static_assert(E >= 4 && L >= 2 * E, "at least two stages, a first radix of 4 or more");
+  static_assert(LDS * S >= L, "room for the mirror exchanges");
+  static constexpr int twiddles_from(int M) { return last(M) ? 0 : (radix(M) - 1) * (M / radix(M)) + twiddles_from(M / radix(M)); }
+  static constexpr int stages_from(int M) { return last(M) ? 1 : 1 + stages_from(M / radix(M)); }
+  static constexpr int NW = (E - 1) * (stages_from(L) - 1);
+
+  float2 w[NW];   // this thread's twiddles (forward sign), stage by stage
+
+  template <int M, int I>
+  __device__ __forceinline__ void load_from(const float2* __restrict__ tw, int t) {
+    if constexpr (!last(M)) {
+      constexpr int Q = M / E;
+#pragma unroll
+      for (int k = 0; k < E - 1; ++k) w[I + k] = tw[k * Q + t % Q];
+      load_from<Q, I + E - 1>(tw + (E - 1) * Q, t);
+    }
+  }
+  __device__ __forceinline__ void load_twiddles(const float2* __restrict__ tw, int t) { load_from<L, 0>(tw, t); }
+
+  template <bool INV, bool HALF, int M, int I, int B>
+  __device__ __forceinline__ void stage(float2 (&x)[E], int t, float2* s) const {
+    constexpr int R = radix(M), K = L / M, SETS = E / R;
+    float2* buf = s + (TWO ? B * ONE * S : 0);
+    if constexpr (last(M)) {
+      float2 y[R];
+#pragma unroll
+      for (int a = 0; a < SETS; ++a) {
+#pragma unroll
+        for (int q = 0; q < R; ++q) y[q] = buf[(q * stride(M) + t + P * a) * S];
+        dft<R, INV, false>(y);
+#pragma unroll
+        for (int q = 0; q < R; ++q) x[a + SETS * q] = y[q];
+      }
+    } else {
+      constexpr int Q = M / E;   // the next stage's M
+      const int k0 = t / Q, n2 = t % Q;
+      if constexpr (M < L) {
+#pragma unroll
+        for (int q = 0; q < E; ++q) x[q] = buf[(k0 * stride(M) + n2 + Q * q) * S];
+      }
+      dft<E, INV, HALF && M == L>(x);
+#pragma unroll
+      for (int k = 1; k < E; ++k) x[k] = twmul<INV>(x[k], w[I + k - 1]);
+      constexpr int NB = M < L ? 1 - B : 0;
+      float2* out = s + (TWO ? NB * ONE * S : 0);
+      if constexpr (M < L && !TWO) __syncthreads();
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const int kk = k0 + K * k;
+        out[(last(Q) ? n2 * stride(Q) + kk : kk * stride(Q) + n2) * S] = x[k];
+      }
+      __syncthreads();
+      stage<INV, HALF, Q, I + E - 1, NB>(x, t, s);
+    }
+  }
+
+  // x[n] = element t + P n in; x[m] = output t + P m out.  s: this
+  // sequence's first LDS element (stride S); every thread of the workgroup
+  // calls it, and the LDS may be overwritten only after a barrier.
+  template <bool INV, bool HALF>
+  __device__ __forceinline__ void run(float2 (&x)[E], int t, float2* s) const {
+    stage<INV, HALF, L, 0, 0>(x, t, s);
+  }
+};
+
+// Rows: pairs of image rows per workgroup (one wave's worth of threads, or
+// one pair where a pair takes more).
+template <int L>
+struct RowCfg {
+  using F = Fft<L, FftShape<L>::ROW_E, 1>;
+  static constexpr int NS = F::P < 64 ? 64 / F::P : 1;
+  static constexpr int THREADS = NS * F::P;
+};
+
+// Columns: FFT_CB columns per workgroup, more where they take less than a wave.
+template <int L>
+struct ColCfg {
+  static constexpr int E = FftShape<L>::COL_E;
+  static constexpr int C = FftShape<L>::COL_C * (L / E) < 64 ? 64 / (L / E) : FftShape<L>::COL_C;
+  using F = Fft<L, E, C>;
+  static constexpr int THREADS = C * F::P;
+  static_assert(C >= 2 && C <= 16, "a workgroup's columns divide Kx / 2 >= 16; two hold the staged mirror column");
+};
+
+// Spectra of the two rows of a packed sequence: x[m] = Z(t + P m), the rows'
+// entries k < L/2 to the row-pass buffer (columns 0 and L/2 share column 0).
+template <int L>
+__device__ __forceinline__ void store_pair(const float2* x, int t, float2* s, int row, int ny, bool ok,
+                                           float2* __restrict__ half) {
+  using F = typename RowCfg<L>::F;
+  constexpr int E = F::E, P = F::P, H = L / 2;
+  __syncthreads();
+#pragma unroll
+  for (int m = E / 2; m < E; ++m) s[t + P * m - H] = x[m];
+  __syncthreads();
+  if (!ok) return;
+#pragma unroll
+  for (int m = 0; m < E / 2; ++m) {
+    const int k = t + P * m;
+    const float2 z = x[m], w = s[k == 0 ? 0 : H - k];   // Z(k), Z(L - k); Z(L/2) for k = 0
+    float2 a, b;
+    if (m == 0 && k == 0) {
+      a = make_float2(z.x, w.x);
+      b = make_float2(z.y, w.y);
+    } else {
+      a = make_float2(0.5f * (z.x + w.x), 0.5f * (z.y - w.y));
+      b = make_float2(0.5f * (z.y + w.y), 0.5f * (w.x - z.x));
+    }
+    float2* dst = half + half_index(k, row, ny);
+    dst[0] = a;
+    dst[FFT_CB] = b;
+  }
+}
+
+// Image column of sequence index n = t + P m for the elements m outside the
+// padding (the middle half): c = (n + nx / 2) mod L, nx = L / 2.
+template <int L>
+__device__ __forceinline__ int pixel_of(int n) {
+  return (n + L / 4) & (L - 1);
+}
+
+// Forward rows: image rows 2 i, 2 i + 1 -> row-pass buffer.
+template <int L>
+__global__ __launch_bounds__(RowCfg<L>::THREADS) void k_fft_rows_fwd(const float* __restrict__ x,
+                                                                     const float* __restrict__ dpx,
+                                                                     const float* __restrict__ dpy,
+                                                                     const float2* __restrict__ tw, int ny,
+                                                                     float2* __restrict__ half) {
+  using F = typename RowCfg<L>::F;
+  constexpr int E = F::E, P = F::P, NX = L / 2;
+  __shared__ float2 sm[RowCfg<L>::NS * F::LDS];
+  const int t = threadIdx.x % P, q = threadIdx.x / P;
+  const int row = 2 * (blockIdx.x * RowCfg<L>::NS + q);
+  const bool ok = row < ny;
+  F f;
+  f.load_twiddles(tw, t);
+  float2 z[E];
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    if (m >= E / 4 && m < 3 * E / 4) continue;
+    const int c = pixel_of<L>(t + P * m);
+    z[m] = make_float2(0.f, 0.f);
+    if (ok) {
+      const float d = dpx[c];
+      z[m] = make_float2(x[size_t(row) * NX + c] * d * dpy[row], x[size_t(row + 1) * NX + c] * d * dpy[row + 1]);
+    }
+  }
+  float2* s = sm + q * F::LDS;
+  f.template run<false, true>(z, t, s);
+  store_pair<L>(z, t, s, row, ny, ok, half);
+}
+
+// Forward columns: stored columns 4 g .. -> grid, with the mirror images that
+// the padding columns hold.
+template <int L>
+__global__ __launch_bounds__(ColCfg<L>::THREADS) void k_fft_cols_fwd(const float2* __restrict__ half,
+                                                                     const float2* __restrict__ tw, int Hx,
+                                                                     int ngroups, float2* __restrict__ grid) {
+  using F = typename ColCfg<L>::F;
+  constexpr int E = F::E, P = F::P, C = ColCfg<L>::C, NY = L / 2;
+  __shared__ float2 sm[C * F::LDS];
+  const int grp = xcd_remap(blockIdx.x, gridDim.x);
+  if (grp >= ngroups) return;
+  const int cc = threadIdx.x % C, t = threadIdx.x / C;
+  const int c = grp * C + cc;
+  F f;
+  float2 z[E];
+#pragma unroll
+  for (int m = 0; m < E; ++m) {
+    if (m >= E / 4 && m < 3 * E / 4) continue;
+    z[m] = half[half_index(c, pixel_of<L>(t + P * m), NY)];
+  }
+  f.load_twiddles(tw, t);
+  float2* s = sm + cc;
+  f.template run<false, true>(z, t, s);
+  if (grp == 0) {   // column 0 carries columns 0 and Hx: Z(k) = F_0(k) + i F_Hx(k), both Hermitian in k
+    __syncthreads();
+    if (cc == 0) {
+#pragma unroll
+      for (int m = 0; m < E; ++m) sm[t + P * m] = z[m];
+    }
+    __syncthreads();
+    if (cc == 0) {
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        const int k = t + P * m;
+        const float2 a = z[m], b = sm[(L - k) & (L - 1)];
+        z[m] = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y - b.y));
+        grid[grid_index(GRID_PAD + Hx, k, L)] = make_float2(0.5f * (a.y + b.y), 0.5f * (b.x - a.x));
+      }
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < E; ++m) grid[grid_index(GRID_PAD + c, t + P * m, L)] = z[m];
+  // mirror images: column -c at row -k (left padding), column 2 Hx - c (right padding)
+  if (c >= 1 && c <= GRID_PAD) {
+#pragma unroll
+    for (int m = 0; m < E; ++m)
+      grid[grid_index(GRID_PAD - c, (L - (t + P * m)) & (L - 1), L)] = conjf2(z[m]);
+  }
+  if (c > Hx - GRID_PAD) {
+#pragma unroll
+    for (int m = 0; m < E; ++m)
+      grid[grid_index(GRID_PAD + 2 * Hx - c, (L - (t + P * m)) & (L - 1), L)] = conjf2(z[m]);
+  }
+}
+
+// Inverse columns of the accumulated grid, keeping the ny rows that map to
+// image rows.  The image takes the real part, so what the padding columns
+// hold is added to their mirror images, and columns 0 and Hx, of which only
+// the Hermitian part counts, go through one transform.
+template <int L>
+__global__ __launch_bounds__(ColCfg<L>::THREADS) void k_fft_cols_inv(const float2* __restrict__ grid,
+                                                                     const float2* __restrict__ tw, int Hx,
+                                                                     int ngroups, float2* __restrict__ half) {
+  using F = typename ColCfg<L>::F;
+  constexpr int E = F::E, P = F::P, C = ColCfg<L>::C, NY = L / 2;
+  __shared__ float2 sm[C * F::LDS];
+  const int grp = xcd_remap(blockIdx.x, gridDim.x);
+  if (grp >= ngroups) return;
+  const int cc = threadIdx.x % C, t = threadIdx.x / C;
+  const int c = grp * C + cc;
+  F f;
+  float2 z[E];
+#pragma unroll
+  for (int m = 0; m < E; ++m) z[m] = grid[grid_index(GRID_PAD + c, t + P * m, L)];
+  f.load_twiddles(tw, t);
+  // the padding column that mirrors c, at row -k; for c = 0 column Hx, at row k
+  const int pm = c == 0 ? GRID_PAD + Hx : c <= GRID_PAD ? GRID_PAD - c : c > Hx - GRID_PAD ? GRID_PAD + 2 * Hx - c : -1;
+  if (pm >= 0) {
+    // (8 elements at a time: all 16 at once would spill)
+    constexpr int B = E < 8 ? E : 8;
+#pragma unroll
+    for (int m0 = 0; m0 < E; m0 += B) {
+      float2 e[B];
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        const int k = t + P * (m0 + i);
+        e[i] = grid[grid_index(pm, c == 0 ? k : (L - k) & (L - 1), L)];
+      }
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        const int m = m0 + i;
+        if (c == 0) {   // staged for the rows -k, as columns sm[0 .. L) and sm[L .. 2 L)
+          sm[t + P * m] = z[m];
+          sm[L + t + P * m] = e[i];
+        } else {
+          z[m] = cadd(z[m], conjf2(e[i]));
+        }
+      }
+    }
+  }
+  if (grp == 0) {
+    __syncthreads();
+    if (c == 0) {
+#pragma unroll
+      for (int m = 0; m < E; ++m) {
+        const int k = t + P * m, kn = (L - k) & (L - 1);
+        const float2 a = sm[k], b = sm[kn], p = sm[L + k], q = sm[L + kn];
+        z[m] = make_float2(0.5f * (a.x + b.x) - 0.5f * (p.y - q.y), 0.5f * (a.y - b.y) + 0.5f * (p.x + q.x));
+      }
     }
     __syncthreads();
   }
-}
-
-// Forward rows: image rows r0 .. r0+rpb-1 -> half rows (length Kx).
-__global__ void k_fft_rows_fwd(const float* __restrict__ x, const float* __restrict__ dpx,
-                               const float* __restrict__ dpy, const float2* __restrict__ tw,
-                               int nx, int log2L, int rpb, float2* __restrict__ half) {
-  extern __shared__ float2 sm[];
-  const int L = 1 << log2L, Lp = padded_len(L);
-  float2* tws = sm + rpb * Lp;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int r0 = blockIdx.x * rpb;
-  // all global loads of the thread are issued before the first LDS store
-  float2 twv[FFT_PER];
-  float xv[FFT_PER];
+  f.template run<true, false>(z, t, sm + cc);
 #pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) twv[k] = tw[i];
-    if (i < rpb * nx) {
-      const int q = i / nx, c = i - q * nx, r = r0 + q;
-      xv[k] = x[size_t(r) * nx + c] * dpx[c] * dpy[r];
-    }
-  }
-  for (int i = tid; i < rpb * Lp; i += nth) sm[i] = make_float2(0.f, 0.f);
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) tws[i] = twv[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < rpb * nx) {
-      const int q = i / nx, c = i - q * nx;
-      const int n = (c - (nx >> 1)) & (L - 1);
-      sm[q * Lp + padi(bitrev(n, log2L))] = make_float2(xv[k], 0.f);
-    }
-  }
-  __syncthreads();
-  lds_fft<false>(sm, log2L, rpb, Lp, tws);
-  for (int i = tid; i < rpb * L; i += nth) {
-    const int q = i >> log2L, k = i & (L - 1);
-    half[size_t(r0 + q) * L + k] = sm[q * Lp + padi(k)];
-  }
-}
-
-// Forward columns: C grid columns from their ny non-zero rows -> grid.
-__global__ void k_fft_cols_fwd(const float2* __restrict__ half, const float2* __restrict__ tw,
-                               int ny, int Kx, int log2L, int C, int ngroups,
-                               float2* __restrict__ grid) {
-  const int grp = xcd_remap(blockIdx.x, gridDim.x);
-  if (grp >= ngroups) return;
-  extern __shared__ float2 sm[];
-  const int L = 1 << log2L, Lp = padded_len(L);
-  float2* tws = sm + C * Lp;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int c0 = grp * C;
-  float2 twv[FFT_PER], hv[FFT_PER];
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) twv[k] = tw[i];
-    if (i < ny * C) {
-      const int r = i / C, cc = i - r * C;
-      hv[k] = half[size_t(r) * Kx + c0 + cc];
-    }
-  }
-  for (int i = tid; i < C * Lp; i += nth) sm[i] = make_float2(0.f, 0.f);
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) tws[i] = twv[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < ny * C) {
-      const int r = i / C, cc = i - r * C;
-      const int g = (r - (ny >> 1)) & (L - 1);
-      sm[cc * Lp + padi(bitrev(g, log2L))] = hv[k];
-    }
-  }
-  __syncthreads();
-  lds_fft<false>(sm, log2L, C, Lp, tws);
-  for (int i = tid; i < L * C; i += nth) {
-    const int g = i / C, cc = i - g * C;
-    grid[size_t(g) * Kx + c0 + cc] = sm[cc * Lp + padi(g)];
-  }
-}
-
-// Inverse columns: full column transforms of the accumulated grid, keeping
-// only the ny rows that map to image rows.
-__global__ void k_fft_cols_inv(const float2* __restrict__ grid, const float2* __restrict__ tw,
-                               int ny, int Kx, int log2L, int C, int ngroups,
-                               float2* __restrict__ half) {
-  const int grp = xcd_remap(blockIdx.x, gridDim.x);
-  if (grp >= ngroups) return;
-  extern __shared__ float2 sm[];
-  const int L = 1 << log2L, Lp = padded_len(L);
-  float2* tws = sm + C * Lp;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int c0 = grp * C;
-  float2 twv[FFT_PER], gv[FFT_PER];
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) twv[k] = tw[i];
-    if (i < L * C) {
-      const int g = i / C, cc = i - g * C;
-      gv[k] = grid[size_t(g) * Kx + c0 + cc];
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) tws[i] = twv[k];
-    if (i < L * C) {
-      const int g = i / C, cc = i - g * C;
-      sm[cc * Lp + padi(bitrev(g, log2L))] = gv[k];
-    }
-  }
-  __syncthreads();
-  lds_fft<true>(sm, log2L, C, Lp, tws);
-  for (int i = tid; i < ny * C; i += nth) {
-    const int r = i / C, cc = i - r * C;
-    const int g = (r - (ny >> 1)) & (L - 1);
-    half[size_t(r) * Kx + c0 + cc] = sm[cc * Lp + padi(g)];
+  for (int m = 0; m < E; ++m) {
+    if (m >= E / 4 && m < 3 * E / 4) continue;
+    half[half_index(c, pixel_of<L>(t + P * m), NY)] = z[m];
   }
 }
 
@@ -227,157 +446,174 @@ __device__ inline double block_sum(double v, double* red) {
   return s;
 }
 
-// Inverse rows: half rows -> image rows.  PRIMAL fuses the primal update of
-// Algorithm 3 (gradient step, projection onto the positive orthant,
-// relaxation and the extrapolated iterate) and the FP64 statistics partials
-// of the new iterate; NEXT also runs
-// the forward row pass of the new x~ (the first transform of the next
-// iteration's F Z x~) on the rows just updated, into half_next.
-template <bool PRIMAL, bool NEXT>
-__global__ void k_fft_rows_inv(const float2* __restrict__ half, const float2* __restrict__ tw,
-                               const float* __restrict__ dpx, const float* __restrict__ dpy,
-                               int nx, int log2L, int rpb, float* __restrict__ x,
-                               float* __restrict__ xt, const float* __restrict__ ut,
-                               const float* __restrict__ x_true, double tau, double eta,
-                               double zeta, double lambda, double* __restrict__ part,
-                               float2* __restrict__ half_next) {
-  static_assert(PRIMAL || !NEXT, "the next forward pass needs the primal update");
-  extern __shared__ float2 sm[];
+// Inverse rows: row-pass buffer -> image rows 2 i, 2 i + 1.  PRIMAL fuses the
+// primal update of Algorithm 3 (gradient step, projection onto the positive
+// orthant, relaxation and the extrapolated iterate), the FP64 statistics
+// partials of the new iterate, and the forward row pass of the new x~ (the
+// first transform of the next iteration's F Z x~) on the rows just updated,
+// into half_next.
+template <int L, bool PRIMAL>
+__global__ __launch_bounds__(RowCfg<L>::THREADS) void k_fft_rows_inv(
+    const float2* __restrict__ half, const float2* __restrict__ tw, const float* __restrict__ dpx,
+    const float* __restrict__ dpy, int ny, float* __restrict__ x, float* __restrict__ xt,
+    const float* __restrict__ ut, const float* __restrict__ x_true, double tau, double eta, double zeta,
+    double lambda, double* __restrict__ part, float2* __restrict__ half_next) {
+  using F = typename RowCfg<L>::F;
+  constexpr int E = F::E, P = F::P, NX = L / 2, H = L / 2;
+  __shared__ float2 sm[RowCfg<L>::NS * F::LDS];
   __shared__ double red[16];
-  const int L = 1 << log2L, Lp = padded_len(L);
-  float2* tws = sm + rpb * Lp;
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int r0 = blockIdx.x * rpb;
-  float2 twv[FFT_PER], hv[FFT_PER];
+  const int t = threadIdx.x % P, q = threadIdx.x / P;
+  const int row = 2 * (blockIdx.x * RowCfg<L>::NS + q);
+  const bool ok = row < ny;
+  // Z = S_a + i S_b of the two rows' Hermitian spectra, twice their value
+  // (the factor is taken out with the deapodisation)
+  float2 z[E];
 #pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) twv[k] = tw[i];
-    if (i < rpb * L) hv[k] = half[size_t(r0 + (i >> log2L)) * L + (i & (L - 1))];
+  for (int m = 0; m < E; ++m) {
+    z[m] = make_float2(0.f, 0.f);
+    if (ok) {
+      const int k = t + P * m;
+      const int kk = m < E / 2 ? k : (L - k) & (H - 1);   // stored column; 0 for k = H too
+      const float2* src = half + half_index(kk, row, ny);
+      const float2 a = src[0], b = src[FFT_CB];
+      if (m < E / 2) z[m] = m == 0 && k == 0 ? make_float2(2.f * a.x, 2.f * b.x) : make_float2(a.x - b.y, a.y + b.x);
+      else z[m] = m == E / 2 && k == H ? make_float2(2.f * a.y, 2.f * b.y) : make_float2(a.x + b.y, b.x - a.y);
+    }
   }
+  F f;
+  f.load_twiddles(tw, t);
+  // the update's operands are loaded before the transform
+  constexpr int NV = PRIMAL ? E / 2 : 1;
+  float xo_a[NV], xo_b[NV], ut_a[NV], ut_b[NV];
+  if (PRIMAL && ok) {
 #pragma unroll
-  for (int k = 0; k < FFT_PER; ++k) {
-    const int i = tid + k * nth;
-    if (i < (L >> 1)) tws[i] = twv[k];
-    if (i < rpb * L) sm[(i >> log2L) * Lp + padi(bitrev(i & (L - 1), log2L))] = hv[k];
+    for (int i = 0; i < E / 2; ++i) {
+      const int m = i < E / 4 ? i : i + E / 2;
+      const size_t idx = size_t(row) * NX + pixel_of<L>(t + P * m);
+      xo_a[i] = x[idx];
+      xo_b[i] = x[idx + NX];
+      ut_a[i] = ut[idx];
+      ut_b[i] = ut[idx + NX];
+    }
   }
-  __syncthreads();
-  lds_fft<true>(sm, log2L, rpb, Lp, tws);
+  float2* s = sm + q * F::LDS;
+  f.template run<true, false>(z, t, s);
   double dx2 = 0.0, xx = 0.0, ee = 0.0, tt = 0.0;
-  // rpb * nx <= 2 * nth (the staging capacity check on the host)
-  float xtn[FFT_PER / 2];
+  const float dy_a = ok ? 0.5f * dpy[row] : 0.f, dy_b = ok ? 0.5f * dpy[row + 1] : 0.f;
 #pragma unroll
-  for (int k = 0; k < FFT_PER / 2; ++k) {
-    const int i = tid + k * nth;
-    if (i >= rpb * nx) break;
-    const int q = i / nx, c = i - q * nx, r = r0 + q;
-    const int n = (c - (nx >> 1)) & (L - 1);
-    const float val = sm[q * Lp + padi(n)].x * dpx[c] * dpy[r];
-    const size_t idx = size_t(r) * nx + c;
-    if (!PRIMAL) {
-      x[idx] = val;
-    } else {
-      const double xo = x[idx];
-      double xb = xo - tau * (eta * double(val) + zeta * double(ut[idx]));   // primal step, then P_C
-      xb = xb > 0.0 ? xb : 0.0;
-      const double xn = xo + lambda * (xb - xo);                              // relaxation
-      const float xnf = float(xn);
-      x[idx] = xnf;
-      const float xtf = float(2.0 * xb - xo);                                 // x~ = 2 xbar - x
-      xt[idx] = xtf;
-      if (NEXT) xtn[k] = xtf;
-      const double dn = double(xnf) - xo;
-      dx2 += dn * dn;
-      xx += double(xnf) * double(xnf);
-      if (part && x_true) {
-        const double tv = x_true[idx];
-        ee += (tv - double(xnf)) * (tv - double(xnf));
-        tt += tv * tv;
+  for (int i = 0; i < E / 2; ++i) {
+    const int m = i < E / 4 ? i : i + E / 2;
+    const int c = pixel_of<L>(t + P * m);
+    const float dx = dpx[c];
+    const float val[2] = {z[m].x * dx * dy_a, z[m].y * dx * dy_b};
+    float nxt[2] = {0.f, 0.f};
+    if (ok) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const size_t idx = size_t(row + r) * NX + c;
+        if constexpr (!PRIMAL) {
+          x[idx] = val[r];
+        } else {
+          const double xo = r ? xo_b[i] : xo_a[i];
+          double xb = xo - tau * (eta * double(val[r]) + zeta * double(r ? ut_b[i] : ut_a[i]));   // primal step, then P_C
+          xb = xb > 0.0 ? xb : 0.0;
+          const double xn = xo + lambda * (xb - xo);                              // relaxation
+          const float xnf = float(xn);
+          x[idx] = xnf;
+          const float xtf = float(2.0 * xb - xo);                                 // x~ = 2 xbar - x
+          xt[idx] = xtf;
+          nxt[r] = xtf * dx * dpy[row + r];
+          if (part) {   // statistics partials only when the call reads them (uniform branch)
+            const double dn = double(xnf) - xo;
+            dx2 += dn * dn;
+            xx += double(xnf) * double(xnf);
+            if (x_true) {
+              const double tv = x_true[idx];
+              ee += (tv - double(xnf)) * (tv - double(xnf));
+              tt += tv * tv;
+            }
+          }
+        }
       }
     }
+    z[m] = make_float2(nxt[0], nxt[1]);
   }
-  if (PRIMAL && part) {   // statistics partials only when the call reads them (uniform branch)
-    dx2 = block_sum(dx2, red);
-    xx = block_sum(xx, red);
-    ee = block_sum(ee, red);
-    tt = block_sum(tt, red);
-    if (tid == 0) {
-      part[4 * blockIdx.x + 0] = dx2;
-      part[4 * blockIdx.x + 1] = xx;
-      part[4 * blockIdx.x + 2] = ee;
-      part[4 * blockIdx.x + 3] = tt;
+  if constexpr (PRIMAL) {
+    if (part) {
+      dx2 = block_sum(dx2, red);
+      xx = block_sum(xx, red);
+      ee = block_sum(ee, red);
+      tt = block_sum(tt, red);
+      if (threadIdx.x == 0) {
+        part[4 * blockIdx.x + 0] = dx2;
+        part[4 * blockIdx.x + 1] = xx;
+        part[4 * blockIdx.x + 2] = ee;
+        part[4 * blockIdx.x + 3] = tt;
+      }
     }
-  }
-  if (NEXT) {
-    // the same deapodisation, zero padding and wrapped placement as
-    // k_fft_rows_fwd, from the x~ values just stored
+    // the forward row pass of the new x~, already in the input's distribution
     __syncthreads();
-    for (int i = tid; i < rpb * Lp; i += nth) sm[i] = make_float2(0.f, 0.f);
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < FFT_PER / 2; ++k) {
-      const int i = tid + k * nth;
-      if (i >= rpb * nx) break;
-      const int q = i / nx, c = i - q * nx, r = r0 + q;
-      const int n = (c - (nx >> 1)) & (L - 1);
-      sm[q * Lp + padi(bitrev(n, log2L))] = make_float2(xtn[k] * dpx[c] * dpy[r], 0.f);
-    }
-    __syncthreads();
-    lds_fft<false>(sm, log2L, rpb, Lp, tws);
-    for (int i = tid; i < rpb * L; i += nth) {
-      const int q = i >> log2L, k = i & (L - 1);
-      half_next[size_t(r0 + q) * L + k] = sm[q * Lp + padi(k)];
-    }
+    f.template run<false, true>(z, t, s);
+    store_pair<L>(z, t, s, row, ny, ok, half_next);
   }
 }
 
-struct RowCfg { int rpb, threads, blocks; size_t lds; bool ok; };
-struct ColCfg { int C, threads, ngroups, blocks; size_t lds; bool ok; };
-
-RowCfg row_cfg(int L, int rows) {
-  RowCfg c;
-  c.rpb = 1;
-  while (c.rpb * L < 1024 && c.rpb * 2 <= rows) c.rpb *= 2;
-  c.threads = std::min(1024, std::max(64, c.rpb * L / 4));
-  c.blocks = rows / c.rpb;
-  c.lds = (size_t(c.rpb) * padded_len(L) + L / 2) * sizeof(float2);
-  c.ok = c.rpb * L <= FFT_PER * c.threads && L / 2 <= FFT_PER * c.threads;
-  return c;
+// Calls fn(std::integral_constant<int, L>) for the transform length L.
+template <typename Fn>
+int with_length(int L, Fn fn) {
+  switch (L) {
+    case 32: return fn(std::integral_constant<int, 32>());
+    case 64: return fn(std::integral_constant<int, 64>());
+    case 128: return fn(std::integral_constant<int, 128>());
+    case 256: return fn(std::integral_constant<int, 256>());
+    case 512: return fn(std::integral_constant<int, 512>());
+    case 1024: return fn(std::integral_constant<int, 1024>());
+    case 2048: return fn(std::integral_constant<int, 2048>());
+    case 4096: return fn(std::integral_constant<int, 4096>());
+    default: return fail(PPD_EUNSUPPORTED, "fft: transform length must be a power of two in [32, 4096]");
+  }
 }
 
-ColCfg col_cfg(int L, int Kx) {
-  ColCfg c;
-  c.C = std::max(1, std::min(PPD_FFT_COLS, 4096 / L));
-  c.C = std::min(c.C, Kx);
-  c.threads = std::min(1024, std::max(64, c.C * L / 4));
-  c.ngroups = Kx / c.C;
-  c.blocks = ((c.ngroups + MAX_XCD - 1) / MAX_XCD) * MAX_XCD;
-  c.lds = (size_t(c.C) * padded_len(L) + L / 2) * sizeof(float2);
-  c.ok = c.C * L <= FFT_PER * c.threads && L / 2 <= FFT_PER * c.threads;
-  return c;
+template <int L>
+int row_blocks(const ppd_plan* p) {
+  return (p->ny / 2 + RowCfg<L>::NS - 1) / RowCfg<L>::NS;
 }
+
+template <int L>
+struct ColLaunch {
+  int groups, blocks;
+  explicit ColLaunch(const ppd_plan* p) {
+    groups = (p->Kx / 2) / ColCfg<L>::C;
+    blocks = (groups + MAX_XCD - 1) / MAX_XCD * MAX_XCD;
+  }
+};
 
 }  // namespace
 
 int fft_rows_forward(ppd_plan* p, const float* x, float2* dst) {
   int slot;
-  const RowCfg rc = row_cfg(p->Kx, p->ny);
-  if (!rc.ok) return fail(PPD_EUNSUPPORTED, "fft: row launch shape exceeds the staging capacity");
   PPD_TRY(timer_begin(p, KK_FFT_ROWS_FWD, &slot));
-  hipLaunchKernelGGL(k_fft_rows_fwd, dim3(rc.blocks), dim3(rc.threads), rc.lds, p->stream, x, p->dpx,
-                     p->dpy, p->twx, p->nx, p->log2Kx, rc.rpb, dst);
-  PPD_HIP(hipGetLastError());
+  PPD_TRY(with_length(p->Kx, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    hipLaunchKernelGGL(k_fft_rows_fwd<L>, dim3(row_blocks<L>(p)), dim3(RowCfg<L>::THREADS), 0, p->stream, x, p->dpx,
+                       p->dpy, p->twx, p->ny, dst);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }));
   return timer_end(p, slot);
 }
 
 int fft_cols_forward(ppd_plan* p, const float2* src) {
   int slot;
-  const ColCfg cc = col_cfg(p->Ky, p->Kx);
-  if (!cc.ok) return fail(PPD_EUNSUPPORTED, "fft: column launch shape exceeds the staging capacity");
   PPD_TRY(timer_begin(p, KK_FFT_COLS_FWD, &slot));
-  hipLaunchKernelGGL(k_fft_cols_fwd, dim3(cc.blocks), dim3(cc.threads), cc.lds, p->stream, src,
-                     p->twy, p->ny, p->Kx, p->log2Ky, cc.C, cc.ngroups, p->grid_f);
-  PPD_HIP(hipGetLastError());
+  PPD_TRY(with_length(p->Ky, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    const ColLaunch<L> c(p);
+    hipLaunchKernelGGL(k_fft_cols_fwd<L>, dim3(c.blocks), dim3(ColCfg<L>::THREADS), 0, p->stream, src, p->twy,
+                       p->Kx / 2, c.groups, p->grid_f);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }));
   return timer_end(p, slot);
 }
 
@@ -388,48 +624,68 @@ int fft_forward(ppd_plan* p, const float* x) {
 
 int fft_cols_inverse(ppd_plan* p) {
   int slot;
-  const ColCfg cc = col_cfg(p->Ky, p->Kx);
-  if (!cc.ok) return fail(PPD_EUNSUPPORTED, "fft: column launch shape exceeds the staging capacity");
   PPD_TRY(timer_begin(p, KK_FFT_COLS_INV, &slot));
-  hipLaunchKernelGGL(k_fft_cols_inv, dim3(cc.blocks), dim3(cc.threads), cc.lds, p->stream, p->grid_a,
-                     p->twy, p->ny, p->Kx, p->log2Ky, cc.C, cc.ngroups, p->half);
-  PPD_HIP(hipGetLastError());
-  PPD_TRY(timer_end(p, slot));
-  return PPD_OK;
+  PPD_TRY(with_length(p->Ky, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    const ColLaunch<L> c(p);
+    hipLaunchKernelGGL(k_fft_cols_inv<L>, dim3(c.blocks), dim3(ColCfg<L>::THREADS), 0, p->stream, p->grid_a, p->twy,
+                       p->Kx / 2, c.groups, p->half);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }));
+  return timer_end(p, slot);
 }
 
 int fft_adjoint(ppd_plan* p, float* x) {
   PPD_TRY(fft_cols_inverse(p));
   int slot;
-  const RowCfg rc = row_cfg(p->Kx, p->ny);
-  if (!rc.ok) return fail(PPD_EUNSUPPORTED, "fft: row launch shape exceeds the staging capacity");
   PPD_TRY(timer_begin(p, KK_FFT_ROWS_INV, &slot));
-  hipLaunchKernelGGL((k_fft_rows_inv<false, false>), dim3(rc.blocks), dim3(rc.threads), rc.lds, p->stream,
-                     p->half, p->twx, p->dpx, p->dpy, p->nx, p->log2Kx, rc.rpb, x, nullptr, nullptr,
-                     nullptr, 0.0, 0.0, 0.0, 0.0, nullptr, nullptr);
-  PPD_HIP(hipGetLastError());
-  PPD_TRY(timer_end(p, slot));
-  return PPD_OK;
+  PPD_TRY(with_length(p->Kx, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    hipLaunchKernelGGL((k_fft_rows_inv<L, false>), dim3(row_blocks<L>(p)), dim3(RowCfg<L>::THREADS), 0, p->stream,
+                       p->half, p->twx, p->dpx, p->dpy, p->ny, x, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0.0,
+                       nullptr, nullptr);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }));
+  return timer_end(p, slot);
 }
 
 int fft_rows_inverse_primal(ppd_plan* p, const PrimalArgs& a, float2* next) {
   int slot;
-  const RowCfg rc = row_cfg(p->Kx, p->ny);
-  if (!rc.ok) return fail(PPD_EUNSUPPORTED, "fft: row launch shape exceeds the staging capacity");
   PPD_TRY(timer_begin(p, KK_FFT_ROWS_INV, &slot));
-  if (next)
-    hipLaunchKernelGGL((k_fft_rows_inv<true, true>), dim3(rc.blocks), dim3(rc.threads), rc.lds, p->stream,
-                       p->half, p->twx, p->dpx, p->dpy, p->nx, p->log2Kx, rc.rpb, a.x, a.xt, a.ut,
-                       a.x_true, a.tau, a.eta, a.zeta, a.lambda, a.part, next);
-  else
-    hipLaunchKernelGGL((k_fft_rows_inv<true, false>), dim3(rc.blocks), dim3(rc.threads), rc.lds, p->stream,
-                       p->half, p->twx, p->dpx, p->dpy, p->nx, p->log2Kx, rc.rpb, a.x, a.xt, a.ut,
-                       a.x_true, a.tau, a.eta, a.zeta, a.lambda, a.part, nullptr);
-  PPD_HIP(hipGetLastError());
-  PPD_TRY(timer_end(p, slot));
-  return PPD_OK;
+  PPD_TRY(with_length(p->Kx, [&](auto l) {
+    constexpr int L = decltype(l)::value;
+    hipLaunchKernelGGL((k_fft_rows_inv<L, true>), dim3(row_blocks<L>(p)), dim3(RowCfg<L>::THREADS), 0, p->stream,
+                       p->half, p->twx, p->dpx, p->dpy, p->ny, a.x, a.xt, a.ut, a.x_true, a.tau, a.eta, a.zeta,
+                       a.lambda, a.part, next);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }));
+  return timer_end(p, slot);
 }
 
-int primal_partial_count(ppd_plan* p) { return row_cfg(p->Kx, p->ny).blocks; }
+int primal_partial_count(ppd_plan* p) {
+  return with_length(p->Kx, [&](auto l) { return row_blocks<decltype(l)::value>(p); });
+}
+
+FftTwiddles fft_twiddles(int L) {
+  FftTwiddles out;
+  (void)with_length(L, [&](auto l) {
+    constexpr int N = decltype(l)::value;
+    auto fill = [](std::vector<float2>& tw, int E) {
+      for (int M = N; M > E; M /= E)
+        for (int k = 1; k < E; ++k)
+          for (int n = 0; n < M / E; ++n) {
+            const double a = -2.0 * M_PI * double(n * k) / double(M);
+            tw.push_back(make_float2(float(std::cos(a)), float(std::sin(a))));
+          }
+    };
+    fill(out.row, FftShape<N>::ROW_E);
+    fill(out.col, FftShape<N>::COL_E);
+    return PPD_OK;
+  });
+  return out;
+}
 
 }  // namespace ppd

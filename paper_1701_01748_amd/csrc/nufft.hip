@@ -23,6 +23,8 @@
 // parts of four degree-9 polynomials (the kernel is even), so only the two
 // float32 frequencies are read per visibility.
 // Items are launched in spatial order through an XCD-aware remap.
+#include <type_traits>
+
 #include "ppd_internal.h"
 
 namespace ppd {
@@ -30,18 +32,22 @@ namespace {
 
 struct Taps {
   int ou, ov;         // first tap relative to the staged region
+  bool conj;          // gridded at its mirror frequency: the grid holds the conjugate
   float wx[KB_TAPS];  // u-axis weights
   float wy[KB_TAPS];  // v-axis weights
 };
 
 template <int T>
-__device__ __forceinline__ void taps_for(float omu, float omv, double su, double sv, int Kx, int Ky,
+__device__ __forceinline__ void taps_for(float omu, float omv, double su, double sv, int Ky,
                                          int c0, int r0, const float* coef, Taps& t) {
-  const double tu = double(omu) * su, tv = double(omv) * sv;
+  double tu = double(omu) * su, tv = double(omv) * sv;
+  t.conj = mirrored(tu);
+  tu = t.conj ? -tu : tu;
+  tv = t.conj ? -tv : tv;
   const double fu = floor(tu), fv = floor(tv);
-  const int cu0 = (int(fu) - 3) & (Kx - 1);
+  const int pu0 = int(fu) - 3 + GRID_PAD;
   const int cv0 = (int(fv) - 3) & (Ky - 1);
-  t.ou = min(max(cu0 - c0, 0), T - 1);
+  t.ou = min(max(pu0 - c0, 0), T - 1);
   t.ov = min(max(cv0 - r0, 0), T - 1);
   kb_weights(float(tu - fu), coef, t.wx);
   kb_weights(float(tv - fv), coef, t.wy);
@@ -89,10 +95,23 @@ struct DegridCfg {
 constexpr int G8_RS = 18;
 constexpr int G8_COPY = 15 * G8_RS;   // float2 per copy
 
-__device__ __forceinline__ void stage8(float2* reg2, int e, float2 g) {
-  const int a = e / 15, b = e - a * 15;
-  reg2[a * G8_RS + b] = g;
-  if (b > 0) reg2[G8_COPY + a * G8_RS + b - 1] = g;
+// The 16 x 15 cells a region's 4 column blocks hold are staged two columns at
+// a time (16-byte loads, consecutive within a block); pair e is block e / 30,
+// row (e mod 30) / 2.  The 16th column is beyond every tap.
+constexpr int G8_PAIRS = 4 * 15 * 2;
+static_assert(FFT_CB == 4 && GRID_PAD == 8, "a tile's region starts on a column block");
+
+__device__ __forceinline__ float4 load_pair8(const float2* __restrict__ grid, int e, int c0, int r0, int Ky) {
+  const int blk = e / 30, w = e - blk * 30;
+  return *reinterpret_cast<const float4*>(grid + grid_index(c0 + 4 * blk + 2 * (w & 1), (r0 + (w >> 1)) & (Ky - 1), Ky));
+}
+
+__device__ __forceinline__ void stage8(float2* reg2, int e, float4 g) {
+  const int blk = e / 30, w = e - blk * 30;
+  const int b = 4 * blk + 2 * (w & 1), o = (w >> 1) * G8_RS + b;
+  *reinterpret_cast<float4*>(reg2 + o) = g;
+  if (b > 0) reg2[G8_COPY + o - 1] = make_float2(g.x, g.y);
+  reg2[G8_COPY + o] = make_float2(g.z, g.w);
 }
 
 __device__ __forceinline__ float2 gather8(const float2* reg2, const Taps& t) {
@@ -129,7 +148,7 @@ __device__ __forceinline__ float2 gather8(const float2* reg2, const Taps& t) {
 
 template <int T, bool DUAL>
 __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
-    const float2* __restrict__ grid, int Kx, int Ky, const Item* __restrict__ items, int n_items,
+    const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
     float2* __restrict__ out, const float2* __restrict__ y, const double* __restrict__ U,
@@ -148,14 +167,20 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
   const int lane = threadIdx.x & 63;
   const int uwid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   // staging: all of the thread's loads are issued before its LDS stores
-  constexpr int RPT = (R * R + 64 * NW - 1) / (64 * NW);
-  float2 gv[RPT];
+  constexpr int CELLS = B128 ? G8_PAIRS : R * R;
+  constexpr int RPT = (CELLS + 64 * NW - 1) / (64 * NW);
+  using Cell = std::conditional_t<B128, float4, float2>;
+  Cell gv[RPT];
 #pragma unroll
   for (int k = 0; k < RPT; ++k) {
     const int i = threadIdx.x + k * 64 * NW;
-    if (i < R * R) {
-      const int a = i / R, b = i - a * R;
-      gv[k] = grid[size_t((r0 + a) & (Ky - 1)) * Kx + ((c0 + b) & (Kx - 1))];
+    if (i < CELLS) {
+      if constexpr (B128) {
+        gv[k] = load_pair8(grid, i, c0, r0, Ky);
+      } else {
+        const int a = i / R, b = i - a * R;
+        gv[k] = c0 + b < PW ? grid[grid_index(c0 + b, (r0 + a) & (Ky - 1), Ky)] : make_float2(0.f, 0.f);
+      }
     }
   }
   load_item_tab(it, segs, tab);
@@ -169,7 +194,7 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
 #pragma unroll
   for (int k = 0; k < RPT; ++k) {
     const int i = threadIdx.x + k * 64 * NW;
-    if (i < R * R) {
+    if (i < CELLS) {
       if constexpr (B128) stage8(reg, i, gv[k]);
       else reg[i] = gv[k];
     }
@@ -221,7 +246,7 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
       const double Ue = DUAL ? cb.U : 1.0;
       const double2 ze = cb.z;
       Taps t;
-      taps_for<T>(omu, omv, su, sv, Kx, Ky, c0, r0, kbw.c, t);
+      taps_for<T>(omu, omv, su, sv, Ky, c0, r0, kbw.c, t);
       float ax = 0.f, ay = 0.f;
       if constexpr (B128) {
         const float2 s2 = gather8(reg, t);
@@ -244,7 +269,7 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
           ay = fmaf(wya, sy, ay);
         }
       }
-      const float2 g = make_float2(ax * th, ay * th);
+      const float2 g = make_float2(ax * th, (t.conj ? -ay : ay) * th);
       if (!DUAL) {
         out[pi] = g;
       } else {
@@ -386,7 +411,7 @@ struct GridCfg {
 
 template <int T, bool DUAL>
 __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
-    float2* __restrict__ scratch, int Kx, int Ky, const Item* __restrict__ items, int n_items,
+    float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
     const float2* __restrict__ vin, const float2* __restrict__ y, const double* __restrict__ U,
@@ -441,10 +466,10 @@ __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
     float vx = 0.f, vy = 0.f;
     Taps t;
     if (lane < nb) {
-      taps_for<T>(bt.ou, bt.ov, su, sv, Kx, Ky, c0, r0, kbw.c, t);
+      taps_for<T>(bt.ou, bt.ov, su, sv, Ky, c0, r0, kbw.c, t);
       const float2 val = grid_value<DUAL>(bt, mu, lambda, exact, znew, vnew);
       vx = val.x * bt.th;
-      vy = val.y * bt.th;
+      vy = (t.conj ? -val.y : val.y) * bt.th;
       pos = t.ov * RS + t.ou;
     } else {
 #pragma unroll
@@ -553,154 +578,9 @@ __device__ __forceinline__ void tab_from_seg(const Seg& sg, int lane, ItemTab& t
   if (lane == 0) tab.pre[0] = 0;
 }
 
-// Degridding of 8 x 8 tiles with the dual update by single-wave workgroups
-// that each take a run of PPD_DEGRID_RUN consecutive items (0: one item per
-// workgroup, k_degrid, which also serves plain Phi).
-// The next item's region and segment list are loaded into registers while
-// the current item is worked on; per-segment sums are kept by the lane of
-// the segment (same order as k_degrid's).
-__global__ __launch_bounds__(64) void k_degrid8(
-    const float2* __restrict__ grid, int Kx, int Ky, const Item* __restrict__ items, int n_items,
-    const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
-    const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
-    const float2* __restrict__ y, const double* __restrict__ U,
-    const float2* __restrict__ v, const double2* __restrict__ z, float2* __restrict__ gout, double mu,
-    double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
-  constexpr int T = 8, R = T + 7, RUN = PPD_DEGRID_RUN > 0 ? PPD_DEGRID_RUN : 1;
-  constexpr int RPT = (R * R + 63) / 64;
-  static_assert(RUN <= 64, "a run's items are held one per lane");
-  __shared__ float2 reg[R * R];
-  __shared__ ItemTab tab;
-  const int unit = xcd_unit(blockIdx.x, xs);
-  if (unit < 0) return;
-  const int i0 = unit * RUN;
-  if (i0 >= n_items) return;
-  const int i1 = min(i0 + RUN, n_items);
-  const int lane = threadIdx.x;
-  Item itl{0, 0, 0, 0};
-  if (i0 + lane < i1) itl = items[i0 + lane];
-  auto field = [&](int f, int i) { return __builtin_amdgcn_readlane(f, i - i0); };
-  float2 gv[RPT];
-  auto region = [&](int i) {
-    const int r0 = field(itl.ty, i) * T, c0 = field(itl.tx, i) * T;
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-      const int e = lane + k * 64;
-      if (e < R * R) {
-        const int a = e / R, b = e - a * R;
-        gv[k] = grid[size_t((r0 + a) & (Ky - 1)) * Kx + ((c0 + b) & (Kx - 1))];
-      }
-    }
-  };
-  region(i0);
-  Seg sgn = item_seg(segs, field(itl.seg0, i0), field(itl.seg1, i0), lane);
-  KbCoef kbw;
-  load_kb(kbc, kbw);
-  struct Batch {
-    float ou, ov, th;
-    float2 v, y;
-    double2 z;
-    double U;
-    int pi, sg, sb;
-  };
-  for (int cur = i0; cur < i1; ++cur) {
-    // the previous item's LDS reads are done (program order within the wave)
-    tab_from_seg(sgn, lane, tab);
-#pragma unroll
-    for (int k = 0; k < RPT; ++k)
-      if (lane + k * 64 < R * R) reg[lane + k * 64] = gv[k];
-    __builtin_amdgcn_wave_barrier();
-    const int r0 = field(itl.ty, cur) * T, c0 = field(itl.tx, cur) * T;
-    const int seg0 = field(itl.seg0, cur), nseg = field(itl.seg1, cur) - seg0;
-    const int total = __builtin_amdgcn_readfirstlane(tab.pre[nseg]);
-    auto load = [&](int bt, int& sb, Batch& b) {
-      while (bt * 64 >= tab.pre[sb + 1]) ++sb;
-      b.sb = sb;
-      const int li = bt * 64 + lane;
-      b.sg = sb;
-      if (li < total) {
-        b.sg = seg_of(li, sb, tab.pre);
-        b.pi = tab.start[b.sg] + (li - tab.pre[b.sg]);
-        b.ou = wu[b.pi];
-        b.ov = wv[b.pi];
-        b.th = theta ? theta[b.pi] : 1.0f;
-        b.v = v[b.pi];
-        b.U = U[b.pi];
-        b.z = z[b.pi];
-        b.y = y[b.pi];
-      }
-    };
-    int sbl = 0;
-    Batch bn{};
-    if (total > 0) load(0, sbl, bn);
-    // the next item's region and segments, behind this item's first batch
-    if (cur + 1 < i1) {
-      region(cur + 1);
-      sgn = item_seg(segs, field(itl.seg0, cur + 1), field(itl.seg1, cur + 1), lane);
-    }
-    double q_acc = 0.0, r_acc = 0.0;   // lane s: segment s of the item
-    for (int bt = 0; bt * 64 < total; ++bt) {
-      const Batch cb = bn;
-      if ((bt + 1) * 64 < total) load(bt + 1, sbl, bn);
-      const int li = bt * 64 + lane;
-      const bool act = li < total;
-      const int sb = __builtin_amdgcn_readfirstlane(cb.sb), sg = cb.sg, pi = cb.pi;
-      double qn = 0.0, rn = 0.0;
-      if (act) {
-        Taps t;
-        taps_for<T>(cb.ou, cb.ov, su, sv, Kx, Ky, c0, r0, kbw.c, t);
-        // 8-byte gathers: the 16-byte form of k_degrid took this kernel to
-        // 158 VGPRs (3 waves per SIMD) and was not faster here
-        float ax = 0.f, ay = 0.f;
-#pragma unroll
-        for (int a = 0; a < KB_TAPS; ++a) {
-          const float2* row = reg + (t.ov + a) * R + t.ou;
-          float sx = 0.f, sy = 0.f;
-#pragma unroll
-          for (int b = 0; b < KB_TAPS; ++b) {
-            const float2 g = row[b];
-            sx = fmaf(t.wx[b], g.x, sx);
-            sy = fmaf(t.wx[b], g.y, sy);
-          }
-          const float wya = a == 0 ? t.wy[0] : a == 1 ? t.wy[1] : a == 2 ? t.wy[2] : a == 3 ? t.wy[3]
-                          : a == 4 ? t.wy[4] : a == 5 ? t.wy[5] : a == 6 ? t.wy[6] : t.wy[7];
-          ax = fmaf(wya, sx, ax);
-          ay = fmaf(wya, sy, ay);
-        }
-        // the data-dual argument of Algorithm 3 and the first Algorithm 2 step, as in
-        // k_degrid
-        const float2 g = make_float2(ax * cb.th, ay * cb.th);
-        gout[pi] = g;
-        const double Ue = cb.U;
-        const double2 we = dual_arg(cb.v, Ue, g), ze = cb.z;
-        const double mU = mu * Ue;
-        const double dx = (ze.x - mU * (ze.x - we.x)) - double(cb.y.x);
-        const double dy = (ze.y - mU * (ze.y - we.y)) - double(cb.y.y);
-        qn = dx * dx + dy * dy;
-        const double ex = double(g.x) - double(cb.y.x), ey = double(g.y) - double(cb.y.y);
-        rn = ex * ex + ey * ey;
-      }
-      const int slast = __builtin_amdgcn_readlane(sg, min(63, total - 1 - bt * 64));
-      for (int ss = sb; ss <= slast; ++ss) {
-        const double a = part ? wave_sum(act && sg == ss ? qn : 0.0) : 0.0;   // Algorithm 2 only
-        const double r = rpart ? wave_sum(act && sg == ss ? rn : 0.0) : 0.0;   // statistics only
-        if (lane == ss) {
-          q_acc += a;
-          r_acc += r;
-        }
-      }
-    }
-    if (lane < nseg) {
-      if (part) part[seg0 + lane] = q_acc;
-      if (rpart) rpart[seg0 + lane] = r_acc;
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
 template <bool DUAL>
 __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
-    float2* __restrict__ scratch, int Kx, int Ky, const Item* __restrict__ items, int n_items,
+    float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
     const float2* __restrict__ vin, const float2* __restrict__ y, const double* __restrict__ U,
@@ -765,10 +645,10 @@ __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
     const int pi = bn.pi;
     const bool zst = DUAL && has && bn.act;
     if (has) {
-      taps_for<T>(bn.ou, bn.ov, su, sv, Kx, Ky, c0, r0, kbw.c, t);
+      taps_for<T>(bn.ou, bn.ov, su, sv, Ky, c0, r0, kbw.c, t);
       const float2 val = grid_value<DUAL>(bn, mu, lambda, exact, znew, vnew);
       vx = val.x * bn.th;
-      vy = val.y * bn.th;
+      vy = (t.conj ? -val.y : val.y) * bn.th;
     }
     // stores before the next step's loads: vector memory operations
     // complete in issue order, so the wait for those loads does not add a
@@ -891,7 +771,7 @@ __device__ __forceinline__ void fold_items(const float2* __restrict__ scratch, i
 template <int T>
 __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ scratch,
                                                      const int32_t* __restrict__ tio, int tiles_x,
-                                                     int tiles_y, int Kx, float2* __restrict__ grid) {
+                                                     int tiles_y, int PW, int Ky, float2* __restrict__ grid) {
   constexpr int R = T + 7;
   constexpr int PARTS = (T * T) / FOLD_CELLS;
   static_assert(PARTS >= 1 && T > 7, "whole workgroups per tile; a cell lies in at most 4 tile regions");
@@ -910,7 +790,7 @@ __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ 
     fold_items(scratch, R * R, (T + a) * R + b, tio[tu], tio[tu + 1], sx, sy);
     if (b < 7) fold_items(scratch, R * R, (T + a) * R + T + b, tio[tul], tio[tul + 1], sx, sy);
   }
-  grid[size_t(ty * T + a) * Kx + (tx * T + b)] = make_float2(sx, sy);
+  if (tx * T + b < PW) grid[grid_index(tx * T + b, ty * T + a, Ky)] = make_float2(sx, sy);
 }
 
 // 8 x 8 tiles, 4-wave workgroups in the plan's fold order (tile rows spread
@@ -939,7 +819,7 @@ __device__ __forceinline__ void fold_items4(const float2* __restrict__ scratch, 
 }
 
 __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratch, const int32_t* __restrict__ tio,
-                                                const int4* __restrict__ wgs, int tiles_x, int tiles_y, int Kx,
+                                                const int4* __restrict__ wgs, int tiles_x, int tiles_y, int Ky,
                                                 float2* __restrict__ grid) {
   constexpr int T = 8, R = T + 7;
   __shared__ float2 part[4][64];
@@ -960,7 +840,7 @@ __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratc
       fold_items(scratch, R * R, (T + a) * R + b, tio[tu], tio[tu + 1], sx, sy);
       if (b < 7) fold_items(scratch, R * R, (T + a) * R + T + b, tio[tul], tio[tul + 1], sx, sy);
     }
-    grid[size_t(ty * T + a) * Kx + (tx * T + b)] = make_float2(sx, sy);
+    grid[grid_index(tx * T + b, ty * T + a, Ky)] = make_float2(sx, sy);
     return;
   }
   fold_items4(scratch, R * R, a * R + b, tio[t] + w, tio[t + 1], sx, sy);
@@ -973,7 +853,7 @@ __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratc
   __syncthreads();
   if (w == 0) {
     const float2 p0 = part[0][c], p1 = part[1][c], p2 = part[2][c], p3 = part[3][c];
-    grid[size_t(ty * T + a) * Kx + (tx * T + b)] =
+    grid[grid_index(tx * T + b, ty * T + a, Ky)] =
         make_float2(((p0.x + p1.x) + p2.x) + p3.x, ((p0.y + p1.y) + p2.y) + p3.y);
   }
 }
@@ -990,23 +870,14 @@ __global__ void k_permute(const int32_t* __restrict__ perm, int64_t M, int to_us
 
 template <int T>
 int launch_degrid(ppd_plan* p, bool dual, float2* out, const DualArgs* a, double* part_out) {
-  // runs for the fused dual pass only: plain Phi is faster one item per
-  // workgroup (27.4 against 29.7 us at 512^2, M = 1.3M)
-  if (T == 8 && PPD_DEGRID_RUN > 0 && dual) {
-    hipLaunchKernelGGL(k_degrid8, dim3(p->split_degrid.launch), dim3(64), 0, p->stream, p->grid_f, p->Kx, p->Ky,
-                       p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
-                       a->y, a->U, a->v, a->z, p->gabuf, a->mu, part_out, a->rpart, p->split_degrid);
-    PPD_HIP(hipGetLastError());
-    return PPD_OK;
-  }
   if (!dual) {
     hipLaunchKernelGGL((k_degrid<T, false>), dim3(p->split1.launch), dim3(64 * DegridCfg<T>::NW), 0, p->stream,
-                       p->grid_f, p->Kx, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
+                       p->grid_f, p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
                        p->sv_scale, p->kbc, out, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0,
                        nullptr, nullptr, p->split1);
   } else {
     hipLaunchKernelGGL((k_degrid<T, true>), dim3(p->split1.launch), dim3(64 * DegridCfg<T>::NW), 0, p->stream,
-                       p->grid_f, p->Kx, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
+                       p->grid_f, p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
                        p->sv_scale, p->kbc, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
                        part_out, a->rpart, p->split1);
   }
@@ -1017,12 +888,12 @@ int launch_degrid(ppd_plan* p, bool dual, float2* out, const DualArgs* a, double
 int launch_grid_mfma(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, int exact) {
   if (!dual) {
     hipLaunchKernelGGL((k_grid_mfma<false>), dim3(p->split_grid.launch), dim3(64 * PPD_GRIDM_WPG), 0, p->stream,
-                       p->gscratch, p->Kx, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta,
+                       p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta,
                        p->su_scale, p->sv_scale, p->kbc, vin, nullptr, nullptr, nullptr, nullptr, nullptr,
                        0.0, 0.0, nullptr, 0, nullptr, p->split_grid);
   } else {
     hipLaunchKernelGGL((k_grid_mfma<true>), dim3(p->split_grid.launch), dim3(64 * PPD_GRIDM_WPG), 0, p->stream,
-                       p->gscratch, p->Kx, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta,
+                       p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta,
                        p->su_scale, p->sv_scale, p->kbc, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
                        a->lambda, p->bfac, exact, a->active, p->split_grid);
   }
@@ -1034,12 +905,12 @@ template <int T>
 int launch_grid(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, int exact) {
   if (!dual) {
     hipLaunchKernelGGL((k_grid<T, false>), dim3(p->split1.launch), dim3(GridCfg<T>::THREADS), 0, p->stream,
-                       p->gscratch, p->Kx, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
+                       p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
                        p->sv_scale, p->kbc, vin, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0,
                        0.0, nullptr, 0, nullptr, p->split1);
   } else {
     hipLaunchKernelGGL((k_grid<T, true>), dim3(p->split1.launch), dim3(GridCfg<T>::THREADS), 0, p->stream,
-                       p->gscratch, p->Kx, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
+                       p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
                        p->sv_scale, p->kbc, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
                        a->lambda, p->bfac, exact, a->active, p->split1);
   }
@@ -1052,14 +923,14 @@ int launch_fold(ppd_plan* p) {
   const int n = p->n_tiles * ((T * T) / FOLD_CELLS);
   const int nl = ((n + MAX_XCD - 1) / MAX_XCD) * MAX_XCD;
   hipLaunchKernelGGL(k_fold<T>, dim3(nl), dim3(FOLD_CELLS), 0, p->stream, p->gscratch,
-                     p->tile_item_off, p->tiles_x, p->tiles_y, p->Kx, p->grid_a);
+                     p->tile_item_off, p->tiles_x, p->tiles_y, p->PW, p->Ky, p->grid_a);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
 
 int launch_fold8(ppd_plan* p) {
   hipLaunchKernelGGL(k_fold8, dim3(p->n_fold_wg), dim3(256), 0, p->stream, p->gscratch, p->tile_item_off,
-                     reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x, p->tiles_y, p->Kx, p->grid_a);
+                     reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x, p->tiles_y, p->Ky, p->grid_a);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }

@@ -180,11 +180,6 @@ int upload_eps(ppd_plan* p, const double* eps_host) {
 using namespace ppd;
 
 static bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
-static int ilog2(int64_t v) {
-  int l = 0;
-  while ((int64_t(1) << l) < v) ++l;
-  return l;
-}
 
 constexpr size_t WS_ALIGN = 256;
 
@@ -301,14 +296,13 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   p->ny = D.ny;
   p->Kx = 2 * D.nx;
   p->Ky = 2 * D.ny;
-  p->log2Kx = ilog2(p->Kx);
-  p->log2Ky = ilog2(p->Ky);
   p->M = D.M;
   p->d = D.d;
   p->levels = levels;
   p->T = std::min(T, std::min(p->Kx, p->Ky));
   p->chunk_max = chunk_max;
-  p->tiles_x = p->Kx / p->T;
+  p->PW = p->Kx / 2 + 2 * GRID_PAD;
+  p->tiles_x = (p->PW + p->T - 1) / p->T;
   p->tiles_y = p->Ky / p->T;
   p->beta = D.kb_beta > 0.0 ? D.kb_beta : M_PI * std::sqrt(35.2);
   p->su_scale = double(p->Kx) / (2.0 * M_PI);
@@ -322,34 +316,44 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   // ---- binning: counting sort by tile inside every block -------------------
   const int64_t M = D.M;
   const int ntiles = p->tiles_x * p->tiles_y;
-  std::vector<int32_t> key(M), cell(M);
+  std::vector<int32_t> key(M);
+  std::vector<uint16_t> cell(M);   // first-tap cell within the tile, row-major
   for (int64_t i = 0; i < M; ++i) {
-    const double tu = double(D.omega_u[i]) * p->su_scale;
-    const double tv = double(D.omega_v[i]) * p->sv_scale;
-    const int cu0 = (int(std::floor(tu)) - 3) & (p->Kx - 1);
+    double tu = double(D.omega_u[i]) * p->su_scale;
+    double tv = double(D.omega_v[i]) * p->sv_scale;
+    if (mirrored(tu)) {
+      tu = -tu;
+      tv = -tv;
+    }
+    const int pu0 = int(std::floor(tu)) - 3 + GRID_PAD;   // 0 .. Kx/2 + GRID_PAD - 4
     const int cv0 = (int(std::floor(tv)) - 3) & (p->Ky - 1);
-    key[i] = (cv0 / p->T) * p->tiles_x + (cu0 / p->T);
-    cell[i] = cv0 * p->Kx + cu0;
+    key[i] = (cv0 / p->T) * p->tiles_x + (pu0 / p->T);
+    cell[i] = uint16_t((cv0 % p->T) * p->T + pu0 % p->T);
   }
   p->perm_host.resize(M);
   std::vector<int64_t> cnt(ntiles + 1);
   // bins (block j, tile t) -> plan range, collected per tile in block order
   struct Bin { int64_t start, count; int32_t block; };
   std::vector<std::vector<Bin>> tile_bins(ntiles);
+  std::vector<int32_t> by_cell;
+  std::vector<int64_t> ccnt(p->T * p->T + 1);
   for (int j = 0; j < p->d; ++j) {
     const int64_t b0 = p->block_off[j], b1 = p->block_off[j + 1];
-    std::fill(cnt.begin(), cnt.end(), 0);
-    for (int64_t i = b0; i < b1; ++i) cnt[key[i] + 1]++;
-    for (int t = 0; t < ntiles; ++t) cnt[t + 1] += cnt[t];
-    std::vector<int64_t> pos(cnt.begin(), cnt.end() - 1);
-    for (int64_t i = b0; i < b1; ++i) p->perm_host[b0 + pos[key[i]]++] = int32_t(i);
     // inside each bin, order by first-tap cell (row-major within the tile):
-    // neighbouring lanes then touch neighbouring cells
-    for (int t = 0; t < ntiles; ++t) {
-      int32_t* a = p->perm_host.data() + b0 + cnt[t];
-      std::stable_sort(a, a + (cnt[t + 1] - cnt[t]),
-                       [&](int32_t x, int32_t y) { return cell[x] < cell[y]; });
+    // neighbouring lanes then touch neighbouring cells.  Two stable counting
+    // passes, by cell and then by tile.
+    std::fill(ccnt.begin(), ccnt.end(), 0);
+    std::fill(cnt.begin(), cnt.end(), 0);
+    for (int64_t i = b0; i < b1; ++i) {
+      ccnt[cell[i] + 1]++;
+      cnt[key[i] + 1]++;
     }
+    std::partial_sum(ccnt.begin(), ccnt.end(), ccnt.begin());
+    std::partial_sum(cnt.begin(), cnt.end(), cnt.begin());
+    by_cell.resize(b1 - b0);
+    for (int64_t i = b0; i < b1; ++i) by_cell[ccnt[cell[i]]++] = int32_t(i);
+    std::vector<int64_t> pos(cnt.begin(), cnt.end() - 1);
+    for (const int32_t i : by_cell) p->perm_host[b0 + pos[key[i]]++] = i;
     for (int t = 0; t < ntiles; ++t)
       if (cnt[t + 1] > cnt[t]) tile_bins[t].push_back({b0 + cnt[t], cnt[t + 1] - cnt[t], j});
   }
@@ -474,7 +478,6 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
       return sp;
     };
     p->split1 = split(1);
-    p->split_degrid = split(PPD_DEGRID_RUN > 0 ? PPD_DEGRID_RUN : 1);
     p->split_grid = split(PPD_GRIDM_RUN * PPD_GRIDM_WPG);
   }
   p->n_tile_launch = ((ntiles + MAX_XCD - 1) / MAX_XCD) * MAX_XCD;
@@ -507,15 +510,7 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   std::vector<float> dpx(p->nx), dpy(p->ny);
   for (int c = 0; c < p->nx; ++c) dpx[c] = float(1.0 / kb_ft(double(c - p->nx / 2) / p->Kx, p->beta));
   for (int r = 0; r < p->ny; ++r) dpy[r] = float(1.0 / kb_ft(double(r - p->ny / 2) / p->Ky, p->beta));
-  auto twiddles = [](int K) {
-    std::vector<float2> t(K / 2);
-    for (int k = 0; k < K / 2; ++k) {
-      const double a = -2.0 * M_PI * double(k) / double(K);
-      t[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
-    }
-    return t;
-  };
-  std::vector<float2> twx = twiddles(p->Kx), twy = twiddles(p->Ky);
+  const std::vector<float2> twx = fft_twiddles(p->Kx).row, twy = fft_twiddles(p->Ky).col;
   std::vector<float> filt(8 * 2 * FILT_STRIDE, 0.0f);
   for (int q = 1; q <= 8; ++q) {
     double h[FILT_STRIDE];
@@ -564,7 +559,7 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   }
 
   // ---- device memory -----------------------------------------------------------
-  const size_t K2 = size_t(p->Kx) * p->Ky;
+  const size_t K2 = size_t(p->PW) * p->Ky;
   const size_t N = size_t(p->nx) * p->ny;
   int st = PPD_OK;
   auto A = [&](int s) { if (st == PPD_OK) st = s; };
@@ -585,13 +580,13 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   A(dalloc(p, &p->kbc, KB_TAPS * KB_NC));
   A(dalloc(p, &p->dpx, p->nx));
   A(dalloc(p, &p->dpy, p->ny));
-  A(dalloc(p, &p->twx, p->Kx / 2));
-  A(dalloc(p, &p->twy, p->Ky / 2));
+  A(dalloc(p, &p->twx, twx.size()));
+  A(dalloc(p, &p->twy, twy.size()));
   A(dalloc(p, &p->filt, filt.size()));
   A(dalloc(p, &p->grid_f, K2));
   A(dalloc(p, &p->grid_a, K2));
-  A(dalloc(p, &p->half, size_t(p->ny) * p->Kx));
-  A(dalloc(p, &p->half_f, size_t(p->ny) * p->Kx));
+  A(dalloc(p, &p->half, size_t(p->ny) * p->Kx / 2));
+  A(dalloc(p, &p->half_f, size_t(p->ny) * p->Kx / 2));
   A(dalloc(p, &p->ybuf, M));
   A(dalloc(p, &p->wbuf, M));
   A(dalloc(p, &p->gabuf, M));

@@ -55,13 +55,6 @@ constexpr uint64_t PA_EMPTY = 0x7ff8000000000000ull;   // quiet NaN: no partial 
 #define PPD_FOLD_HEAVY 16
 #endif
 constexpr int FOLD_HEAVY = PPD_FOLD_HEAVY;   // item regions above which a tile's fold takes a whole workgroup
-// Work items per workgroup of the 8 x 8 degridding with the dual update:
-// 0 takes one item per single-wave workgroup in k_degrid<8, DUAL> (88
-// VGPRs, 5 waves per SIMD), n > 0 runs of n items in k_degrid8 (107 VGPRs,
-// 4 waves per SIMD), which the lighter SARA branch no longer repays.
-#ifndef PPD_DEGRID_RUN
-#define PPD_DEGRID_RUN 0
-#endif
 #ifndef PPD_GRIDM_RUN
 #define PPD_GRIDM_RUN 2
 #endif
@@ -82,6 +75,48 @@ constexpr int GRAPH_RUN = PPD_GRAPH_RUN;
 #ifndef PPD_GRIDM_READ_AHEAD
 #define PPD_GRIDM_READ_AHEAD 2
 #endif
+
+// The spectrum of the (real) image is Hermitian, so the grids hold the columns
+// c = -GRID_PAD .. Kx/2 + GRID_PAD - 1 only, at padded index c + GRID_PAD: the
+// columns 0 .. Kx/2 and, beyond either end, the mirror images that taps reach.
+// A visibility whose first tap lies left of -GRID_PAD is taken at its mirror
+// frequency, conjugated (see mirrored).  8 columns of padding leave the points
+// around the v axis, of either sign, unmirrored in one tile column.
+constexpr int GRID_PAD = 8;
+// Columns per block of the grids and of the row-pass buffers: a block holds
+// all rows of FFT_CB columns, row by row, so a column pass on a block, and the
+// region of an 8 x 8 tile, are runs of consecutive addresses.
+constexpr int FFT_CB = 4;
+__host__ __device__ __forceinline__ size_t grid_index(int p, int row, int Ky) {
+  return (size_t(p / FFT_CB) * Ky + row) * FFT_CB + p % FFT_CB;
+}
+__host__ __device__ __forceinline__ size_t half_index(int c, int row, int ny) { return grid_index(c, row, ny); }
+// Whether a visibility at u grid coordinate tu (K omega_u / 2 pi) is gridded
+// at its mirror frequency: its first tap floor(tu) - 3 is left of -GRID_PAD.
+__host__ __device__ __forceinline__ bool mirrored(double tu) { return tu < 3.0 - GRID_PAD; }
+
+// Elements per thread of a row and of a column transform of length L, and
+// columns per workgroup (more where that is less than a wave).  Short
+// transforms leave the chip nearly empty (64 to 512 sequences), so they take
+// few elements per thread, which shortens every wave's chain of dependent work:
+// rows with the primal update, L = 1024: 12.6 / 9.0 / 8.0 us at 16 / 8 / 4
+// elements; columns 6.7 us at any of these, 5.4 us with 2 instead of 4 columns
+// per workgroup (twice the workgroups).  From L = 2048 on the chip is full and
+// fewer, larger stages win: columns at L = 4096 (2048^2), in SQ busy cycles,
+// 1.76M / 2.33M forward at 16 elements and 4 columns / 8 and 2, rows 2.93M /
+// 2.74M at 16 / 8 elements.
+template <int L>
+struct FftShape {
+  static constexpr int ROW_E = L <= 1024 ? 4 : 8;
+  static constexpr int COL_E = L <= 1024 ? 4 : L == 2048 ? 8 : 16;
+  static constexpr int COL_C = L <= 2048 ? 2 : 4;
+};
+// Two exchange buffers where a workgroup's LDS then still leaves room for a
+// second workgroup on the compute unit (160 KB).
+constexpr int FFT_TWO_LDS = 80 * 1024;
+struct FftTwiddles {
+  std::vector<float2> row, col;   // in the order the threads of a transform read them
+};
 
 // Launch order of the work items over the XCDs: the items, in spatial
 // order, are cut into 8 contiguous bands of near-equal work (64-point
@@ -119,7 +154,8 @@ const char* kernel_kind_name(int k);
 
 struct ppd_plan {
   // geometry
-  int nx = 0, ny = 0, Kx = 0, Ky = 0, log2Kx = 0, log2Ky = 0;
+  int nx = 0, ny = 0, Kx = 0, Ky = 0;
+  int PW = 0;                              // grid columns held: Kx/2 + 2 GRID_PAD
   int64_t M = 0;
   int d = 0, levels = 3, T = 32, chunk_max = 1024;
   int tiles_x = 0, tiles_y = 0;
@@ -141,7 +177,7 @@ struct ppd_plan {
   std::vector<ppd::Seg> segs_host;
   std::vector<int32_t> bseg_off;           // [d+1] into bseg_ids
   int n_items = 0, n_segs = 0;
-  ppd::XcdSplit split1{}, split_degrid{}, split_grid{};   // 1, PPD_DEGRID_RUN, PPD_GRIDM_RUN x WPG items per workgroup
+  ppd::XcdSplit split1{}, split_grid{};   // 1, PPD_GRIDM_RUN x WPG items per workgroup
   int n_tiles = 0, n_tile_launch = 0;
 
   // device: coverage and plan tables
@@ -161,15 +197,15 @@ struct ppd_plan {
   float* kbc = nullptr;                    // [8][10] tap polynomials
   float* dpx = nullptr;                    // [nx] 1/phi_hat(n_c / Kx)
   float* dpy = nullptr;                    // [ny] 1/phi_hat(n_r / Ky)
-  float2* twx = nullptr;                   // [Kx/2] exp(-2 pi i k / Kx)
-  float2* twy = nullptr;                   // [Ky/2]
+  float2* twx = nullptr;                   // row transform's twiddles (fft_twiddles(Kx).row)
+  float2* twy = nullptr;                   // column transform's (fft_twiddles(Ky).col)
   float* filt = nullptr;                   // [8][2][16] lo / hi Daubechies filters
 
   // device: work buffers
-  float2* grid_f = nullptr;                // forward spectrum  Ky x Kx
-  float2* grid_a = nullptr;                // adjoint accumulation Ky x Kx
-  float2* half = nullptr;                  // ny x Kx intermediate
-  float2* half_f = nullptr;                // ny x Kx forward row pass of x~ (iterations)
+  float2* grid_f = nullptr;                // forward spectrum, Ky x PW (grid_index)
+  float2* grid_a = nullptr;                // adjoint accumulation, Ky x PW
+  float2* half = nullptr;                  // ny x Kx/2 row-pass intermediate (half_index)
+  float2* half_f = nullptr;                // ny x Kx/2 forward row pass of x~ (iterations)
   float2* ybuf = nullptr;                  // [M] complex64 scratch
   double2* wbuf = nullptr;                 // [M] complex128 w (plain form)
   float2* gabuf = nullptr;                 // [M] complex64 Theta G a (fused form; w is rebuilt from it)
@@ -244,8 +280,8 @@ int timer_end(ppd_plan* p, int slot);
 
 // ---- component launchers (each returns a PPD_* status) -------------------
 int fft_forward(ppd_plan* p, const float* x);                  // x -> grid_f (via half)
-int fft_rows_forward(ppd_plan* p, const float* x, float2* dst);  // x -> dst (ny x Kx)
-int fft_cols_forward(ppd_plan* p, const float2* src);           // src (ny x Kx) -> grid_f
+int fft_rows_forward(ppd_plan* p, const float* x, float2* dst);  // x -> dst (row-pass buffer)
+int fft_cols_forward(ppd_plan* p, const float2* src);           // src (row-pass buffer) -> grid_f
 int fft_adjoint(ppd_plan* p, float* x);                        // grid_a -> x (plain)
 int fft_cols_inverse(ppd_plan* p);                             // grid_a -> half
 struct PrimalArgs {
@@ -253,8 +289,8 @@ struct PrimalArgs {
   double tau, eta, zeta, lambda;
   double* part;                    // [ny][4] statistics partials, or NULL to skip them
 };
-// half -> primal update; with next != NULL also the forward row pass of the
-// new x~ into next (ny x Kx)
+// half -> primal update and the forward row pass of the new x~ into next
+// (row-pass buffer)
 int fft_rows_inverse_primal(ppd_plan* p, const PrimalArgs& a, float2* next);
 int fold_grid(ppd_plan* p);                                    // gscratch -> grid_a
 
@@ -303,6 +339,7 @@ int upload_eps(ppd_plan* p, const double* eps_host);
 void kb_tap_polynomials(double beta, float* coef /* [8][KB_NC] */);
 double kb_ft(double xi, double beta);
 void daubechies(int p, double* h);
+FftTwiddles fft_twiddles(int L);
 
 }  // namespace ppd
 
