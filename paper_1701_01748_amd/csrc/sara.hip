@@ -3,26 +3,50 @@
 // the Mallat layout of the image.  Float32.
 //
 // Analysis runs one launch per level for the 8 wavelet bases at once
-// (one grid dimension per basis; the Dirac basis rides in the first launch): a
-// workgroup stages the periodic input region of its output tile in LDS,
-// filters the columns, then the rows, and writes the four sub-bands.  In
-// the dual mode (the sparsity dual update of Algorithm 3) every final coefficient c is
-// consumed in place: u <- u + lambda (clip(u + c, +-alpha) - u).
-// Synthesis is the transpose, one launch per level; the last level sums the
-// 8 reconstructions and the Dirac part in registers (no atomics) and applies
-// the 1/3.
+// (one grid dimension per basis; the Dirac basis rides in the first launch).
+// In the dual mode (the sparsity dual update of Algorithm 3) every final
+// coefficient c is consumed in place: u <- u + lambda (clip(u + c, +-alpha) - u).
+// Synthesis is the transpose, one launch per level, the two coarsest in one;
+// the last level sums the 8 reconstructions and the Dirac part (no atomics)
+// and applies the 1/3.
+//
+// Both directions filter along the columns first, straight from memory: a
+// thread owns one column of the tile, loads a run of it into registers
+// (consecutive threads read consecutive addresses) and makes all outputs of
+// the run from them, so that a value is read once for a run's outputs and not
+// once for each.  The results go to LDS, and the row pass makes 4 consecutive
+// output pairs per thread from 16-byte LDS reads in the same way: 3 to 6
+// reads for 8 or 16 outputs instead of 2 per tap and output.  Tiles are 64
+// columns wide (256-byte runs of the duals).  A synthesis tile is one wave's
+// work, so its two passes need no workgroup barrier.
+//
+// Bound by HBM at large sizes (302 MB of duals in and out per dual step at
+// 2048^2) and by the latency of five dependent launches at small ones.  One
+// dual step alone, against the earlier form that staged a tile's window in
+// LDS and read LDS once per tap and output: 2048^2 332 -> 192 us, 1024^2
+// 108 -> 69 us, 512^2 44 -> 36 us, 64^2 31 -> 26 us.
 #include <cmath>
+#include <type_traits>
 
 #include "ppd_internal.h"
 
 namespace ppd {
 namespace {
 
-constexpr int AT = 16;   // analysis output tile per sub-band
-constexpr int ST = 32;   // synthesis output tile (inner levels)
-constexpr int STF = 16;  // synthesis output tile of the last level (8 bases summed)
-constexpr int SIN = 2 * AT + 2 * FILT_STRIDE - 2;   // staged analysis input extent (db8)
-constexpr int SK = ST / 2 + FILT_STRIDE / 2;         // staged synthesis coefficient extent
+constexpr int TX = 64;                        // analysis tile per sub-band: columns
+constexpr int DS = 2 * TX + FILT_STRIDE;      // row stride of its filtered columns in LDS (2 TX + 14, 16-byte rows)
+constexpr int DWT_THREADS = 320;              // 2 runs of at most 2 TX + 14 columns
+constexpr int SX = 64, SY = 16;               // synthesis tile
+constexpr int SP = SY / 2;                    // its coefficient rows per band, without the filter's reach
+constexpr int SS = SX / 2 + 8;                // row stride in LDS (SX / 2 + 7 columns, 16-byte rows)
+// Window of a low-pass band that a synthesis tile reads, with one row and
+// column for its alignment.
+constexpr int WROWS = SP + 8, WCOLS = SX / 2 + 8;
+
+// Workgroups a launch must have for analysis tiles of 16 rows; below it tiles
+// of 8 rows keep more compute units busy (128 tall tiles: 5.7 us against 5.0;
+// 512 tall tiles: 8.6 against 10.4; level 1 at 2048^2, 9216: 82 against 91).
+constexpr int DWT_TALL_MIN = 400;
 
 struct SaraGeom {
   int nx, ny, L;
@@ -37,14 +61,18 @@ enum { A_PLAIN = 0, A_DUAL = 1 };
 // The tile (x, y) and basis (z) of this workgroup.  Consecutive workgroups
 // go round-robin to the XCDs; the tiles are handed out so that each XCD
 // takes a contiguous band of them instead, and neighbouring tiles, whose
-// staged windows overlap, meet in one L2.
+// staged windows overlap, meet in one L2.  INNER: the bases of a tile are
+// consecutive too, so that an XCD reads its band of the image once for all
+// of them (level 1 at 2048^2: 97 -> 83 us, at 512^2 11.9 -> 10.5 us).
 struct TileId {
   int x, y, z;
 };
+template <bool INNER>
 __device__ inline TileId sara_tile() {
-  const int gx = gridDim.x, gy = gridDim.y, total = gx * gy * int(gridDim.z);
+  const int gx = gridDim.x, gy = gridDim.y, gz = gridDim.z, total = gx * gy * gz;
   int lin = int(blockIdx.x) + gx * (int(blockIdx.y) + gy * int(blockIdx.z));
   if (total % MAX_XCD == 0) lin = xcd_remap(lin, total);
+  if (INNER) return TileId{(lin / gz) % gx, lin / (gz * gx), lin % gz};
   return TileId{lin % gx, (lin / gx) % gy, lin / (gx * gy)};
 }
 
@@ -60,114 +88,154 @@ __device__ __forceinline__ void load_filt(const float* __restrict__ filt, float 
   }
 }
 
-// One analysis level of basis db-Q on one output tile: stage the periodic
-// input region, filter the columns (axis 0), then the rows (axis 1).
-// a[k] = sum_n h[n] s[(2k + n) mod L], d[k] likewise with g.
-template <int Q, int MODE>
-__device__ void dwt_tile(const float* __restrict__ src, int sstride, float scale, int hh, int ww, int k0y,
-                         int k0x, int toy, int tox, const float* __restrict__ filt, float* s_in, float* s_lo,
-                         float* s_hi, float* __restrict__ ub, const float* __restrict__ wb, int nx, int oh,
-                         int ow, float* __restrict__ llout, float alpha, float lambda) {
+__device__ __forceinline__ float clip_dual(float u, float c, float alpha, float lambda) {
+  const float cl = fminf(fmaxf(u + c, -alpha), alpha);
+  return u + lambda * (cl - u);
+}
+
+// 4 consecutive floats, of which the first n exist; one 16-byte access if vec
+// (the address is 16-byte aligned and all 4 exist).
+__device__ __forceinline__ void load4(const float* __restrict__ p, bool vec, int n, float (&v)[4]) {
+  if (vec) {
+    const float4 q = *reinterpret_cast<const float4*>(p);
+    v[0] = q.x;
+    v[1] = q.y;
+    v[2] = q.z;
+    v[3] = q.w;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = i < n ? p[i] : 0.f;
+  }
+}
+__device__ __forceinline__ void store4(float* __restrict__ p, bool vec, int n, const float (&v)[4]) {
+  if (vec) {
+    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i < n) p[i] = v[i];
+  }
+}
+
+// One analysis level of basis db-Q on one output tile: columns (axis 0), then
+// rows (axis 1).  a[k] = sum_n h[n] s[(2k + n) mod L], d[k] likewise with g.
+// A column run makes RB outputs of either filter.
+template <int Q, int MODE, int RB>
+__device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstride, float scale, int hh, int ww,
+                                         int k0y, int k0x, int toy, int tox, const float* __restrict__ filt,
+                                         float* s_lo, float* s_hi, float* __restrict__ ub,
+                                         const float* __restrict__ wb, int nx, int oh, int ow,
+                                         float* __restrict__ llout, float alpha, float lambda, bool vec) {
   constexpr int TAPS = 2 * Q;
   float h[TAPS], g[TAPS];
   load_filt<Q>(filt, h, g);
-  // This thread's output position (tiles hold at most blockDim.x outputs):
-  // its weights and, in the dual mode, its u values are loaded before the
-  // input is staged, so both loads are in flight together.
-  const bool mine = int(threadIdx.x) < toy * tox;
-  const int k = mine ? int(threadIdx.x) / tox : 0, m = mine ? int(threadIdx.x) - k * tox : 0;
-  const int r = k0y + k, c = k0x + m;
+  const int tid = threadIdx.x;
+  // This thread's 4 outputs per sub-band in the row pass: its weights and, in
+  // the dual mode, its u values are loaded first, so that they are in flight
+  // beside the columns.
+  const int G = (tox + 3) >> 2;
+  const bool mine = tid < toy * G;
+  const int k = mine ? tid / G : 0, m0 = mine ? 4 * (tid - k * G) : 0;
+  const int r = k0y + k, c = k0x + m0, nv = tox - m0;
   const size_t pos[4] = {size_t(r) * nx + (ow + c), size_t(oh + r) * nx + c, size_t(oh + r) * nx + (ow + c),
                          size_t(r) * nx + c};
   const int nout = llout ? 3 : 4;
-  float wv[4] = {1.f, 1.f, 1.f, 1.f}, uo[4] = {0.f, 0.f, 0.f, 0.f};
-  if (mine) {
+  float uo[4][4];
+  if (MODE == A_DUAL && mine) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s < nout) {
-        if (wb) wv[s] = wb[pos[s]];
-        if (MODE == A_DUAL) uo[s] = ub[pos[s]];
-      }
-    }
+    for (int b = 0; b < 4; ++b)
+      if (b < nout) load4(ub + pos[b], vec, nv, uo[b]);
   }
-  const int IR = 2 * toy + TAPS - 2, IC = 2 * tox + TAPS - 2;
-  const int ty = threadIdx.x >> 6, tx = threadIdx.x & 63, nty = blockDim.x >> 6;
-  // staging: all of the thread's loads are issued before its LDS stores
-  constexpr int SPT = (SIN + 3) / 4;   // rows per thread with 4 row groups
-  float sv[SPT];
-  const int cx = (2 * k0x + tx) & (ww - 1);
+  const int IC = 2 * tox + TAPS - 2;
+  const int groups = (toy + RB - 1) / RB;
+  for (int i = tid; i < IC * groups; i += DWT_THREADS) {
+    const int gr = i / IC, cx = i - gr * IC;
+    const int col = (2 * k0x + cx) & (ww - 1), r0 = 2 * (k0y + gr * RB);
+    float v[2 * RB + TAPS - 2];
 #pragma unroll
-  for (int k = 0; k < SPT; ++k) {
-    const int a = ty + k * nty;
-    if (a < IR && tx < IC) sv[k] = src[size_t((2 * k0y + a) & (hh - 1)) * sstride + cx];
-  }
+    for (int a = 0; a < 2 * RB + TAPS - 2; ++a) v[a] = src[size_t((r0 + a) & (hh - 1)) * sstride + col];
 #pragma unroll
-  for (int k = 0; k < SPT; ++k) {
-    const int a = ty + k * nty;
-    if (a < IR && tx < IC) s_in[a * SIN + tx] = sv[k] * scale;
-  }
-  __syncthreads();
-  for (int kk = ty; kk < toy; kk += nty) {   // columns
-    if (tx < IC) {
-      const float* col = s_in + 2 * kk * SIN + tx;
+    for (int a = 0; a < 2 * RB + TAPS - 2; ++a) v[a] *= scale;
+#pragma unroll
+    for (int q = 0; q < RB; ++q) {
       float lo = 0.f, hi = 0.f;
 #pragma unroll
       for (int n = 0; n < TAPS; ++n) {
-        const float v = col[n * SIN];
-        lo = fmaf(h[n], v, lo);
-        hi = fmaf(g[n], v, hi);
+        lo = fmaf(h[n], v[2 * q + n], lo);
+        hi = fmaf(g[n], v[2 * q + n], hi);
       }
-      s_lo[kk * SIN + tx] = lo;
-      s_hi[kk * SIN + tx] = hi;
+      s_lo[(gr * RB + q) * DS + cx] = lo;
+      s_hi[(gr * RB + q) * DS + cx] = hi;
     }
   }
   __syncthreads();
   if (!mine) return;
-  const float* lrow = s_lo + k * SIN + 2 * m;   // rows
-  const float* hrow = s_hi + k * SIN + 2 * m;
-  float ll = 0.f, lh = 0.f, hl = 0.f, hhv = 0.f;
+  float cv[4][4];   // lh, hl, hh, ll of the 4 outputs
 #pragma unroll
-  for (int n = 0; n < TAPS; ++n) {
-    const float a = lrow[n], d = hrow[n];
-    ll = fmaf(h[n], a, ll);
-    lh = fmaf(g[n], a, lh);
-    hl = fmaf(h[n], d, hl);
-    hhv = fmaf(g[n], d, hhv);
-  }
-  const float cv[4] = {lh, hl, hhv, ll};
+  for (int half = 0; half < 2; ++half) {
+    constexpr int NF = (TAPS + 6 + 3) / 4;
+    float v[4 * NF];
+    const float4* row = reinterpret_cast<const float4*>((half ? s_hi : s_lo) + k * DS + 2 * m0);
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    if (s >= nout) break;
-    const float cs = cv[s] * wv[s];
-    if (MODE == A_PLAIN) {
-      ub[pos[s]] = cs;
-    } else {
-      // the sparsity dual update of Algorithm 3 on the coefficient of Psi^H x~
-      const float cl = fminf(fmaxf(uo[s] + cs, -alpha), alpha);
-      ub[pos[s]] = uo[s] + lambda * (cl - uo[s]);
+    for (int n = 0; n < NF; ++n) {
+      const float4 q = row[n];
+      v[4 * n] = q.x;
+      v[4 * n + 1] = q.y;
+      v[4 * n + 2] = q.z;
+      v[4 * n + 3] = q.w;
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      float a = 0.f, d = 0.f;
+#pragma unroll
+      for (int n = 0; n < TAPS; ++n) {
+        a = fmaf(h[n], v[2 * m + n], a);
+        d = fmaf(g[n], v[2 * m + n], d);
+      }
+      cv[half ? 1 : 3][m] = a;
+      cv[half ? 2 : 0][m] = d;
     }
   }
-  if (llout) llout[size_t(r) * ow + c] = ll;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (b >= nout) break;
+    float o[4];
+    if (wb) {
+      float wv[4];
+      load4(wb + pos[b], vec, nv, wv);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) o[m] = cv[b][m] * wv[m];
+    } else {
+#pragma unroll
+      for (int m = 0; m < 4; ++m) o[m] = cv[b][m];
+    }
+    if (MODE == A_DUAL) {   // the sparsity dual update of Algorithm 3 on the coefficient of Psi^H x~
+#pragma unroll
+      for (int m = 0; m < 4; ++m) o[m] = clip_dual(uo[b][m], o[m], alpha, lambda);
+    }
+    store4(ub + pos[b], vec, nv, o);
+  }
+  if (llout) store4(llout + size_t(r) * ow + c, vec, nv, cv[3]);
 }
-
-static_assert(AT * AT <= 256, "an analysis tile must fit one output per thread of 256");
 
 // Level l of the 8 wavelet bases (tile z = basis - 1); at level 1 the
 // Dirac basis is z = 8.  `active` (dual mode, may be NULL) masks
 // the bases updated this iteration.  Level 1 reads the image scaled by 1/3,
-// deeper levels the low-pass band of the previous level.
-template <int MODE>
-__global__ __launch_bounds__(256) void k_dwt(const float* __restrict__ x, float* __restrict__ tmp,
-                                             float* __restrict__ out, const float* __restrict__ filt,
-                                             const float* __restrict__ W, SaraGeom g, int l, float alpha,
-                                             float lambda, const uint8_t* __restrict__ active) {
-  __shared__ float s_in[SIN * SIN];
-  __shared__ float s_lo[AT * SIN];
-  __shared__ float s_hi[AT * SIN];
+// deeper levels the low-pass band of the previous level.  vec: every array is
+// 16-byte aligned and a level's rows are whole float4s.
+template <int MODE, int RB>
+__global__ __launch_bounds__(DWT_THREADS) void k_dwt(const float* __restrict__ x, float* __restrict__ tmp,
+                                                     float* __restrict__ out, const float* __restrict__ filt,
+                                                     const float* __restrict__ W, SaraGeom g, int l, float alpha,
+                                                     float lambda, const uint8_t* __restrict__ active, int vec) {
+  constexpr int TY = 2 * RB;
+  static_assert(TY * (TX / 4) <= DWT_THREADS, "one thread per 4 outputs of the tile");
+  __shared__ __align__(16) float s_lo[TY * DS];
+  __shared__ __align__(16) float s_hi[TY * DS];
   const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
   const int oh = hh >> 1, ow = ww >> 1;
-  const int toy = min(AT, oh), tox = min(AT, ow);
-  const TileId tl = sara_tile();
+  const int toy = min(TY, oh), tox = min(TX, ow);
+  const TileId tl = sara_tile<true>();
   const int k0y = tl.y * toy, k0x = tl.x * tox;
   const int q = tl.z + 1;   // 1..8 wavelets, 9 = Dirac (level 1 only)
   const float third = 1.0f / 3.0f;
@@ -175,35 +243,22 @@ __global__ __launch_bounds__(256) void k_dwt(const float* __restrict__ x, float*
   // its u_i (basis index 0 is the Dirac basis)
   if (active && !active[q == 9 ? 0 : q]) return;
   if (q == 9) {
-    // Dirac basis: coefficient x / 3 at every pixel of this tile's footprint
-    // (at most 4 pixels per thread; all loads issued first)
-    constexpr int DPT = 4 * AT * AT / 256;
-    float xv[DPT], wv[DPT], uo[DPT];
-    size_t Pv[DPT];
+    // Dirac basis: coefficient x / 3 at every pixel of this tile's footprint,
+    // 4 pixels at a time (its rows are 2 tox >= 4 wide: images are at least 16)
+    const int F = tox >> 1;
+    for (int i = threadIdx.x; i < 2 * toy * F; i += DWT_THREADS) {
+      const int a = i / F;
+      const size_t P = size_t(2 * k0y + a) * g.nx + (2 * k0x + 4 * (i - a * F));
+      float xv[4], wv[4] = {1.f, 1.f, 1.f, 1.f}, uo[4], o[4];
+      load4(x + P, vec, 4, xv);
+      if (W) load4(W + P, vec, 4, wv);
+      if (MODE == A_DUAL) load4(out + P, vec, 4, uo);
 #pragma unroll
-    for (int k = 0; k < DPT; ++k) {
-      const int i = threadIdx.x + k * 256;
-      Pv[k] = 0;
-      if (i < 4 * toy * tox) {
-        const int a = i / (2 * tox), b = i - a * (2 * tox);
-        Pv[k] = size_t(2 * k0y + a) * g.nx + (2 * k0x + b);
-        xv[k] = x[Pv[k]];
-        wv[k] = W ? W[Pv[k]] : 1.0f;
-        uo[k] = MODE == A_DUAL ? out[Pv[k]] : 0.f;
+      for (int m = 0; m < 4; ++m) {
+        const float c = xv[m] * third * wv[m];
+        o[m] = MODE == A_DUAL ? clip_dual(uo[m], c, alpha, lambda) : c;
       }
-    }
-#pragma unroll
-    for (int k = 0; k < DPT; ++k) {
-      const int i = threadIdx.x + k * 256;
-      if (i < 4 * toy * tox) {
-        const float c = xv[k] * third * wv[k];
-        if (MODE == A_PLAIN) {
-          out[Pv[k]] = c;
-        } else {
-          const float cl = fminf(fmaxf(uo[k] + c, -alpha), alpha);
-          out[Pv[k]] = uo[k] + lambda * (cl - uo[k]);
-        }
-      }
+      store4(out + P, vec, 4, o);
     }
     return;
   }
@@ -213,10 +268,10 @@ __global__ __launch_bounds__(256) void k_dwt(const float* __restrict__ x, float*
   float* ub = out + size_t(q) * g.N;
   const float* wb = W ? W + size_t(q) * g.N : nullptr;
   float* llout = l == g.L ? nullptr : tmp + g.off[l] + size_t(q - 1) * lvl_size(g, l);
-#define PPD_DWT_CASE(Q)                                                                                     \
-  case Q:                                                                                                   \
-    dwt_tile<Q, MODE>(src, sstride, scale, hh, ww, k0y, k0x, toy, tox, filt, s_in, s_lo, s_hi, ub, wb, g.nx, \
-                      oh, ow, llout, alpha, lambda);                                                        \
+#define PPD_DWT_CASE(Q)                                                                                       \
+  case Q:                                                                                                     \
+    dwt_tile<Q, MODE, RB>(src, sstride, scale, hh, ww, k0y, k0x, toy, tox, filt, s_lo, s_hi, ub, wb, g.nx, oh, \
+                          ow, llout, alpha, lambda, vec != 0);                                                \
     break;
   switch (q) {
     PPD_DWT_CASE(1) PPD_DWT_CASE(2) PPD_DWT_CASE(3) PPD_DWT_CASE(4)
@@ -225,368 +280,303 @@ __global__ __launch_bounds__(256) void k_dwt(const float* __restrict__ x, float*
 #undef PPD_DWT_CASE
 }
 
-// Inverse of one level for basis db-Q: sub-bands (oh x ow) -> (hh x ww) on
-// the output tile (y0, x0, tsy x tsx).  Transposing the analysis gives
-// s[2j + e] = sum_t h[2t + e] a[j - t] + g[2t + e] d[j - t], e in {0, 1}, so
-// each thread makes an even / odd output pair from the same Q coefficients.
-// Rows (axis 1) first, then columns (axis 0).  sink(slot, r, c, v) receives
-// the outputs; slot counts the thread's outputs in a fixed order.
-// The low-pass band of a coefficient window taken from LDS instead of
-// memory: window entry (a, b) of the tile is p[(a + offy) * stride + b + offx].
-struct LLWin {
-  const float* p = nullptr;
-  int stride = 0, offy = 0, offx = 0;
-};
-
-template <int Q, typename Sink>
-__device__ void idwt_tile(const float* __restrict__ llsrc, int llstride, const float* __restrict__ ucoef,
-                          const float* __restrict__ wcoef, const float* __restrict__ llw, int nx, int hh,
-                          int ww, int y0, int x0, int tsy, int tsx, const float* __restrict__ filt,
-                          float* s_ll, float* s_lh, float* s_hl, float* s_hh, float* s_a, float* s_d,
-                          Sink sink, const LLWin win = LLWin{}) {
-  float h[2 * Q], g[2 * Q];
-  load_filt<Q>(filt, h, g);
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int oh = hh >> 1, ow = ww >> 1;
-  const int hx = tsx >> 1, hy = tsy >> 1;
-  const int KR = hy + Q, KC = hx + Q;
-  const int krb = (y0 >> 1) - Q, kcb = (x0 >> 1) - Q;
-  // staging: all of the thread's loads are issued before its LDS stores
-  constexpr int IPT = (SK * SK + 255) / 256;
-  float v4[IPT][4];
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const int i = tid + k * nth;
-    if (i < KR * KC) {
-      const int a = i / KC, b = i - a * KC;
-      const int r = (krb + a) & (oh - 1), c = (kcb + b) & (ow - 1);
-      const size_t pll = size_t(r) * llstride + c;
-      const size_t plh = size_t(r) * nx + (ow + c), phl = size_t(oh + r) * nx + c;
-      const size_t phh = size_t(oh + r) * nx + (ow + c);
-      v4[k][0] = win.p ? win.p[(a + win.offy) * win.stride + (b + win.offx)]
-                       : llsrc[pll] * (llw ? llw[pll] : 1.0f);
-      v4[k][1] = ucoef[plh] * (wcoef ? wcoef[plh] : 1.0f);
-      v4[k][2] = ucoef[phl] * (wcoef ? wcoef[phl] : 1.0f);
-      v4[k][3] = ucoef[phh] * (wcoef ? wcoef[phh] : 1.0f);
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < IPT; ++k) {
-    const int i = tid + k * nth;
-    if (i < KR * KC) {
-      const int a = i / KC, b = i - a * KC;
-      const int li = a * SK + b;
-      s_ll[li] = v4[k][0];
-      s_lh[li] = v4[k][1];
-      s_hl[li] = v4[k][2];
-      s_hh[li] = v4[k][3];
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < KR * hx; i += nth) {   // rows: A from (LL, LH), D from (HL, HH)
-    const int kr = i / hx, j = i - kr * hx;
-    const int base = kr * SK + j + Q;
-    float a0 = 0.f, a1 = 0.f, d0 = 0.f, d1 = 0.f;
-#pragma unroll
-    for (int t = 0; t < Q; ++t) {
-      const float ll = s_ll[base - t], lh = s_lh[base - t], hl = s_hl[base - t], hv = s_hh[base - t];
-      a0 = fmaf(h[2 * t], ll, fmaf(g[2 * t], lh, a0));
-      a1 = fmaf(h[2 * t + 1], ll, fmaf(g[2 * t + 1], lh, a1));
-      d0 = fmaf(h[2 * t], hl, fmaf(g[2 * t], hv, d0));
-      d1 = fmaf(h[2 * t + 1], hl, fmaf(g[2 * t + 1], hv, d1));
-    }
-    s_a[kr * ST + 2 * j] = a0;
-    s_a[kr * ST + 2 * j + 1] = a1;
-    s_d[kr * ST + 2 * j] = d0;
-    s_d[kr * ST + 2 * j + 1] = d1;
-  }
-  __syncthreads();
-  int slot = 0;
-  for (int i = tid; i < hy * tsx; i += nth, slot += 2) {   // columns: S from (A, D)
-    const int j = i / tsx, m = i - j * tsx;
-    float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-    for (int t = 0; t < Q; ++t) {
-      const int lr = (j + Q - t) * ST + m;
-      const float av = s_a[lr], dv = s_d[lr];
-      s0 = fmaf(h[2 * t], av, fmaf(g[2 * t], dv, s0));
-      s1 = fmaf(h[2 * t + 1], av, fmaf(g[2 * t + 1], dv, s1));
-    }
-    sink(slot, 2 * j, m, s0);
-    sink(slot + 1, 2 * j + 1, m, s1);
-  }
-  __syncthreads();
+// Orders the LDS accesses of one wave's lanes (LDS operations of a wave take
+// effect in program order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-#define PPD_IDWT_SWITCH(q, ...)                       \
-  switch (q) {                                        \
-    case 1: idwt_tile<1>(__VA_ARGS__); break;         \
-    case 2: idwt_tile<2>(__VA_ARGS__); break;         \
-    case 3: idwt_tile<3>(__VA_ARGS__); break;         \
-    case 4: idwt_tile<4>(__VA_ARGS__); break;         \
-    case 5: idwt_tile<5>(__VA_ARGS__); break;         \
-    case 6: idwt_tile<6>(__VA_ARGS__); break;         \
-    case 7: idwt_tile<7>(__VA_ARGS__); break;         \
-    default: idwt_tile<8>(__VA_ARGS__); break;        \
+// The four sub-bands of one level of one basis in the Mallat layout, periodic,
+// with optional weights, and where the low-pass band is read instead if it is
+// not LL of u (row stride lls, unweighted).
+struct Bands {
+  const float* u;    // coefficients of the basis (stride nx)
+  const float* w;    // weights or NULL
+  const float* ll;   // low-pass band of the level below, or NULL
+  int nx, oh, ow, lls;
+};
+
+// Inverse of one level for basis db-Q on one tile by one wave.  Transposing
+// the analysis gives s[2j + e] = sum_t h[2t + e] a[j - t] + g[2t + e] d[j - t],
+// e in {0, 1}.  Column pass: the axis-1 low band (from LL, HL) and high band
+// (from LH, HH) of 2 SP output rows, at coefficient columns c0 - (Q - 1) + b,
+// b < hx + Q - 1, to s_x[band][row][b].  WIN: the low-pass entry at
+// coefficient row j0 - (Q - 1) + a, column index b is win[a WCOLS + b].
+template <int Q, bool WIN>
+__device__ __forceinline__ void synth_cols(const float (&h)[2 * Q], const float (&g)[2 * Q], const Bands& bd, int j0,
+                                           int c0, int hx, const float* win, float* s_x) {
+  constexpr int NR = SP + Q - 1;
+  const int nb = hx + Q - 1;
+  for (int i = threadIdx.x & 63; i < 2 * nb; i += 64) {
+    const int band = i >= nb ? 1 : 0, b = i - band * nb;
+    const int c = (c0 - (Q - 1) + b) & (bd.ow - 1);
+    // row indices in vector registers: as scalars they would take more than there are
+    int r0 = j0 - (Q - 1);
+    asm volatile("" : "+v"(r0));
+    float av[NR], dv[NR];
+    int off[NR];
+#pragma unroll
+    for (int a = 0; a < NR; ++a) off[a] = (r0 + a) & (bd.oh - 1);
+    const int cd = bd.oh * bd.nx + band * bd.ow + c, ca = band * bd.ow + c;
+#pragma unroll
+    for (int a = 0; a < NR; ++a) dv[a] = bd.u[off[a] * bd.nx + cd];
+    if constexpr (WIN) {
+      if (band) {
+#pragma unroll
+        for (int a = 0; a < NR; ++a) av[a] = bd.u[off[a] * bd.nx + ca];
+      } else {
+#pragma unroll
+        for (int a = 0; a < NR; ++a) av[a] = win[a * WCOLS + b];
+      }
+    } else {
+      const bool low = bd.ll && !band;
+      const float* pa = low ? bd.ll + c : bd.u + ca;
+      const int sa = low ? bd.lls : bd.nx;
+#pragma unroll
+      for (int a = 0; a < NR; ++a) av[a] = pa[off[a] * sa];
+    }
+    if (bd.w) {
+      float wd[NR], wa[NR];
+#pragma unroll
+      for (int a = 0; a < NR; ++a) {
+        wd[a] = bd.w[off[a] * bd.nx + cd];
+        wa[a] = bd.w[off[a] * bd.nx + ca];
+      }
+      const bool low = (WIN || bd.ll) && !band;   // an unweighted low-pass band
+#pragma unroll
+      for (int a = 0; a < NR; ++a) {
+        dv[a] *= wd[a];
+        av[a] = low ? av[a] : av[a] * wa[a];
+      }
+    }
+    float* dst = s_x + band * (SY * SS) + b;
+#pragma unroll
+    for (int j = 0; j < SP; ++j) {
+      float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+      for (int t = 0; t < Q; ++t) {
+        const float a = av[j - t + Q - 1], d = dv[j - t + Q - 1];
+        s0 = fmaf(h[2 * t], a, fmaf(g[2 * t], d, s0));
+        s1 = fmaf(h[2 * t + 1], a, fmaf(g[2 * t + 1], d, s1));
+      }
+      dst[(2 * j) * SS] = s0;
+      dst[(2 * j + 1) * SS] = s1;
+    }
   }
+}
+
+// Row pass: 8 outputs (columns 8 mg ..) of tile row `row`, added to o.
+template <int Q>
+__device__ __forceinline__ void synth_row8(const float (&h)[2 * Q], const float (&g)[2 * Q], const float* s_x, int row,
+                                           int mg, float (&o)[8]) {
+  constexpr int NF = (Q + 3 + 3) / 4;
+  float lv[4 * NF], hv[4 * NF];
+  const float4* lr = reinterpret_cast<const float4*>(s_x + row * SS + 4 * mg);
+  const float4* hr = reinterpret_cast<const float4*>(s_x + (SY + row) * SS + 4 * mg);
+#pragma unroll
+  for (int n = 0; n < NF; ++n) {
+    const float4 a = lr[n], d = hr[n];
+    lv[4 * n] = a.x;
+    lv[4 * n + 1] = a.y;
+    lv[4 * n + 2] = a.z;
+    lv[4 * n + 3] = a.w;
+    hv[4 * n] = d.x;
+    hv[4 * n + 1] = d.y;
+    hv[4 * n + 2] = d.z;
+    hv[4 * n + 3] = d.w;
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int t = 0; t < Q; ++t) {
+      const float a = lv[m - t + Q - 1], d = hv[m - t + Q - 1];
+      o[2 * m] = fmaf(h[2 * t], a, fmaf(g[2 * t], d, o[2 * m]));
+      o[2 * m + 1] = fmaf(h[2 * t + 1], a, fmaf(g[2 * t + 1], d, o[2 * m + 1]));
+    }
+}
+
+// 8 floats at p, of which n exist.
+__device__ __forceinline__ void store8(float* __restrict__ p, bool vec, int n, const float (&o)[8]) {
+  const float a[4] = {o[0], o[1], o[2], o[3]}, b[4] = {o[4], o[5], o[6], o[7]};
+  store4(p, vec, n, a);
+  store4(p + 4, vec, n - 4, b);
+}
+
+// Calls fn(std::integral_constant<int, q>) for basis db-q (wave-uniform).
+template <typename Fn>
+__device__ __forceinline__ void with_basis(int q, Fn fn) {
+  switch (q) {
+    case 1: fn(std::integral_constant<int, 1>()); break;
+    case 2: fn(std::integral_constant<int, 2>()); break;
+    case 3: fn(std::integral_constant<int, 3>()); break;
+    case 4: fn(std::integral_constant<int, 4>()); break;
+    case 5: fn(std::integral_constant<int, 5>()); break;
+    case 6: fn(std::integral_constant<int, 6>()); break;
+    case 7: fn(std::integral_constant<int, 7>()); break;
+    default: fn(std::integral_constant<int, 8>()); break;
+  }
+}
+
+// The basis of a wave of the per-basis synthesis launches (workgroup z = 0, 1):
+// 1, 8, 3, 6 and 2, 7, 4, 5, the same number of taps in both.
+__device__ __forceinline__ int wave_basis(int z) {
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  return w == 0 ? 1 + z : w == 1 ? 8 - z : w == 2 ? 3 + z : 6 - z;
+}
 
 // Intermediate synthesis level l >= 2 (output = low-pass band of level l-1).
 __global__ __launch_bounds__(256) void k_idwt(const float* __restrict__ u, float* __restrict__ rec,
                                               const float* __restrict__ filt, const float* __restrict__ W,
                                               SaraGeom g, int l) {
-  __shared__ float s_ll[SK * SK], s_lh[SK * SK], s_hl[SK * SK], s_hh[SK * SK];
-  __shared__ float s_a[SK * ST], s_d[SK * ST];
+  __shared__ __align__(16) float s_all[4][2 * SY * SS];
   const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-  const int tsy = min(ST, hh), tsx = min(ST, ww);
-  const TileId tl = sara_tile();
+  const int tsy = min(SY, hh), tsx = min(SX, ww), hx = tsx >> 1;
+  const TileId tl = sara_tile<false>();
   const int y0 = tl.y * tsy, x0 = tl.x * tsx;
-  const int q = tl.z + 1;
-  const float* ucoef = u + size_t(q) * g.N;
-  const float* wcoef = W ? W + size_t(q) * g.N : nullptr;
-  const float* llsrc;
-  const float* llw = nullptr;
-  int llstride = ww >> 1;
-  if (l == g.L) {
-    llsrc = ucoef;
-    llw = wcoef;
-    llstride = g.nx;
-  } else {
-    llsrc = rec + g.off[l] + size_t(q - 1) * lvl_size(g, l);
-  }
+  const int q = wave_basis(tl.z), lane = threadIdx.x & 63;
+  float* s_x = s_all[threadIdx.x >> 6];
+  const Bands bd{u + size_t(q) * g.N, W ? W + size_t(q) * g.N : nullptr,
+                 l == g.L ? nullptr : rec + g.off[l] + size_t(q - 1) * lvl_size(g, l), g.nx, hh >> 1, ww >> 1, ww >> 1};
   float* dst = rec + g.off[l - 1] + size_t(q - 1) * lvl_size(g, l - 1);
-  auto sink = [&](int, int r, int c, float v) { dst[size_t(y0 + r) * ww + (x0 + c)] = v; };
-  PPD_IDWT_SWITCH(q, llsrc, llstride, ucoef, wcoef, llw, g.nx, hh, ww, y0, x0, tsy, tsx, filt, s_ll, s_lh,
-                  s_hl, s_hh, s_a, s_d, sink)
+  const bool vec = (tsx & 7) == 0;
+  with_basis(q, [&](auto ql) {
+    constexpr int Q = decltype(ql)::value;
+    float h[2 * Q], gf[2 * Q];
+    load_filt<Q>(filt, h, gf);
+    synth_cols<Q, false>(h, gf, bd, y0 >> 1, x0 >> 1, hx, nullptr, s_x);
+    wave_sync();
+    const int G = (hx + 3) >> 2;
+    for (int i = lane; i < tsy * G; i += 64) {
+      const int row = i / G, mg = i - row * G;
+      float o[8] = {};
+      synth_row8<Q>(h, gf, s_x, row, mg, o);
+      store8(dst + size_t(y0 + row) * ww + (x0 + 8 * mg), vec, tsx - 8 * mg, o);
+    }
+  });
 }
 
-// The two coarsest synthesis levels L and L-1 (L >= 3) in one launch: a
-// workgroup first rebuilds, from the level-L coefficients, the window of
-// the level-(L-1) low-pass band its level-(L-1) tile reads (periodic, even
-// aligned; neighbouring workgroups recompute the overlap), keeps it in LDS,
-// then synthesises its tile of the level-(L-2) low-pass band.  One launch
-// fewer on SARA's chain of dependent launches.
-constexpr int WIN = ST / 2 + FILT_STRIDE / 2 + 2;   // LL window edge (outer window + alignment, even)
-
-template <int Q>
-__device__ void idwt2_body(const float* __restrict__ ucoef, const float* __restrict__ wcoef, float* dst,
-                           const float* __restrict__ filt, int nx, int hh, int ww, int y0, int x0, int tsy,
-                           int tsx, float* s_ll, float* s_lh, float* s_hl, float* s_hh, float* s_a, float* s_d,
-                           float* s_win) {
-  const int oh = hh >> 1, ow = ww >> 1;                      // level-(L-1) band = inner output
-  const int wy0 = (y0 >> 1) - Q, wx0 = (x0 >> 1) - Q;        // outer coefficient window origin
-  const int ya = wy0 - (wy0 & 1), xa = wx0 - (wx0 & 1);      // even-aligned inner tile origin
-  const int offy = wy0 - ya, offx = wx0 - xa;
-  const int ti_y = ((tsy >> 1) + Q + offy + 1) & ~1, ti_x = ((tsx >> 1) + Q + offx + 1) & ~1;
-  auto sink_win = [&](int, int r, int c, float v) { s_win[r * WIN + c] = v; };
-  // level L: its low-pass band and details are coefficients (in u, weighted)
-  idwt_tile<Q>(ucoef, nx, ucoef, wcoef, wcoef, nx, oh, ow, ya, xa, ti_y, ti_x, filt, s_ll, s_lh, s_hl, s_hh,
-               s_a, s_d, sink_win);
-  auto sink = [&](int, int r, int c, float v) { dst[size_t(y0 + r) * ww + (x0 + c)] = v; };
-  LLWin win;
-  win.p = s_win;
-  win.stride = WIN;
-  win.offy = offy;
-  win.offx = offx;
-  idwt_tile<Q>(nullptr, 0, ucoef, wcoef, nullptr, nx, hh, ww, y0, x0, tsy, tsx, filt, s_ll, s_lh, s_hl, s_hh,
-               s_a, s_d, sink, win);
-}
+// The two coarsest synthesis levels L and L-1 (L >= 3) in one launch: a wave
+// first rebuilds, from the level-L coefficients, the window of the level-(L-1)
+// low-pass band its level-(L-1) tile reads (periodic, even aligned;
+// neighbouring tiles recompute the overlap), keeps it in LDS, then
+// synthesises its tile of the level-(L-2) low-pass band.  One launch fewer on
+// SARA's chain of dependent launches.
+static_assert(WROWS <= SY && WCOLS <= SS && WCOLS / 2 + 7 <= SS, "the window is an inner tile of its own");
 
 __global__ __launch_bounds__(256) void k_idwt2(const float* __restrict__ u, float* __restrict__ rec,
                                                const float* __restrict__ filt, const float* __restrict__ W,
                                                SaraGeom g) {
-  __shared__ float s_ll[SK * SK], s_lh[SK * SK], s_hl[SK * SK], s_hh[SK * SK];
-  __shared__ float s_a[SK * ST], s_d[SK * ST];
-  __shared__ float s_win[WIN * WIN];
+  __shared__ __align__(16) float s_all[4][2 * SY * SS];
+  __shared__ __align__(16) float w_all[4][WROWS * WCOLS];
   const int l = g.L - 1;                                      // outer level
   const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-  const int tsy = min(ST, hh), tsx = min(ST, ww);
-  const TileId tl = sara_tile();
+  const int tsy = min(SY, hh), tsx = min(SX, ww), hx = tsx >> 1;
+  const TileId tl = sara_tile<false>();
   const int y0 = tl.y * tsy, x0 = tl.x * tsx;
-  const int q = tl.z + 1;
-  const float* ucoef = u + size_t(q) * g.N;
-  const float* wcoef = W ? W + size_t(q) * g.N : nullptr;
+  const int q = wave_basis(tl.z), lane = threadIdx.x & 63;
+  float* s_x = s_all[threadIdx.x >> 6];
+  float* s_w = w_all[threadIdx.x >> 6];
+  const Bands bo{u + size_t(q) * g.N, W ? W + size_t(q) * g.N : nullptr, nullptr, g.nx, hh >> 1, ww >> 1, 0};
+  const Bands bi{bo.u, bo.w, nullptr, g.nx, hh >> 2, ww >> 2, 0};
   float* dst = rec + g.off[l - 1] + size_t(q - 1) * lvl_size(g, l - 1);
-  switch (q) {
-    case 1: idwt2_body<1>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    case 2: idwt2_body<2>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    case 3: idwt2_body<3>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    case 4: idwt2_body<4>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    case 5: idwt2_body<5>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    case 6: idwt2_body<6>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    case 7: idwt2_body<7>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-    default: idwt2_body<8>(ucoef, wcoef, dst, filt, g.nx, hh, ww, y0, x0, tsy, tsx, s_ll, s_lh, s_hl, s_hh, s_a, s_d, s_win); break;
-  }
-}
-static_assert(ST / 2 + FILT_STRIDE / 2 + 1 <= WIN && WIN <= ST, "the LL window fits an inner tile");
-static_assert(WIN / 2 + FILT_STRIDE / 2 <= SK, "the inner coefficient window fits the staging");
-
-// Level 1 for all 8 wavelet bases, plus the Dirac part, times 1/3, on a
-// STF x STF output tile.  The coefficient windows of all 8 bases are loaded
-// in one pass (one round of global loads, into registers), then staged in
-// LDS FPARTS bases at a time: the row passes of a part, then its column
-// passes, which each thread sums over the bases in registers in basis
-// order.  Parts keep the workgroup's LDS small, which leaves room on each
-// compute unit for the concurrent data-path launches.
-#ifndef PPD_FINAL_PARTS
-#define PPD_FINAL_PARTS 2
-#endif
-constexpr int FPARTS = PPD_FINAL_PARTS;
-constexpr int FB = 8 / FPARTS;                       // bases per part
-static_assert(FB * FPARTS == 8, "the parts split the 8 bases evenly");
-constexpr int FINAL_THREADS = 128;
-constexpr int FH = STF / 2;                          // coefficients per tile side and band
-constexpr int FKS = FH + FILT_STRIDE / 2;            // staged row stride (FH + max Q)
-constexpr int FELEM = 8 * FH * FH + 2 * FH * 36 + 204;   // sum over Q of (FH + Q)^2
-constexpr int FEPT = (FELEM + FINAL_THREADS - 1) / FINAL_THREADS;
-constexpr int FROWS = FB * FH + FB * (17 - FB) / 2;  // rows of the last (largest) part: sum of FH + Q over it
-constexpr int FPART = FROWS * FKS;                   // staging index offset of one part
-static_assert(FH * STF == FINAL_THREADS, "one column pair per thread");
-
-// first staged row of basis q within its part (each part from row 0)
-__device__ __forceinline__ int final_row0(int q) {
-  const int q0 = (q - 1) / FB * FB + 1;
-  return (q - q0) * FH + ((q - 1) * q - (q0 - 1) * q0) / 2;
-}
-__device__ __forceinline__ int final_elem0(int q) {
-  int e = 0;
-  for (int p = 1; p < q; ++p) e += (FH + p) * (FH + p);
-  return e;
-}
-
-template <int Q>
-__device__ __forceinline__ void final_rows(const float* __restrict__ filt, const float* s_c, float* s_a,
-                                           float* s_d) {
-  float h[2 * Q], g[2 * Q];
-  load_filt<Q>(filt, h, g);
-  constexpr int KR = FH + Q;
-  const int r0 = final_row0(Q);
-  const float* s_ll = s_c;
-  const float* s_lh = s_c + FROWS * FKS;
-  const float* s_hl = s_c + 2 * FROWS * FKS;
-  const float* s_hh = s_c + 3 * FROWS * FKS;
-  for (int i = threadIdx.x; i < KR * FH; i += blockDim.x) {
-    const int kr = i / FH, j = i - kr * FH;
-    const int base = (r0 + kr) * FKS + j + Q;
-    float a0 = 0.f, a1 = 0.f, d0 = 0.f, d1 = 0.f;
-#pragma unroll
-    for (int t = 0; t < Q; ++t) {
-      const float ll = s_ll[base - t], lh = s_lh[base - t], hl = s_hl[base - t], hv = s_hh[base - t];
-      a0 = fmaf(h[2 * t], ll, fmaf(g[2 * t], lh, a0));
-      a1 = fmaf(h[2 * t + 1], ll, fmaf(g[2 * t + 1], lh, a1));
-      d0 = fmaf(h[2 * t], hl, fmaf(g[2 * t], hv, d0));
-      d1 = fmaf(h[2 * t + 1], hl, fmaf(g[2 * t + 1], hv, d1));
+  const bool vec = (tsx & 7) == 0;
+  with_basis(q, [&](auto ql) {
+    constexpr int Q = decltype(ql)::value;
+    float h[2 * Q], gf[2 * Q];
+    load_filt<Q>(filt, h, gf);
+    const int j0 = y0 >> 1, c0 = x0 >> 1;
+    const int wy0 = j0 - (Q - 1), wx0 = c0 - (Q - 1);         // outer window origin
+    const int ya = wy0 - (wy0 & 1), xa = wx0 - (wx0 & 1);     // even-aligned inner tile origin
+    const int offy = wy0 - ya, offx = wx0 - xa;
+    const int hxi = (hx + Q - 1 + offx + 1) >> 1;             // inner coefficient columns
+    // level L: its low-pass band and details are coefficients (in u, weighted)
+    synth_cols<Q, false>(h, gf, bi, ya >> 1, xa >> 1, hxi, nullptr, s_x);
+    wave_sync();
+    const int Gi = (hxi + 3) >> 2;
+    for (int i = lane; i < WROWS * Gi; i += 64) {
+      const int row = i / Gi, mg = i - row * Gi;
+      float o[8] = {};
+      synth_row8<Q>(h, gf, s_x, row, mg, o);
+      *reinterpret_cast<float4*>(s_w + row * WCOLS + 8 * mg) = make_float4(o[0], o[1], o[2], o[3]);
+      *reinterpret_cast<float4*>(s_w + row * WCOLS + 8 * mg + 4) = make_float4(o[4], o[5], o[6], o[7]);
     }
-    s_a[(r0 + kr) * STF + 2 * j] = a0;
-    s_a[(r0 + kr) * STF + 2 * j + 1] = a1;
-    s_d[(r0 + kr) * STF + 2 * j] = d0;
-    s_d[(r0 + kr) * STF + 2 * j + 1] = d1;
-  }
-}
-
-template <int Q>
-__device__ __forceinline__ void final_cols(const float* __restrict__ filt, const float* s_a, const float* s_d,
-                                           int j, int m, float& o0, float& o1) {
-  float h[2 * Q], g[2 * Q];
-  load_filt<Q>(filt, h, g);
-  const int r0 = final_row0(Q);
-#pragma unroll
-  for (int t = 0; t < Q; ++t) {
-    const int lr = (r0 + j + Q - t) * STF + m;
-    const float av = s_a[lr], dv = s_d[lr];
-    o0 = fmaf(h[2 * t], av, fmaf(g[2 * t], dv, o0));
-    o1 = fmaf(h[2 * t + 1], av, fmaf(g[2 * t + 1], dv, o1));
-  }
-}
-
-template <int Q, int QE>
-__device__ __forceinline__ void final_rows_range(const float* __restrict__ filt, const float* s_c, float* s_a,
-                                                 float* s_d) {
-  final_rows<Q>(filt, s_c, s_a, s_d);
-  if constexpr (Q < QE) final_rows_range<Q + 1, QE>(filt, s_c, s_a, s_d);
-}
-
-template <int Q, int QE>
-__device__ __forceinline__ void final_cols_range(const float* __restrict__ filt, const float* s_a,
-                                                 const float* s_d, int j, int m, float& o0, float& o1) {
-  final_cols<Q>(filt, s_a, s_d, j, m, o0, o1);
-  if constexpr (Q < QE) final_cols_range<Q + 1, QE>(filt, s_a, s_d, j, m, o0, o1);
-}
-
-// Part PART of the bases: stage its windows (s_c was last read by the
-// previous part's row passes, before the barrier ahead of its column
-// passes), then its row and column passes.
-template <int PART>
-__device__ __forceinline__ void final_part(const float* __restrict__ filt, float* s_c, float* s_a, float* s_d,
-                                           const float (&vals)[FEPT][4], const int (&at)[FEPT], int j, int m,
-                                           float& o0, float& o1) {
-#pragma unroll
-  for (int k = 0; k < FEPT; ++k) {
-    if (at[k] >= PART * FPART && at[k] < (PART + 1) * FPART) {
-#pragma unroll
-      for (int c4 = 0; c4 < 4; ++c4) s_c[c4 * FPART + at[k] - PART * FPART] = vals[k][c4];
+    wave_sync();
+    synth_cols<Q, true>(h, gf, bo, j0, c0, hx, s_w + offy * WCOLS + offx, s_x);
+    wave_sync();
+    const int G = (hx + 3) >> 2;
+    for (int i = lane; i < tsy * G; i += 64) {
+      const int row = i / G, mg = i - row * G;
+      float o[8] = {};
+      synth_row8<Q>(h, gf, s_x, row, mg, o);
+      store8(dst + size_t(y0 + row) * ww + (x0 + 8 * mg), vec, tsx - 8 * mg, o);
     }
-  }
-  __syncthreads();
-  final_rows_range<PART * FB + 1, PART * FB + FB>(filt, s_c, s_a, s_d);
-  __syncthreads();
-  final_cols_range<PART * FB + 1, PART * FB + FB>(filt, s_a, s_d, j, m, o0, o1);
-  if constexpr (PART + 1 < FPARTS) final_part<PART + 1>(filt, s_c, s_a, s_d, vals, at, j, m, o0, o1);
+  });
 }
 
-__global__ __launch_bounds__(FINAL_THREADS) void k_idwt_final(const float* __restrict__ u,
-                                                              const float* __restrict__ rec,
-                                                              const float* __restrict__ filt,
-                                                              const float* __restrict__ W, SaraGeom g,
-                                                              float* __restrict__ out) {
-  __shared__ float s_c[4 * FPART];   // one part's LL, LH, HL, HH windows
-  __shared__ float s_a[FROWS * STF], s_d[FROWS * STF];
-  const int nx = g.nx, ww = g.nx, hh = g.ny;
-  const int oh = hh >> 1, ow = ww >> 1;
-  const TileId tl = sara_tile();
-  const int y0 = tl.y * STF, x0 = tl.x * STF;
-  const int tid = threadIdx.x;
-  // stage: element e of the flattened (basis, row, column) windows
-  float vals[FEPT][4];
-  int at[FEPT];
+// Level 1 for all 8 wavelet bases, plus the Dirac part, times 1/3.  Wave w of
+// the workgroup takes bases 8 - w and 1 + w (the same number of taps in every
+// wave) on the same tile; their sums are added in wave order.
+__global__ __launch_bounds__(256) void k_idwt_final(const float* __restrict__ u, const float* __restrict__ rec,
+                                                    const float* __restrict__ filt, const float* __restrict__ W,
+                                                    SaraGeom g, float* __restrict__ out, int vec) {
+  __shared__ __align__(16) float s_all[4][2 * SY * SS];
+  static_assert(SY * SX <= 2 * SY * SS, "a wave's sums take the place of its columns");
+  constexpr int IPL = SY * (SX / 8) / 64;   // runs of 8 outputs per lane
+  const int nx = g.nx, tsx = min(SX, nx), hx = tsx >> 1;   // images are at least 16 x 16
+  const TileId tl = sara_tile<false>();
+  const int y0 = tl.y * SY, x0 = tl.x * tsx;
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = threadIdx.x & 63;
+  float* s_x = s_all[w];
+  const int j0 = y0 >> 1, c0 = x0 >> 1, G = tsx >> 3;
+  float o[IPL][8] = {};
+#pragma unroll 1
+  for (int part = 0; part < 2; ++part) {
+    const int q = part == 0 ? 8 - w : 1 + w;
+    const Bands bd{u + size_t(q) * g.N, W ? W + size_t(q) * g.N : nullptr,
+                   g.L == 1 ? nullptr : rec + g.off[1] + size_t(q - 1) * lvl_size(g, 1), nx, g.ny >> 1, nx >> 1,
+                   nx >> 1};
+    with_basis(q, [&](auto ql) {
+      constexpr int Q = decltype(ql)::value;
+      float h[2 * Q], gf[2 * Q];
+      load_filt<Q>(filt, h, gf);
+      synth_cols<Q, false>(h, gf, bd, j0, c0, hx, nullptr, s_x);
+      wave_sync();
 #pragma unroll
-  for (int k = 0; k < FEPT; ++k) {
-    const int e = tid + k * FINAL_THREADS;
-    at[k] = -1;
-    if (e < FELEM) {
-      int q = 1;
-#pragma unroll
-      for (int p = 2; p <= 8; ++p)
-        if (e >= final_elem0(p)) q = p;
-      const int KC = FH + q;
-      const int le = e - final_elem0(q);
-      const int a = le / KC, b = le - a * KC;
-      const int r = ((y0 >> 1) - q + a) & (oh - 1), c = ((x0 >> 1) - q + b) & (ow - 1);
-      const float* ucoef = u + size_t(q) * g.N;
-      const float* wcoef = W ? W + size_t(q) * g.N : nullptr;
-      const size_t plh = size_t(r) * nx + (ow + c), phl = size_t(oh + r) * nx + c;
-      const size_t phh = size_t(oh + r) * nx + (ow + c);
-      if (g.L == 1) {
-        const size_t pll = size_t(r) * nx + c;
-        vals[k][0] = ucoef[pll] * (wcoef ? wcoef[pll] : 1.0f);
-      } else {
-        vals[k][0] = rec[g.off[1] + size_t(q - 1) * lvl_size(g, 1) + size_t(r) * ow + c];
+      for (int n = 0; n < IPL; ++n) {
+        const int i = lane + 64 * n;
+        if (i < SY * G) synth_row8<Q>(h, gf, s_x, i / G, i % G, o[n]);
       }
-      vals[k][1] = ucoef[plh] * (wcoef ? wcoef[plh] : 1.0f);
-      vals[k][2] = ucoef[phl] * (wcoef ? wcoef[phl] : 1.0f);
-      vals[k][3] = ucoef[phh] * (wcoef ? wcoef[phh] : 1.0f);
-      at[k] = (final_row0(q) + a) * FKS + b + (q - 1) / FB * FPART;
-    }
+      wave_sync();
+    });
   }
-  const int j = tid / STF, m = tid - j * STF;
-  const size_t P0 = size_t(y0 + 2 * j) * nx + (x0 + m), P1 = P0 + nx;
-  const float dirac0 = u[P0] * (W ? W[P0] : 1.0f), dirac1 = u[P1] * (W ? W[P1] : 1.0f);
-  float o0 = 0.f, o1 = 0.f;
-  final_part<0>(filt, s_c, s_a, s_d, vals, at, j, m, o0, o1);
+  // run i of 8 outputs of every wave at s_x[n][i], n-th of 8 words apart: conflict-free
+#pragma unroll
+  for (int n = 0; n < IPL; ++n)
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s_x[k * (64 * IPL) + lane + 64 * n] = o[n][k];
+  __syncthreads();
   const float third = 1.0f / 3.0f;
-  out[P0] = (o0 + dirac0) * third;
-  out[P1] = (o1 + dirac1) * third;
+  for (int i = threadIdx.x; i < SY * G * 2; i += 256) {   // 4 outputs each
+    const int run = i >> 1, k0 = 4 * (i & 1);
+    const size_t P = size_t(y0 + run / G) * nx + (x0 + 8 * (run % G) + k0);
+    float d[4], v[4];
+    load4(u + P, vec, 4, d);
+    if (W) {
+      float wv[4];
+      load4(W + P, vec, 4, wv);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) d[k] *= wv[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int a = (k0 + k) * (64 * IPL) + run;
+      v[k] = ((((s_all[0][a] + s_all[1][a]) + s_all[2][a]) + s_all[3][a]) + d[k]) * third;
+    }
+    store4(out + P, vec, 4, v);
+  }
 }
-#undef PPD_IDWT_SWITCH
 
 // Algorithm 1 weights (eq. reweighting): W = omega / (omega + |c|), in
 // place over the analysis coefficients c.
@@ -609,21 +599,31 @@ SaraGeom geom(const ppd_plan* p) {
   return g;
 }
 
+bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+template <int MODE, int RB>
+void launch_dwt(ppd_plan* p, dim3 grid, const float* x, float* out, const float* W, const SaraGeom& g, int l,
+                float alpha, float lambda, const uint8_t* active, int vec) {
+  hipLaunchKernelGGL((k_dwt<MODE, RB>), grid, dim3(DWT_THREADS), 0, p->stream, x, p->sara_ll, out, p->filt, W, g, l,
+                     alpha, lambda, active, vec);
+}
+
 int analysis_launch(ppd_plan* p, const float* x, float* out, const float* W, bool dual, float alpha,
                     float lambda, const uint8_t* active) {
   const SaraGeom g = geom(p);
   for (int l = 1; l <= g.L; ++l) {
     const int oh = (g.ny >> l), ow = (g.nx >> l);
-    const int toy = std::min(AT, oh), tox = std::min(AT, ow);
-    dim3 grid(ow / tox, oh / toy, l == 1 ? 9 : 8);
+    const int tox = std::min(TX, ow), nz = l == 1 ? 9 : 8;
+    const int vec = ow % 4 == 0 && aligned16(out) && aligned16(W) && aligned16(x);
+    // tiles of 16 rows while they fill the chip, else of 8
+    const bool tall = int64_t(ow / tox) * (oh / std::min(16, oh)) * nz >= DWT_TALL_MIN;
+    const dim3 grid(ow / tox, oh / std::min(tall ? 16 : 8, oh), nz);
     int slot;
     PPD_TRY(timer_begin(p, KK_DWT, &slot));
-    if (dual)
-      hipLaunchKernelGGL(k_dwt<A_DUAL>, grid, dim3(256), 0, p->stream, x, p->sara_ll, out, p->filt, W, g, l,
-                         alpha, lambda, active);
-    else
-      hipLaunchKernelGGL(k_dwt<A_PLAIN>, grid, dim3(256), 0, p->stream, x, p->sara_ll, out, p->filt, W, g, l,
-                         alpha, lambda, nullptr);
+    if (dual && tall) launch_dwt<A_DUAL, 8>(p, grid, x, out, W, g, l, alpha, lambda, active, vec);
+    else if (dual) launch_dwt<A_DUAL, 4>(p, grid, x, out, W, g, l, alpha, lambda, active, vec);
+    else if (tall) launch_dwt<A_PLAIN, 8>(p, grid, x, out, W, g, l, alpha, lambda, nullptr, vec);
+    else launch_dwt<A_PLAIN, 4>(p, grid, x, out, W, g, l, alpha, lambda, nullptr, vec);
     PPD_HIP(hipGetLastError());
     PPD_TRY(timer_end(p, slot));
   }
@@ -648,10 +648,10 @@ int sara_synthesis(ppd_plan* p, const float* u, float* out, const float* W) {
     // levels L and L-1 in one launch
     const int l = g.L - 1;
     const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-    const int tsy = std::min(ST, hh), tsx = std::min(ST, ww);
+    const int tsy = std::min(SY, hh), tsx = std::min(SX, ww);
     int slot;
     PPD_TRY(timer_begin(p, KK_IDWT, &slot));
-    hipLaunchKernelGGL(k_idwt2, dim3(ww / tsx, hh / tsy, 8), dim3(256), 0, p->stream, u, p->sara_rec, p->filt,
+    hipLaunchKernelGGL(k_idwt2, dim3(ww / tsx, hh / tsy, 2), dim3(256), 0, p->stream, u, p->sara_rec, p->filt,
                        W, g);
     PPD_HIP(hipGetLastError());
     PPD_TRY(timer_end(p, slot));
@@ -659,18 +659,19 @@ int sara_synthesis(ppd_plan* p, const float* u, float* out, const float* W) {
   }
   for (int l = top; l >= 2; --l) {
     const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-    const int tsy = std::min(ST, hh), tsx = std::min(ST, ww);
+    const int tsy = std::min(SY, hh), tsx = std::min(SX, ww);
     int slot;
     PPD_TRY(timer_begin(p, KK_IDWT, &slot));
-    hipLaunchKernelGGL(k_idwt, dim3(ww / tsx, hh / tsy, 8), dim3(256), 0, p->stream, u, p->sara_rec, p->filt,
+    hipLaunchKernelGGL(k_idwt, dim3(ww / tsx, hh / tsy, 2), dim3(256), 0, p->stream, u, p->sara_rec, p->filt,
                        W, g, l);
     PPD_HIP(hipGetLastError());
     PPD_TRY(timer_end(p, slot));
   }
   int slot;
   PPD_TRY(timer_begin(p, KK_IDWT, &slot));
-  hipLaunchKernelGGL(k_idwt_final, dim3(g.nx / STF, g.ny / STF), dim3(FINAL_THREADS), 0, p->stream, u, p->sara_rec,
-                     p->filt, W, g, out);
+  const int vec = aligned16(u) && aligned16(W) && aligned16(out);
+  hipLaunchKernelGGL(k_idwt_final, dim3(g.nx / std::min(SX, g.nx), g.ny / SY), dim3(256), 0, p->stream, u,
+                     p->sara_rec, p->filt, W, g, out, vec);
   PPD_HIP(hipGetLastError());
   return timer_end(p, slot);
 }
