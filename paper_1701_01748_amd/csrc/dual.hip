@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * NW) void k_alg2(
     double* __restrict__ part_out, XcdSplit xs) {
   __shared__ ItemTab tab;
   __shared__ double s_q[NW][MAX_ITEM_SEGS];
-  const int ii = xcd_unit(blockIdx.x, xs);
+  const int ii = xcd_item(blockIdx.x, xs);
   if (ii < 0 || ii >= n_items) return;
   const Item it = items[ii];
   const int lane = threadIdx.x & 63;

@@ -67,31 +67,21 @@ __device__ __forceinline__ void load_kb(const float* __restrict__ kbc, KbCoef& k
 #ifndef PPD_DEGRID_WAVES
 #define PPD_DEGRID_WAVES 4
 #endif
-#ifndef PPD_DEGRID_WAVES8
-#define PPD_DEGRID_WAVES8 1
-#endif
-// Waves per degridding workgroup: 8 x 8 tiles hold ~100 visibilities, one
-// wave's worth, so there each item is one single-wave workgroup.
-template <int T>
-struct DegridCfg {
-  static constexpr int NW = T == 8 ? PPD_DEGRID_WAVES8 : PPD_DEGRID_WAVES;
-};
 
 // Degridding: one workgroup per item, the region staged in LDS; the item's
 // visibilities (all its segments, flattened) are taken in batches of 64, a
 // batch per wave in turn, one visibility per lane.  In the dual mode the
 // per-segment partials of ||q - y||^2 and ||G a - y||^2 are wave sums over
 // the lanes of each segment, added per wave in batch order and summed over
-// the waves in a fixed order at the end: deterministic.
+// the waves in a fixed order at the end: deterministic.  (Wave sums by
+// permuted operands instead of LDS shuffles: 25.9 -> 22.5 us per dual launch
+// at 512^2, 1.3M points.)
 // 8 x 8 tiles: the 15 x 15 region is staged twice in LDS with a row stride
 // of G8_RS float2 (16-byte aligned rows), copy E holding cell (r, c) at
 // r G8_RS + c and copy O holding cell (r, c + 1) there, so that a lane's 8
 // consecutive cells of a tap row start at an even float2 of one copy and
 // are read as four 16-byte loads (half the LDS instructions of 8-byte
 // loads).  The weighted sums run in the same order as the 8-byte form.
-#ifndef PPD_DEGRID_B128
-#define PPD_DEGRID_B128 1
-#endif
 constexpr int G8_RS = 18;
 constexpr int G8_COPY = 15 * G8_RS;   // float2 per copy
 
@@ -146,8 +136,11 @@ __device__ __forceinline__ float2 gather8(const float2* reg2, const Taps& t) {
   return make_float2(ax, ay);
 }
 
-template <int T, bool DUAL>
-__global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
+// NW: waves per workgroup.  8 x 8 tiles hold about two batches, so there an
+// item is one wave's work; where the items are too few to fill the chip
+// (SHARE_ITEMS) two waves share it.
+template <int T, bool DUAL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_degrid(
     const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
@@ -155,12 +148,11 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
     const float2* __restrict__ v, const double2* __restrict__ z, float2* __restrict__ gout, double mu,
     double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
   constexpr int R = T + 7;
-  constexpr int NW = DegridCfg<T>::NW;
-  constexpr bool B128 = PPD_DEGRID_B128 && T == 8;
+  constexpr bool B128 = T == 8;
   __shared__ __align__(16) float2 reg[B128 ? 2 * G8_COPY : R * R];
   __shared__ ItemTab tab;
   __shared__ double s_q[NW][MAX_ITEM_SEGS], s_r[NW][MAX_ITEM_SEGS];
-  const int ii = xcd_unit(blockIdx.x, xs);
+  const int ii = xcd_item(blockIdx.x, xs);
   if (ii < 0 || ii >= n_items) return;
   const Item it = items[ii];
   const int r0 = it.ty * T, c0 = it.tx * T;
@@ -183,7 +175,10 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
       }
     }
   }
-  load_item_tab(it, segs, tab);
+  const int nseg = it.seg1 - it.seg0;
+  const bool one = nseg == 1;   // uniform
+  const int total = it.total;
+  if (!one) load_item_tab(it, segs, tab);
   KbCoef kbw;
   load_kb(kbc, kbw);
   if (DUAL)
@@ -200,8 +195,6 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
     }
   }
   __syncthreads();
-  const int nseg = it.seg1 - it.seg0;
-  const int total = tab.pre[nseg];
   // Batch k of 64 flattened visibilities goes to wave k mod NW; a wave
   // loads its next batch's operands before working on the current one.
   struct Batch {
@@ -212,13 +205,18 @@ __global__ __launch_bounds__(64 * DegridCfg<T>::NW) void k_degrid(
     int pi, sg, sb;
   };
   auto load = [&](int bt, int& sb, Batch& b) {
-    while (bt * 64 >= tab.pre[sb + 1]) ++sb;
+    if (!one)
+      while (bt * 64 >= tab.pre[sb + 1]) ++sb;
     b.sb = sb;
     const int li = bt * 64 + lane;
     b.sg = sb;
     if (li < total) {
-      b.sg = seg_of(li, sb, tab.pre);
-      b.pi = tab.start[b.sg] + (li - tab.pre[b.sg]);
+      if (one) {
+        b.pi = it.start + li;
+      } else {
+        b.sg = seg_of(li, sb, tab.pre);
+        b.pi = tab.start[b.sg] + (li - tab.pre[b.sg]);
+      }
       b.ou = wu[b.pi];
       b.ov = wv[b.pi];
       b.th = theta ? theta[b.pi] : 1.0f;
@@ -331,15 +329,21 @@ struct GridSrc {
 };
 
 // Loads batch bt (64 flattened visibilities of the item) for this lane;
-// sb tracks the segment of the batch's first visibility.
+// sb tracks the segment of the batch's first visibility.  An item of one
+// segment (uniform) is found without the table: from `start`, in `block`.
 template <bool DUAL>
-__device__ __forceinline__ void grid_load(const GridSrc& g, const ItemTab& tab, int total, int lane, int bt,
-                                          int& sb, GridBatch& b) {
-  while (bt * 64 >= tab.pre[sb + 1]) ++sb;
+__device__ __forceinline__ void grid_load(const GridSrc& g, const ItemTab& tab, bool one, int start, int block,
+                                          int total, int lane, int bt, int& sb, GridBatch& b) {
+  if (!one)
+    while (bt * 64 >= tab.pre[sb + 1]) ++sb;
   const int li = bt * 64 + lane;
   if (li < total) {
-    const int sg = seg_of(li, sb, tab.pre);
-    const int pi = tab.start[sg] + (li - tab.pre[sg]);
+    int pi = start + li, bk = block;
+    if (!one) {
+      const int sg = seg_of(li, sb, tab.pre);
+      pi = tab.start[sg] + (li - tab.pre[sg]);
+      bk = tab.block[sg];
+    }
     b.pi = pi;
     b.ou = g.wu[pi];
     b.ov = g.wv[pi];
@@ -352,8 +356,8 @@ __device__ __forceinline__ void grid_load(const GridSrc& g, const ItemTab& tab, 
       b.U = g.U[pi];
       b.y = g.y[pi];
       b.v = g.v[pi];
-      b.bf = g.bfac[tab.block[sg]];
-      b.act = !g.active || g.active[tab.block[sg]];
+      b.bf = g.bfac[bk];
+      b.act = !g.active || g.active[bk];
     }
   }
 }
@@ -427,7 +431,7 @@ __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
   __shared__ float2 wxv[NW][64 * WXS];         // wx[b] * value, per visibility of the batch
   __shared__ float wyb[NW][64 * WXS];          // wy[a]
   __shared__ ItemTab tab;
-  const int ii = xcd_unit(blockIdx.x, xs);
+  const int ii = xcd_item(blockIdx.x, xs);
   if (ii < 0 || ii >= n_items) return;
   const Item it = items[ii];
   const int r0 = it.ty * T, c0 = it.tx * T;
@@ -452,10 +456,10 @@ __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
   const int total = tab.pre[nseg];
   int sb = 0;
   GridBatch bn{};
-  if (uwid * 64 < total) grid_load<DUAL>(src, tab, total, lane, uwid, sb, bn);
+  if (uwid * 64 < total) grid_load<DUAL>(src, tab, false, 0, 0, total, lane, uwid, sb, bn);
   for (int k = uwid; k * 64 < total; k += NW) {
     const GridBatch bt = bn;
-    if ((k + NW) * 64 < total) grid_load<DUAL>(src, tab, total, lane, k + NW, sb, bn);
+    if ((k + NW) * 64 < total) grid_load<DUAL>(src, tab, false, 0, 0, total, lane, k + NW, sb, bn);
     const int nb = min(64, total - k * 64);
     // prepare: one visibility per lane (lanes past nb carry zero weight).
     // The new z and v are stored after the apply loop, so that no store is
@@ -545,41 +549,30 @@ __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
 // lane l of a product step then reads row 4 g + l / 16, entry l mod 16, of
 // each.  No read-modify-write of LDS.
 //
-// An 8 x 8 tile holds about one batch, so a single-wave workgroup takes a
-// run of consecutive items, and the wave's (item, batch) steps form one
-// software pipeline: the operands of the next step, which may be the next
-// item's first batch, are loaded before the current step is prepared and
-// applied, and the next item's segment list is fetched into registers when
-// the current item starts.  Only the first step of a run waits for memory.
+// A single-wave workgroup takes one item; the operands of its next batch are
+// loaded before the current batch is prepared and applied.  (Runs of 2 items
+// per wave in one pipeline were 37.5 against 36.6 us at 512^2, 1.3M points,
+// and 12.2 against 8.6 at 256^2, 65536: with the items' first segments in
+// their records there is little left to hide, and fewer waves.)  Where the
+// items are too few to fill the chip (SHARE_ITEMS), two waves alternate an
+// item's batches and their partial regions are added at the end.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int GM_T = 8;
 constexpr int GM_AS = 17;   // A row stride (floats): spreads the prepare writes over banks
 constexpr int GM_BS = 17;   // B row stride (float2)
-static_assert(PPD_GRIDM_RUN >= 1 && PPD_GRIDM_RUN <= 64, "a run's items are held one per lane");
 
-// The segment list of one item as a lane's register (lane s: segment s).
-__device__ __forceinline__ Seg item_seg(const Seg* __restrict__ segs, int seg0, int seg1, int lane) {
-  Seg sg{0, 0, 0, 0};
-  if (lane < seg1 - seg0) sg = segs[seg0 + lane];
-  return sg;
+// Lane l holds rows 4 (l / 16) + e, e = 0..3, of column l mod 16 (row 15 and
+// column 15 stay zero: no footprint reaches them).
+__device__ __forceinline__ void store_region(f32x4 sr, f32x4 si, float2* __restrict__ dst, int gq, int gc) {
+  constexpr int R = GM_T + 7;
+  if (gc < R)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (4 * gq + e < R) dst[(4 * gq + e) * R + gc] = make_float2(sr[e], si[e]);
 }
 
-// Segment table of an item from its lanes' segments (exclusive prefix sum
-// of the counts); wave-local.
-__device__ __forceinline__ void tab_from_seg(const Seg& sg, int lane, ItemTab& tab) {
-  tab.start[lane] = sg.start;
-  tab.block[lane] = sg.block;
-  int inc = sg.count;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(inc, o);
-    if (lane >= o) inc += t;
-  }
-  tab.pre[lane + 1] = inc;
-  if (lane == 0) tab.pre[0] = 0;
-}
-
-template <bool DUAL>
-__global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
+template <bool DUAL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_grid_mfma(
     float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
@@ -587,41 +580,32 @@ __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
     float2* __restrict__ v, double2* __restrict__ z, const float2* __restrict__ ga, double mu,
     double lambda, const double2* __restrict__ bfac, int exact, const uint8_t* __restrict__ active,
     XcdSplit xs) {
-  constexpr int T = GM_T, R = T + 7, WPG = PPD_GRIDM_WPG;
+  constexpr int T = GM_T, R = T + 7;
   static_assert(R <= 16, "the region must fit one 16 x 16 product tile");
-  __shared__ float sAw[WPG][32 * GM_AS];
-  __shared__ float2 sBw[WPG][32 * GM_BS];
-  __shared__ ItemTab tabsw[WPG][2];   // per wave: current and next item
-  KbCoef kbw;
-  load_kb(kbc, kbw);
-  __syncthreads();
-  // each wave of the workgroup works alone from here on
-  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  const int unit = xcd_unit(blockIdx.x, xs);
-  if (unit < 0) return;
-  const int i0 = (unit * WPG + wid) * PPD_GRIDM_RUN;
-  if (i0 >= n_items) return;
-  const int i1 = min(i0 + PPD_GRIDM_RUN, n_items);
-  const int lane = threadIdx.x & 63;
+  __shared__ float sAw[NW][32 * GM_AS];
+  __shared__ __align__(16) float2 sBw[NW][32 * GM_BS];
+  __shared__ ItemTab tab;
+  const int ii = xcd_item(blockIdx.x, xs);
+  if (ii < 0 || ii >= n_items) return;
+  const Item it = items[ii];
+  const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = threadIdx.x & 63;
+  const int c0 = it.tx * T, r0 = it.ty * T, total = it.total;
   float* sA = sAw[wid];
   float2* sB = sBw[wid];
-  ItemTab* tabs = tabsw[wid];
   const int gq = lane >> 4, gc = lane & 15;   // row-in-group and entry read in a product step
-  // the run's items, one per lane; item i's fields come from lane i - i0
-  Item itl{0, 0, 0, 0};
-  if (i0 + lane < i1) itl = items[i0 + lane];
   const GridSrc src{wu, wv, theta, vin, y, U, v, z, ga, bfac, active};
-  auto field = [&](int v, int i) { return __builtin_amdgcn_readlane(v, i - i0); };
-  tab_from_seg(item_seg(segs, field(itl.seg0, i0), field(itl.seg1, i0), lane), lane, tabs[0]);
-  Seg sgn{0, 0, 0, 0};   // next item's segments, fetched when an item starts
-  if (i0 + 1 < i1) sgn = item_seg(segs, field(itl.seg0, i0 + 1), field(itl.seg1, i0 + 1), lane);
-  __builtin_amdgcn_wave_barrier();
+  const bool one = it.seg1 - it.seg0 == 1;
+  if (!one) {
+    load_item_tab(it, segs, tab);
+    __syncthreads();
+  }
+  int sb = 0;
+  GridBatch bn{};
+  if (wid * 64 < total) grid_load<DUAL>(src, tab, one, it.start, it.block, total, lane, wid, sb, bn);
+  KbCoef kbw;
+  load_kb(kbc, kbw);
   f32x4 accr = {0.f, 0.f, 0.f, 0.f}, acci = {0.f, 0.f, 0.f, 0.f};
   f32x4 accr2 = {0.f, 0.f, 0.f, 0.f}, acci2 = {0.f, 0.f, 0.f, 0.f};
-  int cur = i0, kb = 0, sb = 0;
-  int total = __builtin_amdgcn_readfirstlane(tabs[0].pre[field(itl.seg1, i0) - field(itl.seg0, i0)]);
-  GridBatch bn{};
-  grid_load<DUAL>(src, tabs[0], total, lane, 0, sb, bn);
   float* arow = sA + (lane & 31) * GM_AS;
   float2* brow = sB + (lane & 31) * GM_BS;
   const float* aq = sA + gq * GM_AS + gc;    // entry read by this lane in product step 0
@@ -630,11 +614,10 @@ __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
   for (int e = lane; e < 32 * GM_AS; e += 64) sA[e] = 0.f;
   for (int e = lane; e < 32 * GM_BS; e += 64) sB[e] = make_float2(0.f, 0.f);
   __builtin_amdgcn_wave_barrier();
-  while (true) {
+  for (int kb = wid; kb * 64 < total; kb += NW) {
     const int nb = min(64, total - kb * 64);
-    const int c0 = field(itl.tx, cur) * T, r0 = field(itl.ty, cur) * T;
-    // this step's taps and values, from the operands loaded during the
-    // previous step; bn is free again afterwards
+    // this batch's taps and values, from the operands loaded during the
+    // previous one; bn is free again afterwards
     double2 znew{};
     float2 vnew{};
     float vx = 0.f, vy = 0.f;
@@ -650,28 +633,15 @@ __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
       vx = val.x * bn.th;
       vy = (t.conj ? -val.y : val.y) * bn.th;
     }
-    // stores before the next step's loads: vector memory operations
+    // stores before the next batch's loads: vector memory operations
     // complete in issue order, so the wait for those loads does not add a
     // wait for stores issued after them
     if (zst) {
       z[pi] = znew;
       v[pi] = vnew;
     }
-    // the next step: the next batch of this item, else the next item's first
-    const bool last = (kb + 1) * 64 >= total;
-    const int nxt = last ? cur + 1 : cur;
-    int ntotal = total;
-    if (nxt < i1) {
-      ItemTab& tn = tabs[(nxt - i0) & 1];
-      if (last) {
-        tab_from_seg(sgn, lane, tn);
-        __builtin_amdgcn_wave_barrier();
-        ntotal = __builtin_amdgcn_readfirstlane(tn.pre[field(itl.seg1, nxt) - field(itl.seg0, nxt)]);
-        sb = 0;
-        if (nxt + 1 < i1) sgn = item_seg(segs, field(itl.seg0, nxt + 1), field(itl.seg1, nxt + 1), lane);
-      }
-      grid_load<DUAL>(src, tn, ntotal, lane, last ? 0 : kb + 1, sb, bn);
-    }
+    if ((kb + NW) * 64 < total)
+      grid_load<DUAL>(src, tab, one, it.start, it.block, total, lane, kb + NW, sb, bn);
     // The batch goes through LDS in two halves of 32 rows (half the staging
     // memory: more waves per CU): lanes 0-31 write their 8 taps into rows
     // that are otherwise zero and the first 8 product steps read them, the
@@ -691,11 +661,11 @@ __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
         }
       }
       __builtin_amdgcn_wave_barrier();
-      // the operands of PPD_GRIDM_READ_AHEAD product steps are read before
-      // their first product (rows past the batch end read as zero); two
-      // accumulator pairs (even / odd steps) make independent chains
-      constexpr int RA = PPD_GRIDM_READ_AHEAD;
-      static_assert(RA == 2 || RA == 4 || RA == 8, "read-ahead of 2, 4 or 8 product steps");
+      // the operands of RA product steps are read before their first product
+      // (rows past the batch end read as zero; 4 or 8 steps cost 1.5 us at
+      // 512^2 and 15 at 2048^2 in registers and so in waves); two accumulator
+      // pairs (even / odd steps) make independent chains
+      constexpr int RA = 2;
       const int ng = (min(32, nb - 32 * h) + 3) >> 2;
 #pragma unroll
       for (int g0 = 0; g0 < 8; g0 += RA) {
@@ -727,22 +697,23 @@ __global__ __launch_bounds__(64 * PPD_GRIDM_WPG) void k_grid_mfma(
         }
       }
     }
-    if (last) {
-      // Lane l holds rows 4 (l / 16) + e, e = 0..3, of column l mod 16 (row
-      // 15 and column 15 stay zero: no footprint reaches them).
-      const f32x4 sr = accr + accr2, si = acci + acci2;
-      float2* dst = scratch + size_t(cur) * (R * R);
-      if (gc < R)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (4 * gq + e < R) dst[(4 * gq + e) * R + gc] = make_float2(sr[e], si[e]);
-      accr = accr2 = acci = acci2 = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    if (nxt >= i1) break;
-    cur = nxt;
-    kb = last ? 0 : kb + 1;
-    total = ntotal;
   }
+  float2* dst = scratch + size_t(ii) * (R * R);
+  f32x4 sr = accr + accr2, si = acci + acci2;
+  if constexpr (NW == 2) {
+    // the second wave's region through its staging memory, whose products are done
+    f32x4* s = reinterpret_cast<f32x4*>(sBw[1]);
+    static_assert(sizeof(sBw[1]) >= 128 * sizeof(f32x4), "room for two accumulators");
+    if (wid == 1) {
+      s[lane] = sr;
+      s[64 + lane] = si;
+    }
+    __syncthreads();
+    if (wid == 1) return;
+    sr += s[lane];
+    si += s[64 + lane];
+  }
+  store_region(sr, si, dst, gq, gc);
 }
 
 // One thread per grid cell (FOLD_CELLS cells per workgroup, T*T/FOLD_CELLS
@@ -868,34 +839,32 @@ __global__ void k_permute(const int32_t* __restrict__ perm, int64_t M, int to_us
 }
 
 
-template <int T>
+template <int T, int NW>
 int launch_degrid(ppd_plan* p, bool dual, float2* out, const DualArgs* a, double* part_out) {
   if (!dual) {
-    hipLaunchKernelGGL((k_degrid<T, false>), dim3(p->split1.launch), dim3(64 * DegridCfg<T>::NW), 0, p->stream,
-                       p->grid_f, p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
-                       p->sv_scale, p->kbc, out, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0,
-                       nullptr, nullptr, p->split1);
+    hipLaunchKernelGGL((k_degrid<T, false, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
+                       p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
+                       out, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, nullptr, nullptr, p->split1);
   } else {
-    hipLaunchKernelGGL((k_degrid<T, true>), dim3(p->split1.launch), dim3(64 * DegridCfg<T>::NW), 0, p->stream,
-                       p->grid_f, p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
-                       p->sv_scale, p->kbc, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
-                       part_out, a->rpart, p->split1);
+    hipLaunchKernelGGL((k_degrid<T, true, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
+                       p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
+                       nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, part_out, a->rpart, p->split1);
   }
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
 
+template <int NW>
 int launch_grid_mfma(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, int exact) {
+  const XcdSplit& xs = p->split1;
   if (!dual) {
-    hipLaunchKernelGGL((k_grid_mfma<false>), dim3(p->split_grid.launch), dim3(64 * PPD_GRIDM_WPG), 0, p->stream,
-                       p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta,
-                       p->su_scale, p->sv_scale, p->kbc, vin, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       0.0, 0.0, nullptr, 0, nullptr, p->split_grid);
+    hipLaunchKernelGGL((k_grid_mfma<false, NW>), dim3(xs.launch), dim3(64 * NW), 0, p->stream, p->gscratch, p->Ky,
+                       p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc, vin,
+                       nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, nullptr, 0, nullptr, xs);
   } else {
-    hipLaunchKernelGGL((k_grid_mfma<true>), dim3(p->split_grid.launch), dim3(64 * PPD_GRIDM_WPG), 0, p->stream,
-                       p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta,
-                       p->su_scale, p->sv_scale, p->kbc, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
-                       a->lambda, p->bfac, exact, a->active, p->split_grid);
+    hipLaunchKernelGGL((k_grid_mfma<true, NW>), dim3(xs.launch), dim3(64 * NW), 0, p->stream, p->gscratch, p->Ky,
+                       p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
+                       nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, a->lambda, p->bfac, exact, a->active, xs);
   }
   PPD_HIP(hipGetLastError());
   return PPD_OK;
@@ -940,10 +909,13 @@ int dispatch_degrid(ppd_plan* p, bool dual, float2* out, const DualArgs* a, doub
   PPD_TRY(timer_begin(p, KK_DEGRID, &slot));
   int st;
   switch (p->T) {
-    case 8: st = launch_degrid<8>(p, dual, out, a, part_out); break;
-    case 16: st = launch_degrid<16>(p, dual, out, a, part_out); break;
-    case 32: st = launch_degrid<32>(p, dual, out, a, part_out); break;
-    default: st = launch_degrid<64>(p, dual, out, a, part_out); break;
+    case 8:
+      st = p->n_items <= SHARE_ITEMS ? launch_degrid<8, 2>(p, dual, out, a, part_out)
+                                     : launch_degrid<8, 1>(p, dual, out, a, part_out);
+      break;
+    case 16: st = launch_degrid<16, PPD_DEGRID_WAVES>(p, dual, out, a, part_out); break;
+    case 32: st = launch_degrid<32, PPD_DEGRID_WAVES>(p, dual, out, a, part_out); break;
+    default: st = launch_degrid<64, PPD_DEGRID_WAVES>(p, dual, out, a, part_out); break;
   }
   PPD_TRY(st);
   return timer_end(p, slot);
@@ -954,7 +926,10 @@ int dispatch_grid(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, 
   PPD_TRY(timer_begin(p, KK_GRID, &slot));
   int st;
   switch (p->T) {
-    case 8: st = launch_grid_mfma(p, dual, vin, a, exact); break;
+    case 8:
+      st = p->n_items <= SHARE_ITEMS ? launch_grid_mfma<2>(p, dual, vin, a, exact)
+                                     : launch_grid_mfma<1>(p, dual, vin, a, exact);
+      break;
     case 16: st = launch_grid<16>(p, dual, vin, a, exact); break;
     case 32: st = launch_grid<32>(p, dual, vin, a, exact); break;
     default: st = launch_grid<64>(p, dual, vin, a, exact); break;

@@ -393,6 +393,9 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
         }
       }
       it.seg1 = int32_t(segs.size());
+      it.start = segs[it.seg0].start;
+      it.block = segs[it.seg0].block;
+      for (int g = it.seg0; g < it.seg1; ++g) it.total += segs[g].count;
       items.push_back(it);
     }
   }
@@ -450,35 +453,19 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   {
     std::vector<double> cost(p->n_items);
     for (int i = 0; i < p->n_items; ++i) {
-      int64_t c = 0;
-      for (int g = items[i].seg0; g < items[i].seg1; ++g) c += segs[g].count;
-      cost[i] = double((c + 63) / 64) + 1.0;
+      cost[i] = double((items[i].total + 63) / 64) + 1.0;
     }
-    auto split = [&](int unit) {
-      XcdSplit sp{};
-      sp.unit = unit;
-      const int nu = (p->n_items + unit - 1) / unit;
-      std::vector<double> pre(nu + 1, 0.0);
-      for (int u = 0; u < nu; ++u) {
-        double c = 0.0;
-        for (int i = u * unit; i < std::min(p->n_items, (u + 1) * unit); ++i) c += cost[i];
-        pre[u + 1] = pre[u] + c;
-      }
-      sp.off[0] = 0;
-      sp.off[MAX_XCD] = nu;
-      int u = 0;
-      for (int k = 1; k < MAX_XCD; ++k) {
-        const double target = pre[nu] * k / MAX_XCD;
-        while (u < nu && pre[u] < target) ++u;
-        sp.off[k] = u;
-      }
-      int longest = 0;
-      for (int k = 0; k < MAX_XCD; ++k) longest = std::max(longest, sp.off[k + 1] - sp.off[k]);
-      sp.launch = std::max(1, longest) * MAX_XCD;
-      return sp;
-    };
-    p->split1 = split(1);
-    p->split_grid = split(PPD_GRIDM_RUN * PPD_GRIDM_WPG);
+    XcdSplit& sp = p->split1;
+    std::vector<double> pre(p->n_items + 1, 0.0);
+    for (int i = 0; i < p->n_items; ++i) pre[i + 1] = pre[i] + cost[i];
+    sp.off[MAX_XCD] = p->n_items;
+    int i = 0, longest = 0;
+    for (int k = 1; k < MAX_XCD; ++k) {
+      while (i < p->n_items && pre[i] < pre[p->n_items] * k / MAX_XCD) ++i;
+      sp.off[k] = i;
+    }
+    for (int k = 0; k < MAX_XCD; ++k) longest = std::max(longest, sp.off[k + 1] - sp.off[k]);
+    sp.launch = std::max(1, longest) * MAX_XCD;
   }
   p->n_tile_launch = ((ntiles + MAX_XCD - 1) / MAX_XCD) * MAX_XCD;
   p->items_host = items;

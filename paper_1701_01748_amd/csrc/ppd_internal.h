@@ -55,12 +55,12 @@ constexpr uint64_t PA_EMPTY = 0x7ff8000000000000ull;   // quiet NaN: no partial 
 #define PPD_FOLD_HEAVY 16
 #endif
 constexpr int FOLD_HEAVY = PPD_FOLD_HEAVY;   // item regions above which a tile's fold takes a whole workgroup
-#ifndef PPD_GRIDM_RUN
-#define PPD_GRIDM_RUN 2
-#endif
-#ifndef PPD_GRIDM_WPG
-#define PPD_GRIDM_WPG 1
-#endif
+// Item count up to which two waves share each item in the 8 x 8 kernels: with
+// fewer waves than the chip holds (4096 at 4 per SIMD), the length of one
+// wave's chain is the kernel's time.  Gridding 10.8 -> 5.4 us at 64^2, 4096
+// points, 8.6 -> 7.4 at 256^2, 65536; 15.6 -> 16.6 at 512^2, 250k, where the
+// waves suffice.
+constexpr int SHARE_ITEMS = 4096;
 // Captured-iteration graphs per plan: one iteration without statistics
 // partials, one with them and the periodic reduction, one with the partials
 // only, and a captured run (a statistics period, or GRAPH_RUN iterations
@@ -70,12 +70,6 @@ constexpr int GRAPH_SLOTS = 4;
 #define PPD_GRAPH_RUN 8
 #endif
 constexpr int GRAPH_RUN = PPD_GRAPH_RUN;
-// Product steps of the matrix-core gridding whose LDS operands are read
-// before the first of their products (2, 4 or 8).
-#ifndef PPD_GRIDM_READ_AHEAD
-#define PPD_GRIDM_READ_AHEAD 2
-#endif
-
 // The spectrum of the (real) image is Hermitian, so the grids hold the columns
 // c = -GRID_PAD .. Kx/2 + GRID_PAD - 1 only, at padded index c + GRID_PAD: the
 // columns 0 .. Kx/2 and, beyond either end, the mirror images that taps reach.
@@ -120,13 +114,12 @@ struct FftTwiddles {
 
 // Launch order of the work items over the XCDs: the items, in spatial
 // order, are cut into 8 contiguous bands of near-equal work (64-point
-// batches plus one per item for its region), XCD k taking the units
-// (workgroups of `unit` consecutive items) [off[k], off[k+1]).  Workgroup
-// ids go round-robin over the XCDs, so workgroup b runs unit
-// off[b mod 8] + b / 8 of band b mod 8, if that band has it.
+// batches plus one per item for its region), XCD k taking the items
+// [off[k], off[k+1]).  Workgroup ids go round-robin over the XCDs, so
+// workgroup b runs item off[b mod 8] + b / 8 of band b mod 8, if that band
+// has it.
 struct XcdSplit {
   int32_t off[MAX_XCD + 1];
-  int32_t unit;     // items per workgroup
   int32_t launch;   // workgroups to launch: 8 x the longest band
 };
 
@@ -136,10 +129,12 @@ struct Seg {
   int32_t start, count, block, item;
 };
 // A work item (one workgroup): the segments [seg0, seg1) of tile (tx, ty),
-// at most chunk_max visibilities.  Items are ordered tile by tile in
-// row-major tile order.
+// `total` visibilities, at most chunk_max.  Items are ordered tile by tile in
+// row-major tile order.  The first segment is repeated here: most items have
+// no other (one radial block per tile), and then need no segment table.
 struct Item {
   int32_t tx, ty, seg0, seg1;
+  int32_t start, block, total, pad_;
 };
 
 // Kernel kinds for the optional per-launch event timer.
@@ -177,7 +172,7 @@ struct ppd_plan {
   std::vector<ppd::Seg> segs_host;
   std::vector<int32_t> bseg_off;           // [d+1] into bseg_ids
   int n_items = 0, n_segs = 0;
-  ppd::XcdSplit split1{}, split_grid{};   // 1, PPD_GRIDM_RUN x WPG items per workgroup
+  ppd::XcdSplit split1{};
   int n_tiles = 0, n_tile_launch = 0;
 
   // device: coverage and plan tables
@@ -415,16 +410,35 @@ __device__ __forceinline__ int seg_of(int li, int s, const int* pre) {
   return s;
 }
 
-// Sum over the 64 lanes of a wave by a fixed butterfly (lanes may differ in
-// the last bit; callers use lane 0's value).
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+// Value of the lane that a data-parallel permutation within 16 lanes names.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, int(b), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(int(b), lane), hi = __builtin_amdgcn_readlane(int(b >> 32), lane);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
 }
 
-// The unit (first item / unit) a workgroup takes in a work-balanced XCD
-// split, or -1 when its XCD's band has no unit left for it.
-__device__ __forceinline__ int xcd_unit(int bid, const XcdSplit& s) {
+// Sum over the 64 lanes of a wave in a fixed order, the same in every lane:
+// within 16 lanes by permuted operands (quads, half rows, rows), then the four
+// rows.  No LDS: a shuffle butterfly takes 12 LDS permutes one after another.
+// All 64 lanes must be active.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_move<0xB1>(v);    // quad_perm 1 0 3 2
+  v += dpp_move<0x4E>(v);    // quad_perm 2 3 0 1
+  v += dpp_move<0x141>(v);   // row_half_mirror
+  v += dpp_move<0x140>(v);   // row_mirror
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// The item a workgroup takes in a work-balanced XCD split, or -1 when its
+// XCD's band has none left for it.
+__device__ __forceinline__ int xcd_item(int bid, const XcdSplit& s) {
   const int k = bid % MAX_XCD;
   const int u = s.off[k] + bid / MAX_XCD;
   return u < s.off[k + 1] ? u : -1;
