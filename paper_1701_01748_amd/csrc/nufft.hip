@@ -144,9 +144,9 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
     const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
-    float2* __restrict__ out, const float2* __restrict__ y, const double* __restrict__ U,
-    const float2* __restrict__ v, const double2* __restrict__ z, float2* __restrict__ gout, double mu,
-    double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
+    float2* __restrict__ out, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
+    const double* __restrict__ U, const float2* __restrict__ v, const double2* __restrict__ z,
+    float2* __restrict__ gout, double mu, double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
   constexpr int R = T + 7;
   constexpr bool B128 = T == 8;
   __shared__ __align__(16) float2 reg[B128 ? 2 * G8_COPY : R * R];
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
     float2 v, y;
     double2 z;
     double U;
-    int pi, sg, sb;
+    int pi, sg, sb, po;
   };
   auto load = [&](int bt, int& sb, Batch& b) {
     if (!one)
@@ -225,6 +225,8 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
         b.U = U[b.pi];
         b.z = z[b.pi];
         b.y = y[b.pi];
+      } else {
+        b.po = uperm ? uperm[b.pi] : b.pi;   // where the caller's order has it
       }
     }
   };
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
       }
       const float2 g = make_float2(ax * th, (t.conj ? -ay : ay) * th);
       if (!DUAL) {
-        out[pi] = g;
+        out[cb.po] = g;
       } else {
         // argument of the data-dual update of Algorithm 3: w = U^-1 v + Theta G a (Theta G a kept for the
         // gridding pass, which rebuilds w); first Algorithm 2 step
@@ -326,6 +328,7 @@ struct GridSrc {
   const float* wu; const float* wv; const float* theta;
   const float2* vin; const float2* y; const double* U; const float2* v; const double2* z;
   const float2* ga; const double2* bfac; const uint8_t* active;
+  const int32_t* uperm;   // plain: vin is in the caller's order (plan -> caller), NULL: in plan order
 };
 
 // Loads batch bt (64 flattened visibilities of the item) for this lane;
@@ -349,7 +352,7 @@ __device__ __forceinline__ void grid_load(const GridSrc& g, const ItemTab& tab, 
     b.ov = g.wv[pi];
     b.th = g.theta ? g.theta[pi] : 1.0f;
     if (!DUAL) {
-      b.vin = g.vin[pi];
+      b.vin = g.vin[g.uperm ? g.uperm[pi] : pi];
     } else {
       b.ga = g.ga[pi];
       b.z = g.z[pi];
@@ -418,7 +421,8 @@ __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
     float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
-    const float2* __restrict__ vin, const float2* __restrict__ y, const double* __restrict__ U,
+    const float2* __restrict__ vin, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
+    const double* __restrict__ U,
     float2* __restrict__ v, double2* __restrict__ z, const float2* __restrict__ ga, double mu,
     double lambda, const double2* __restrict__ bfac, int exact, const uint8_t* __restrict__ active,
     XcdSplit xs) {
@@ -451,7 +455,7 @@ __global__ __launch_bounds__(GridCfg<T>::THREADS) void k_grid(
   // of 64, batch k by wave k mod NW.  The global operands of a wave's next
   // batch are loaded before its current batch is prepared and applied, so
   // their latency overlaps the LDS work.
-  const GridSrc src{wu, wv, theta, vin, y, U, v, z, ga, bfac, active};
+  const GridSrc src{wu, wv, theta, vin, y, U, v, z, ga, bfac, active, uperm};
   const int nseg = it.seg1 - it.seg0;
   const int total = tab.pre[nseg];
   int sb = 0;
@@ -576,7 +580,8 @@ __global__ __launch_bounds__(64 * NW) void k_grid_mfma(
     float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
-    const float2* __restrict__ vin, const float2* __restrict__ y, const double* __restrict__ U,
+    const float2* __restrict__ vin, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
+    const double* __restrict__ U,
     float2* __restrict__ v, double2* __restrict__ z, const float2* __restrict__ ga, double mu,
     double lambda, const double2* __restrict__ bfac, int exact, const uint8_t* __restrict__ active,
     XcdSplit xs) {
@@ -593,7 +598,7 @@ __global__ __launch_bounds__(64 * NW) void k_grid_mfma(
   float* sA = sAw[wid];
   float2* sB = sBw[wid];
   const int gq = lane >> 4, gc = lane & 15;   // row-in-group and entry read in a product step
-  const GridSrc src{wu, wv, theta, vin, y, U, v, z, ga, bfac, active};
+  const GridSrc src{wu, wv, theta, vin, y, U, v, z, ga, bfac, active, uperm};
   const bool one = it.seg1 - it.seg0 == 1;
   if (!one) {
     load_item_tab(it, segs, tab);
@@ -840,47 +845,48 @@ __global__ void k_permute(const int32_t* __restrict__ perm, int64_t M, int to_us
 
 
 template <int T, int NW>
-int launch_degrid(ppd_plan* p, bool dual, float2* out, const DualArgs* a, double* part_out) {
+int launch_degrid(ppd_plan* p, bool dual, float2* out, const int32_t* uperm, const DualArgs* a, double* part_out) {
   if (!dual) {
     hipLaunchKernelGGL((k_degrid<T, false, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
                        p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
-                       out, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, nullptr, nullptr, p->split1);
+                       out, uperm, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, nullptr, nullptr, p->split1);
   } else {
     hipLaunchKernelGGL((k_degrid<T, true, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
                        p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
-                       nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, part_out, a->rpart, p->split1);
+                       nullptr, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, part_out, a->rpart, p->split1);
   }
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
 
 template <int NW>
-int launch_grid_mfma(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, int exact) {
+int launch_grid_mfma(ppd_plan* p, bool dual, const float2* vin, const int32_t* uperm, const DualArgs* a, int exact) {
   const XcdSplit& xs = p->split1;
   if (!dual) {
     hipLaunchKernelGGL((k_grid_mfma<false, NW>), dim3(xs.launch), dim3(64 * NW), 0, p->stream, p->gscratch, p->Ky,
                        p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc, vin,
-                       nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, nullptr, 0, nullptr, xs);
+                       uperm, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, 0.0, nullptr, 0, nullptr, xs);
   } else {
     hipLaunchKernelGGL((k_grid_mfma<true, NW>), dim3(xs.launch), dim3(64 * NW), 0, p->stream, p->gscratch, p->Ky,
                        p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
-                       nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, a->lambda, p->bfac, exact, a->active, xs);
+                       nullptr, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, a->lambda, p->bfac, exact, a->active,
+                       xs);
   }
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
 
 template <int T>
-int launch_grid(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, int exact) {
+int launch_grid(ppd_plan* p, bool dual, const float2* vin, const int32_t* uperm, const DualArgs* a, int exact) {
   if (!dual) {
     hipLaunchKernelGGL((k_grid<T, false>), dim3(p->split1.launch), dim3(GridCfg<T>::THREADS), 0, p->stream,
                        p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
-                       p->sv_scale, p->kbc, vin, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0,
+                       p->sv_scale, p->kbc, vin, uperm, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0,
                        0.0, nullptr, 0, nullptr, p->split1);
   } else {
     hipLaunchKernelGGL((k_grid<T, true>), dim3(p->split1.launch), dim3(GridCfg<T>::THREADS), 0, p->stream,
                        p->gscratch, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
-                       p->sv_scale, p->kbc, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
+                       p->sv_scale, p->kbc, nullptr, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu,
                        a->lambda, p->bfac, exact, a->active, p->split1);
   }
   PPD_HIP(hipGetLastError());
@@ -904,35 +910,35 @@ int launch_fold8(ppd_plan* p) {
   return PPD_OK;
 }
 
-int dispatch_degrid(ppd_plan* p, bool dual, float2* out, const DualArgs* a, double* part_out) {
+int dispatch_degrid(ppd_plan* p, bool dual, float2* out, const int32_t* uperm, const DualArgs* a, double* part_out) {
   int slot;
   PPD_TRY(timer_begin(p, KK_DEGRID, &slot));
   int st;
   switch (p->T) {
     case 8:
-      st = p->n_items <= SHARE_ITEMS ? launch_degrid<8, 2>(p, dual, out, a, part_out)
-                                     : launch_degrid<8, 1>(p, dual, out, a, part_out);
+      st = p->n_items <= SHARE_ITEMS ? launch_degrid<8, 2>(p, dual, out, uperm, a, part_out)
+                                     : launch_degrid<8, 1>(p, dual, out, uperm, a, part_out);
       break;
-    case 16: st = launch_degrid<16, PPD_DEGRID_WAVES>(p, dual, out, a, part_out); break;
-    case 32: st = launch_degrid<32, PPD_DEGRID_WAVES>(p, dual, out, a, part_out); break;
-    default: st = launch_degrid<64, PPD_DEGRID_WAVES>(p, dual, out, a, part_out); break;
+    case 16: st = launch_degrid<16, PPD_DEGRID_WAVES>(p, dual, out, uperm, a, part_out); break;
+    case 32: st = launch_degrid<32, PPD_DEGRID_WAVES>(p, dual, out, uperm, a, part_out); break;
+    default: st = launch_degrid<64, PPD_DEGRID_WAVES>(p, dual, out, uperm, a, part_out); break;
   }
   PPD_TRY(st);
   return timer_end(p, slot);
 }
 
-int dispatch_grid(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, int exact) {
+int dispatch_grid(ppd_plan* p, bool dual, const float2* vin, const int32_t* uperm, const DualArgs* a, int exact) {
   int slot;
   PPD_TRY(timer_begin(p, KK_GRID, &slot));
   int st;
   switch (p->T) {
     case 8:
-      st = p->n_items <= SHARE_ITEMS ? launch_grid_mfma<2>(p, dual, vin, a, exact)
-                                     : launch_grid_mfma<1>(p, dual, vin, a, exact);
+      st = p->n_items <= SHARE_ITEMS ? launch_grid_mfma<2>(p, dual, vin, uperm, a, exact)
+                                     : launch_grid_mfma<1>(p, dual, vin, uperm, a, exact);
       break;
-    case 16: st = launch_grid<16>(p, dual, vin, a, exact); break;
-    case 32: st = launch_grid<32>(p, dual, vin, a, exact); break;
-    default: st = launch_grid<64>(p, dual, vin, a, exact); break;
+    case 16: st = launch_grid<16>(p, dual, vin, uperm, a, exact); break;
+    case 32: st = launch_grid<32>(p, dual, vin, uperm, a, exact); break;
+    default: st = launch_grid<64>(p, dual, vin, uperm, a, exact); break;
   }
   PPD_TRY(st);
   return timer_end(p, slot);
@@ -940,29 +946,31 @@ int dispatch_grid(ppd_plan* p, bool dual, const float2* vin, const DualArgs* a, 
 
 }  // namespace
 
-int degrid_plain(ppd_plan* p, float2* out) { return dispatch_degrid(p, false, out, nullptr, nullptr); }
+int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm) {
+  return dispatch_degrid(p, false, out, uperm, nullptr, nullptr);
+}
 int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out) {
-  return dispatch_degrid(p, true, nullptr, &a, part_out);
+  return dispatch_degrid(p, true, nullptr, nullptr, &a, part_out);
 }
 
-int grid_plain(ppd_plan* p, const float2* v) {
-  PPD_TRY(dispatch_grid(p, false, v, nullptr, 0));
+int grid_plain(ppd_plan* p, const float2* v, const int32_t* uperm) {
+  PPD_TRY(dispatch_grid(p, false, v, uperm, nullptr, 0));
   return fold_grid(p);
 }
 
 int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in) {
   PPD_TRY(block_factors(p, part_in));
-  PPD_TRY(dispatch_grid(p, true, nullptr, &a, 0));
+  PPD_TRY(dispatch_grid(p, true, nullptr, nullptr, &a, 0));
   return fold_grid(p);
 }
 
 int grid_dual_factored(ppd_plan* p, const DualArgs& a) {
-  PPD_TRY(dispatch_grid(p, true, nullptr, &a, 0));
+  PPD_TRY(dispatch_grid(p, true, nullptr, nullptr, &a, 0));
   return fold_grid(p);
 }
 
 int grid_dual_exact(ppd_plan* p, const DualArgs& a) {
-  PPD_TRY(dispatch_grid(p, true, nullptr, &a, 1));
+  PPD_TRY(dispatch_grid(p, true, nullptr, nullptr, &a, 1));
   return fold_grid(p);
 }
 
@@ -1011,19 +1019,13 @@ extern "C" int ppd_phi(ppd_plan* p, const float* x, float* y, int order) {
   if (!p || !x || !y) return fail(PPD_EINVAL, "ppd_phi: NULL argument");
   if (order != PPD_ORDER_PLAN && order != PPD_ORDER_USER) return fail(PPD_EINVAL, "ppd_phi: bad order");
   PPD_TRY(fft_forward(p, x));
-  if (order == PPD_ORDER_PLAN) return degrid_plain(p, reinterpret_cast<float2*>(y));
-  PPD_TRY(degrid_plain(p, p->ybuf));
-  return permute(p, PPD_PLAN_TO_USER, p->ybuf, y, 8);
+  // in the caller's order the degridding stores through the permutation
+  return degrid_plain(p, reinterpret_cast<float2*>(y), order == PPD_ORDER_USER ? p->perm : nullptr);
 }
 
 extern "C" int ppd_phit(ppd_plan* p, const float* y, float* x, int order) {
   if (!p || !x || !y) return fail(PPD_EINVAL, "ppd_phit: NULL argument");
   if (order != PPD_ORDER_PLAN && order != PPD_ORDER_USER) return fail(PPD_EINVAL, "ppd_phit: bad order");
-  const float2* v = reinterpret_cast<const float2*>(y);
-  if (order == PPD_ORDER_USER) {
-    PPD_TRY(permute(p, PPD_USER_TO_PLAN, y, p->ybuf, 8));
-    v = p->ybuf;
-  }
-  PPD_TRY(grid_plain(p, v));
+  PPD_TRY(grid_plain(p, reinterpret_cast<const float2*>(y), order == PPD_ORDER_USER ? p->perm : nullptr));
   return fft_adjoint(p, x);
 }

@@ -289,7 +289,8 @@ struct PrimalArgs {
 int fft_rows_inverse_primal(ppd_plan* p, const PrimalArgs& a, float2* next);
 int fold_grid(ppd_plan* p);                                    // gscratch -> grid_a
 
-int degrid_plain(ppd_plan* p, float2* out);                    // grid_f -> out (plan order)
+// grid_f -> out, in plan order, or with uperm (plan -> caller) in the caller's
+int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm = nullptr);
 struct DualArgs {
   const float2* y; const double* U; float2* v; double2* z;
   double mu, lambda;
@@ -298,7 +299,8 @@ struct DualArgs {
   double* rpart = nullptr; // DEVICE [n_segs] residual partials for the statistics, NULL = skip them
 };
 int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out);   // grid_f -> gabuf; part_out NULL: no Algorithm 2 partials
-int grid_plain(ppd_plan* p, const float2* v);                 // v -> grid_a (accumulate)
+// v -> grid_a; v in plan order, or with uperm in the caller's
+int grid_plain(ppd_plan* p, const float2* v, const int32_t* uperm = nullptr);
 int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in);  // dual finish + grid
 int grid_dual_factored(ppd_plan* p, const DualArgs& a);   // the same with the block factors already in bfac
 
