@@ -177,11 +177,12 @@ int ppd_ellipsoid_proj(ppd_plan* plan, const double* w, const float* y, const do
  * stream: hipStream_t (NULL = default stream).  Limits: d <= 4096 and at
  * most 65536 chunks of 8192 points (about 5.4e8 visibilities); beyond them
  * PPD_EINVAL and nothing is launched.  The per-block partial sums and
- * factors live in one fixed device array of about 0.7 MiB that each GPU the
+ * factors live in one fixed device array of about 1.2 MiB that each GPU the
  * library runs on holds until the process ends; every call on a GPU uses
  * that GPU's array, so calls that overlap on one GPU (on different streams
  * or host threads) race and must be ordered by the caller.  Asynchronous on
- * `stream` (the host tables are staged by the runtime before it returns). */
+ * `stream` (the host tables are kernel arguments up to d = 64, else staged by
+ * the runtime before it returns). */
 int ppd_ellipsoid_proj_noalloc(const double* w, const float* y, const double* U, int32_t d,
                                const int64_t* block_off, const double* eps, int n_itr, double mu,
                                double* zbar_inout, void* stream);

@@ -20,78 +20,84 @@ __device__ inline double block_sum(double v, double* red) {
   return s;
 }
 
-// One Algorithm 2 iteration over every block, item by item (the item's
-// segments flattened into batches of 64, as in the degridding).
-//   mode 0: partials of ||q - y||^2, q = z - mu U (z - w)   (z unchanged)
-//   mode 1: z <- P_B(q) with the block factors, then partials of the next q
-//   mode 2: z <- P_B(q) only
-// NW waves per workgroup: 1 for items of at most two batches (the 8 x 8
-// default, 128 points: 4 waves left half of them idle, 296 against 242 us
-// per iteration with n_itr = 5 at 512^2, 1.3M), else 4.
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void k_alg2(
-    int mode, const Item* __restrict__ items, int n_items, const Seg* __restrict__ segs,
-    const double2* __restrict__ w, const float2* __restrict__ v, const float2* __restrict__ ga,
-    const float2* __restrict__ y, const double* __restrict__ U,
-    double2* __restrict__ z, double mu, const double2* __restrict__ bfac, const uint8_t* __restrict__ active,
-    double* __restrict__ part_out, XcdSplit xs) {
-  __shared__ ItemTab tab;
-  __shared__ double s_q[NW][MAX_ITEM_SEGS];
-  const int ii = xcd_item(blockIdx.x, xs);
-  if (ii < 0 || ii >= n_items) return;
-  const Item it = items[ii];
-  const int lane = threadIdx.x & 63;
-  const int uwid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  load_item_tab(it, segs, tab);
-  for (int i = threadIdx.x; i < NW * MAX_ITEM_SEGS; i += blockDim.x) (&s_q[0][0])[i] = 0.0;
+// Sum of v over a 256-thread workgroup in a fixed order, in every thread.
+// Every thread must call it; red is free again after the next barrier.
+__device__ __forceinline__ double sum256(double v, double* red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  const int nseg = it.seg1 - it.seg0;
-  const int total = tab.pre[nseg];
-  int sb = 0;
-  for (int bt = uwid; bt * 64 < total; bt += NW) {
-    while (bt * 64 >= tab.pre[sb + 1]) ++sb;
-    const int li = bt * 64 + lane;
-    const bool act = li < total;
-    const int sg = act ? seg_of(li, sb, tab.pre) : sb;
-    double qn = 0.0;
-    if (act) {
-      const int pi = tab.start[sg] + (li - tab.pre[sg]);
-      const double Ue = U[pi];
-      const double2 we = w ? w[pi] : dual_arg(v[pi], Ue, ga[pi]);
-      double2 ze = z[pi];
-      const double mU = mu * Ue;
-      const float2 ye = y[pi];
-      // randomised updates of Algorithm 3: an inactive block keeps z
-      if (mode != 0 && (!active || active[tab.block[sg]])) {
-        const double2 bf = bfac[tab.block[sg]];
-        const double qx = ze.x - mU * (ze.x - we.x), qy = ze.y - mU * (ze.y - we.y);
-        ze.x = bf.y != 0.0 ? qx : double(ye.x) + (qx - double(ye.x)) * bf.x;
-        ze.y = bf.y != 0.0 ? qy : double(ye.y) + (qy - double(ye.y)) * bf.x;
-        z[pi] = ze;
-      }
-      if (mode != 2) {
-        const double dx = (ze.x - mU * (ze.x - we.x)) - double(ye.x);
-        const double dy = (ze.y - mU * (ze.y - we.y)) - double(ye.y);
-        qn = dx * dx + dy * dy;
-      }
-    }
-    if (mode != 2) {
-      const int slast = __builtin_amdgcn_readlane(sg, min(63, total - 1 - bt * 64));
-      for (int ss = sb; ss <= slast; ++ss) {
-        const double a = wave_sum(act && sg == ss ? qn : 0.0);
-        if (lane == 0) s_q[uwid][ss] += a;
-      }
+  return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// P_B factor of a block from its squared norm (Sec. 3.3, eq. proj-L2):
+// (eps_j / r, 0) outside the ball, (1, 1) inside.
+__device__ __forceinline__ double2 ball_factor(double r2, double eps) {
+  const double r = sqrt(r2);
+  return r > eps ? make_double2(eps / r, 0.0) : make_double2(1.0, 1.0);
+}
+
+// One Algorithm 2 step on a chunk of consecutive plan-order points of one
+// block: z <- P_B(q), q = z - mu U (z - w), then the chunk's partial of
+// ||q - y||^2 of the next q.  Every workgroup of a block adds up the previous
+// step's partials itself, in the same order (pin), so that a step is one
+// launch; the partials alternate between two buffers.  APPLY: there is a
+// factor; NEXT: there is a next step.  HBM carries 80 bytes per point and
+// step; a step of 65536 points is bound by the launch's latency.
+template <bool APPLY, bool NEXT>
+__global__ __launch_bounds__(256) void k_ball_step(BallIn in, const int32_t* __restrict__ cstart,
+                                                   const int32_t* __restrict__ cblock,
+                                                   const int32_t* __restrict__ coff, const double* __restrict__ eps,
+                                                   const double2* __restrict__ fac, const double* __restrict__ pin,
+                                                   double2* __restrict__ z, double* __restrict__ pout) {
+  __shared__ double red[8];
+  const int c = blockIdx.x, j = cblock[c];
+  const int i0 = cstart[c], i1 = cstart[c + 1];
+  double2 bf = make_double2(1.0, 1.0);
+  if (APPLY) {
+    if (fac) {
+      bf = fac[j];
+    } else {
+      double t = 0.0;
+      for (int k = coff[j] + int(threadIdx.x); k < coff[j + 1]; k += 256) t += pin[k];
+      bf = ball_factor(sum256(t, red), eps[j]);
     }
   }
-  if (mode != 2) {
-    __syncthreads();
-    for (int k = threadIdx.x; k < nseg; k += blockDim.x) {
-      double q = 0.0;
-#pragma unroll
-      for (int wv = 0; wv < NW; ++wv) q += s_q[wv][k];
-      part_out[it.seg0 + k] = q;
+  // randomised updates of Algorithm 3: an inactive block keeps z
+  const bool act = !in.active || in.active[j];
+  double acc = 0.0;
+#pragma unroll 2
+  for (int i = i0 + int(threadIdx.x); i < i1; i += 256) {
+    const double Ue = in.U[i], mU = in.mu * Ue;
+    const double2 we = in.w ? in.w[i] : dual_arg(in.v[i], Ue, in.ga[i]);
+    const float2 ye = in.y[i];
+    double2 ze = z[i];
+    if (APPLY && act) {
+      const double qx = ze.x - mU * (ze.x - we.x), qy = ze.y - mU * (ze.y - we.y);
+      ze.x = bf.y != 0.0 ? qx : double(ye.x) + (qx - double(ye.x)) * bf.x;
+      ze.y = bf.y != 0.0 ? qy : double(ye.y) + (qy - double(ye.y)) * bf.x;
+      z[i] = ze;
+    }
+    if (NEXT) {
+      const double dx = (ze.x - mU * (ze.x - we.x)) - double(ye.x);
+      const double dy = (ze.y - mU * (ze.y - we.y)) - double(ye.y);
+      acc += dx * dx + dy * dy;
     }
   }
+  if (NEXT) {
+    acc = sum256(acc, red + 4);
+    if (threadIdx.x == 0) pout[c] = acc;
+  }
+}
+
+// bfac[j] from block j's chunk partials.
+__global__ __launch_bounds__(256) void k_ball_factors(const int32_t* __restrict__ coff, const double* __restrict__ eps,
+                                                      const double* __restrict__ pin, double2* __restrict__ bfac) {
+  __shared__ double red[4];
+  const int j = blockIdx.x;
+  double t = 0.0;
+  for (int k = coff[j] + int(threadIdx.x); k < coff[j + 1]; k += 256) t += pin[k];
+  t = sum256(t, red);
+  if (threadIdx.x == 0) bfac[j] = ball_factor(t, eps[j]);
 }
 
 // Projection factor of every data block for P_B (Sec. 3.3, eq. proj-L2):
@@ -129,8 +135,7 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factors(const double* __re
   if (threadIdx.x == 0) {
     double t = 0.0;
     for (int q = 0; q < BF_THREADS / 64; ++q) t += red[q];
-    const double r = sqrt(t), e = eps[j];
-    bfac[j] = r > e ? make_double2(e / r, 0.0) : make_double2(1.0, 1.0);
+    bfac[j] = ball_factor(t, eps[j]);
   }
 }
 
@@ -333,7 +338,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
 // nu = 0 climbs to the root without overshooting; g'(nu) = S3 / r^3 with
 // S3 = sum a^2 / (U + nu)^3.  bfac[j].x carries nu between the passes.
 
-// A pass runs over chunks of SEC_CHUNK consecutive plan-order points inside
+// A pass runs over chunks of consecutive plan-order points (sec_chunk) inside
 // one block (blocks are contiguous in plan order).  The first pass forms
 // a^2 = U^2 |w - y|^2 and keeps (a^2, U) per point, the later ones read only
 // that (16 bytes per point); each workgroup writes its chunk's S2, S3 at the
@@ -594,18 +599,28 @@ int grid_blocks(int64_t n) { return int(std::min<int64_t>((n + PL_THREADS - 1) /
 
 }  // namespace
 
-int alg2_launch(ppd_plan* p, int mode, const double2* w, const float2* v, const float2* ga, const float2* y,
-                const double* U, double2* z, double mu, const double* part_in, double* part_out,
-                const uint8_t* active) {
-  if (mode != 0) PPD_TRY(block_factors(p, part_in));
+int ball_factors(ppd_plan* p, const double* pin) {
+  int slot;
+  PPD_TRY(timer_begin(p, KK_MISC, &slot));
+  hipLaunchKernelGGL(k_ball_factors, dim3(p->d), dim3(256), 0, p->stream, p->sec_coff, p->eps_d, pin, p->bfac);
+  PPD_HIP(hipGetLastError());
+  return timer_end(p, slot);
+}
+
+int ball_step(ppd_plan* p, const BallIn& in, double2* z, const double2* fac, const double* pin, double* pout) {
+  if (pin && !fac && !p->own_sums) {   // blocks of too many chunks for every workgroup to add up
+    PPD_TRY(ball_factors(p, pin));
+    fac = p->bfac;
+  }
   int slot;
   PPD_TRY(timer_begin(p, KK_SUBITER, &slot));
-  if (p->chunk_max <= 128)
-    hipLaunchKernelGGL(k_alg2<1>, dim3(p->split1.launch), dim3(64), 0, p->stream, mode, p->items, p->n_items,
-                       p->segs, w, v, ga, y, U, z, mu, p->bfac, active, part_out, p->split1);
-  else
-    hipLaunchKernelGGL(k_alg2<4>, dim3(p->split1.launch), dim3(256), 0, p->stream, mode, p->items, p->n_items,
-                       p->segs, w, v, ga, y, U, z, mu, p->bfac, active, part_out, p->split1);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(p->n_sec_chunks), dim3(256), 0, p->stream, in, p->sec_cstart, p->sec_cblock,
+                       p->sec_coff, p->eps_d, fac, pin, z, pout);
+  };
+  if (!fac && !pin) launch(k_ball_step<false, true>);
+  else if (pout) launch(k_ball_step<true, true>);
+  else launch(k_ball_step<true, false>);
   PPD_HIP(hipGetLastError());
   return timer_end(p, slot);
 }
@@ -729,17 +744,13 @@ extern "C" int ppd_ellipsoid_proj(ppd_plan* p, const double* w, const float* y, 
   if (n_itr < 1) return fail(PPD_EINVAL, "ppd_ellipsoid_proj: n_itr must be >= 1");
   if (!(mu > 0.0) || !std::isfinite(mu)) return fail(PPD_EINVAL, "ppd_ellipsoid_proj: mu must be > 0");
   PPD_TRY(upload_eps(p, eps));
-  const double2* w2 = reinterpret_cast<const double2*>(w);
-  const float2* y2 = reinterpret_cast<const float2*>(y);
+  const BallIn in{reinterpret_cast<const double2*>(w), nullptr, nullptr, reinterpret_cast<const float2*>(y), U, mu,
+                  nullptr};
   double2* z2 = reinterpret_cast<double2*>(zbar);
-  double* pa = p->part;
-  double* pb = p->part + p->n_segs;
-  PPD_TRY(alg2_launch(p, 0, w2, nullptr, nullptr, y2, U, z2, mu, nullptr, pa, nullptr));
-  for (int s = 1; s < n_itr; ++s) {
-    PPD_TRY(alg2_launch(p, 1, w2, nullptr, nullptr, y2, U, z2, mu, pa, pb, nullptr));
-    std::swap(pa, pb);
-  }
-  return alg2_launch(p, 2, w2, nullptr, nullptr, y2, U, z2, mu, pa, nullptr, nullptr);
+  double* part[2] = {p->sec_part, p->sec_part + p->n_sec_chunks};
+  PPD_TRY(ball_step(p, in, z2, nullptr, nullptr, part[0]));
+  for (int s = 1; s < n_itr; ++s) PPD_TRY(ball_step(p, in, z2, nullptr, part[(s - 1) & 1], part[s & 1]));
+  return ball_step(p, in, z2, nullptr, part[(n_itr - 1) & 1], nullptr);
 }
 
 extern "C" int ppd_prox_metric(ppd_plan* p, const double* w, const float* y, const double* U, const double* eps,

@@ -10,9 +10,6 @@
 namespace ppd {
 
 int primal_partial_count(ppd_plan* p);
-int alg2_launch(ppd_plan* p, int mode, const double2* w, const float2* v, const float2* ga, const float2* y,
-                const double* U, double2* z, double mu, const double* part_in, double* part_out,
-                const uint8_t* active);
 
 namespace {
 
@@ -194,25 +191,27 @@ int data_path(ppd_plan* p, const IterCtx& c) {
     PPD_TRY(secular_solve(p, nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.n_newton));  // prox^U_h(w)
     PPD_TRY(grid_dual_exact(p, c.dual));                    // dual finish, relaxation, gridding
   } else if (c.form == PPD_FORM_FUSED) {
-    double* pa = p->part;
-    double* pb = p->part + p->n_segs;
-    PPD_TRY(degrid_dual(p, c.dual, pa));                    // dual argument, first Alg. 2 step
-    if (c.dual.n_itr > 1 && c.persistent) {
-      // the middle steps in one launch, state in registers; it leaves the
-      // last step's factors for the gridding.  It runs beside the SARA
-      // branch: workgroups of it that the SARA launches keep from being
-      // resident at first get room as those finish (they never wait on
-      // this launch), while the resident ones wait for their partials.
-      PPD_TRY(block_factors(p, pa));
-      PPD_TRY(alg2_persistent(p, c.dual, c.spin_limit));
+    PPD_TRY(degrid_dual(p, c.dual, p->part));               // dual argument, first Alg. 2 step
+    if (c.dual.n_itr > 1) {
+      PPD_TRY(block_factors(p, p->part));
+      if (c.persistent) {
+        // the middle steps in one launch, state in registers; it leaves the
+        // last step's factors for the gridding.  It runs beside the SARA
+        // branch: workgroups of it that the SARA launches keep from being
+        // resident at first get room as those finish (they never wait on
+        // this launch), while the resident ones wait for their partials.
+        PPD_TRY(alg2_persistent(p, c.dual, c.spin_limit));
+      } else {
+        const BallIn in{nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.dual.mu, c.dual.active};
+        double* part[2] = {p->sec_part, p->sec_part + p->n_sec_chunks};
+        PPD_TRY(ball_step(p, in, c.dual.z, p->bfac, nullptr, part[0]));
+        for (int s = 2; s < c.dual.n_itr; ++s)
+          PPD_TRY(ball_step(p, in, c.dual.z, nullptr, part[s & 1], part[(s - 1) & 1]));
+        PPD_TRY(ball_factors(p, part[c.dual.n_itr & 1]));
+      }
       PPD_TRY(grid_dual_factored(p, c.dual));               // last projection, dual finish, gridding
     } else {
-      for (int s = 1; s < c.dual.n_itr; ++s) {
-        PPD_TRY(alg2_launch(p, 1, nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.dual.z, c.dual.mu, pa, pb,
-                            c.dual.active));
-        std::swap(pa, pb);
-      }
-      PPD_TRY(grid_dual(p, c.dual, pa));                    // last projection, dual finish, gridding
+      PPD_TRY(grid_dual(p, c.dual, p->part));               // projection, dual finish, gridding
     }
   } else {
     PPD_TRY(degrid_plain(p, p->ybuf));

@@ -4,13 +4,21 @@
 // in one file-scope device array instead of a plan's buffers.
 //
 // The visibilities of block j are the contiguous range
-// [block_off[j], block_off[j+1]); each block is cut into chunks of NA_CHUNK
-// consecutive points, one workgroup each.  A step forms, per chunk, the
-// partial sum of ||q - y_j||^2 with q = z - mu U (z - w); a second launch
-// sums each block's chunk partials in a fixed order and stores the block's
-// P_B factor; the next step first applies z <- P_B(q) with it.  All partial
-// and factor slots are written before they are read in every call, so
-// nothing has to start at zero.
+// [block_off[j], block_off[j+1]); each block is cut into chunks of
+// consecutive points, one workgroup each: 512 points up to 2048 chunks, twice
+// as many while there are more, at most 8192.  A step applies z <- P_B(q) and
+// forms, per chunk, the partial sum of ||q - y_j||^2 of the next
+// q = z - mu U (z - w); every workgroup of a block adds up the previous
+// step's partials itself, in the same order, so a step is one launch (a block
+// of more than NA_OWN_SUM chunks has its sum formed by a launch between).  All
+// partial and factor slots are written before they are read in every call, so
+// nothing has to start at zero.  Up to NA_ARG_BLOCKS blocks the block tables
+// are kernel arguments: nothing is copied, and a captured call holds them.
+//
+// Bound by the launches' latency at the sizes of one observation: 307,780
+// points in 7 blocks, 5 steps, took 98 us as 3 table copies and 11 launches of
+// 41 workgroups, now 31 us as 6 launches of 603.
+#include <algorithm>
 #include <mutex>
 
 #include "ppd_internal.h"
@@ -18,25 +26,38 @@
 namespace ppd {
 namespace {
 
-constexpr int NA_CHUNK = 8192;        // points per workgroup
+constexpr int NA_CHUNK = 8192;        // most points per workgroup
+constexpr int NA_MIN_CHUNK = 512;
+constexpr int NA_FILL_CHUNKS = 2048;  // chunks that fill the chip
+constexpr int NA_OWN_SUM = 4096;      // partials of a block that every workgroup adds up itself
+constexpr int NA_ARG_BLOCKS = 64;
 constexpr int NA_THREADS = 256;
 constexpr int NA_MAX_BLOCKS = 4096;
 constexpr int NA_MAX_CHUNKS = 65536;
 
 // Layout of the array (byte offsets): eps [d] f64, block offsets [d+1] i64,
 // chunk offsets [d+1] i32 (chunks of block j: [coff[j], coff[j+1])), block
-// factors [d] (factor, inside) f64 pairs, chunk partials [n_chunks] f64.
+// factors [d] (factor, inside) f64 pairs, two buffers of chunk partials
+// [n_chunks] f64 (steps alternate).
 constexpr size_t NA_OFF_EPS = 0;
 constexpr size_t NA_OFF_BOFF = NA_OFF_EPS + 8 * NA_MAX_BLOCKS;
 constexpr size_t NA_OFF_COFF = NA_OFF_BOFF + 8 * (NA_MAX_BLOCKS + 1);
 constexpr size_t NA_OFF_FAC = (NA_OFF_COFF + 4 * (NA_MAX_BLOCKS + 1) + 255) / 256 * 256;
 constexpr size_t NA_OFF_PART = NA_OFF_FAC + 16 * NA_MAX_BLOCKS;
-constexpr size_t NA_BYTES = NA_OFF_PART + 8 * NA_MAX_CHUNKS;
+constexpr size_t NA_BYTES = NA_OFF_PART + 2 * 8 * NA_MAX_CHUNKS;
 
-// One copy per GPU, held until the process ends (about 0.7 MiB).  Host code
+// One copy per GPU, held until the process ends (about 1.2 MiB).  Host code
 // never uses this name as an address: it takes the device address from
 // hipGetSymbolAddress once per device (see scratch_for_device).
 static __device__ __align__(256) unsigned char scratch[NA_BYTES];
+
+// Block tables of a call: as a kernel argument, or in the array.
+struct NaArgs {
+  int64_t boff[NA_ARG_BLOCKS + 1];
+  double eps[NA_ARG_BLOCKS];
+  int32_t coff[NA_ARG_BLOCKS + 1];
+};
+struct NaNone {};
 
 struct NaView {
   const double* eps;
@@ -51,9 +72,18 @@ __device__ __forceinline__ NaView na_view(unsigned char* base) {
           reinterpret_cast<const int32_t*>(base + NA_OFF_COFF), reinterpret_cast<double2*>(base + NA_OFF_FAC),
           reinterpret_cast<double*>(base + NA_OFF_PART)};
 }
+__device__ __forceinline__ NaView na_tables(const NaArgs& t, unsigned char* base) {
+  NaView s = na_view(base);
+  s.eps = t.eps;
+  s.boff = t.boff;
+  s.coff = t.coff;
+  return s;
+}
+__device__ __forceinline__ NaView na_tables(const NaNone&, unsigned char* base) { return na_view(base); }
 
+// Sum over the workgroup in a fixed order, in every thread.
 __device__ __forceinline__ double na_block_sum(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double s = 0.0;
@@ -62,14 +92,24 @@ __device__ __forceinline__ double na_block_sum(double v, double* red) {
   return s;
 }
 
-// mode 0: partials of ||q - y||^2 from z; mode 1: z <- P_B(q) with the block
-// factors, then partials of the next q; mode 2: z <- P_B(q) only.
-__global__ __launch_bounds__(NA_THREADS) void k_na_step(int mode, int d, const double2* __restrict__ w,
+// P_B factor from the block's squared norm: (eps / r, 0) if r > eps, else
+// (1, 1) (Sec. 3.3, eq. proj-L2).
+__device__ __forceinline__ double2 na_factor(double r2, double e) {
+  const double r = sqrt(r2);
+  return r > e ? make_double2(e / r, 0.0) : make_double2(1.0, 1.0);
+}
+
+// mode 0: partials of ||q - y||^2 from z; mode 1: z <- P_B(q), then partials
+// of the next q; mode 2: z <- P_B(q) only.  The factors are those of the
+// partials in buffer `from`, or with own = 0 the ones stored.
+template <typename Tab>
+__global__ __launch_bounds__(NA_THREADS) void k_na_step(int mode, int own, int from, int chunk, int d, Tab tab,
+                                                        const double2* __restrict__ w,
                                                         const float2* __restrict__ y, const double* __restrict__ U,
                                                         double2* __restrict__ z, double mu,
                                                         unsigned char* __restrict__ base) {
-  __shared__ double red[NA_THREADS / 64];
-  const NaView s = na_view(base);
+  __shared__ double red[2 * (NA_THREADS / 64)];
+  const NaView s = na_tables(tab, base);
   const int c = blockIdx.x;
   int lo = 0, hi = d;   // the block of chunk c: the last j with coff[j] <= c
   while (hi - lo > 1) {
@@ -78,10 +118,21 @@ __global__ __launch_bounds__(NA_THREADS) void k_na_step(int mode, int d, const d
     else hi = mid;
   }
   const int j = lo;
-  const int64_t i0 = s.boff[j] + int64_t(c - s.coff[j]) * NA_CHUNK;
-  const int64_t i1 = min(i0 + NA_CHUNK, s.boff[j + 1]);
-  const double2 bf = mode != 0 ? s.fac[j] : make_double2(1.0, 1.0);
+  const int64_t i0 = s.boff[j] + int64_t(c - s.coff[j]) * chunk;
+  const int64_t i1 = min(i0 + chunk, s.boff[j + 1]);
+  double2 bf = make_double2(1.0, 1.0);
+  if (mode != 0) {
+    if (own) {
+      const double* pin = s.part + size_t(from) * NA_MAX_CHUNKS;
+      double t = 0.0;
+      for (int k = s.coff[j] + int(threadIdx.x); k < s.coff[j + 1]; k += NA_THREADS) t += pin[k];
+      bf = na_factor(na_block_sum(t, red), s.eps[j]);
+    } else {
+      bf = s.fac[j];
+    }
+  }
   double acc = 0.0;
+#pragma unroll 2
   for (int64_t i = i0 + threadIdx.x; i < i1; i += NA_THREADS) {
     const double Ue = U[i], mU = mu * Ue;
     const double2 we = w[i];
@@ -100,24 +151,43 @@ __global__ __launch_bounds__(NA_THREADS) void k_na_step(int mode, int d, const d
     }
   }
   if (mode != 2) {
-    acc = na_block_sum(acc, red);
-    if (threadIdx.x == 0) s.part[c] = acc;
+    acc = na_block_sum(acc, red + NA_THREADS / 64);
+    if (threadIdx.x == 0) s.part[size_t(mode == 0 ? 0 : 1 - from) * NA_MAX_CHUNKS + c] = acc;
   }
 }
 
-// Block j: r = sqrt(sum of its chunk partials in chunk order); the P_B
-// factor (eps_j / r, 0) if r > eps_j, else (1, 1) (Sec. 3.3, eq. proj-L2).
-__global__ __launch_bounds__(NA_THREADS) void k_na_factors(unsigned char* __restrict__ base) {
+// Block j's factor from its chunk partials in buffer `from`, stored.
+template <typename Tab>
+__global__ __launch_bounds__(NA_THREADS) void k_na_factors(int from, Tab tab, unsigned char* __restrict__ base) {
   __shared__ double red[NA_THREADS / 64];
-  const NaView s = na_view(base);
+  const NaView s = na_tables(tab, base);
   const int j = blockIdx.x;
   double acc = 0.0;
-  for (int c = s.coff[j] + int(threadIdx.x); c < s.coff[j + 1]; c += NA_THREADS) acc += s.part[c];
+  for (int c = s.coff[j] + int(threadIdx.x); c < s.coff[j + 1]; c += NA_THREADS)
+    acc += s.part[size_t(from) * NA_MAX_CHUNKS + c];
   acc = na_block_sum(acc, red);
-  if (threadIdx.x == 0) {
-    const double r = sqrt(acc), e = s.eps[j];
-    s.fac[j] = r > e ? make_double2(e / r, 0.0) : make_double2(1.0, 1.0);
+  if (threadIdx.x == 0) s.fac[j] = na_factor(acc, s.eps[j]);
+}
+
+struct NaCall {
+  int d, n_itr, chunk, nchunks, own;
+  const double2* w; const float2* y; const double* U; double2* z;
+  double mu;
+  unsigned char* base;
+  hipStream_t stream;
+};
+
+template <typename Tab>
+int na_run(const NaCall& a, const Tab& tab) {
+  for (int k = 0; k <= a.n_itr; ++k) {
+    const int mode = k == 0 ? 0 : k < a.n_itr ? 1 : 2, from = (k + 1) & 1;
+    if (k > 0 && !a.own)
+      hipLaunchKernelGGL(k_na_factors<Tab>, dim3(a.d), dim3(NA_THREADS), 0, a.stream, from, tab, a.base);
+    hipLaunchKernelGGL(k_na_step<Tab>, dim3(a.nchunks), dim3(NA_THREADS), 0, a.stream, mode, a.own, from, a.chunk, a.d,
+                       tab, a.w, a.y, a.U, a.z, a.mu, a.base);
   }
+  PPD_HIP(hipGetLastError());
+  return PPD_OK;
 }
 
 constexpr int NA_MAX_DEVICES = 64;
@@ -173,25 +243,42 @@ extern "C" int ppd_ellipsoid_proj_noalloc(const double* w, const float* y, const
                                   std::to_string(int64_t(NA_MAX_CHUNKS) * NA_CHUNK) + " visibilities)");
     coff[j + 1] = int32_t(nc);
   }
-  const int nchunks = coff[d];
-  unsigned char* base = nullptr;
-  PPD_TRY(scratch_for_device(&base));
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  NaCall c{};
+  c.d = d;
+  c.n_itr = n_itr;
+  c.chunk = NA_CHUNK;
+  for (int len = NA_MIN_CHUNK; len < NA_CHUNK; len *= 2) {   // the shortest chunks that do not overfill the chip
+    int64_t n = 0;
+    for (int j = 0; j < d; ++j) n += (block_off[j + 1] - block_off[j] + len - 1) / len;
+    if (n <= std::max(NA_FILL_CHUNKS, d)) {
+      c.chunk = len;
+      break;
+    }
+  }
+  c.own = 1;
+  for (int j = 0; j < d; ++j) {
+    coff[j + 1] = coff[j] + int32_t((block_off[j + 1] - block_off[j] + c.chunk - 1) / c.chunk);
+    if (coff[j + 1] - coff[j] > NA_OWN_SUM) c.own = 0;
+  }
+  c.nchunks = coff[d];
+  PPD_TRY(scratch_for_device(&c.base));
+  c.w = reinterpret_cast<const double2*>(w);
+  c.y = reinterpret_cast<const float2*>(y);
+  c.U = U;
+  c.z = reinterpret_cast<double2*>(zbar);
+  c.mu = mu;
+  c.stream = static_cast<hipStream_t>(stream);
+  if (d <= NA_ARG_BLOCKS) {
+    NaArgs t{};
+    std::copy(eps, eps + d, t.eps);
+    std::copy(block_off, block_off + d + 1, t.boff);
+    std::copy(coff, coff + d + 1, t.coff);
+    return na_run(c, t);
+  }
   // the block tables into the array (pageable host sources are staged by the
   // runtime before these calls return)
-  PPD_HIP(hipMemcpyAsync(base + NA_OFF_EPS, eps, sizeof(double) * d, hipMemcpyHostToDevice, s));
-  PPD_HIP(hipMemcpyAsync(base + NA_OFF_BOFF, block_off, sizeof(int64_t) * (d + 1), hipMemcpyHostToDevice, s));
-  PPD_HIP(hipMemcpyAsync(base + NA_OFF_COFF, coff, sizeof(int32_t) * (d + 1), hipMemcpyHostToDevice, s));
-  const double2* w2 = reinterpret_cast<const double2*>(w);
-  const float2* y2 = reinterpret_cast<const float2*>(y);
-  double2* z2 = reinterpret_cast<double2*>(zbar);
-  hipLaunchKernelGGL(k_na_step, dim3(nchunks), dim3(NA_THREADS), 0, s, 0, d, w2, y2, U, z2, mu, base);
-  hipLaunchKernelGGL(k_na_factors, dim3(d), dim3(NA_THREADS), 0, s, base);
-  for (int k = 1; k < n_itr; ++k) {
-    hipLaunchKernelGGL(k_na_step, dim3(nchunks), dim3(NA_THREADS), 0, s, 1, d, w2, y2, U, z2, mu, base);
-    hipLaunchKernelGGL(k_na_factors, dim3(d), dim3(NA_THREADS), 0, s, base);
-  }
-  hipLaunchKernelGGL(k_na_step, dim3(nchunks), dim3(NA_THREADS), 0, s, 2, d, w2, y2, U, z2, mu, base);
-  PPD_HIP(hipGetLastError());
-  return PPD_OK;
+  PPD_HIP(hipMemcpyAsync(c.base + NA_OFF_EPS, eps, sizeof(double) * d, hipMemcpyHostToDevice, c.stream));
+  PPD_HIP(hipMemcpyAsync(c.base + NA_OFF_BOFF, block_off, sizeof(int64_t) * (d + 1), hipMemcpyHostToDevice, c.stream));
+  PPD_HIP(hipMemcpyAsync(c.base + NA_OFF_COFF, coff, sizeof(int32_t) * (d + 1), hipMemcpyHostToDevice, c.stream));
+  return na_run(c, NaNone{});
 }

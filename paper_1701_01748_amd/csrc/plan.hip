@@ -509,17 +509,19 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
     }
   }
 
-  // chunks of the exact prox's Newton passes (SEC_CHUNK points, one block each)
+  // chunks of the passes over plan-order points, one block each
+  const int64_t chunk_len = sec_chunk(M);
   std::vector<int32_t> cstart, cblock, coff(p->d + 1, 0);
   for (int j = 0; j < p->d; ++j) {
     coff[j] = int32_t(cblock.size());
-    for (int64_t s0 = p->block_off[j]; s0 < p->block_off[j + 1]; s0 += SEC_CHUNK) {
+    for (int64_t s0 = p->block_off[j]; s0 < p->block_off[j + 1]; s0 += chunk_len) {
       cstart.push_back(int32_t(s0));
       cblock.push_back(j);
     }
   }
   coff[p->d] = int32_t(cblock.size());
   cstart.push_back(int32_t(M));
+  for (int j = 0; j < p->d; ++j) p->own_sums = p->own_sums && coff[j + 1] - coff[j] <= OWN_SUM_CHUNKS;
   p->n_sec_chunks = int(cblock.size());
 
   // persistent Algorithm 2: workgroup g owns plan-order points

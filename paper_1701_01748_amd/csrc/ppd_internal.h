@@ -34,7 +34,15 @@ constexpr int KB_DEG = 9;         // polynomial degree per tap
 constexpr int KB_NC = KB_DEG + 1; // coefficients per tap
 constexpr int N_BASES = 9;        // Dirac + db1..db8
 constexpr int FILT_STRIDE = 16;   // max Daubechies taps (db8)
-constexpr int SEC_CHUNK = 2048;   // points per workgroup of an exact-prox Newton pass
+// Points per workgroup of the passes over plan-order chunks of one block
+// (Algorithm 2 steps, Newton steps, the differentiable dual update): fewer
+// points where the chip would be left empty, and few enough chunks for every
+// workgroup to add up its block's partials itself.
+inline int64_t sec_chunk(int64_t M) { return M <= (int64_t(1) << 20) ? 512 : M <= (int64_t(1) << 22) ? 1024 : 2048; }
+// Chunks of a block up to which the workgroups do that (each reads all the
+// block's partials: 32 KB, 16 a thread); beyond it a launch of one workgroup
+// per block forms the block's sum.
+constexpr int OWN_SUM_CHUNKS = 4096;
 constexpr int MAX_ITEM_SEGS = 64; // per-block segments of one work item (one wave scans them)
 constexpr int MAX_XCD = 8;
 constexpr int PA_THREADS = 256;   // persistent Algorithm 2: threads per workgroup
@@ -208,6 +216,7 @@ struct ppd_plan {
   // Newton passes of the exact prox: chunks of consecutive plan-order
   // visibilities inside one block
   int n_sec_chunks = 0;
+  bool own_sums = true;                    // no block has more than OWN_SUM_CHUNKS chunks
   int32_t* sec_cstart = nullptr;           // [n_sec_chunks + 1] first visibility of each chunk
   int32_t* sec_cblock = nullptr;           // [n_sec_chunks] block of each chunk
   int32_t* sec_coff = nullptr;             // [d + 1] chunks of block j: [sec_coff[j], sec_coff[j+1])
@@ -305,6 +314,17 @@ int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in);  // dual f
 int grid_dual_factored(ppd_plan* p, const DualArgs& a);   // the same with the block factors already in bfac
 
 int plain_dual(ppd_plan* p, const DualArgs& a);               // per-block unfused dual update
+// z <- P_B(q) for every block and, if pout, chunk partials of the next
+// ||q - y_j||^2; the factors of P_B come from fac, else from the chunk
+// partials pin.  Without either: the partials of the present z only.  w, or
+// v and ga (w = U^-1 v + ga); active: DEVICE [d] mask, NULL = all.
+struct BallIn {
+  const double2* w; const float2* v; const float2* ga; const float2* y; const double* U;
+  double mu;
+  const uint8_t* active;
+};
+int ball_step(ppd_plan* p, const BallIn& in, double2* z, const double2* fac, const double* pin, double* pout);
+int ball_factors(ppd_plan* p, const double* pin);   // bfac from chunk partials
 // Per-block projection factors of P_B from per-segment partials of
 // ||q - y||^2: bfac[j] = (min(1, eps_j / r_j), r_j <= eps_j), r_j the block norm.
 int block_factors(ppd_plan* p, const double* part);

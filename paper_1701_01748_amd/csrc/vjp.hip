@@ -6,8 +6,8 @@
 // convention for complex tensors (dL/dRe + i dL/dIm of a real loss L).
 //
 // The data-dual update works on plan-order vectors, block by block, in
-// chunks of SEC_CHUNK consecutive points of one block (the chunk table of
-// the exact prox); every block norm or block inner product is a sum of
+// chunks of consecutive points of one block (the chunk table of the exact
+// prox); every block norm or block inner product is a sum of
 // chunk partials in chunk order (deterministic).
 #include <cmath>
 
@@ -19,7 +19,7 @@ namespace {
 constexpr int DU_THREADS = 256;
 
 __device__ __forceinline__ double du_block_sum(double v, double* red) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_sum(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double s = 0.0;
@@ -40,46 +40,27 @@ __device__ __forceinline__ double2 du_w(const DuIn& a, int64_t i, double Ue) {
   return dual_arg(ve, Ue, ge);
 }
 
-// Chunk partials of ||q - y||^2 (and, with gz, of Re <q - y, gz>) for
-// q = z - mu U (z - w), z = zprev.
-__global__ __launch_bounds__(DU_THREADS) void k_du_partials(DuIn a, const int32_t* __restrict__ cstart,
-                                                            const double2* __restrict__ zprev,
-                                                            const double2* __restrict__ gz,
-                                                            double* __restrict__ p2, double* __restrict__ pd) {
-  __shared__ double red[DU_THREADS / 64];
-  const int c = blockIdx.x;
-  double s2 = 0.0, sd = 0.0;
-  for (int64_t i = cstart[c] + threadIdx.x; i < cstart[c + 1]; i += DU_THREADS) {
-    const double Ue = a.U[i], mU = a.mu * Ue;
-    const double2 we = du_w(a, i, Ue), ze = zprev[i];
-    const float2 ye = a.y[i];
-    const double dx = (ze.x - mU * (ze.x - we.x)) - double(ye.x);
-    const double dy = (ze.y - mU * (ze.y - we.y)) - double(ye.y);
-    s2 += dx * dx + dy * dy;
-    if (gz) {
-      const double2 ge = gz[i];
-      sd += dx * ge.x + dy * ge.y;
-    }
-  }
-  s2 = du_block_sum(s2, red);
-  if (gz) sd = du_block_sum(sd, red);
-  if (threadIdx.x == 0) {
-    p2[c] = s2;
-    if (gz) pd[c] = sd;
-  }
+// q - y for q = z - mu U (z - w).
+__device__ __forceinline__ double2 du_offset(double2 ze, double2 we, float2 ye, double mU) {
+  return make_double2((ze.x - mU * (ze.x - we.x)) - double(ye.x), (ze.y - mU * (ze.y - we.y)) - double(ye.y));
 }
 
-// Per block j: r = ||q - y||, and (forward) the P_B factor, or (VJP) the
-// coefficients of the P_B Jacobian's transpose applied to gz:
-// outside the ball gq = (eps / r) gz - (eps <d, gz> / r^3) d.
-// blk[j] = (factor or eps / r, eps <d, gz> / r^3, inside, r).
-__global__ __launch_bounds__(DU_THREADS) void k_du_blocks(const int32_t* __restrict__ coff,
-                                                          const double* __restrict__ eps,
-                                                          const double* __restrict__ p2,
-                                                          const double* __restrict__ pd,
-                                                          double4* __restrict__ blk) {
-  __shared__ double red[DU_THREADS / 64];
-  const int j = blockIdx.x;
+// A block's coefficients from r^2 = ||q - y||^2 and (VJP) sd = Re <q - y, gz>:
+// (eps / r or 1, eps sd / r^3 or 0, inside, r).  Forward uses the factor; the
+// transposed Jacobian of P_B outside the ball is gq = (eps / r) gz - (eps
+// <d, gz> / r^3) d.
+__device__ __forceinline__ double4 du_coef(double s2, double sd, double e) {
+  const double r = sqrt(s2);
+  return r <= e ? make_double4(1.0, 0.0, 1.0, r) : make_double4(e / r, e * sd / (r * r * r), 0.0, r);
+}
+
+// The coefficients of block j: blk[j], else from its chunk partials, which
+// every workgroup of the block adds up in the same order (pd: VJP).  Every
+// thread calls it.
+__device__ __forceinline__ double4 du_block(const double4* __restrict__ blk, const int32_t* __restrict__ coff,
+                                            const double* __restrict__ eps, const double* __restrict__ p2,
+                                            const double* __restrict__ pd, int j, double* red) {
+  if (blk) return blk[j];
   double s2 = 0.0, sd = 0.0;
   for (int c = coff[j] + int(threadIdx.x); c < coff[j + 1]; c += DU_THREADS) {
     s2 += p2[c];
@@ -87,98 +68,143 @@ __global__ __launch_bounds__(DU_THREADS) void k_du_blocks(const int32_t* __restr
   }
   s2 = du_block_sum(s2, red);
   if (pd) sd = du_block_sum(sd, red);
-  if (threadIdx.x == 0) {
-    const double r = sqrt(s2), e = eps[j];
-    const bool inside = r <= e;
-    blk[j] = inside ? make_double4(1.0, 0.0, 1.0, r) : make_double4(e / r, e * sd / (r * r * r), 0.0, r);
-  }
+  return du_coef(s2, sd, eps[j]);
 }
 
-// Forward step s: z_s = P_B(q_s), q_s from zprev.
-__global__ void k_du_apply(DuIn a, int64_t M, const int32_t* __restrict__ vblk, const double4* __restrict__ blk,
-                           const double2* __restrict__ zprev, double2* __restrict__ znext) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < M; i += int64_t(gridDim.x) * blockDim.x) {
+__global__ __launch_bounds__(DU_THREADS) void k_du_blocks(const int32_t* __restrict__ coff,
+                                                          const double* __restrict__ eps,
+                                                          const double* __restrict__ p2,
+                                                          const double* __restrict__ pd,
+                                                          double4* __restrict__ blk) {
+  __shared__ double red[DU_THREADS / 64];
+  const int j = blockIdx.x;
+  const double4 b = du_block(nullptr, coff, eps, p2, pd, j, red);
+  if (threadIdx.x == 0) blk[j] = b;
+}
+
+struct DuChunks {
+  const int32_t* cstart; const int32_t* cblock; const int32_t* coff;
+  const double* eps;
+};
+
+// Forward.  FIRST: the chunk's partial of ||q_1 - y||^2 from z_0 = zprev.
+// Else step s: z_s = P_B(q_s) with the factor of the partials p_in (or blk),
+// then the partial of the next step's, or after the last step (v_out)
+// v' = v + lambda (U (w - z_n) - v).  A step is one launch: 72 bytes of inputs
+// and 16 of z per point; five steps and the finish take 6 launches instead of
+// the 16 that separate partials, factors and updates took.
+template <bool FIRST>
+__global__ __launch_bounds__(DU_THREADS) void k_du_step(DuIn a, DuChunks t, const double4* __restrict__ blk,
+                                                        const double* __restrict__ p_in, double* __restrict__ p_out,
+                                                        const double2* zprev, double2* znext, double lambda,
+                                                        float2* __restrict__ v_out, double2* __restrict__ z_out) {
+  __shared__ double red[DU_THREADS / 64];
+  const int c = blockIdx.x;
+  double4 b = make_double4(1.0, 0.0, 1.0, 0.0);
+  if (!FIRST) b = du_block(blk, t.coff, t.eps, p_in, nullptr, t.cblock[c], red);
+  double s2 = 0.0;
+#pragma unroll 2
+  for (int64_t i = t.cstart[c] + threadIdx.x; i < t.cstart[c + 1]; i += DU_THREADS) {
     const double Ue = a.U[i], mU = a.mu * Ue;
-    const double2 we = du_w(a, i, Ue), ze = zprev[i];
+    const double2 we = du_w(a, i, Ue);
     const float2 ye = a.y[i];
-    const double4 b = blk[vblk[i]];
-    const double qx = ze.x - mU * (ze.x - we.x), qy = ze.y - mU * (ze.y - we.y);
-    znext[i] = b.z != 0.0 ? make_double2(qx, qy)
-                          : make_double2(double(ye.x) + (qx - double(ye.x)) * b.x,
-                                         double(ye.y) + (qy - double(ye.y)) * b.x);
-  }
-}
-
-// v' = v + lambda (U (w - z_n) - v), z' = z_n.
-__global__ void k_du_finish(DuIn a, int64_t M, double lambda, const double2* __restrict__ zn,
-                            float2* __restrict__ v_out, double2* __restrict__ z_out) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < M; i += int64_t(gridDim.x) * blockDim.x) {
-    const double Ue = a.U[i];
-    const double2 we = du_w(a, i, Ue), ze = zn[i];
-    const float2 ve = a.v[i];
-    const double vbx = Ue * (we.x - ze.x), vby = Ue * (we.y - ze.y);
-    v_out[i] = make_float2(float(double(ve.x) + lambda * (vbx - double(ve.x))),
-                           float(double(ve.y) + lambda * (vby - double(ve.y))));
-    if (z_out != zn) z_out[i] = ze;
-  }
-}
-
-// VJP start: gz_n = gz' - lambda U gv', gw = lambda U gv', gy = 0.
-__global__ void k_du_vjp_init(int64_t M, const double* __restrict__ U, double lambda,
-                              const float2* __restrict__ gv, const double2* __restrict__ gz,
-                              double2* __restrict__ gzc, double2* __restrict__ gw, double2* __restrict__ gy) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < M; i += int64_t(gridDim.x) * blockDim.x) {
-    const double lU = lambda * U[i];
-    const float2 g = gv ? gv[i] : make_float2(0.f, 0.f);
-    const double2 z = gz ? gz[i] : make_double2(0.0, 0.0);
-    gzc[i] = make_double2(z.x - lU * double(g.x), z.y - lU * double(g.y));
-    gw[i] = make_double2(lU * double(g.x), lU * double(g.y));
-    gy[i] = make_double2(0.0, 0.0);
-  }
-}
-
-// VJP of step s: gq = P_B Jacobian^T gz_s; gy += gz_s - gq;
-// gz_{s-1} = (1 - mu U) gq; gw += mu U gq.  (In place on gzc.)
-__global__ void k_du_vjp_step(DuIn a, int64_t M, const int32_t* __restrict__ vblk, const double4* __restrict__ blk,
-                              const double2* __restrict__ zprev, double2* __restrict__ gzc,
-                              double2* __restrict__ gw, double2* __restrict__ gy) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < M; i += int64_t(gridDim.x) * blockDim.x) {
-    const double Ue = a.U[i], mU = a.mu * Ue;
-    const double4 b = blk[vblk[i]];
-    const double2 g = gzc[i];
-    double2 gq;
-    if (b.z != 0.0) {
-      gq = g;
-    } else {
-      const double2 we = du_w(a, i, Ue), ze = zprev[i];
-      const float2 ye = a.y[i];
-      const double dx = (ze.x - mU * (ze.x - we.x)) - double(ye.x);
-      const double dy = (ze.y - mU * (ze.y - we.y)) - double(ye.y);
-      gq = make_double2(b.x * g.x - b.y * dx, b.x * g.y - b.y * dy);
+    double2 ze = zprev[i];
+    if (!FIRST) {
+      const double qx = ze.x - mU * (ze.x - we.x), qy = ze.y - mU * (ze.y - we.y);
+      ze = b.z != 0.0 ? make_double2(qx, qy)
+                      : make_double2(double(ye.x) + (qx - double(ye.x)) * b.x,
+                                     double(ye.y) + (qy - double(ye.y)) * b.x);
+      znext[i] = ze;
     }
-    const double2 yo = gy[i];
-    gy[i] = make_double2(yo.x + (g.x - gq.x), yo.y + (g.y - gq.y));
-    gzc[i] = make_double2((1.0 - mU) * gq.x, (1.0 - mU) * gq.y);
-    const double2 wo = gw[i];
-    gw[i] = make_double2(wo.x + mU * gq.x, wo.y + mU * gq.y);
+    if (p_out) {
+      const double2 d = du_offset(ze, we, ye, mU);
+      s2 += d.x * d.x + d.y * d.y;
+    } else {
+      const float2 ve = a.v[i];
+      const double vbx = Ue * (we.x - ze.x), vby = Ue * (we.y - ze.y);
+      v_out[i] = make_float2(float(double(ve.x) + lambda * (vbx - double(ve.x))),
+                             float(double(ve.y) + lambda * (vby - double(ve.y))));
+      if (z_out != znext) z_out[i] = ze;
+    }
+  }
+  if (p_out) {
+    s2 = du_block_sum(s2, red);
+    if (threadIdx.x == 0) p_out[c] = s2;
   }
 }
 
-// VJP end: gg = gw, gv = (1 - lambda) gv' + gw / U, gy to complex64.
-__global__ void k_du_vjp_finish(int64_t M, const double* __restrict__ U, double lambda,
-                                const float2* __restrict__ gv_out, const double2* __restrict__ gw,
-                                const double2* __restrict__ gy, float2* __restrict__ g_g, float2* __restrict__ g_v,
-                                float2* __restrict__ g_y) {
-  for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < M; i += int64_t(gridDim.x) * blockDim.x) {
-    const double2 w = gw[i];
-    const float2 g = gv_out ? gv_out[i] : make_float2(0.f, 0.f);
-    const double Ue = U[i];
-    if (g_g) g_g[i] = make_float2(float(w.x), float(w.y));
-    if (g_v)
-      g_v[i] = make_float2(float((1.0 - lambda) * double(g.x) + w.x / Ue), float((1.0 - lambda) * double(g.y) + w.y / Ue));
-    if (g_y) {
-      const double2 yy = gy[i];
-      g_y[i] = make_float2(float(yy.x), float(yy.y));
+// VJP.  FIRST: gz_n = gz' - lambda U gv', gw = lambda U gv', gy = 0.  Else the
+// VJP of step s: gq = P_B Jacobian^T gz_s (block coefficients of p2 / pd or
+// blk; zprev = z_{s-1}); gy += gz_s - gq; gz_{s-1} = (1 - mu U) gq;
+// gw += mu U gq.  Then the partials of step s - 1 (zprev2 = z_{s-2}), or after
+// step 1 the outputs: gg = gw, gv = (1 - lambda) gv' + gw / U, gy.
+struct DuGrad {
+  const float2* gv_out; const double2* gz_out;
+  double2* gzc; double2* gw; double2* gy;
+  float2* g_g; float2* g_v; float2* g_y;
+  double lambda;
+};
+template <bool FIRST>
+__global__ __launch_bounds__(DU_THREADS) void k_du_vjp_step(DuIn a, DuChunks t, DuGrad o,
+                                                            const double4* __restrict__ blk,
+                                                            const double* __restrict__ p2,
+                                                            const double* __restrict__ pd, double* __restrict__ p2n,
+                                                            double* __restrict__ pdn,
+                                                            const double2* __restrict__ zprev,
+                                                            const double2* __restrict__ zprev2) {
+  __shared__ double red[DU_THREADS / 64];
+  const int c = blockIdx.x;
+  double4 b = make_double4(1.0, 0.0, 1.0, 0.0);
+  if (!FIRST) b = du_block(blk, t.coff, t.eps, p2, pd, t.cblock[c], red);
+  double s2 = 0.0, sd = 0.0;
+#pragma unroll 2
+  for (int64_t i = t.cstart[c] + threadIdx.x; i < t.cstart[c + 1]; i += DU_THREADS) {
+    const double Ue = a.U[i], mU = a.mu * Ue;
+    const double2 we = du_w(a, i, Ue);
+    const float2 ye = a.y[i];
+    double2 g, gw, gy;
+    if (FIRST) {
+      const double lU = o.lambda * Ue;
+      const float2 gv = o.gv_out ? o.gv_out[i] : make_float2(0.f, 0.f);
+      const double2 z = o.gz_out ? o.gz_out[i] : make_double2(0.0, 0.0);
+      g = make_double2(z.x - lU * double(gv.x), z.y - lU * double(gv.y));
+      gw = make_double2(lU * double(gv.x), lU * double(gv.y));
+      gy = make_double2(0.0, 0.0);
+    } else {
+      g = o.gzc[i];
+      gw = o.gw[i];
+      gy = o.gy[i];
+      double2 gq = g;
+      if (b.z == 0.0) {
+        const double2 d = du_offset(zprev[i], we, ye, mU);
+        gq = make_double2(b.x * g.x - b.y * d.x, b.x * g.y - b.y * d.y);
+      }
+      gy = make_double2(gy.x + (g.x - gq.x), gy.y + (g.y - gq.y));
+      g = make_double2((1.0 - mU) * gq.x, (1.0 - mU) * gq.y);
+      gw = make_double2(gw.x + mU * gq.x, gw.y + mU * gq.y);
+    }
+    o.gzc[i] = g;
+    if (p2n) {
+      o.gw[i] = gw;
+      o.gy[i] = gy;
+      const double2 d = du_offset(zprev2[i], we, ye, mU);
+      s2 += d.x * d.x + d.y * d.y;
+      sd += d.x * g.x + d.y * g.y;
+    } else {
+      const float2 gv = o.gv_out ? o.gv_out[i] : make_float2(0.f, 0.f);
+      if (o.g_g) o.g_g[i] = make_float2(float(gw.x), float(gw.y));
+      if (o.g_v)
+        o.g_v[i] = make_float2(float((1.0 - o.lambda) * double(gv.x) + gw.x / Ue),
+                               float((1.0 - o.lambda) * double(gv.y) + gw.y / Ue));
+      if (o.g_y) o.g_y[i] = make_float2(float(gy.x), float(gy.y));
+    }
+  }
+  if (p2n) {
+    s2 = du_block_sum(s2, red);
+    sd = du_block_sum(sd, red);
+    if (threadIdx.x == 0) {
+      p2n[c] = s2;
+      pdn[c] = sd;
     }
   }
 }
@@ -236,15 +262,15 @@ __global__ void k_pu_vjp(int64_t n, const float* __restrict__ x, const float* __
 
 int ew_blocks(int64_t n) { return int(std::min<int64_t>((n + 255) / 256, 4096)); }
 
-// q partials, block coefficients (r and, with gz, the Jacobian terms)
-int du_blocks(ppd_plan* p, const DuIn& in, const double2* zprev, const double2* gz) {
-  double* p2 = p->sec_part;
-  double* pd = p->sec_part + p->n_sec_chunks;
-  hipLaunchKernelGGL(k_du_partials, dim3(p->n_sec_chunks), dim3(DU_THREADS), 0, p->stream, in, p->sec_cstart, zprev,
-                     gz, p2, pd);
-  hipLaunchKernelGGL(k_du_blocks, dim3(p->d), dim3(DU_THREADS), 0, p->stream, p->sec_coff, p->eps_d, p2,
-                     gz ? pd : nullptr, p->du_blk);
+// The block coefficients of partials p2 (and pd), for plans with a block of
+// too many chunks for every workgroup to add up; else NULL.
+int du_blocks(ppd_plan* p, const double* p2, const double* pd, const double4** blk) {
+  *blk = nullptr;
+  if (p->own_sums) return PPD_OK;
+  hipLaunchKernelGGL(k_du_blocks, dim3(p->d), dim3(DU_THREADS), 0, p->stream, p->sec_coff, p->eps_d, p2, pd,
+                     p->du_blk);
   PPD_HIP(hipGetLastError());
+  *blk = p->du_blk;
   return PPD_OK;
 }
 
@@ -266,18 +292,24 @@ extern "C" int ppd_dual_update(ppd_plan* p, const float* g, const float* y, cons
   const DuIn in{reinterpret_cast<const float2*>(g), reinterpret_cast<const float2*>(y), U,
                 reinterpret_cast<const float2*>(v), mu};
   double2* zo = reinterpret_cast<double2*>(z_out);
+  float2* vo = reinterpret_cast<float2*>(v_out);
   double2* hist = reinterpret_cast<double2*>(zs);
   const double2* zprev = reinterpret_cast<const double2*>(z);
+  const DuChunks t{p->sec_cstart, p->sec_cblock, p->sec_coff, p->eps_d};
+  const dim3 grid(p->n_sec_chunks), block(DU_THREADS);
+  double* part[2] = {p->sec_part, p->sec_part + p->n_sec_chunks};
+  hipLaunchKernelGGL(k_du_step<true>, grid, block, 0, p->stream, in, t, nullptr, nullptr, part[0], zprev, nullptr,
+                     lambda, nullptr, nullptr);
   for (int s = 1; s <= n_itr; ++s) {
     // z_s goes to zs[s - 1] when a history is kept, else to z_out
     double2* znext = hist ? hist + size_t(s - 1) * p->M : zo;
-    PPD_TRY(du_blocks(p, in, zprev, nullptr));
-    hipLaunchKernelGGL(k_du_apply, dim3(ew_blocks(p->M)), dim3(256), 0, p->stream, in, p->M, p->vis_block, p->du_blk,
-                       zprev, znext);
+    const double* pin = part[(s - 1) & 1];
+    const double4* blk;
+    PPD_TRY(du_blocks(p, pin, nullptr, &blk));
+    hipLaunchKernelGGL(k_du_step<false>, grid, block, 0, p->stream, in, t, blk, pin, s < n_itr ? part[s & 1] : nullptr,
+                       zprev, znext, lambda, vo, zo);
     zprev = znext;
   }
-  hipLaunchKernelGGL(k_du_finish, dim3(ew_blocks(p->M)), dim3(256), 0, p->stream, in, p->M, lambda, zprev,
-                     reinterpret_cast<float2*>(v_out), zo);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
@@ -296,21 +328,27 @@ extern "C" int ppd_dual_update_vjp(ppd_plan* p, const float* g, const float* y, 
   PPD_TRY(upload_eps(p, eps));
   const DuIn in{reinterpret_cast<const float2*>(g), reinterpret_cast<const float2*>(y), U,
                 reinterpret_cast<const float2*>(v), mu};
-  double2* gzc = reinterpret_cast<double2*>(g_z);   // the running gradient of z_s
-  double2* gw = p->wbuf;
-  double2* gy = p->qbuf;
+  // gzc: the running gradient of z_s
+  const DuGrad o{reinterpret_cast<const float2*>(gv_out), reinterpret_cast<const double2*>(gz_out),
+                 reinterpret_cast<double2*>(g_z), p->wbuf, p->qbuf, reinterpret_cast<float2*>(g_g),
+                 reinterpret_cast<float2*>(g_v), reinterpret_cast<float2*>(g_y), lambda};
+  const double2* z0 = reinterpret_cast<const double2*>(z);
   const double2* hist = reinterpret_cast<const double2*>(zs);
-  hipLaunchKernelGGL(k_du_vjp_init, dim3(ew_blocks(p->M)), dim3(256), 0, p->stream, p->M, U, lambda,
-                     reinterpret_cast<const float2*>(gv_out), reinterpret_cast<const double2*>(gz_out), gzc, gw, gy);
+  auto z_at = [&](int s) { return s == 0 ? z0 : hist + size_t(s - 1) * p->M; };
+  const DuChunks t{p->sec_cstart, p->sec_cblock, p->sec_coff, p->eps_d};
+  const dim3 grid(p->n_sec_chunks), block(DU_THREADS);
+  const int nc = p->n_sec_chunks;
+  double* part[2] = {p->sec_part, p->sec_part + 2 * nc};
+  hipLaunchKernelGGL(k_du_vjp_step<true>, grid, block, 0, p->stream, in, t, o, nullptr, nullptr, nullptr,
+                     part[n_itr & 1], part[n_itr & 1] + nc, nullptr, z_at(n_itr - 1));
   for (int s = n_itr; s >= 1; --s) {
-    const double2* zprev = s == 1 ? reinterpret_cast<const double2*>(z) : hist + size_t(s - 2) * p->M;
-    PPD_TRY(du_blocks(p, in, zprev, gzc));
-    hipLaunchKernelGGL(k_du_vjp_step, dim3(ew_blocks(p->M)), dim3(256), 0, p->stream, in, p->M, p->vis_block,
-                       p->du_blk, zprev, gzc, gw, gy);
+    const double* p2 = part[s & 1];
+    double* p2n = s > 1 ? part[(s - 1) & 1] : nullptr;
+    const double4* blk;
+    PPD_TRY(du_blocks(p, p2, p2 + nc, &blk));
+    hipLaunchKernelGGL(k_du_vjp_step<false>, grid, block, 0, p->stream, in, t, o, blk, p2, p2 + nc, p2n,
+                       p2n ? p2n + nc : nullptr, z_at(s - 1), s > 1 ? z_at(s - 2) : nullptr);
   }
-  hipLaunchKernelGGL(k_du_vjp_finish, dim3(ew_blocks(p->M)), dim3(256), 0, p->stream, p->M, U, lambda,
-                     reinterpret_cast<const float2*>(gv_out), gw, gy, reinterpret_cast<float2*>(g_g),
-                     reinterpret_cast<float2*>(g_v), reinterpret_cast<float2*>(g_y));
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
