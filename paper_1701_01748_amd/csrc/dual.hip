@@ -142,7 +142,7 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factors(const double* __re
 // ---- persistent middle steps of Algorithm 2 ---------------------------------
 // One launch runs the n_itr - 1 middle forward-backward steps of every block
 // with the per-point state (w, z, U, y) held in registers: workgroup g owns
-// the PA_CHUNK plan-order points from g PA_CHUNK (blocks are contiguous in
+// PER PA_THREADS consecutive plan-order points (blocks are contiguous in
 // plan order, so these span at most PA_MAXB blocks; the plan checks it).  A
 // step applies z <- P_B(q) with the block factors and forms the workgroup's
 // partial ||q - y_j||^2 of the next q per block it touches; every workgroup
@@ -199,7 +199,9 @@ __device__ double pa_wait(uint64_t* slot, uint64_t tag, uint32_t* sync, int spin
   }
 }
 
+template <int PER>
 __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
+  static_assert(PA_PER_MAX % PER == 0, "shorter chunks divide the longest");
   static_assert(PA_THREADS == 256, "partials are summed over exactly 4 waves");
   __shared__ double red[PA_THREADS / 64][PA_MAXB];
   __shared__ double2 fac[PA_MAXB];
@@ -207,17 +209,17 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
   __shared__ int quit;
   const int g = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
-  const int64_t i0 = int64_t(g) * PA_CHUNK;
-  const int64_t i1 = min(i0 + PA_CHUNK, a.M);
+  const int64_t i0 = int64_t(g) * PER * PA_THREADS;
+  const int64_t i1 = min(i0 + int64_t(PER) * PA_THREADS, a.M);
   const int b0 = a.wgb0[g];
   int nb = 1;
   while (nb < PA_MAXB && b0 + nb < a.d && a.voff[b0 + nb] < i1) ++nb;
-  double2 w[PA_PER], z[PA_PER];
-  double U[PA_PER];
-  float2 y[PA_PER];
-  int sl[PA_PER];
+  double2 w[PER], z[PER];
+  double U[PER];
+  float2 y[PER];
+  int sl[PER];
 #pragma unroll
-  for (int k = 0; k < PA_PER; ++k) {
+  for (int k = 0; k < PER; ++k) {
     const int64_t i = i0 + int64_t(k) * PA_THREADS + tid;
     sl[k] = -1;
     if (i < i1) {
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
 #pragma unroll
     for (int b = 0; b < PA_MAXB; ++b) acc[b] = 0.0;
 #pragma unroll
-    for (int k = 0; k < PA_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
       if (sl[k] < 0) continue;
       const int b = sl[k];
       const double mU = a.mu * U[k];
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
     if (quit) break;   // uniform: read after the barrier
   }
 #pragma unroll
-  for (int k = 0; k < PA_PER; ++k) {
+  for (int k = 0; k < PER; ++k) {
     const int64_t i = i0 + int64_t(k) * PA_THREADS + tid;
     if (sl[k] >= 0 && act[sl[k]]) a.z[i] = z[k];
   }
@@ -659,14 +661,19 @@ int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* 
   return timer_end(p, slot);
 }
 
-int alg2_persistent_capacity() {
-  int dev = 0, cus = 0, per = 0;
+using PaKernel = void (*)(PaArgs);
+static PaKernel pa_kernel(int per) {
+  return per == 2 ? k_alg2_persistent<2> : per == 4 ? k_alg2_persistent<4> : k_alg2_persistent<PA_PER_MAX>;
+}
+
+int alg2_persistent_capacity(int per) {
+  int dev = 0, cus = 0, blocks = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(k_alg2_persistent),
-                                                   PA_THREADS, 0) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void*>(pa_kernel(per)), PA_THREADS,
+                                                   0) != hipSuccess)
     return 0;
-  return cus * per;
+  return cus * blocks;
 }
 
 int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit) {
@@ -694,7 +701,7 @@ int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit) {
   pa.sync = p->pa_sync;
   int slot;
   PPD_TRY(timer_begin(p, KK_SUBITER, &slot));
-  hipLaunchKernelGGL(k_alg2_persistent, dim3(pa.G), dim3(PA_THREADS), 0, p->stream, pa);
+  hipLaunchKernelGGL(pa_kernel(p->pa_per), dim3(pa.G), dim3(PA_THREADS), 0, p->stream, pa);
   PPD_HIP(hipGetLastError());
   return timer_end(p, slot);
 }

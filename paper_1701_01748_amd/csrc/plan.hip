@@ -524,25 +524,30 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   for (int j = 0; j < p->d; ++j) p->own_sums = p->own_sums && coff[j + 1] - coff[j] <= OWN_SUM_CHUNKS;
   p->n_sec_chunks = int(cblock.size());
 
-  // persistent Algorithm 2: workgroup g owns plan-order points
-  // [g PA_CHUNK, (g+1) PA_CHUNK); its first block, and each block's range of
-  // workgroups (blocks are contiguous in plan order)
-  p->pa_groups = int((M + PA_CHUNK - 1) / PA_CHUNK);
+  // persistent Algorithm 2: workgroup g owns the pa_len plan-order points from
+  // g pa_len; its first block, and each block's range of workgroups (blocks are
+  // contiguous in plan order).  Whether the blocks are long enough is asked of
+  // the longest chunks (PA_CHUNK_MAX, a multiple of pa_len) at every M.
+  p->pa_per = pa_points(M);
+  const int64_t pa_len = int64_t(p->pa_per) * PA_THREADS;
+  p->pa_groups = int((M + pa_len - 1) / pa_len);
   std::vector<int32_t> wgb0(p->pa_groups), gfirst(p->d), glast(p->d), voff(p->d + 1);
   bool pa_fits = true;
   {
-    int j = 0;
-    for (int g = 0; g < p->pa_groups; ++g) {
-      const int64_t a0 = int64_t(g) * PA_CHUNK, a1 = std::min<int64_t>(a0 + PA_CHUNK, M);
+    for (int64_t a0 = 0, j = 0; a0 < M; a0 += PA_CHUNK_MAX) {
+      const int64_t a1 = std::min<int64_t>(a0 + PA_CHUNK_MAX, M);
       while (p->block_off[j + 1] <= a0) ++j;
-      wgb0[g] = j;
       int nb = 1;
       while (j + nb < p->d && p->block_off[j + nb] < a1) ++nb;
       if (nb > PA_MAXB) pa_fits = false;
     }
+    for (int g = 0, j = 0; g < p->pa_groups; ++g) {
+      while (p->block_off[j + 1] <= g * pa_len) ++j;
+      wgb0[g] = j;
+    }
     for (int jj = 0; jj < p->d; ++jj) {
-      gfirst[jj] = int32_t(p->block_off[jj] / PA_CHUNK);
-      glast[jj] = int32_t((p->block_off[jj + 1] - 1) / PA_CHUNK);
+      gfirst[jj] = int32_t(p->block_off[jj] / pa_len);
+      glast[jj] = int32_t((p->block_off[jj + 1] - 1) / pa_len);
     }
     for (int jj = 0; jj <= p->d; ++jj) voff[jj] = int32_t(p->block_off[jj]);
   }
@@ -660,7 +665,7 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   }
   // the persistent launch needs all its workgroups on the device at once
   if (st == PPD_OK) {
-    p->pa_ok = pa_fits && p->pa_groups <= alg2_persistent_capacity();
+    p->pa_ok = pa_fits && p->pa_groups <= alg2_persistent_capacity(p->pa_per);
   }
   // mapped pinned host memory the final statistics reduction writes into
   if (st == PPD_OK && (hipHostMalloc(reinterpret_cast<void**>(&p->host_stats), sizeof(double) * (9 + p->d),

@@ -46,14 +46,14 @@ constexpr int OWN_SUM_CHUNKS = 4096;
 constexpr int MAX_ITEM_SEGS = 64; // per-block segments of one work item (one wave scans them)
 constexpr int MAX_XCD = 8;
 constexpr int PA_THREADS = 256;   // persistent Algorithm 2: threads per workgroup
-#ifndef PPD_PA_PER
-#define PPD_PA_PER 12
-#endif
-// points per thread held in registers: 12 (230 VGPRs, 2 waves per SIMD)
-// leaves fewer workgroups to wait for at each step than 8 and still fits
-// the co-residency limit at 1.3M points
-constexpr int PA_PER = PPD_PA_PER;
-constexpr int PA_CHUNK = PA_THREADS * PA_PER;
+// Points per thread held in registers: 12 (230 VGPRs, 2 waves per SIMD)
+// leaves few workgroups to wait for at each step and still fits the
+// co-residency limit at 1.3M points.  Fewer points are spread over more
+// compute units: a step's own arithmetic is then short against the exchange
+// (four middle steps at 65536 points: 28.3 us at 12, 18.2 at 4, 16.2 at 2).
+constexpr int PA_PER_MAX = 12;
+inline int pa_points(int64_t M) { return M <= (1 << 17) ? 2 : M <= (1 << 19) ? 4 : PA_PER_MAX; }
+constexpr int PA_CHUNK_MAX = PA_THREADS * PA_PER_MAX;
 constexpr int PA_MAXB = 4;        // data blocks one workgroup's points may span
 constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag
 // tagged partial slots of the persistent launch (see k_alg2_persistent)
@@ -224,7 +224,8 @@ struct ppd_plan {
   double* sec_nu = nullptr;                // [2][d] nu of the last two Newton passes
   double4* du_blk = nullptr;               // [d] block terms of the differentiable dual update
   // persistent Algorithm 2 middle steps (one launch, state in registers):
-  // workgroup g holds plan-order points [g PA_CHUNK, (g+1) PA_CHUNK)
+  // workgroup g holds the pa_per PA_THREADS plan-order points from there on
+  int pa_per = 0;                          // points per thread
   int pa_groups = 0;                       // workgroups of the persistent launch
   bool pa_ok = false;                      // every workgroup co-resident and within PA_MAXB blocks
   int32_t* voff_d = nullptr;               // [d+1] block offsets (plan order)
@@ -333,9 +334,9 @@ int block_factors(ppd_plan* p, const double* part);
 // last step's factors in bfac).  spin_limit bounds each wait
 // (0: default).
 int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit);
-// Maximum co-resident workgroups of the persistent launch on the current
-// device (0 if it cannot be determined).
-int alg2_persistent_capacity();
+// Maximum co-resident workgroups of the persistent launch at `per` points per
+// thread on the current device (0 if it cannot be determined).
+int alg2_persistent_capacity(int per);
 // n_newton Newton steps of the exact prox per block; nu_j in bfac[j].x.
 // The prox argument is w if non-NULL, else U^-1 v + ga (see dual_arg).
 int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
