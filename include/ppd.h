@@ -400,6 +400,44 @@ int ppd_primal_update_vjp(ppd_plan* plan, const float* x, const float* a, const 
                           double zeta, double lambda, const float* gx_out, const float* gxt_out, float* g_x,
                           float* g_a, float* g_b);
 
+/* One differentiable iteration as one call: what ppd_phi, ppd_dual_update,
+ * ppd_sara (analysis), ppd_sparsity_update, ppd_phit, ppd_sara (synthesis) and
+ * ppd_primal_update give in the data flow above.  The arrays of the
+ * parameters are as there; g [M]
+ * complex64, c [9][ny][nx], a, b [ny][nx] and zs [n_itr][M] complex128 are
+ * outputs that the VJP reads. */
+typedef struct {
+  const float* x; const float* xt; const float* v; const float* u; const double* z;
+  const float* y; const double* U;
+  const double* eps;                 /* HOST [d]                                  */
+  double tau, eta, zeta, lambda, alpha, mu;
+  int32_t n_itr, pad_;
+  float* g; float* c; float* a; float* b; double* zs;
+  float* x_out; float* xt_out; float* v_out; float* u_out; double* z_out;
+} ppd_step_args;
+int ppd_step(ppd_plan* plan, const ppd_step_args* step);
+/* Its VJP, from the gradients gx_out, gxt_out, gv_out, gu_out, gz_out of its
+ * outputs (each NULL = 0).  Gradients are formed where asked for (NULL = not):
+ * g_x; of the data dual g_z, and with it g_v, g_y and g_g; of the sparsity dual
+ * g_u and g_c; g_xt, which needs g_g and g_c (those of the two that are asked
+ * for).  g_g and g_c are the gradients of the intermediate g and c.  Work
+ * arrays: with gx_out or gxt_out g_a, g_b ([ny][nx]), t_v ([M] complex64, data
+ * dual) and t_u ([9][ny][nx], sparsity dual). */
+typedef struct {
+  const float* gx_out; const float* gxt_out; const float* gv_out; const float* gu_out; const double* gz_out;
+  float* g_x; float* g_xt; float* g_v; float* g_u; double* g_z; float* g_y;
+  float* g_a; float* g_b; float* g_g; float* g_c; float* t_v; float* t_u;
+} ppd_step_grads;
+int ppd_step_vjp(ppd_plan* plan, const ppd_step_args* step, const ppd_step_grads* grads);
+
+/* Data fidelity of one channel: r = Theta G F Z x - y ([M] complex64, plan
+ * order, may not alias y) and ||r||^2, summed in FP64: *acc (DEVICE) receives
+ * it, added to its present value if `add`, and *loss (DEVICE) *acc in float32.
+ * Its gradient with respect to x is 2 Re Phi^H r. */
+int ppd_fidelity(ppd_plan* plan, const float* x, const float* y, float* r, int add, double* acc, float* loss);
+/* x += Re Phi^H y (y in plan order), as ppd_phit. */
+int ppd_phit_add(ppd_plan* plan, const float* y, float* x);
+
 /* ---- per-kernel timing (HIP events around each launch) ----------------- */
 /* When enabled, the plan records a pair of HIP events around every kernel
  * it launches (not inside captured graphs).  ppd_timing_read synchronises

@@ -446,7 +446,8 @@ __device__ inline double block_sum(double v, double* red) {
   return s;
 }
 
-// Inverse rows: row-pass buffer -> image rows 2 i, 2 i + 1.  PRIMAL fuses the
+// Inverse rows: row-pass buffer -> image rows 2 i, 2 i + 1 (add: added to
+// them).  PRIMAL fuses the
 // primal update of Algorithm 3 (gradient step, projection onto the positive
 // orthant, relaxation and the extrapolated iterate), the FP64 statistics
 // partials of the new iterate, and the forward row pass of the new x~ (the
@@ -457,7 +458,7 @@ __global__ __launch_bounds__(RowCfg<L>::THREADS) void k_fft_rows_inv(
     const float2* __restrict__ half, const float2* __restrict__ tw, const float* __restrict__ dpx,
     const float* __restrict__ dpy, int ny, float* __restrict__ x, float* __restrict__ xt,
     const float* __restrict__ ut, const float* __restrict__ x_true, double tau, double eta, double zeta,
-    double lambda, double* __restrict__ part, float2* __restrict__ half_next) {
+    double lambda, double* __restrict__ part, float2* __restrict__ half_next, int add) {
   using F = typename RowCfg<L>::F;
   constexpr int E = F::E, P = F::P, NX = L / 2, H = L / 2;
   __shared__ float2 sm[RowCfg<L>::NS * F::LDS];
@@ -512,7 +513,7 @@ __global__ __launch_bounds__(RowCfg<L>::THREADS) void k_fft_rows_inv(
       for (int r = 0; r < 2; ++r) {
         const size_t idx = size_t(row + r) * NX + c;
         if constexpr (!PRIMAL) {
-          x[idx] = val[r];
+          x[idx] = add ? x[idx] + val[r] : val[r];
         } else {
           const double xo = r ? xo_b[i] : xo_a[i];
           double xb = xo - tau * (eta * double(val[r]) + zeta * double(r ? ut_b[i] : ut_a[i]));   // primal step, then P_C
@@ -636,7 +637,7 @@ int fft_cols_inverse(ppd_plan* p) {
   return timer_end(p, slot);
 }
 
-int fft_adjoint(ppd_plan* p, float* x) {
+int fft_adjoint(ppd_plan* p, float* x, bool add) {
   PPD_TRY(fft_cols_inverse(p));
   int slot;
   PPD_TRY(timer_begin(p, KK_FFT_ROWS_INV, &slot));
@@ -644,7 +645,7 @@ int fft_adjoint(ppd_plan* p, float* x) {
     constexpr int L = decltype(l)::value;
     hipLaunchKernelGGL((k_fft_rows_inv<L, false>), dim3(row_blocks<L>(p)), dim3(RowCfg<L>::THREADS), 0, p->stream,
                        p->half, p->twx, p->dpx, p->dpy, p->ny, x, nullptr, nullptr, nullptr, 0.0, 0.0, 0.0, 0.0,
-                       nullptr, nullptr);
+                       nullptr, nullptr, add ? 1 : 0);
     PPD_HIP(hipGetLastError());
     return PPD_OK;
   }));
@@ -658,7 +659,7 @@ int fft_rows_inverse_primal(ppd_plan* p, const PrimalArgs& a, float2* next) {
     constexpr int L = decltype(l)::value;
     hipLaunchKernelGGL((k_fft_rows_inv<L, true>), dim3(row_blocks<L>(p)), dim3(RowCfg<L>::THREADS), 0, p->stream,
                        p->half, p->twx, p->dpx, p->dpy, p->ny, a.x, a.xt, a.ut, a.x_true, a.tau, a.eta, a.zeta,
-                       a.lambda, a.part, next);
+                       a.lambda, a.part, next, 0);
     PPD_HIP(hipGetLastError());
     return PPD_OK;
   }));

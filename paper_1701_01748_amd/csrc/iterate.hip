@@ -133,6 +133,25 @@ __global__ void k_vis_mul_U(float2* __restrict__ y, const double* __restrict__ U
   }
 }
 
+// The segments' squared residual norms added up (one workgroup, fixed order):
+// *acc (+)= their sum, *loss = *acc.
+__global__ __launch_bounds__(STAT_THREADS) void k_fidelity(const double* __restrict__ rpart, int n, int add,
+                                                           double* __restrict__ acc, float* __restrict__ loss) {
+  __shared__ double red[STAT_THREADS / 64];
+  double s = 0.0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += STAT_THREADS) s += rpart[i];
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = add ? *acc : 0.0;
+    for (int q = 0; q < STAT_THREADS / 64; ++q) t += red[q];
+    *acc = t;
+    *loss = float(t);
+  }
+}
+
 int img_norm(ppd_plan* p, const float* a, double* out_host) {
   const int64_t n = int64_t(p->nx) * p->ny;
   const int G = int(std::min<int64_t>((n + 255) / 256, 512));
@@ -171,14 +190,6 @@ struct IterCtx {
   double* stats_out = nullptr;
   bool stats_cursor = false;
   int has_truth = 0, use_res_sq = 0;
-};
-
-// Runs the plan's launches on another stream for the lifetime of the object.
-struct OnStream {
-  ppd_plan* p;
-  hipStream_t saved;
-  OnStream(ppd_plan* pl, hipStream_t s) : p(pl), saved(pl->stream) { p->stream = s; }
-  ~OnStream() { p->stream = saved; }
 };
 
 // The data-fidelity path of one iteration (F Z x~, the data-dual update
@@ -497,6 +508,21 @@ extern "C" int ppd_iterate(ppd_plan* p, ppd_state* st, const ppd_params* prm, in
       return fail(PPD_ENONFINITE, "ppd_iterate: non-finite statistics");
   }
   return PPD_OK;
+}
+
+extern "C" int ppd_fidelity(ppd_plan* p, const float* x, const float* y, float* r, int add, double* acc, float* loss) {
+  if (!p || !x || !y || !r || !acc || !loss) return fail(PPD_EINVAL, "ppd_fidelity: NULL argument");
+  PPD_TRY(fft_forward(p, x));
+  PPD_TRY(degrid_residual(p, reinterpret_cast<const float2*>(y), reinterpret_cast<float2*>(r)));
+  hipLaunchKernelGGL(k_fidelity, dim3(1), dim3(STAT_THREADS), 0, p->stream, p->rpart, p->n_segs, add, acc, loss);
+  PPD_HIP(hipGetLastError());
+  return PPD_OK;
+}
+
+extern "C" int ppd_phit_add(ppd_plan* p, const float* y, float* x) {
+  if (!p || !x || !y) return fail(PPD_EINVAL, "ppd_phit_add: NULL argument");
+  PPD_TRY(grid_plain(p, reinterpret_cast<const float2*>(y)));
+  return fft_adjoint(p, x, true);
 }
 
 extern "C" int ppd_op_norm(ppd_plan* p, const double* U, const float* x0, int max_iter, double tol,

@@ -139,7 +139,10 @@ __device__ __forceinline__ float2 gather8(const float2* reg2, const Taps& t) {
 // NW: waves per workgroup.  8 x 8 tiles hold about two batches, so there an
 // item is one wave's work; where the items are too few to fill the chip
 // (SHARE_ITEMS) two waves share it.
-template <int T, bool DUAL, int NW>
+// MODE: plain (out = Theta G a), the dual update, or the residual
+// (out = Theta G a - y, with the partials of its squared norm).
+enum { DEGRID_PLAIN = 0, DEGRID_DUAL = 1, DEGRID_RES = 2 };
+template <int T, int MODE, int NW>
 __global__ __launch_bounds__(64 * NW) void k_degrid(
     const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
@@ -148,10 +151,11 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
     const double* __restrict__ U, const float2* __restrict__ v, const double2* __restrict__ z,
     float2* __restrict__ gout, double mu, double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
   constexpr int R = T + 7;
+  constexpr bool DUAL = MODE == DEGRID_DUAL, RES = MODE == DEGRID_RES;
   constexpr bool B128 = T == 8;
   __shared__ __align__(16) float2 reg[B128 ? 2 * G8_COPY : R * R];
   __shared__ ItemTab tab;
-  __shared__ double s_q[NW][MAX_ITEM_SEGS], s_r[NW][MAX_ITEM_SEGS];
+  __shared__ double s_q[NW][DUAL ? MAX_ITEM_SEGS : 1], s_r[NW][DUAL || RES ? MAX_ITEM_SEGS : 1];
   const int ii = xcd_item(blockIdx.x, xs);
   if (ii < 0 || ii >= n_items) return;
   const Item it = items[ii];
@@ -181,9 +185,9 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
   if (!one) load_item_tab(it, segs, tab);
   KbCoef kbw;
   load_kb(kbc, kbw);
-  if (DUAL)
+  if (DUAL || RES)
     for (int i = threadIdx.x; i < NW * MAX_ITEM_SEGS; i += blockDim.x) {
-      (&s_q[0][0])[i] = 0.0;
+      if (DUAL) (&s_q[0][0])[i] = 0.0;
       (&s_r[0][0])[i] = 0.0;
     }
 #pragma unroll
@@ -227,6 +231,7 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
         b.y = y[b.pi];
       } else {
         b.po = uperm ? uperm[b.pi] : b.pi;   // where the caller's order has it
+        if (RES) b.y = y[b.pi];
       }
     }
   };
@@ -270,7 +275,11 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
         }
       }
       const float2 g = make_float2(ax * th, (t.conj ? -ay : ay) * th);
-      if (!DUAL) {
+      if (RES) {
+        out[cb.po] = make_float2(g.x - ye.x, g.y - ye.y);
+        const double ex = double(g.x) - double(ye.x), ey = double(g.y) - double(ye.y);
+        rn = ex * ex + ey * ey;
+      } else if (!DUAL) {
         out[cb.po] = g;
       } else {
         // argument of the data-dual update of Algorithm 3: w = U^-1 v + Theta G a (Theta G a kept for the
@@ -286,28 +295,28 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
         rn = ex * ex + ey * ey;
       }
     }
-    if (DUAL) {
+    if (DUAL || RES) {
       const int slast = __builtin_amdgcn_readlane(sg, min(63, total - 1 - bt * 64));
       for (int ss = sb; ss <= slast; ++ss) {
-        const double a = part ? wave_sum(act && sg == ss ? qn : 0.0) : 0.0;
+        const double a = DUAL && part ? wave_sum(act && sg == ss ? qn : 0.0) : 0.0;
         const double r = rpart ? wave_sum(act && sg == ss ? rn : 0.0) : 0.0;
         if (lane == 0) {
-          s_q[uwid][ss] += a;
+          if (DUAL) s_q[uwid][ss] += a;
           s_r[uwid][ss] += r;
         }
       }
     }
   }
-  if (DUAL) {
+  if (DUAL || RES) {
     __syncthreads();
     for (int k = threadIdx.x; k < nseg; k += blockDim.x) {
       double q = 0.0, r = 0.0;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
-        q += s_q[w][k];
+        if (DUAL) q += s_q[w][k];
         r += s_r[w][k];
       }
-      if (part) part[it.seg0 + k] = q;
+      if (DUAL && part) part[it.seg0 + k] = q;
       if (rpart) rpart[it.seg0 + k] = r;
     }
   }
@@ -845,13 +854,18 @@ __global__ void k_permute(const int32_t* __restrict__ perm, int64_t M, int to_us
 
 
 template <int T, int NW>
-int launch_degrid(ppd_plan* p, bool dual, float2* out, const int32_t* uperm, const DualArgs* a, double* part_out) {
-  if (!dual) {
-    hipLaunchKernelGGL((k_degrid<T, false, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
+int launch_degrid(ppd_plan* p, int mode, float2* out, const int32_t* uperm, const float2* y, const DualArgs* a,
+                  double* part_out) {
+  if (mode == DEGRID_RES) {
+    hipLaunchKernelGGL((k_degrid<T, DEGRID_RES, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f,
+                       p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale,
+                       p->kbc, out, nullptr, y, nullptr, nullptr, nullptr, nullptr, 0.0, nullptr, p->rpart, p->split1);
+  } else if (mode == DEGRID_PLAIN) {
+    hipLaunchKernelGGL((k_degrid<T, DEGRID_PLAIN, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
                        p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
                        out, uperm, nullptr, nullptr, nullptr, nullptr, nullptr, 0.0, nullptr, nullptr, p->split1);
   } else {
-    hipLaunchKernelGGL((k_degrid<T, true, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
+    hipLaunchKernelGGL((k_degrid<T, DEGRID_DUAL, NW>), dim3(p->split1.launch), dim3(64 * NW), 0, p->stream, p->grid_f, p->PW,
                        p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
                        nullptr, nullptr, a->y, a->U, a->v, a->z, p->gabuf, a->mu, part_out, a->rpart, p->split1);
   }
@@ -910,18 +924,19 @@ int launch_fold8(ppd_plan* p) {
   return PPD_OK;
 }
 
-int dispatch_degrid(ppd_plan* p, bool dual, float2* out, const int32_t* uperm, const DualArgs* a, double* part_out) {
+int dispatch_degrid(ppd_plan* p, int mode, float2* out, const int32_t* uperm, const float2* y, const DualArgs* a,
+                    double* part_out) {
   int slot;
   PPD_TRY(timer_begin(p, KK_DEGRID, &slot));
   int st;
   switch (p->T) {
     case 8:
-      st = p->n_items <= SHARE_ITEMS ? launch_degrid<8, 2>(p, dual, out, uperm, a, part_out)
-                                     : launch_degrid<8, 1>(p, dual, out, uperm, a, part_out);
+      st = p->n_items <= SHARE_ITEMS ? launch_degrid<8, 2>(p, mode, out, uperm, y, a, part_out)
+                                     : launch_degrid<8, 1>(p, mode, out, uperm, y, a, part_out);
       break;
-    case 16: st = launch_degrid<16, PPD_DEGRID_WAVES>(p, dual, out, uperm, a, part_out); break;
-    case 32: st = launch_degrid<32, PPD_DEGRID_WAVES>(p, dual, out, uperm, a, part_out); break;
-    default: st = launch_degrid<64, PPD_DEGRID_WAVES>(p, dual, out, uperm, a, part_out); break;
+    case 16: st = launch_degrid<16, PPD_DEGRID_WAVES>(p, mode, out, uperm, y, a, part_out); break;
+    case 32: st = launch_degrid<32, PPD_DEGRID_WAVES>(p, mode, out, uperm, y, a, part_out); break;
+    default: st = launch_degrid<64, PPD_DEGRID_WAVES>(p, mode, out, uperm, y, a, part_out); break;
   }
   PPD_TRY(st);
   return timer_end(p, slot);
@@ -947,10 +962,13 @@ int dispatch_grid(ppd_plan* p, bool dual, const float2* vin, const int32_t* uper
 }  // namespace
 
 int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm) {
-  return dispatch_degrid(p, false, out, uperm, nullptr, nullptr);
+  return dispatch_degrid(p, DEGRID_PLAIN, out, uperm, nullptr, nullptr, nullptr);
 }
 int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out) {
-  return dispatch_degrid(p, true, nullptr, nullptr, &a, part_out);
+  return dispatch_degrid(p, DEGRID_DUAL, nullptr, nullptr, nullptr, &a, part_out);
+}
+int degrid_residual(ppd_plan* p, const float2* y, float2* out) {
+  return dispatch_degrid(p, DEGRID_RES, out, nullptr, y, nullptr, nullptr);
 }
 
 int grid_plain(ppd_plan* p, const float2* v, const int32_t* uperm) {

@@ -287,7 +287,7 @@ int timer_end(ppd_plan* p, int slot);
 int fft_forward(ppd_plan* p, const float* x);                  // x -> grid_f (via half)
 int fft_rows_forward(ppd_plan* p, const float* x, float2* dst);  // x -> dst (row-pass buffer)
 int fft_cols_forward(ppd_plan* p, const float2* src);           // src (row-pass buffer) -> grid_f
-int fft_adjoint(ppd_plan* p, float* x);                        // grid_a -> x (plain)
+int fft_adjoint(ppd_plan* p, float* x, bool add = false);      // grid_a -> x, or added to x (plain)
 int fft_cols_inverse(ppd_plan* p);                             // grid_a -> half
 struct PrimalArgs {
   float* x; float* xt; const float* ut; const float* x_true;
@@ -301,6 +301,8 @@ int fold_grid(ppd_plan* p);                                    // gscratch -> gr
 
 // grid_f -> out, in plan order, or with uperm (plan -> caller) in the caller's
 int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm = nullptr);
+// grid_f -> Theta G a - y (plan order), squared norms per segment in rpart
+int degrid_residual(ppd_plan* p, const float2* y, float2* out);
 struct DualArgs {
   const float2* y; const double* U; float2* v; double2* z;
   double mu, lambda;
@@ -358,6 +360,18 @@ void kb_tap_polynomials(double beta, float* coef /* [8][KB_NC] */);
 double kb_ft(double xi, double beta);
 void daubechies(int p, double* h);
 FftTwiddles fft_twiddles(int L);
+
+}  // namespace ppd
+
+namespace ppd {
+
+// Runs the plan's launches on another stream for the lifetime of the object.
+struct OnStream {
+  ppd_plan* p;
+  hipStream_t saved;
+  OnStream(ppd_plan* pl, hipStream_t s) : p(pl), saved(pl->stream) { p->stream = s; }
+  ~OnStream() { p->stream = saved; }
+};
 
 }  // namespace ppd
 

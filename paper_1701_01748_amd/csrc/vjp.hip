@@ -139,11 +139,21 @@ __global__ __launch_bounds__(DU_THREADS) void k_du_step(DuIn a, DuChunks t, cons
 // gw += mu U gq.  Then the partials of step s - 1 (zprev2 = z_{s-2}), or after
 // step 1 the outputs: gg = gw, gv = (1 - lambda) gv' + gw / U, gy.
 struct DuGrad {
-  const float2* gv_out; const double2* gz_out;
+  const float2* gv_out; const float2* gv_more;   // added, each NULL = 0
+  const double2* gz_out;
   double2* gzc; double2* gw; double2* gy;
   float2* g_g; float2* g_v; float2* g_y;
   double lambda;
 };
+__device__ __forceinline__ float2 du_gv(const DuGrad& o, int64_t i) {
+  float2 g = o.gv_out ? o.gv_out[i] : make_float2(0.f, 0.f);
+  if (o.gv_more) {
+    const float2 m = o.gv_more[i];
+    g.x += m.x;
+    g.y += m.y;
+  }
+  return g;
+}
 template <bool FIRST>
 __global__ __launch_bounds__(DU_THREADS) void k_du_vjp_step(DuIn a, DuChunks t, DuGrad o,
                                                             const double4* __restrict__ blk,
@@ -165,7 +175,7 @@ __global__ __launch_bounds__(DU_THREADS) void k_du_vjp_step(DuIn a, DuChunks t, 
     double2 g, gw, gy;
     if (FIRST) {
       const double lU = o.lambda * Ue;
-      const float2 gv = o.gv_out ? o.gv_out[i] : make_float2(0.f, 0.f);
+      const float2 gv = du_gv(o, i);
       const double2 z = o.gz_out ? o.gz_out[i] : make_double2(0.0, 0.0);
       g = make_double2(z.x - lU * double(gv.x), z.y - lU * double(gv.y));
       gw = make_double2(lU * double(gv.x), lU * double(gv.y));
@@ -191,7 +201,7 @@ __global__ __launch_bounds__(DU_THREADS) void k_du_vjp_step(DuIn a, DuChunks t, 
       s2 += d.x * d.x + d.y * d.y;
       sd += d.x * g.x + d.y * g.y;
     } else {
-      const float2 gv = o.gv_out ? o.gv_out[i] : make_float2(0.f, 0.f);
+      const float2 gv = du_gv(o, i);
       if (o.g_g) o.g_g[i] = make_float2(float(gw.x), float(gw.y));
       if (o.g_v)
         o.g_v[i] = make_float2(float((1.0 - o.lambda) * double(gv.x) + gw.x / Ue),
@@ -221,12 +231,14 @@ __global__ void k_su(int64_t n, const float* __restrict__ u, const float* __rest
 }
 
 __global__ void k_su_vjp(int64_t n, const float* __restrict__ u, const float* __restrict__ c, float alpha,
-                         float lambda, const float* __restrict__ g, float* __restrict__ g_u, float* __restrict__ g_c) {
+                         float lambda, const float* __restrict__ g, const float* __restrict__ g_more,
+                         float* __restrict__ g_u, float* __restrict__ g_c) {
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x) {
     const float s = u[i] + c[i];
     const float m = fabsf(s) < alpha ? 1.0f : 0.0f;
-    if (g_u) g_u[i] = (1.0f - lambda) * g[i] + lambda * m * g[i];
-    if (g_c) g_c[i] = lambda * m * g[i];
+    const float gi = g_more ? g[i] + g_more[i] : g[i];
+    if (g_u) g_u[i] = (1.0f - lambda) * gi + lambda * m * gi;
+    if (g_c) g_c[i] = lambda * m * gi;
   }
 }
 
@@ -314,10 +326,10 @@ extern "C" int ppd_dual_update(ppd_plan* p, const float* g, const float* y, cons
   return PPD_OK;
 }
 
-extern "C" int ppd_dual_update_vjp(ppd_plan* p, const float* g, const float* y, const double* U, const double* eps,
-                                   const float* v, const double* z, int n_itr, double mu, double lambda,
-                                   const double* zs, const float* gv_out, const double* gz_out, float* g_g,
-                                   float* g_v, double* g_z, float* g_y) {
+static int dual_update_vjp(ppd_plan* p, const float* g, const float* y, const double* U, const double* eps,
+                           const float* v, const double* z, int n_itr, double mu, double lambda, const double* zs,
+                           const float* gv_out, const float* gv_more, const double* gz_out, float* g_g, float* g_v,
+                           double* g_z, float* g_y) {
   if (!p || !g || !y || !U || !eps || !v || !z || !zs || !g_z)
     return fail(PPD_EINVAL, "ppd_dual_update_vjp: NULL argument");
   if (n_itr < 1) return fail(PPD_EINVAL, "ppd_dual_update_vjp: n_itr must be >= 1");
@@ -329,7 +341,8 @@ extern "C" int ppd_dual_update_vjp(ppd_plan* p, const float* g, const float* y, 
   const DuIn in{reinterpret_cast<const float2*>(g), reinterpret_cast<const float2*>(y), U,
                 reinterpret_cast<const float2*>(v), mu};
   // gzc: the running gradient of z_s
-  const DuGrad o{reinterpret_cast<const float2*>(gv_out), reinterpret_cast<const double2*>(gz_out),
+  const DuGrad o{reinterpret_cast<const float2*>(gv_out), reinterpret_cast<const float2*>(gv_more),
+                 reinterpret_cast<const double2*>(gz_out),
                  reinterpret_cast<double2*>(g_z), p->wbuf, p->qbuf, reinterpret_cast<float2*>(g_g),
                  reinterpret_cast<float2*>(g_v), reinterpret_cast<float2*>(g_y), lambda};
   const double2* z0 = reinterpret_cast<const double2*>(z);
@@ -353,6 +366,13 @@ extern "C" int ppd_dual_update_vjp(ppd_plan* p, const float* g, const float* y, 
   return PPD_OK;
 }
 
+extern "C" int ppd_dual_update_vjp(ppd_plan* p, const float* g, const float* y, const double* U, const double* eps,
+                                   const float* v, const double* z, int n_itr, double mu, double lambda,
+                                   const double* zs, const float* gv_out, const double* gz_out, float* g_g,
+                                   float* g_v, double* g_z, float* g_y) {
+  return dual_update_vjp(p, g, y, U, eps, v, z, n_itr, mu, lambda, zs, gv_out, nullptr, gz_out, g_g, g_v, g_z, g_y);
+}
+
 extern "C" int ppd_sparsity_update(ppd_plan* p, const float* u, const float* c, float alpha, float lambda,
                                    float* u_out) {
   if (!p || !u || !c || !u_out) return fail(PPD_EINVAL, "ppd_sparsity_update: NULL argument");
@@ -364,15 +384,21 @@ extern "C" int ppd_sparsity_update(ppd_plan* p, const float* u, const float* c, 
   return PPD_OK;
 }
 
-extern "C" int ppd_sparsity_update_vjp(ppd_plan* p, const float* u, const float* c, float alpha, float lambda,
-                                       const float* g_out, float* g_u, float* g_c) {
+static int sparsity_update_vjp(ppd_plan* p, const float* u, const float* c, float alpha, float lambda,
+                               const float* g_out, const float* g_more, float* g_u, float* g_c) {
   if (!p || !u || !c || !g_out) return fail(PPD_EINVAL, "ppd_sparsity_update_vjp: NULL argument");
   if (!(alpha >= 0.0f) || !(lambda > 0.0f && lambda <= 1.0f))
     return fail(PPD_EINVAL, "ppd_sparsity_update_vjp: need alpha >= 0 and 0 < lambda <= 1");
   const int64_t n = int64_t(N_BASES) * p->nx * p->ny;
-  hipLaunchKernelGGL(k_su_vjp, dim3(ew_blocks(n)), dim3(256), 0, p->stream, n, u, c, alpha, lambda, g_out, g_u, g_c);
+  hipLaunchKernelGGL(k_su_vjp, dim3(ew_blocks(n)), dim3(256), 0, p->stream, n, u, c, alpha, lambda, g_out,
+                     g_more, g_u, g_c);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
+}
+
+extern "C" int ppd_sparsity_update_vjp(ppd_plan* p, const float* u, const float* c, float alpha, float lambda,
+                                       const float* g_out, float* g_u, float* g_c) {
+  return sparsity_update_vjp(p, u, c, alpha, lambda, g_out, nullptr, g_u, g_c);
 }
 
 extern "C" int ppd_primal_update(ppd_plan* p, const float* x, const float* a, const float* b, double tau, double eta,
@@ -397,5 +423,53 @@ extern "C" int ppd_primal_update_vjp(ppd_plan* p, const float* x, const float* a
   hipLaunchKernelGGL(k_pu_vjp, dim3(ew_blocks(n)), dim3(256), 0, p->stream, n, x, a, b, tau, eta, zeta, lambda,
                      gx_out, gxt_out, g_x, g_a, g_b);
   PPD_HIP(hipGetLastError());
+  return PPD_OK;
+}
+
+// One differentiable iteration as one call, on one stream: at 256^2 with
+// 65536 points its 16 launches (14 in the VJP) take less time on the GPU than
+// on the host, and a fork to the second stream and back cost 40 us of host
+// time each (450 us per forward and backward against 365).
+extern "C" int ppd_step(ppd_plan* p, const ppd_step_args* s) {
+  if (!p || !s || !s->x || !s->xt || !s->v || !s->u || !s->z || !s->y || !s->U || !s->eps || !s->g || !s->c || !s->a ||
+      !s->b || !s->zs || !s->x_out || !s->xt_out || !s->v_out || !s->u_out || !s->z_out)
+    return fail(PPD_EINVAL, "ppd_step: NULL argument");
+  PPD_TRY(ppd_sara_w(p, PPD_SARA_ANALYSIS, s->xt, s->c, nullptr, nullptr, 0.f, 0.f));
+  PPD_TRY(ppd_sparsity_update(p, s->u, s->c, float(s->alpha), float(s->lambda), s->u_out));
+  PPD_TRY(ppd_sara_w(p, PPD_SARA_SYNTHESIS, s->u_out, s->b, nullptr, nullptr, 0.f, 0.f));
+  PPD_TRY(ppd_phi(p, s->xt, s->g, PPD_ORDER_PLAN));
+  PPD_TRY(ppd_dual_update(p, s->g, s->y, s->U, s->eps, s->v, s->z, s->n_itr, s->mu, s->lambda, s->v_out, s->z_out,
+                          s->zs));
+  PPD_TRY(ppd_phit(p, s->v_out, s->a, PPD_ORDER_PLAN));
+  return ppd_primal_update(p, s->x, s->a, s->b, s->tau, s->eta, s->zeta, s->lambda, s->x_out, s->xt_out);
+}
+
+extern "C" int ppd_step_vjp(ppd_plan* p, const ppd_step_args* s, const ppd_step_grads* q) {
+  if (!p || !s || !q || !s->x || !s->v || !s->u || !s->z || !s->y || !s->U || !s->eps || !s->g || !s->c || !s->a ||
+      !s->b || !s->zs)
+    return fail(PPD_EINVAL, "ppd_step_vjp: NULL argument");
+  // what flows back through the primal update, the data dual, the sparsity dual
+  const bool prim = q->gx_out || q->gxt_out, dual = q->g_z != nullptr, sparse = q->g_u || q->g_c;
+  if (prim && (!q->g_a || !q->g_b)) return fail(PPD_EINVAL, "ppd_step_vjp: g_a and g_b are needed");
+  if (dual && prim && !q->t_v) return fail(PPD_EINVAL, "ppd_step_vjp: t_v is needed");
+  if (!dual && (q->g_v || q->g_y || q->g_g)) return fail(PPD_EINVAL, "ppd_step_vjp: the data dual's gradients need g_z");
+  if (sparse && (prim ? !q->t_u : !q->gu_out)) return fail(PPD_EINVAL, "ppd_step_vjp: t_u (or gu_out) is needed");
+  if (q->g_xt && ((!dual && !sparse) || (dual && !q->g_g) || (sparse && !q->g_c)))
+    return fail(PPD_EINVAL, "ppd_step_vjp: g_xt needs g_g and g_c");
+  if (prim)
+    PPD_TRY(ppd_primal_update_vjp(p, s->x, s->a, s->b, s->tau, s->eta, s->zeta, s->lambda, q->gx_out, q->gxt_out,
+                                  q->g_x, q->g_a, q->g_b));
+  if (sparse) {
+    if (prim) PPD_TRY(ppd_sara_w(p, PPD_SARA_ANALYSIS, q->g_b, q->t_u, nullptr, nullptr, 0.f, 0.f));
+    PPD_TRY(sparsity_update_vjp(p, s->u, s->c, float(s->alpha), float(s->lambda), prim ? q->t_u : q->gu_out,
+                                prim ? q->gu_out : nullptr, q->g_u, q->g_c));
+    if (q->g_xt) PPD_TRY(ppd_sara_w(p, PPD_SARA_SYNTHESIS, q->g_c, q->g_xt, nullptr, nullptr, 0.f, 0.f));
+  }
+  if (dual) {
+    if (prim) PPD_TRY(ppd_phi(p, q->g_a, q->t_v, PPD_ORDER_PLAN));
+    PPD_TRY(dual_update_vjp(p, s->g, s->y, s->U, s->eps, s->v, s->z, s->n_itr, s->mu, s->lambda, s->zs,
+                            prim ? q->t_v : nullptr, q->gv_out, q->gz_out, q->g_g, q->g_v, q->g_z, q->g_y));
+    if (q->g_xt) PPD_TRY(sparse ? ppd_phit_add(p, q->g_g, q->g_xt) : ppd_phit(p, q->g_g, q->g_xt, PPD_ORDER_PLAN));
+  }
   return PPD_OK;
 }

@@ -64,6 +64,19 @@ class Stats(ctypes.Structure):
                 ("residual_max", c_double)]
 
 
+class StepArgs(ctypes.Structure):
+    _fields_ = [(k, c_void_p) for k in ("x", "xt", "v", "u", "z", "y", "U")] + [
+        ("eps", ctypes.POINTER(c_double))] + [
+        (k, c_double) for k in ("tau", "eta", "zeta", "lambda_", "alpha", "mu")] + [
+        ("n_itr", c_int32), ("pad_", c_int32)] + [
+        (k, c_void_p) for k in ("g", "c", "a", "b", "zs", "x_out", "xt_out", "v_out", "u_out", "z_out")]
+
+
+class StepGrads(ctypes.Structure):
+    _fields_ = [(k, c_void_p) for k in ("gx_out", "gxt_out", "gv_out", "gu_out", "gz_out", "g_x", "g_xt", "g_v", "g_u",
+                                        "g_z", "g_y", "g_a", "g_b", "g_g", "g_c", "t_v", "t_u")]
+
+
 _PROTOS = {
     "ppd_strerror": (ctypes.c_char_p, [c_int32]),
     "ppd_last_error": (ctypes.c_char_p, []),
@@ -107,6 +120,10 @@ _PROTOS = {
                                     c_void_p, c_void_p]),
     "ppd_primal_update_vjp": (c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_double, c_double, c_double,
                                         c_double, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]),
+    "ppd_step": (c_int32, [c_void_p, ctypes.POINTER(StepArgs)]),
+    "ppd_step_vjp": (c_int32, [c_void_p, ctypes.POINTER(StepArgs), ctypes.POINTER(StepGrads)]),
+    "ppd_fidelity": (c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_int32, c_void_p, c_void_p]),
+    "ppd_phit_add": (c_int32, [c_void_p, c_void_p, c_void_p]),
     "ppd_timing_enable": (c_int32, [c_void_p, c_int32]),
     "ppd_timing_reset": (c_int32, [c_void_p]),
     "ppd_timing_read": (c_int32, [c_void_p, c_int32, ctypes.POINTER(ctypes.c_char_p),
@@ -522,6 +539,89 @@ def ppd_primal_update_vjp(plan: Plan, x, a, b, tau: float, eta: float, zeta: flo
         plan.handle, _ptr(x), _ptr(a), _ptr(b), float(tau), float(eta), float(zeta), float(lam), _ptr(gx_out),
         _ptr(gxt_out), _ptr(g_x), _ptr(g_a), _ptr(g_b)))
     return g_x, g_a, g_b
+
+
+def ppd_step(plan: Plan, x, xt, v, u, z, y, U, eps, *, tau: float, eta: float, zeta: float, lam: float,
+             alpha: float, mu: float, n_itr: int):
+    """One iteration from its differentiable pieces, in one call: the outputs
+    (x', x~', v', u', z') and the intermediates (g, c, a, b, zs) of its VJP."""
+    import torch
+    N, M = plan.N, plan.M
+    for t, dt, n, name in ((x, torch.float32, N, "x"), (xt, torch.float32, N, "xt"), (v, torch.complex64, M, "v"),
+                           (u, torch.float32, 9 * N, "u"), (z, torch.complex128, M, "z"), (y, torch.complex64, M, "y"),
+                           (U, torch.float64, M, "U")):
+        _need(t, dt, n, name)
+    e, ep = _eps_arg(plan, eps)
+    img, coef, f32 = (plan.ny, plan.nx), (9, plan.ny, plan.nx), torch.float32
+    g, v_out = _alloc((M,), torch.complex64), _alloc((M,), torch.complex64)
+    c, u_out = _alloc(coef, f32), _alloc(coef, f32)
+    a, b, x_out, xt_out = (_alloc(img, f32) for _ in range(4))
+    zs, z_out = _alloc((int(n_itr), M), torch.complex128), _alloc((M,), torch.complex128)
+    args = StepArgs(_ptr(x), _ptr(xt), _ptr(v), _ptr(u), _ptr(z), _ptr(y), _ptr(U), ep, tau, eta, zeta, lam, alpha, mu,
+                    int(n_itr), 0, _ptr(g), _ptr(c), _ptr(a), _ptr(b), _ptr(zs), _ptr(x_out), _ptr(xt_out),
+                    _ptr(v_out), _ptr(u_out), _ptr(z_out))
+    _check("ppd_step", lib().ppd_step(plan.handle, ctypes.byref(args)))
+    return (x_out, xt_out, v_out, u_out, z_out), (g, c, a, b, zs)
+
+
+def ppd_step_vjp(plan: Plan, x, v, u, z, y, U, eps, mids, grads, needs, *, tau: float, eta: float, zeta: float,
+                 lam: float, alpha: float, mu: float, n_itr: int):
+    """Gradients of ppd_step's (x, xt, v, u, z, y) from those of its outputs
+    (None = 0), each formed where `needs` asks for it (else None)."""
+    import torch
+    g, c, a, b, zs = mids
+    gx, gxt, gv, gu, gz = grads
+    N, M = plan.N, plan.M
+    for t, dt, n, name in ((gx, torch.float32, N, "gx"), (gxt, torch.float32, N, "gxt"), (gv, torch.complex64, M, "gv"),
+                           (gu, torch.float32, 9 * N, "gu"), (gz, torch.complex128, M, "gz")):
+        if t is not None:
+            _need(t, dt, n, name)
+    e, ep = _eps_arg(plan, eps)
+    nx_, nxt, nv, nu, nz, ny_ = needs
+    prim = gx is not None or gxt is not None
+    dual = (nxt or nv or nz or ny_) and (prim or gv is not None or gz is not None)
+    sparse = (nxt or nu) and (prim or gu is not None)
+    img, coef, f32, c64 = (plan.ny, plan.nx), (9, plan.ny, plan.nx), torch.float32, torch.complex64
+
+    def new(want, shape, dtype):
+        return _alloc(shape, dtype) if want else None
+    g_x = new(nx_ and prim, img, f32)
+    g_xt = new(nxt and (dual or sparse), img, f32)
+    g_v, g_y, g_z = new(nv and dual, (M,), c64), new(ny_ and dual, (M,), c64), new(dual, (M,), torch.complex128)
+    g_u = new(nu and sparse, coef, f32)
+    g_g, g_c = new(nxt and dual, (M,), c64), new(nxt and sparse, coef, f32)
+    g_a, g_b = new(prim, img, f32), new(prim, img, f32)
+    t_v, t_u = new(prim and dual, (M,), c64), new(prim and sparse, coef, f32)
+    args = StepArgs(_ptr(x), 0, _ptr(v), _ptr(u), _ptr(z), _ptr(y), _ptr(U), ep, tau, eta, zeta, lam, alpha, mu,
+                    int(n_itr), 0, _ptr(g), _ptr(c), _ptr(a), _ptr(b), _ptr(zs), 0, 0, 0, 0, 0)
+    q = StepGrads(*(_ptr(t) for t in (gx, gxt, gv, gu, gz, g_x, g_xt, g_v, g_u, g_z, g_y, g_a, g_b, g_g, g_c, t_v,
+                                      t_u)))
+    _check("ppd_step_vjp", lib().ppd_step_vjp(plan.handle, ctypes.byref(args), ctypes.byref(q)))
+    return g_x, g_xt, g_v, g_u, g_z if nz else None, g_y
+
+
+def ppd_fidelity(plan: Plan, x, y, acc, loss, add: bool, r=None):
+    """r = Phi x - y (plan order); acc (float64, 1 element) receives ||r||^2, or
+    has it added, and loss (float32, 1 element) its value."""
+    import torch
+    _need(x, torch.float32, plan.N, "x")
+    _need(y, torch.complex64, plan.M, "y")
+    _need(acc, torch.float64, 1, "acc")
+    _need(loss, torch.float32, 1, "loss")
+    if r is None:
+        r = _alloc((plan.M,), torch.complex64)
+    _need(r, torch.complex64, plan.M, "r")
+    _check("ppd_fidelity", lib().ppd_fidelity(plan.handle, _ptr(x), _ptr(y), _ptr(r), int(add), _ptr(acc), _ptr(loss)))
+    return r
+
+
+def ppd_phit_add(plan: Plan, y, x):
+    """x += Re Phi^H y (y in plan order)."""
+    import torch
+    _need(y, torch.complex64, plan.M, "y")
+    _need(x, torch.float32, plan.N, "x")
+    _check("ppd_phit_add", lib().ppd_phit_add(plan.handle, _ptr(y), _ptr(x)))
+    return x
 
 
 class PPDState:
