@@ -182,15 +182,15 @@ struct PaArgs {
 
 // Waits for the tagged partial in *slot; returns its value, or -1 after a
 // give-up (polls exceeded here, or the flag raised elsewhere).
-__device__ double pa_wait(uint64_t* slot, uint64_t tag, uint32_t* sync, int spin_limit) {
+__device__ double pa_wait(uint64_t* slot, uint64_t tag, uint32_t* flag, int spin_limit) {
   int polls = 0;
   while (true) {
     const uint64_t b = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (b != PA_EMPTY && (b & PA_SIGN) == tag) return __longlong_as_double(int64_t(b & ~PA_SIGN));
-    if ((polls & 31) == 31 && __hip_atomic_load(&sync[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
+    if ((polls & 31) == 31 && __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
       return -1.0;
     if (++polls > spin_limit) {
-      __hip_atomic_store(&sync[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       return -1.0;
     }
 #if PPD_PA_SLEEP > 0
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
       double t = 0.0;
       int bad = 0;
       for (int gg = a.gfirst[j] + tid; gg <= a.glast[j]; gg += PA_THREADS) {
-        const double v = pa_wait(&part[size_t(gg) * PA_MAXB + (j - a.wgb0[gg])], tag, a.sync, a.spin_limit);
+        const double v = pa_wait(&part[size_t(gg) * PA_MAXB + (j - a.wgb0[gg])], tag, &a.sync[2], a.spin_limit);
         if (v < 0.0) bad = 1;
         else t += v;
       }
@@ -351,9 +351,16 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
 // between two buffers, and a last k_sec_update takes the final step.
 constexpr int SEC_THREADS = 256;
 
-// Newton step of block j from its chunk partials [c0, c1): nu = max(0, nu0
-// - g / g'), g = 1 / r - 1 / eps.  All SEC_THREADS threads take part; the
-// result is returned to every thread.
+// nu = max(0, nu0 - g / g'), g = 1 / r - 1 / eps; 0 if nothing is left to move.
+__device__ __forceinline__ double newton_step(double S2, double S3, double eps, double nu0) {
+  if (!(S2 > 0.0 && S3 > 0.0)) return 0.0;
+  const double r = sqrt(S2);
+  const double g = 1.0 / r - 1.0 / eps, gp = S3 / (r * r * r);
+  return fmax(0.0, nu0 - g / gp);
+}
+
+// Newton step of block j from its chunk partials [c0, c1).  All SEC_THREADS
+// threads take part; the result is returned to every thread.
 __device__ double newton_nu(const double* __restrict__ p2, const double* __restrict__ p3, int c0, int c1,
                             double eps, double nu0, double* red2, double* red3, double* out) {
   double a = 0.0, b = 0.0;
@@ -375,13 +382,7 @@ __device__ double newton_nu(const double* __restrict__ p2, const double* __restr
       S2 += red2[k];
       S3 += red3[k];
     }
-    double nu = 0.0;
-    if (S2 > 0.0 && S3 > 0.0) {
-      const double r = sqrt(S2);
-      const double g = 1.0 / r - 1.0 / eps, gp = S3 / (r * r * r);
-      nu = fmax(0.0, nu0 - g / gp);
-    }
-    *out = nu;
+    *out = newton_step(S2, S3, eps, nu0);
   }
   __syncthreads();
   return *out;
@@ -459,6 +460,206 @@ __global__ __launch_bounds__(SEC_THREADS) void k_sec_update(const double* __rest
   const int j = blockIdx.x;
   const double nu = newton_nu(p2, p3, coff[j], coff[j + 1], eps[j], pnu ? pnu[j] : 0.0, red2, red3, &s_nu);
   if (threadIdx.x == 0) bfac[j] = make_double2(nu, 0.0);
+}
+
+// The whole solve as one launch, with (a^2, U) of every point in registers and
+// the tagged partials and bounded waits of k_alg2_persistent (two sums per
+// block and step).  A block is done when a step leaves nu where it was: a
+// relative step of 2^-50 puts r within that of eps (-g / g' >= (r / eps - 1)
+// nu), and the steps left would only repeat its rounding.  So a solve costs
+// the steps its blocks need, n_newton at most, and none costs a launch: at
+// 512 x 256, 200003 points and 12 steps one launch of 25.5 us instead of 13 of
+// 4.2 and the gaps between them; ten eager iterations 1680 (with the launches
+// of today's other kernels 1291) -> 1065 us.
+// A wait that gives up costs time, not the result: the workgroups run to the
+// end and the last one out solves all blocks alone, from memory.  So other
+// work on the device, and workgroups that are not resident at once, are no
+// error.
+struct SecArgs {
+  int steps, G, d, spin_limit;
+  int64_t M;
+  const double2* w;   // NULL: from v, ga and U
+  const float2* v; const float2* ga; const float2* y; const double* U;
+  const int32_t* voff; const int32_t* wgb0; const int32_t* gfirst; const int32_t* glast;
+  const double* eps;
+  double2* bfac;
+  uint64_t* part;   // [2][G][PA_MAXB][2] tagged partials
+  uint32_t* sync;   // [1] exits, [3] give-up flag
+};
+
+__device__ __forceinline__ double sec_a2(const SecArgs& a, int64_t i, double Ue) {
+  const double2 we = a.w ? a.w[i] : dual_arg(a.v[i], Ue, a.ga[i]);
+  const float2 ye = a.y[i];
+  const double dx = we.x - double(ye.x), dy = we.y - double(ye.y);
+  return Ue * Ue * (dx * dx + dy * dy);
+}
+
+// bfac[j].x = nu.  At device scope: after a give-up the last workgroup out
+// stores once more what another one may have stored before its exit.
+__device__ __forceinline__ void sec_store(const SecArgs& a, int j, double nu) {
+  __hip_atomic_store(&a.bfac[j].x, nu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ bool sec_done(double nu, double nu0) {
+  return nu == nu0 || fabs(nu - nu0) <= 0x1p-50 * nu;
+}
+
+template <int PER>
+__global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
+  static_assert(PA_THREADS == 256, "partials are summed over exactly 4 waves");
+  __shared__ double red[PA_THREADS / 64][PA_MAXB][2];
+  __shared__ double s_nu[PA_MAXB];
+  __shared__ int done[PA_MAXB], quit, last_out;
+  const int g = blockIdx.x, tid = threadIdx.x;
+  const int lane = tid & 63, wid = tid >> 6;
+  const int64_t i0 = int64_t(g) * PER * PA_THREADS;
+  const int64_t i1 = min(i0 + int64_t(PER) * PA_THREADS, a.M);
+  const int b0 = a.wgb0[g];
+  int nb = 1;
+  while (nb < PA_MAXB && b0 + nb < a.d && a.voff[b0 + nb] < i1) ++nb;
+  double a2[PER], U[PER];
+  int sl[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    const int64_t i = i0 + int64_t(k) * PA_THREADS + tid;
+    sl[k] = -1;
+    a2[k] = 0.0;
+    U[k] = 1.0;
+    if (i < i1) {
+      U[k] = a.U[i];
+      a2[k] = sec_a2(a, i, U[k]);
+      int b = 0;
+      while (b + 1 < nb && i >= a.voff[b0 + b + 1]) ++b;
+      sl[k] = b;
+    }
+  }
+  if (tid < PA_MAXB) {
+    s_nu[tid] = 0.0;
+    done[tid] = tid >= nb;
+  }
+  if (tid == 0) quit = 0;
+  __syncthreads();
+  for (int s = 0; s < a.steps; ++s) {
+    // the workgroup's partials per block, summed in a fixed order
+    for (int b = 0; b < nb; ++b) {
+      if (done[b]) continue;
+      const double nu = s_nu[b];
+      double t2 = 0.0, t3 = 0.0;
+#pragma unroll
+      for (int k = 0; k < PER; ++k) {
+        const double inv = 1.0 / (U[k] + nu);
+        const double s2 = sl[k] == b ? a2[k] * inv * inv : 0.0;
+        t2 += s2;
+        t3 += s2 * inv;
+      }
+      t2 = wave_sum(t2);
+      t3 = wave_sum(t3);
+      if (lane == 0) {
+        red[wid][b][0] = t2;
+        red[wid][b][1] = t3;
+      }
+    }
+    __syncthreads();
+    uint64_t* part = a.part + size_t(s & 1) * size_t(a.G) * (2 * PA_MAXB);
+    const uint64_t tag = (s & 2) ? PA_SIGN : 0ull;
+    if (wid == 0) {
+      // as in k_alg2_persistent: this wave's earlier exchanges are
+      // acknowledged before the slot of step s - 2 is overwritten
+      __builtin_amdgcn_s_waitcnt(0);
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    }
+    if (tid < 2 * nb && !done[tid >> 1]) {
+      const int b = tid >> 1, q = tid & 1;
+      const double p = ((red[0][b][q] + red[1][b][q]) + red[2][b][q]) + red[3][b][q];
+      uint64_t bits = uint64_t(__double_as_longlong(p)) & ~PA_SIGN;
+      if (bits == PA_EMPTY) bits |= 1ull;   // a NaN partial must not read as an empty slot
+      (void)__hip_atomic_exchange(&part[size_t(g) * (2 * PA_MAXB) + tid], bits | tag, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+    }
+    for (int b = 0; b < nb; ++b) {
+      if (done[b]) continue;   // uniform: written before a barrier
+      const int j = b0 + b;
+      double t2 = 0.0, t3 = 0.0;
+      int bad = 0;
+      for (int gg = a.gfirst[j] + tid; gg <= a.glast[j] && !bad; gg += PA_THREADS) {
+        uint64_t* slot = &part[size_t(gg) * (2 * PA_MAXB) + 2 * (j - a.wgb0[gg])];
+        const double v2 = pa_wait(slot, tag, &a.sync[3], a.spin_limit);
+        const double v3 = v2 < 0.0 ? -1.0 : pa_wait(slot + 1, tag, &a.sync[3], a.spin_limit);
+        if (v3 < 0.0) {
+          bad = 1;
+        } else {
+          t2 += v2;
+          t3 += v3;
+        }
+      }
+      t2 = wave_sum(t2);
+      t3 = wave_sum(t3);
+      __syncthreads();   // red[..][0] and done[b] have been read
+      if (lane == 0) {
+        red[wid][0][0] = t2;
+        red[wid][0][1] = t3;
+      }
+      if (bad) quit = 1;
+      __syncthreads();
+      if (tid == 0) {
+        const double nu = newton_step(((red[0][0][0] + red[1][0][0]) + red[2][0][0]) + red[3][0][0],
+                                      ((red[0][0][1] + red[1][0][1]) + red[2][0][1]) + red[3][0][1], a.eps[j], s_nu[b]);
+        done[b] = sec_done(nu, s_nu[b]);
+        s_nu[b] = nu;
+      }
+    }
+    __syncthreads();
+    bool left = false;
+    for (int b = 0; b < nb; ++b) left |= !done[b];
+    if (quit || !left) break;   // uniform: read after the barrier
+  }
+  // stored by the first workgroup of each block (all others hold the same)
+  if (tid < nb && a.gfirst[b0 + tid] == g && !quit) sec_store(a, b0 + tid, s_nu[tid]);
+  // what each wave stored (partials, results, the flag) is acknowledged before
+  // the exit is counted
+  __builtin_amdgcn_s_waitcnt(0);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t out = __hip_atomic_fetch_add(&a.sync[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last_out = out == uint32_t(a.G) - 1u;
+  }
+  __syncthreads();
+  if (!last_out) return;
+  // the last workgroup out empties every slot for the next launch and clears
+  // the exit count and the flag
+  for (size_t e = tid; e < 4 * size_t(a.G) * PA_MAXB; e += PA_THREADS)
+    __hip_atomic_store(&a.part[e], PA_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) {
+    __hip_atomic_store(&a.sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    quit = int(__hip_atomic_exchange(&a.sync[3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  }
+  __syncthreads();
+  if (!quit) return;
+  for (int j = 0; j < a.d; ++j) {
+    double nu = 0.0;
+    for (int s = 0; s < a.steps; ++s) {
+      double t2 = 0.0, t3 = 0.0;
+      for (int64_t i = a.voff[j] + tid; i < a.voff[j + 1]; i += PA_THREADS) {
+        const double Ue = a.U[i], inv = 1.0 / (Ue + nu), s2 = sec_a2(a, i, Ue) * inv * inv;
+        t2 += s2;
+        t3 += s2 * inv;
+      }
+      t2 = wave_sum(t2);
+      t3 = wave_sum(t3);
+      __syncthreads();
+      if (lane == 0) {
+        red[wid][0][0] = t2;
+        red[wid][0][1] = t3;
+      }
+      __syncthreads();
+      const double nu0 = nu;
+      nu = newton_step(((red[0][0][0] + red[1][0][0]) + red[2][0][0]) + red[3][0][0],
+                       ((red[0][0][1] + red[1][0][1]) + red[2][0][1]) + red[3][0][1], a.eps[j], nu0);
+      if (sec_done(nu, nu0)) break;   // the same in every thread
+    }
+    if (tid == 0) sec_store(a, j, nu);
+  }
 }
 
 // z = (U w + nu y) / (U + nu) with the block's nu (z = w when nu = 0).
@@ -627,8 +828,40 @@ int ball_step(ppd_plan* p, const BallIn& in, double2* z, const double2* fac, con
   return timer_end(p, slot);
 }
 
+using SecKernel = void (*)(SecArgs);
+static SecKernel sec_kernel(int per) {
+  return per == 2 ? k_sec_persistent<2> : per == 4 ? k_sec_persistent<4> : k_sec_persistent<PA_PER_MAX>;
+}
+
+// Workgroups of a persistent kernel that the device holds at once.
+static int resident_groups(const void* kernel) {
+  int dev = 0, cus = 0, blocks = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, kernel, PA_THREADS, 0) != hipSuccess) return 0;
+  return cus * blocks;
+}
+
+int sec_persistent_capacity(int per) { return resident_groups(reinterpret_cast<const void*>(sec_kernel(per))); }
+
+// Polls of one wait before the last workgroup out solves alone: a poll sleeps
+// 64 clocks, so at least 7 ms, where a step takes 4 us.
+constexpr int SEC_SPIN = 1 << 18;
+
+static int secular_persistent(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
+                              const double* U, int n_newton, int spin_limit) {
+  const SecArgs a{n_newton, p->pa_groups, p->d, spin_limit > 0 ? spin_limit : SEC_SPIN, p->M, w, v, ga, y, U,
+                  p->voff_d, p->pa_wgb0, p->pa_gfirst, p->pa_glast, p->eps_d, p->bfac, p->pa_part, p->pa_sync};
+  int slot;
+  PPD_TRY(timer_begin(p, KK_SUBITER, &slot));
+  hipLaunchKernelGGL(sec_kernel(p->pa_per), dim3(a.G), dim3(PA_THREADS), 0, p->stream, a);
+  PPD_HIP(hipGetLastError());
+  return timer_end(p, slot);
+}
+
 int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
-                  const double* U, int n_newton) {
+                  const double* U, int n_newton, bool persistent, int spin_limit) {
+  if (persistent && p->sec_ok) return secular_persistent(p, w, v, ga, y, U, n_newton, spin_limit);
   // pass s writes its partials to buffer s & 1 and (s >= 1) its nu to
   // nu buffer s & 1
   const int nc = p->n_sec_chunks;
@@ -666,15 +899,7 @@ static PaKernel pa_kernel(int per) {
   return per == 2 ? k_alg2_persistent<2> : per == 4 ? k_alg2_persistent<4> : k_alg2_persistent<PA_PER_MAX>;
 }
 
-int alg2_persistent_capacity(int per) {
-  int dev = 0, cus = 0, blocks = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void*>(pa_kernel(per)), PA_THREADS,
-                                                   0) != hipSuccess)
-    return 0;
-  return cus * blocks;
-}
+int alg2_persistent_capacity(int per) { return resident_groups(reinterpret_cast<const void*>(pa_kernel(per))); }
 
 int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit) {
   if (!p->pa_ok) return fail(PPD_EUNSUPPORTED, "persistent Algorithm 2 is not available for this plan");
@@ -767,7 +992,7 @@ extern "C" int ppd_prox_metric(ppd_plan* p, const double* w, const float* y, con
   PPD_TRY(upload_eps(p, eps));
   const double2* w2 = reinterpret_cast<const double2*>(w);
   const float2* y2 = reinterpret_cast<const float2*>(y);
-  PPD_TRY(secular_solve(p, w2, nullptr, nullptr, y2, U, n_newton));
+  PPD_TRY(secular_solve(p, w2, nullptr, nullptr, y2, U, n_newton, true, 0));
   int slot;
   PPD_TRY(timer_begin(p, KK_MISC, &slot));
   hipLaunchKernelGGL(k_prox_apply, dim3(int(std::min<int64_t>((p->M + 255) / 256, 4096))), dim3(256), 0, p->stream,

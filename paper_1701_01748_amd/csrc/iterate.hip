@@ -183,7 +183,7 @@ struct IterCtx {
   int prox, n_newton;
   const uint8_t* basis_active;
   bool sara_forked;   // SARA on the second stream (eager), else the data path (graph)
-  bool persistent;    // Algorithm 2 middle steps in one persistent launch
+  bool persistent;    // Algorithm 2 middle steps, or the exact prox's, in one persistent launch
   int spin_limit;     // polls per wait of the persistent launch (0: default)
   // statistics reduced right after the iteration (captured graphs): into
   // stats_out, at the plan's history cursor if stats_cursor
@@ -199,7 +199,8 @@ int data_path(ppd_plan* p, const IterCtx& c) {
   PPD_TRY(fft_cols_forward(p, p->half_f));                  // a = F Z x~ (rows done)
   if (c.form == PPD_FORM_FUSED && c.prox == PPD_PROX_EXACT) {
     PPD_TRY(degrid_dual(p, c.dual, nullptr));               // dual argument w (no Algorithm 2 partials)
-    PPD_TRY(secular_solve(p, nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.n_newton));  // prox^U_h(w)
+    PPD_TRY(secular_solve(p, nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.n_newton, c.persistent,
+                          c.spin_limit));                       // prox^U_h(w)
     PPD_TRY(grid_dual_exact(p, c.dual));                    // dual finish, relaxation, gridding
   } else if (c.form == PPD_FORM_FUSED) {
     PPD_TRY(degrid_dual(p, c.dual, p->part));               // dual argument, first Alg. 2 step
@@ -406,8 +407,8 @@ extern "C" int ppd_iterate(ppd_plan* p, ppd_state* st, const ppd_params* prm, in
   if (prm->persistent != PPD_PERSIST_AUTO && prm->persistent != PPD_PERSIST_OFF)
     return fail(PPD_EINVAL, "ppd_iterate: unknown persistent mode");
   if (prm->spin_limit < 0) return fail(PPD_EINVAL, "ppd_iterate: spin_limit must be >= 0");
-  c.persistent = prm->persistent == PPD_PERSIST_AUTO && p->pa_ok && prm->form == PPD_FORM_FUSED &&
-                 prm->prox == PPD_PROX_FB && prm->n_itr > 1;
+  c.persistent = prm->persistent == PPD_PERSIST_AUTO && prm->form == PPD_FORM_FUSED &&
+                 (prm->prox == PPD_PROX_EXACT ? p->sec_ok : p->pa_ok && prm->n_itr > 1);
   c.spin_limit = prm->spin_limit;
 
   if (n_iter > 0) {

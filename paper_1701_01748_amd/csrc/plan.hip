@@ -595,7 +595,7 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   A(dalloc(p, &p->pa_wgb0, p->pa_groups));
   A(dalloc(p, &p->pa_gfirst, p->d));
   A(dalloc(p, &p->pa_glast, p->d));
-  A(dalloc(p, &p->pa_part, 2 * size_t(p->pa_groups) * PA_MAXB));
+  A(dalloc(p, &p->pa_part, 4 * size_t(p->pa_groups) * PA_MAXB));
   A(dalloc(p, &p->pa_sync, PA_SYNC_WORDS));
   A(dalloc(p, &p->part, 2 * size_t(p->n_segs)));
   A(dalloc(p, &p->rpart, p->n_segs));
@@ -660,12 +660,13 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   {
     const std::vector<uint32_t> zeros(PA_SYNC_WORDS, 0u);
     up(p->pa_sync, zeros.data(), sizeof(uint32_t) * zeros.size());
-    const std::vector<uint64_t> empty(2 * size_t(p->pa_groups) * PA_MAXB, PA_EMPTY);
+    const std::vector<uint64_t> empty(4 * size_t(p->pa_groups) * PA_MAXB, PA_EMPTY);
     up(p->pa_part, empty.data(), sizeof(uint64_t) * empty.size());
   }
   // the persistent launch needs all its workgroups on the device at once
   if (st == PPD_OK) {
     p->pa_ok = pa_fits && p->pa_groups <= alg2_persistent_capacity(p->pa_per);
+    p->sec_ok = pa_fits && p->pa_groups <= sec_persistent_capacity(p->pa_per);
   }
   // mapped pinned host memory the final statistics reduction writes into
   if (st == PPD_OK && (hipHostMalloc(reinterpret_cast<void**>(&p->host_stats), sizeof(double) * (9 + p->d),

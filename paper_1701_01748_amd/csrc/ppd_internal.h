@@ -55,7 +55,7 @@ constexpr int PA_PER_MAX = 12;
 inline int pa_points(int64_t M) { return M <= (1 << 17) ? 2 : M <= (1 << 19) ? 4 : PA_PER_MAX; }
 constexpr int PA_CHUNK_MAX = PA_THREADS * PA_PER_MAX;
 constexpr int PA_MAXB = 4;        // data blocks one workgroup's points may span
-constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag
+constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag, [3] the Newton steps' flag
 // tagged partial slots of the persistent launch (see k_alg2_persistent)
 constexpr uint64_t PA_SIGN = 0x8000000000000000ull;
 constexpr uint64_t PA_EMPTY = 0x7ff8000000000000ull;   // quiet NaN: no partial yet
@@ -228,12 +228,13 @@ struct ppd_plan {
   int pa_per = 0;                          // points per thread
   int pa_groups = 0;                       // workgroups of the persistent launch
   bool pa_ok = false;                      // every workgroup co-resident and within PA_MAXB blocks
+  bool sec_ok = false;                     // the same for the exact prox's persistent Newton steps
   int32_t* voff_d = nullptr;               // [d+1] block offsets (plan order)
   int32_t* pa_wgb0 = nullptr;              // [pa_groups] first block of each workgroup
   int32_t* pa_gfirst = nullptr;            // [d] first workgroup of each block
   int32_t* pa_glast = nullptr;             // [d] last workgroup of each block
-  uint64_t* pa_part = nullptr;             // [2][pa_groups][PA_MAXB] tagged per-workgroup block partials
-  uint32_t* pa_sync = nullptr;             // [PA_SYNC_WORDS] exit count, give-up flag
+  uint64_t* pa_part = nullptr;             // [2][pa_groups][PA_MAXB][2] tagged per-workgroup block partials
+  uint32_t* pa_sync = nullptr;             // [PA_SYNC_WORDS] exit count, give-up flags
   double* part = nullptr;                  // [2][n_segs] block-norm partials
   double* rpart = nullptr;                 // [n_segs] residual partials
   double* eps_d = nullptr;                 // [d]
@@ -339,10 +340,12 @@ int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit);
 // Maximum co-resident workgroups of the persistent launch at `per` points per
 // thread on the current device (0 if it cannot be determined).
 int alg2_persistent_capacity(int per);
+int sec_persistent_capacity(int per);
 // n_newton Newton steps of the exact prox per block; nu_j in bfac[j].x.
 // The prox argument is w if non-NULL, else U^-1 v + ga (see dual_arg).
+// persistent: as one launch where the plan's points fit the device.
 int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
-                  const double* U, int n_newton);
+                  const double* U, int n_newton, bool persistent, int spin_limit);
 int grid_dual_exact(ppd_plan* p, const DualArgs& a);   // dual finish with the exact prox + grid
 int permute(ppd_plan* p, int direction, const void* in, void* out, int elem_bytes);
 
