@@ -4,7 +4,7 @@
 // preconditioner (inverse local sampling density, Sec. 4.3).
 #include <cmath>
 
-#include "ppd_internal.h"
+#include "sara_device.h"
 
 namespace ppd {
 namespace {
@@ -100,20 +100,17 @@ __global__ __launch_bounds__(256) void k_ball_factors(const int32_t* __restrict_
   if (threadIdx.x == 0) bfac[j] = ball_factor(t, eps[j]);
 }
 
-// Projection factor of every data block for P_B (Sec. 3.3, eq. proj-L2):
-// workgroup j sums the segment partials of ||q - y_j||^2 in a fixed order
+// Projection factor of a data block for P_B (Sec. 3.3, eq. proj-L2):
+// a workgroup sums the segment partials of ||q - y_j||^2 in a fixed order
 // and stores (eps_j / r, 0) if r > eps_j, else (1, 1).
 constexpr int BF_PER = 8;
 // One pass of 1024 threads covers up to 8192 segments (the largest block of
 // the 512^2, 1.3M workload has ~3k); 256 threads took two passes there.
 constexpr int BF_THREADS = 1024;
-__global__ __launch_bounds__(BF_THREADS) void k_block_factors(const double* __restrict__ part,
-                                                              const int32_t* __restrict__ bids,
-                                                              const int32_t* __restrict__ boff,
-                                                              const double* __restrict__ eps,
-                                                              double2* __restrict__ bfac) {
+__device__ __forceinline__ void block_factor(int j, const double* __restrict__ part, const int32_t* __restrict__ bids,
+                                             const int32_t* __restrict__ boff, const double* __restrict__ eps,
+                                             double2* __restrict__ bfac) {
   __shared__ double red[BF_THREADS / 64];
-  const int j = blockIdx.x;
   const int c0 = boff[j], c1 = boff[j + 1];
   double s = 0.0;
   for (int base = c0; base < c1; base += BF_THREADS * BF_PER) {
@@ -137,6 +134,25 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factors(const double* __re
     for (int q = 0; q < BF_THREADS / 64; ++q) t += red[q];
     bfac[j] = ball_factor(t, eps[j]);
   }
+}
+
+__global__ __launch_bounds__(BF_THREADS) void k_block_factors(const double* __restrict__ part,
+                                                              const int32_t* __restrict__ bids,
+                                                              const int32_t* __restrict__ boff,
+                                                              const double* __restrict__ eps,
+                                                              double2* __restrict__ bfac) {
+  block_factor(blockIdx.x, part, bids, boff, eps, bfac);
+}
+
+// The same after an analysis level of SARA in the first workgroups.
+__global__ __launch_bounds__(BF_THREADS) void k_block_factors_dwt(const double* __restrict__ part,
+                                                                  const int32_t* __restrict__ bids,
+                                                                  const int32_t* __restrict__ boff,
+                                                                  const double* __restrict__ eps,
+                                                                  double2* __restrict__ bfac, SaraJob job) {
+  const int b = int(blockIdx.x) - job.blocks();
+  if (b < 0) sara_dwt_part(job, blockIdx.x);
+  else block_factor(b, part, bids, boff, eps, bfac);
 }
 
 // ---- persistent middle steps of Algorithm 2 ---------------------------------
@@ -931,11 +947,15 @@ int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit) {
   return timer_end(p, slot);
 }
 
-int block_factors(ppd_plan* p, const double* part) {
+int block_factors(ppd_plan* p, const double* part, const SaraJob* with) {
   int slot;
   PPD_TRY(timer_begin(p, KK_MISC, &slot));
-  hipLaunchKernelGGL(k_block_factors, dim3(p->d), dim3(BF_THREADS), 0, p->stream, part, p->bseg_ids, p->bseg_off_d,
-                     p->eps_d, p->bfac);
+  if (with)
+    hipLaunchKernelGGL(k_block_factors_dwt, dim3(p->d + with->blocks()), dim3(BF_THREADS), 0, p->stream, part,
+                       p->bseg_ids, p->bseg_off_d, p->eps_d, p->bfac, *with);
+  else
+    hipLaunchKernelGGL(k_block_factors, dim3(p->d), dim3(BF_THREADS), 0, p->stream, part, p->bseg_ids, p->bseg_off_d,
+                       p->eps_d, p->bfac);
   PPD_HIP(hipGetLastError());
   return timer_end(p, slot);
 }

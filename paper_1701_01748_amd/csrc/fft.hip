@@ -34,13 +34,15 @@
 // forward): 64^2 columns 4.7 -> 3.6 and 5.4 -> 3.0, rows 6.9 -> 4.2; 512^2
 // columns 9.0 -> 4.8 and 8.7 -> 4.8, rows 9.8 -> 6.8; 2048^2 columns
 // 343 -> 151 and 160 -> 103, rows 92 -> 40.
-#include "ppd_internal.h"
+#include "sara_device.h"
 
 namespace ppd {
 namespace {
 
+// Which product is fused is written out, so that a transform rounds the same
+// in every kernel it is compiled into.
 __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+  return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.y, b.x, a.x * b.y));
 }
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
@@ -317,13 +319,13 @@ __global__ __launch_bounds__(RowCfg<L>::THREADS) void k_fft_rows_fwd(const float
 // Forward columns: stored columns 4 g .. -> grid, with the mirror images that
 // the padding columns hold.
 template <int L>
-__global__ __launch_bounds__(ColCfg<L>::THREADS) void k_fft_cols_fwd(const float2* __restrict__ half,
-                                                                     const float2* __restrict__ tw, int Hx,
-                                                                     int ngroups, float2* __restrict__ grid) {
+__device__ __forceinline__ void cols_fwd_block(int block, int nblocks, const float2* __restrict__ half,
+                                               const float2* __restrict__ tw, int Hx, int ngroups,
+                                               float2* __restrict__ grid) {
   using F = typename ColCfg<L>::F;
   constexpr int E = F::E, P = F::P, C = ColCfg<L>::C, NY = L / 2;
   __shared__ float2 sm[C * F::LDS];
-  const int grp = xcd_remap(blockIdx.x, gridDim.x);
+  const int grp = xcd_remap(block, nblocks);
   if (grp >= ngroups) return;
   const int cc = threadIdx.x % C, t = threadIdx.x / C;
   const int c = grp * C + cc;
@@ -367,6 +369,23 @@ __global__ __launch_bounds__(ColCfg<L>::THREADS) void k_fft_cols_fwd(const float
     for (int m = 0; m < E; ++m)
       grid[grid_index(GRID_PAD + 2 * Hx - c, (L - (t + P * m)) & (L - 1), L)] = conjf2(z[m]);
   }
+}
+
+template <int L>
+__global__ __launch_bounds__(ColCfg<L>::THREADS) void k_fft_cols_fwd(const float2* __restrict__ half,
+                                                                     const float2* __restrict__ tw, int Hx,
+                                                                     int ngroups, float2* __restrict__ grid) {
+  cols_fwd_block<L>(blockIdx.x, gridDim.x, half, tw, Hx, ngroups, grid);
+}
+
+// The same after an analysis level of SARA in the first workgroups.
+template <int L>
+__global__ __launch_bounds__(std::max(ColCfg<L>::THREADS, DWT_THREADS)) void k_fft_cols_fwd_dwt(
+    int nblocks, const float2* __restrict__ half, const float2* __restrict__ tw, int Hx, int ngroups,
+    float2* __restrict__ grid, SaraJob j) {
+  const int b = int(blockIdx.x) - j.blocks();
+  if (b < 0) sara_dwt_part(j, blockIdx.x);
+  else if (threadIdx.x < ColCfg<L>::THREADS) cols_fwd_block<L>(b, nblocks, half, tw, Hx, ngroups, grid);
 }
 
 // Inverse columns of the accumulated grid, keeping the ny rows that map to
@@ -604,14 +623,24 @@ int fft_rows_forward(ppd_plan* p, const float* x, float2* dst) {
   return timer_end(p, slot);
 }
 
-int fft_cols_forward(ppd_plan* p, const float2* src) {
+int fft_cols_forward(ppd_plan* p, const float2* src, const SaraJob* with) {
   int slot;
   PPD_TRY(timer_begin(p, KK_FFT_COLS_FWD, &slot));
   PPD_TRY(with_length(p->Ky, [&](auto l) {
     constexpr int L = decltype(l)::value;
     const ColLaunch<L> c(p);
-    hipLaunchKernelGGL(k_fft_cols_fwd<L>, dim3(c.blocks), dim3(ColCfg<L>::THREADS), 0, p->stream, src, p->twy,
-                       p->Kx / 2, c.groups, p->grid_f);
+    if (with) {
+      if constexpr (L <= PAIR_MAX_KY) {
+        hipLaunchKernelGGL(k_fft_cols_fwd_dwt<L>, dim3(c.blocks + with->blocks()),
+                           dim3(std::max(ColCfg<L>::THREADS, DWT_THREADS)), 0, p->stream, c.blocks, src, p->twy,
+                           p->Kx / 2, c.groups, p->grid_f, *with);
+      } else {
+        return fail(PPD_EUNSUPPORTED, "fft: no launch with an analysis level at this length");
+      }
+    } else {
+      hipLaunchKernelGGL(k_fft_cols_fwd<L>, dim3(c.blocks), dim3(ColCfg<L>::THREADS), 0, p->stream, src, p->twy,
+                         p->Kx / 2, c.groups, p->grid_f);
+    }
     PPD_HIP(hipGetLastError());
     return PPD_OK;
   }));

@@ -182,6 +182,7 @@ struct IterCtx {
   int form;
   int prox, n_newton;
   const uint8_t* basis_active;
+  bool paired;        // SARA's launches ride in the data path's
   bool sara_forked;   // SARA on the second stream (eager), else the data path (graph)
   bool persistent;    // Algorithm 2 middle steps, or the exact prox's, in one persistent launch
   int spin_limit;     // polls per wait of the persistent launch (0: default)
@@ -191,6 +192,21 @@ struct IterCtx {
   bool stats_cursor = false;
   int has_truth = 0, use_res_sq = 0;
 };
+
+// The n_itr - 1 middle Algorithm 2 steps, from the first step's factors to the
+// last one's.
+int middle_steps(ppd_plan* p, const IterCtx& c) {
+  // one launch, state in registers.  It may run beside the SARA branch:
+  // workgroups of it that the SARA launches keep from being resident at first
+  // get room as those finish (they never wait on this launch), while the
+  // resident ones wait for their partials.
+  if (c.persistent) return alg2_persistent(p, c.dual, c.spin_limit);
+  const BallIn in{nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.dual.mu, c.dual.active};
+  double* part[2] = {p->sec_part, p->sec_part + p->n_sec_chunks};
+  PPD_TRY(ball_step(p, in, c.dual.z, p->bfac, nullptr, part[0]));
+  for (int s = 2; s < c.dual.n_itr; ++s) PPD_TRY(ball_step(p, in, c.dual.z, nullptr, part[s & 1], part[(s - 1) & 1]));
+  return ball_factors(p, part[c.dual.n_itr & 1]);
+}
 
 // The data-fidelity path of one iteration (F Z x~, the data-dual update
 // of every block and the gridding, then the inverse column FFT of the
@@ -206,21 +222,7 @@ int data_path(ppd_plan* p, const IterCtx& c) {
     PPD_TRY(degrid_dual(p, c.dual, p->part));               // dual argument, first Alg. 2 step
     if (c.dual.n_itr > 1) {
       PPD_TRY(block_factors(p, p->part));
-      if (c.persistent) {
-        // the middle steps in one launch, state in registers; it leaves the
-        // last step's factors for the gridding.  It runs beside the SARA
-        // branch: workgroups of it that the SARA launches keep from being
-        // resident at first get room as those finish (they never wait on
-        // this launch), while the resident ones wait for their partials.
-        PPD_TRY(alg2_persistent(p, c.dual, c.spin_limit));
-      } else {
-        const BallIn in{nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.dual.mu, c.dual.active};
-        double* part[2] = {p->sec_part, p->sec_part + p->n_sec_chunks};
-        PPD_TRY(ball_step(p, in, c.dual.z, p->bfac, nullptr, part[0]));
-        for (int s = 2; s < c.dual.n_itr; ++s)
-          PPD_TRY(ball_step(p, in, c.dual.z, nullptr, part[s & 1], part[(s - 1) & 1]));
-        PPD_TRY(ball_factors(p, part[c.dual.n_itr & 1]));
-      }
+      PPD_TRY(middle_steps(p, c));
       PPD_TRY(grid_dual_factored(p, c.dual));               // last projection, dual finish, gridding
     } else {
       PPD_TRY(grid_dual(p, c.dual, p->part));               // projection, dual finish, gridding
@@ -239,6 +241,28 @@ int sara_path(ppd_plan* p, const IterCtx& c) {
   return sara_synthesis(p, c.u, p->ut, c.W);                // Psi u, summed over the bases
 }
 
+// Whether an iteration is one chain of launches, each of the data path's with
+// one of SARA's in its grid: for problems so small that a launch of either
+// leaves the chip mostly empty (PAIR_ITEMS).
+bool can_pair(const ppd_plan* p, const IterCtx& c, bool graph) {
+  const int most = graph && c.dual.n_itr > 1 ? PAIR_ITEMS_MIDDLE : PAIR_ITEMS;
+  static_assert(PAIR_ITEMS <= SHARE_ITEMS, "the paired launches share items");
+  return c.form == PPD_FORM_FUSED && c.prox == PPD_PROX_FB && p->T == 8 && p->n_items <= most &&
+         p->Ky <= PAIR_MAX_KY && sara_pairs(p) && !p->timing;
+}
+
+int paired_iteration(ppd_plan* p, const IterCtx& c) {
+  SaraJob j[5];
+  sara_jobs(p, c.primal.xt, c.u, c.alpha, c.lambda, c.W, c.basis_active, p->ut, j);
+  PPD_TRY(fft_cols_forward(p, p->half_f, &j[0]));
+  PPD_TRY(degrid_dual(p, c.dual, p->part, &j[1]));
+  PPD_TRY(block_factors(p, p->part, &j[2]));
+  if (c.dual.n_itr > 1) PPD_TRY(middle_steps(p, c));
+  PPD_TRY(grid_dual_factored(p, c.dual, &j[3], &j[4]));
+  PPD_TRY(fft_cols_inverse(p));
+  return fft_rows_inverse_primal(p, c.primal, p->half_f);
+}
+
 // One iteration of Algorithm 3 on the plan's stream.  SARA needs only x~
 // and u, so it runs concurrently with the data-fidelity path, one of the two
 // forked to the plan's second stream; the primal update waits
@@ -248,6 +272,7 @@ int sara_path(ppd_plan* p, const IterCtx& c) {
 // branch's join, and with it the primal update, on the other hardware queue
 // (measured 142.5 against 132.7 us per iteration at 512^2).
 int one_iteration(ppd_plan* p, const IterCtx& c) {
+  if (c.paired) return paired_iteration(p, c);
   PPD_HIP(hipEventRecord(p->ev_fork, p->stream));
   PPD_HIP(hipStreamWaitEvent(p->aux, p->ev_fork, 0));
   if (c.sara_forked) {
@@ -410,6 +435,7 @@ extern "C" int ppd_iterate(ppd_plan* p, ppd_state* st, const ppd_params* prm, in
   c.persistent = prm->persistent == PPD_PERSIST_AUTO && prm->form == PPD_FORM_FUSED &&
                  (prm->prox == PPD_PROX_EXACT ? p->sec_ok : p->pa_ok && prm->n_itr > 1);
   c.spin_limit = prm->spin_limit;
+  c.paired = can_pair(p, c, prm->use_graph != 0);
 
   if (n_iter > 0) {
     // the first iteration's forward row pass; each iteration then leaves

@@ -25,7 +25,7 @@
 // Items are launched in spatial order through an XCD-aware remap.
 #include <type_traits>
 
-#include "ppd_internal.h"
+#include "sara_device.h"
 
 namespace ppd {
 namespace {
@@ -143,20 +143,20 @@ __device__ __forceinline__ float2 gather8(const float2* reg2, const Taps& t) {
 // (out = Theta G a - y, with the partials of its squared norm).
 enum { DEGRID_PLAIN = 0, DEGRID_DUAL = 1, DEGRID_RES = 2 };
 template <int T, int MODE, int NW>
-__global__ __launch_bounds__(64 * NW) void k_degrid(
-    const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
+__device__ __forceinline__ void degrid_block(
+    int block, const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
     float2* __restrict__ out, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
     const double* __restrict__ U, const float2* __restrict__ v, const double2* __restrict__ z,
-    float2* __restrict__ gout, double mu, double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
+    float2* __restrict__ gout, double mu, double* __restrict__ part, double* __restrict__ rpart, const XcdSplit& xs) {
   constexpr int R = T + 7;
   constexpr bool DUAL = MODE == DEGRID_DUAL, RES = MODE == DEGRID_RES;
   constexpr bool B128 = T == 8;
   __shared__ __align__(16) float2 reg[B128 ? 2 * G8_COPY : R * R];
   __shared__ ItemTab tab;
   __shared__ double s_q[NW][DUAL ? MAX_ITEM_SEGS : 1], s_r[NW][DUAL || RES ? MAX_ITEM_SEGS : 1];
-  const int ii = xcd_item(blockIdx.x, xs);
+  const int ii = xcd_item(block, xs);
   if (ii < 0 || ii >= n_items) return;
   const Item it = items[ii];
   const int r0 = it.ty * T, c0 = it.tx * T;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
   KbCoef kbw;
   load_kb(kbc, kbw);
   if (DUAL || RES)
-    for (int i = threadIdx.x; i < NW * MAX_ITEM_SEGS; i += blockDim.x) {
+    for (int i = threadIdx.x; i < NW * MAX_ITEM_SEGS; i += 64 * NW) {
       if (DUAL) (&s_q[0][0])[i] = 0.0;
       (&s_r[0][0])[i] = 0.0;
     }
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
   }
   if (DUAL || RES) {
     __syncthreads();
-    for (int k = threadIdx.x; k < nseg; k += blockDim.x) {
+    for (int k = threadIdx.x; k < nseg; k += 64 * NW) {
       double q = 0.0, r = 0.0;
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
@@ -320,6 +320,34 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
       if (rpart) rpart[it.seg0 + k] = r;
     }
   }
+}
+
+template <int T, int MODE, int NW>
+__global__ __launch_bounds__(64 * NW) void k_degrid(
+    const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
+    const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
+    const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
+    float2* __restrict__ out, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
+    const double* __restrict__ U, const float2* __restrict__ v, const double2* __restrict__ z,
+    float2* __restrict__ gout, double mu, double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs) {
+  degrid_block<T, MODE, NW>(blockIdx.x, grid, PW, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc, out, uperm, y, U, v, z, gout, mu, part, rpart, xs);
+}
+
+// The shared 8 x 8 items in the dual mode, after an analysis level of SARA in
+// the first workgroups.
+__global__ __launch_bounds__(DWT_THREADS) void k_degrid_dwt(
+    const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
+    const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
+    const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc, const float2* __restrict__ y,
+    const double* __restrict__ U, const float2* __restrict__ v, const double2* __restrict__ z,
+    float2* __restrict__ gout, double mu, double* __restrict__ part, double* __restrict__ rpart, XcdSplit xs,
+    SaraJob j) {
+  const int b = int(blockIdx.x) - j.blocks();
+  if (b < 0)
+    sara_dwt_part(j, blockIdx.x);
+  else if (threadIdx.x < 128)
+    degrid_block<8, DEGRID_DUAL, 2>(b, grid, PW, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc,
+                                    nullptr, nullptr, y, U, v, z, gout, mu, part, rpart, xs);
 }
 
 // Operands of one gridding batch (one visibility per lane), loaded a batch
@@ -585,21 +613,21 @@ __device__ __forceinline__ void store_region(f32x4 sr, f32x4 si, float2* __restr
 }
 
 template <bool DUAL, int NW>
-__global__ __launch_bounds__(64 * NW) void k_grid_mfma(
-    float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
+__device__ __forceinline__ void grid_mfma_block(
+    int block, float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
     const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
     const float2* __restrict__ vin, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
     const double* __restrict__ U,
     float2* __restrict__ v, double2* __restrict__ z, const float2* __restrict__ ga, double mu,
     double lambda, const double2* __restrict__ bfac, int exact, const uint8_t* __restrict__ active,
-    XcdSplit xs) {
+    const XcdSplit& xs) {
   constexpr int T = GM_T, R = T + 7;
   static_assert(R <= 16, "the region must fit one 16 x 16 product tile");
   __shared__ float sAw[NW][32 * GM_AS];
   __shared__ __align__(16) float2 sBw[NW][32 * GM_BS];
   __shared__ ItemTab tab;
-  const int ii = xcd_item(blockIdx.x, xs);
+  const int ii = xcd_item(block, xs);
   if (ii < 0 || ii >= n_items) return;
   const Item it = items[ii];
   const int wid = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = threadIdx.x & 63;
@@ -730,6 +758,35 @@ __global__ __launch_bounds__(64 * NW) void k_grid_mfma(
   store_region(sr, si, dst, gq, gc);
 }
 
+template <bool DUAL, int NW>
+__global__ __launch_bounds__(64 * NW) void k_grid_mfma(
+    float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items,
+    const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
+    const float* __restrict__ theta, double su, double sv, const float* __restrict__ kbc,
+    const float2* __restrict__ vin, const int32_t* __restrict__ uperm, const float2* __restrict__ y,
+    const double* __restrict__ U,
+    float2* __restrict__ v, double2* __restrict__ z, const float2* __restrict__ ga, double mu,
+    double lambda, const double2* __restrict__ bfac, int exact, const uint8_t* __restrict__ active,
+    XcdSplit xs) {
+  grid_mfma_block<DUAL, NW>(blockIdx.x, scratch, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc, vin, uperm, y, U, v, z, ga, mu, lambda, bfac, exact, active, xs);
+}
+
+// The shared items in the dual mode, after SARA's two coarsest synthesis
+// levels in the first workgroups.
+__global__ __launch_bounds__(256) void k_grid_idwt2(
+    float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items, const Seg* __restrict__ segs,
+    const float* __restrict__ wu, const float* __restrict__ wv, const float* __restrict__ theta, double su, double sv,
+    const float* __restrict__ kbc, const float2* __restrict__ y, const double* __restrict__ U, float2* __restrict__ v,
+    double2* __restrict__ z, const float2* __restrict__ ga, double mu, double lambda, const double2* __restrict__ bfac,
+    const uint8_t* __restrict__ active, XcdSplit xs, SaraJob j) {
+  const int b = int(blockIdx.x) - j.blocks();
+  if (b < 0)
+    sara_idwt2_part(j, blockIdx.x);
+  else if (threadIdx.x < 128)
+    grid_mfma_block<true, 2>(b, scratch, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc, nullptr,
+                             nullptr, y, U, v, z, ga, mu, lambda, bfac, 0, active, xs);
+}
+
 // One thread per grid cell (FOLD_CELLS cells per workgroup, T*T/FOLD_CELLS
 // workgroups per tile); the item loops are unrolled so their independent
 // loads overlap.
@@ -803,12 +860,12 @@ __device__ __forceinline__ void fold_items4(const float2* __restrict__ scratch, 
   }
 }
 
-__global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratch, const int32_t* __restrict__ tio,
-                                                const int4* __restrict__ wgs, int tiles_x, int tiles_y, int Ky,
-                                                float2* __restrict__ grid) {
+__device__ __forceinline__ void fold8_block(int block, int nblocks, const float2* __restrict__ scratch,
+                                            const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
+                                            int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid) {
   constexpr int T = 8, R = T + 7;
   __shared__ float2 part[4][64];
-  const int4 e = wgs[xcd_remap(blockIdx.x, gridDim.x)];
+  const int4 e = wgs[xcd_remap(block, nblocks)];
   const int w = threadIdx.x >> 6, c = threadIdx.x & 63;
   const int a = c / T, b = c - a * T;
   const bool heavy = e.y == -2;   // uniform over the workgroup
@@ -841,6 +898,22 @@ __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratc
     grid[grid_index(tx * T + b, ty * T + a, Ky)] =
         make_float2(((p0.x + p1.x) + p2.x) + p3.x, ((p0.y + p1.y) + p2.y) + p3.y);
   }
+}
+
+__global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratch, const int32_t* __restrict__ tio,
+                                                const int4* __restrict__ wgs, int tiles_x, int tiles_y, int Ky,
+                                                float2* __restrict__ grid) {
+  fold8_block(blockIdx.x, gridDim.x, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
+}
+
+// The same after SARA's last synthesis level in the first workgroups.
+__global__ __launch_bounds__(256) void k_fold8_final(int nblocks, const float2* __restrict__ scratch,
+                                                     const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
+                                                     int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid,
+                                                     SaraJob j) {
+  const int b = int(blockIdx.x) - j.blocks();
+  if (b < 0) sara_final_part(j, blockIdx.x);
+  else fold8_block(b, nblocks, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
 }
 
 template <typename E>
@@ -964,7 +1037,14 @@ int dispatch_grid(ppd_plan* p, bool dual, const float2* vin, const int32_t* uper
 int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm) {
   return dispatch_degrid(p, DEGRID_PLAIN, out, uperm, nullptr, nullptr, nullptr);
 }
-int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out) {
+int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out, const SaraJob* with) {
+  if (with) {
+    hipLaunchKernelGGL(k_degrid_dwt, dim3(p->split1.launch + with->blocks()), dim3(DWT_THREADS), 0, p->stream,
+                       p->grid_f, p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
+                       p->sv_scale, p->kbc, a.y, a.U, a.v, a.z, p->gabuf, a.mu, part_out, a.rpart, p->split1, *with);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }
   return dispatch_degrid(p, DEGRID_DUAL, nullptr, nullptr, nullptr, &a, part_out);
 }
 int degrid_residual(ppd_plan* p, const float2* y, float2* out) {
@@ -982,7 +1062,14 @@ int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in) {
   return fold_grid(p);
 }
 
-int grid_dual_factored(ppd_plan* p, const DualArgs& a) {
+int grid_dual_factored(ppd_plan* p, const DualArgs& a, const SaraJob* with, const SaraJob* with_fold) {
+  if (with) {
+    hipLaunchKernelGGL(k_grid_idwt2, dim3(p->split1.launch + with->blocks()), dim3(256), 0, p->stream, p->gscratch,
+                       p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
+                       a.y, a.U, a.v, a.z, p->gabuf, a.mu, a.lambda, p->bfac, a.active, p->split1, *with);
+    PPD_HIP(hipGetLastError());
+    return fold_grid(p, with_fold);
+  }
   PPD_TRY(dispatch_grid(p, true, nullptr, nullptr, &a, 0));
   return fold_grid(p);
 }
@@ -992,7 +1079,14 @@ int grid_dual_exact(ppd_plan* p, const DualArgs& a) {
   return fold_grid(p);
 }
 
-int fold_grid(ppd_plan* p) {
+int fold_grid(ppd_plan* p, const SaraJob* with) {
+  if (with) {
+    hipLaunchKernelGGL(k_fold8_final, dim3(p->n_fold_wg + with->blocks()), dim3(256), 0, p->stream, p->n_fold_wg,
+                       p->gscratch, p->tile_item_off, reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x,
+                       p->tiles_y, p->Ky, p->grid_a, *with);
+    PPD_HIP(hipGetLastError());
+    return PPD_OK;
+  }
   int slot;
   PPD_TRY(timer_begin(p, KK_FOLD, &slot));
   int st;

@@ -69,6 +69,19 @@ constexpr int FOLD_HEAVY = PPD_FOLD_HEAVY;   // item regions above which a tile'
 // points, 8.6 -> 7.4 at 256^2, 65536; 15.6 -> 16.6 at 512^2, 250k, where the
 // waves suffice.
 constexpr int SHARE_ITEMS = 4096;
+// Item count up to which SARA's launches ride in the data path's (each launch
+// then has the registers and LDS of the larger part).  Per replayed iteration,
+// on two streams and in pairs: 51.7 and 32.9 us at 64^2 (125 items), 51 and 42
+// at 128^2 (1043), 55.6 and 50.7 at 256^2 (1777), 62 and 71 at 256^2 (3118);
+// eager 70 and 38, 70 and 45, 71 and 52, 73 and 72 (512 x 256, 3379).
+constexpr int PAIR_ITEMS = 2048;
+// The same for replayed iterations with middle Algorithm 2 steps, in which the
+// second stream has SARA run beside those: 54 and 48 us at 64^2 (125 items),
+// 60 and 66 at 256^2 (1777).
+constexpr int PAIR_ITEMS_MIDDLE = 512;
+// Largest 2 ny of the launches that a SARA level rides in (its kernels exist
+// for the lengths up to there).
+constexpr int PAIR_MAX_KY = 1024;
 // Captured-iteration graphs per plan: one iteration without statistics
 // partials, one with them and the periodic reduction, one with the partials
 // only, and a captured run (a statistics period, or GRAPH_RUN iterations
@@ -284,10 +297,29 @@ namespace ppd {
 int timer_begin(ppd_plan* p, int kind, int* slot);
 int timer_end(ppd_plan* p, int slot);
 
+struct SaraGeom {
+  int nx, ny, L;
+  size_t N;
+  size_t off[8];   // per-level temporaries: off[l] for level l (1 <= l < L)
+};
+// One SARA launch of an iteration (sara_jobs), to ride in a launch of the data
+// path (`with` below; NULL: nothing rides).
+struct SaraJob {
+  const float* in; float* tmp; float* out;
+  const float* filt; const float* W;
+  SaraGeom g;
+  int l;
+  float alpha, lambda;
+  const uint8_t* active;
+  int vec, gx, gy, gz;
+  __host__ __device__ int blocks() const { return gx * gy * gz; }
+};
+
 // ---- component launchers (each returns a PPD_* status) -------------------
 int fft_forward(ppd_plan* p, const float* x);                  // x -> grid_f (via half)
 int fft_rows_forward(ppd_plan* p, const float* x, float2* dst);  // x -> dst (row-pass buffer)
-int fft_cols_forward(ppd_plan* p, const float2* src);           // src (row-pass buffer) -> grid_f
+// src (row-pass buffer) -> grid_f; with: a SARA analysis level
+int fft_cols_forward(ppd_plan* p, const float2* src, const SaraJob* with = nullptr);
 int fft_adjoint(ppd_plan* p, float* x, bool add = false);      // grid_a -> x, or added to x (plain)
 int fft_cols_inverse(ppd_plan* p);                             // grid_a -> half
 struct PrimalArgs {
@@ -298,7 +330,7 @@ struct PrimalArgs {
 // half -> primal update and the forward row pass of the new x~ into next
 // (row-pass buffer)
 int fft_rows_inverse_primal(ppd_plan* p, const PrimalArgs& a, float2* next);
-int fold_grid(ppd_plan* p);                                    // gscratch -> grid_a
+int fold_grid(ppd_plan* p, const SaraJob* with = nullptr);     // gscratch -> grid_a; with: the last synthesis level
 
 // grid_f -> out, in plan order, or with uperm (plan -> caller) in the caller's
 int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm = nullptr);
@@ -311,11 +343,15 @@ struct DualArgs {
   const uint8_t* active;   // DEVICE [d] block mask of this iteration, NULL = all
   double* rpart = nullptr; // DEVICE [n_segs] residual partials for the statistics, NULL = skip them
 };
-int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out);   // grid_f -> gabuf; part_out NULL: no Algorithm 2 partials
+// grid_f -> gabuf; part_out NULL: no Algorithm 2 partials; with: a SARA analysis level
+int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out, const SaraJob* with = nullptr);
 // v -> grid_a; v in plan order, or with uperm in the caller's
 int grid_plain(ppd_plan* p, const float2* v, const int32_t* uperm = nullptr);
 int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in);  // dual finish + grid
-int grid_dual_factored(ppd_plan* p, const DualArgs& a);   // the same with the block factors already in bfac
+// the same with the block factors already in bfac; with: the two coarsest
+// synthesis levels beside the gridding, the last one beside the fold
+int grid_dual_factored(ppd_plan* p, const DualArgs& a, const SaraJob* with = nullptr,
+                       const SaraJob* with_fold = nullptr);
 
 int plain_dual(ppd_plan* p, const DualArgs& a);               // per-block unfused dual update
 // z <- P_B(q) for every block and, if pout, chunk partials of the next
@@ -331,7 +367,8 @@ int ball_step(ppd_plan* p, const BallIn& in, double2* z, const double2* fac, con
 int ball_factors(ppd_plan* p, const double* pin);   // bfac from chunk partials
 // Per-block projection factors of P_B from per-segment partials of
 // ||q - y||^2: bfac[j] = (min(1, eps_j / r_j), r_j <= eps_j), r_j the block norm.
-int block_factors(ppd_plan* p, const double* part);
+// with: a SARA analysis level.
+int block_factors(ppd_plan* p, const double* part, const SaraJob* with = nullptr);
 // The n_itr - 1 middle Algorithm 2 steps of the fused form in one persistent
 // launch (needs p->pa_ok and the first step's factors in bfac; leaves the
 // last step's factors in bfac).  spin_limit bounds each wait
@@ -349,6 +386,12 @@ int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* 
 int grid_dual_exact(ppd_plan* p, const DualArgs& a);   // dual finish with the exact prox + grid
 int permute(ppd_plan* p, int direction, const void* in, void* out, int elem_bytes);
 
+// The SARA launches of one iteration (analysis levels 1 to 3 with the dual
+// update of u from x, the two coarsest synthesis levels, the last one into
+// out), for plans where sara_pairs: three levels and low analysis tiles.
+bool sara_pairs(const ppd_plan* p);
+void sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W, const uint8_t* active,
+               float* out, SaraJob (&jobs)[5]);
 int sara_analysis(ppd_plan* p, const float* x, float* coef, const float* W);
 int sara_dual(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W,
               const uint8_t* active = nullptr);   // active: DEVICE [9] basis mask, NULL = all
