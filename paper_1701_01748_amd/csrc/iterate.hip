@@ -242,23 +242,37 @@ int sara_path(ppd_plan* p, const IterCtx& c) {
 }
 
 // Whether an iteration is one chain of launches, each of the data path's with
-// one of SARA's in its grid: for problems so small that a launch of either
+// one of SARA's in its grid where there is one left: for problems so small that a launch of either
 // leaves the chip mostly empty (PAIR_ITEMS).
 bool can_pair(const ppd_plan* p, const IterCtx& c, bool graph) {
-  const int most = graph && c.dual.n_itr > 1 ? PAIR_ITEMS_MIDDLE : PAIR_ITEMS;
+  const bool middle = c.prox == PPD_PROX_EXACT || c.dual.n_itr > 1;
+  const int most = graph && middle ? PAIR_ITEMS_MIDDLE : PAIR_ITEMS;
   static_assert(PAIR_ITEMS <= SHARE_ITEMS, "the paired launches share items");
-  return c.form == PPD_FORM_FUSED && c.prox == PPD_PROX_FB && p->T == 8 && p->n_items <= most &&
-         p->Ky <= PAIR_MAX_KY && sara_pairs(p) && !p->timing;
+  return c.form == PPD_FORM_FUSED && p->T == 8 && p->n_items <= most && p->Ky <= PAIR_MAX_KY && sara_pairs(p) &&
+         !p->timing;
 }
 
+// The launches with their riders; analysis and synthesis levels that find no
+// launch to ride in (a third analysis level with the exact prox, a fourth one,
+// a third synthesis launch) are launches of their own in between.
 int paired_iteration(ppd_plan* p, const IterCtx& c) {
-  SaraJob j[5];
-  sara_jobs(p, c.primal.xt, c.u, c.alpha, c.lambda, c.W, c.basis_active, p->ut, j);
-  PPD_TRY(fft_cols_forward(p, p->half_f, &j[0]));
-  PPD_TRY(degrid_dual(p, c.dual, p->part, &j[1]));
-  PPD_TRY(block_factors(p, p->part, &j[2]));
-  if (c.dual.n_itr > 1) PPD_TRY(middle_steps(p, c));
-  PPD_TRY(grid_dual_factored(p, c.dual, &j[3], &j[4]));
+  const bool exact = c.prox == PPD_PROX_EXACT;
+  const SaraJobs js = sara_jobs(p, c.primal.xt, c.u, c.alpha, c.lambda, c.W, c.basis_active, p->ut);
+  auto dwt = [&](int k) { return k < js.n_dwt ? &js.dwt[k] : nullptr; };
+  PPD_TRY(fft_cols_forward(p, p->half_f, dwt(0)));
+  PPD_TRY(degrid_dual(p, c.dual, exact ? nullptr : p->part, dwt(1)));
+  int next = 2;
+  if (exact) {
+    PPD_TRY(secular_solve(p, nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.n_newton, c.persistent, c.spin_limit));
+  } else {
+    PPD_TRY(block_factors(p, p->part, dwt(next++)));
+    if (c.dual.n_itr > 1) PPD_TRY(middle_steps(p, c));
+  }
+  for (; next < js.n_dwt; ++next) PPD_TRY(sara_launch(p, js.dwt[next]));
+  const SaraJob* last = &js.synth[js.n_synth - 1];
+  PPD_TRY(grid_dual_paired(p, c.dual, exact, js.n_synth > 1 ? &js.synth[0] : nullptr,
+                           js.n_synth > 2 ? &js.synth[1] : last));
+  if (js.n_synth > 2) PPD_TRY(sara_launch(p, *last));
   PPD_TRY(fft_cols_inverse(p));
   return fft_rows_inverse_primal(p, c.primal, p->half_f);
 }

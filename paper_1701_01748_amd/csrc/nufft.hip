@@ -771,20 +771,21 @@ __global__ __launch_bounds__(64 * NW) void k_grid_mfma(
   grid_mfma_block<DUAL, NW>(blockIdx.x, scratch, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc, vin, uperm, y, U, v, z, ga, mu, lambda, bfac, exact, active, xs);
 }
 
-// The shared items in the dual mode, after SARA's two coarsest synthesis
-// levels in the first workgroups.
-__global__ __launch_bounds__(256) void k_grid_idwt2(
+// The shared items in the dual mode, after a synthesis launch of SARA in the
+// first workgroups.
+template <int KIND>
+__global__ __launch_bounds__(256) void k_grid_synth(
     float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items, const Seg* __restrict__ segs,
     const float* __restrict__ wu, const float* __restrict__ wv, const float* __restrict__ theta, double su, double sv,
     const float* __restrict__ kbc, const float2* __restrict__ y, const double* __restrict__ U, float2* __restrict__ v,
     double2* __restrict__ z, const float2* __restrict__ ga, double mu, double lambda, const double2* __restrict__ bfac,
-    const uint8_t* __restrict__ active, XcdSplit xs, SaraJob j) {
+    int exact, const uint8_t* __restrict__ active, XcdSplit xs, SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
   if (b < 0)
-    sara_idwt2_part(j, blockIdx.x);
+    sara_synth_part<KIND>(j, blockIdx.x);
   else if (threadIdx.x < 128)
     grid_mfma_block<true, 2>(b, scratch, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc, nullptr,
-                             nullptr, y, U, v, z, ga, mu, lambda, bfac, 0, active, xs);
+                             nullptr, y, U, v, z, ga, mu, lambda, bfac, exact, active, xs);
 }
 
 // One thread per grid cell (FOLD_CELLS cells per workgroup, T*T/FOLD_CELLS
@@ -906,13 +907,14 @@ __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratc
   fold8_block(blockIdx.x, gridDim.x, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
 }
 
-// The same after SARA's last synthesis level in the first workgroups.
-__global__ __launch_bounds__(256) void k_fold8_final(int nblocks, const float2* __restrict__ scratch,
+// The same after a synthesis launch of SARA in the first workgroups.
+template <int KIND>
+__global__ __launch_bounds__(256) void k_fold8_synth(int nblocks, const float2* __restrict__ scratch,
                                                      const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
                                                      int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid,
                                                      SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
-  if (b < 0) sara_final_part(j, blockIdx.x);
+  if (b < 0) sara_synth_part<KIND>(j, blockIdx.x);
   else fold8_block(b, nblocks, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
 }
 
@@ -1062,14 +1064,23 @@ int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in) {
   return fold_grid(p);
 }
 
-int grid_dual_factored(ppd_plan* p, const DualArgs& a, const SaraJob* with, const SaraJob* with_fold) {
-  if (with) {
-    hipLaunchKernelGGL(k_grid_idwt2, dim3(p->split1.launch + with->blocks()), dim3(256), 0, p->stream, p->gscratch,
-                       p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc,
-                       a.y, a.U, a.v, a.z, p->gabuf, a.mu, a.lambda, p->bfac, a.active, p->split1, *with);
-    PPD_HIP(hipGetLastError());
+int grid_dual_paired(ppd_plan* p, const DualArgs& a, int exact, const SaraJob* with, const SaraJob* with_fold) {
+  if (!with) {
+    PPD_TRY(dispatch_grid(p, true, nullptr, nullptr, &a, exact));
     return fold_grid(p, with_fold);
   }
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(p->split1.launch + with->blocks()), dim3(256), 0, p->stream, p->gscratch, p->Ky,
+                       p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc, a.y,
+                       a.U, a.v, a.z, p->gabuf, a.mu, a.lambda, p->bfac, exact, a.active, p->split1, *with);
+  };
+  if (with->kind == SARA_IDWT2) launch(k_grid_synth<SARA_IDWT2>);
+  else launch(k_grid_synth<SARA_IDWT>);
+  PPD_HIP(hipGetLastError());
+  return fold_grid(p, with_fold);
+}
+
+int grid_dual_factored(ppd_plan* p, const DualArgs& a) {
   PPD_TRY(dispatch_grid(p, true, nullptr, nullptr, &a, 0));
   return fold_grid(p);
 }
@@ -1081,9 +1092,13 @@ int grid_dual_exact(ppd_plan* p, const DualArgs& a) {
 
 int fold_grid(ppd_plan* p, const SaraJob* with) {
   if (with) {
-    hipLaunchKernelGGL(k_fold8_final, dim3(p->n_fold_wg + with->blocks()), dim3(256), 0, p->stream, p->n_fold_wg,
-                       p->gscratch, p->tile_item_off, reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x,
-                       p->tiles_y, p->Ky, p->grid_a, *with);
+    auto launch = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(p->n_fold_wg + with->blocks()), dim3(256), 0, p->stream, p->n_fold_wg,
+                         p->gscratch, p->tile_item_off, reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x,
+                         p->tiles_y, p->Ky, p->grid_a, *with);
+    };
+    if (with->kind == SARA_IDWT) launch(k_fold8_synth<SARA_IDWT>);
+    else launch(k_fold8_synth<SARA_FINAL>);
     PPD_HIP(hipGetLastError());
     return PPD_OK;
   }

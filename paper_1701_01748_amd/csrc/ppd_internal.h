@@ -75,10 +75,12 @@ constexpr int SHARE_ITEMS = 4096;
 // at 128^2 (1043), 55.6 and 50.7 at 256^2 (1777), 62 and 71 at 256^2 (3118);
 // eager 70 and 38, 70 and 45, 71 and 52, 73 and 72 (512 x 256, 3379).
 constexpr int PAIR_ITEMS = 2048;
-// The same for replayed iterations with middle Algorithm 2 steps, in which the
-// second stream has SARA run beside those: 54 and 48 us at 64^2 (125 items),
-// 60 and 66 at 256^2 (1777).
-constexpr int PAIR_ITEMS_MIDDLE = 512;
+// The same for replayed iterations with middle Algorithm 2 steps or the exact
+// prox, in which the second stream has SARA run beside those: five steps 54 and
+// 48 us at 64^2 (125 items), 56 and 53 at 128^2 (471), 59 and 59.5 at 128^2
+// (1043), 60 and 66 at 256^2 (1777); exact 59 and 56 at 64^2 (140), 61 and 63 at
+// 128^2 (502).
+constexpr int PAIR_ITEMS_MIDDLE = 480;
 // Largest 2 ny of the launches that a SARA level rides in (its kernels exist
 // for the lengths up to there).
 constexpr int PAIR_MAX_KY = 1024;
@@ -304,7 +306,9 @@ struct SaraGeom {
 };
 // One SARA launch of an iteration (sara_jobs), to ride in a launch of the data
 // path (`with` below; NULL: nothing rides).
+enum SaraKind { SARA_DWT, SARA_IDWT2, SARA_IDWT, SARA_FINAL };
 struct SaraJob {
+  int kind;
   const float* in; float* tmp; float* out;
   const float* filt; const float* W;
   SaraGeom g;
@@ -330,7 +334,7 @@ struct PrimalArgs {
 // half -> primal update and the forward row pass of the new x~ into next
 // (row-pass buffer)
 int fft_rows_inverse_primal(ppd_plan* p, const PrimalArgs& a, float2* next);
-int fold_grid(ppd_plan* p, const SaraJob* with = nullptr);     // gscratch -> grid_a; with: the last synthesis level
+int fold_grid(ppd_plan* p, const SaraJob* with = nullptr);     // gscratch -> grid_a; with: a synthesis level
 
 // grid_f -> out, in plan order, or with uperm (plan -> caller) in the caller's
 int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm = nullptr);
@@ -348,10 +352,11 @@ int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out, const SaraJob*
 // v -> grid_a; v in plan order, or with uperm in the caller's
 int grid_plain(ppd_plan* p, const float2* v, const int32_t* uperm = nullptr);
 int grid_dual(ppd_plan* p, const DualArgs& a, const double* part_in);  // dual finish + grid
-// the same with the block factors already in bfac; with: the two coarsest
-// synthesis levels beside the gridding, the last one beside the fold
-int grid_dual_factored(ppd_plan* p, const DualArgs& a, const SaraJob* with = nullptr,
-                       const SaraJob* with_fold = nullptr);
+// the same with the block factors already in bfac
+int grid_dual_factored(ppd_plan* p, const DualArgs& a);
+// the same, or with the exact prox, and a synthesis launch (a level or the two
+// coarsest) beside the gridding, one (a level or the last) beside the fold
+int grid_dual_paired(ppd_plan* p, const DualArgs& a, int exact, const SaraJob* with, const SaraJob* with_fold);
 
 int plain_dual(ppd_plan* p, const DualArgs& a);               // per-block unfused dual update
 // z <- P_B(q) for every block and, if pout, chunk partials of the next
@@ -386,12 +391,18 @@ int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* 
 int grid_dual_exact(ppd_plan* p, const DualArgs& a);   // dual finish with the exact prox + grid
 int permute(ppd_plan* p, int direction, const void* in, void* out, int elem_bytes);
 
-// The SARA launches of one iteration (analysis levels 1 to 3 with the dual
-// update of u from x, the two coarsest synthesis levels, the last one into
-// out), for plans where sara_pairs: three levels and low analysis tiles.
+// The SARA launches of one iteration: analysis levels with the dual update of
+// u from x, then the synthesis levels, the last one into out.  For plans where
+// sara_pairs: at most SARA_PAIR_LEVELS levels and low analysis tiles.
+constexpr int SARA_PAIR_LEVELS = 4;
+struct SaraJobs {
+  SaraJob dwt[SARA_PAIR_LEVELS], synth[3];
+  int n_dwt, n_synth;
+};
 bool sara_pairs(const ppd_plan* p);
-void sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W, const uint8_t* active,
-               float* out, SaraJob (&jobs)[5]);
+SaraJobs sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W,
+                   const uint8_t* active, float* out);
+int sara_launch(ppd_plan* p, const SaraJob& j);   // a launch of its own
 int sara_analysis(ppd_plan* p, const float* x, float* coef, const float* W);
 int sara_dual(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W,
               const uint8_t* active = nullptr);   // active: DEVICE [9] basis mask, NULL = all

@@ -131,22 +131,48 @@ int sara_dual(ppd_plan* p, const float* x, float* u, float alpha, float lambda, 
   return analysis_launch(p, x, u, W, true, alpha, lambda, active);
 }
 
-bool sara_pairs(const ppd_plan* p) { return p->levels == 3 && !tall_tiles(geom(p), 1); }
+bool sara_pairs(const ppd_plan* p) { return p->levels <= SARA_PAIR_LEVELS && !tall_tiles(geom(p), 1); }
 
-void sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W, const uint8_t* active,
-               float* out, SaraJob (&jobs)[5]) {
+SaraJobs sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W,
+                   const uint8_t* active, float* out) {
+  SaraJobs js{};
   const SaraGeom g = geom(p);
-  for (int l = 1; l <= 3; ++l) {
+  for (int l = 1; l <= g.L; ++l) {
     const int oh = g.ny >> l, ow = g.nx >> l;
-    jobs[l - 1] = SaraJob{x, p->sara_ll, u, p->filt, W, g, l, alpha, lambda, active,
-                          ow % 4 == 0 && aligned16(u) && aligned16(W) && aligned16(x),
-                          ow / std::min(TX, ow), oh / std::min(8, oh), l == 1 ? 9 : 8};
+    js.dwt[js.n_dwt++] = SaraJob{SARA_DWT, x, p->sara_ll, u, p->filt, W, g, l, alpha, lambda, active,
+                                 ow % 4 == 0 && aligned16(u) && aligned16(W) && aligned16(x),
+                                 ow / std::min(TX, ow), oh / std::min(8, oh), l == 1 ? 9 : 8};
   }
-  const int hh = g.ny >> 1, ww = g.nx >> 1;
-  jobs[3] = SaraJob{u, p->sara_rec, nullptr, p->filt, W, g, 0, 0.f, 0.f, nullptr, 0, ww / std::min(SX, ww),
-                    hh / std::min(SY, hh), 2};
-  jobs[4] = SaraJob{u, p->sara_rec, out, p->filt, W, g, 0, 0.f, 0.f, nullptr,
-                    aligned16(u) && aligned16(W) && aligned16(out), g.nx / std::min(SX, g.nx), g.ny / SY, 1};
+  auto level = [&](int kind, int l) {
+    const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
+    js.synth[js.n_synth++] = SaraJob{kind, u, p->sara_rec, nullptr, p->filt, W, g, l, 0.f, 0.f, nullptr, 0,
+                                     ww / std::min(SX, ww), hh / std::min(SY, hh), 2};
+  };
+  int top = g.L;
+  if (g.L >= 3) {
+    level(SARA_IDWT2, g.L - 1);
+    top = g.L - 2;
+  }
+  for (int l = top; l >= 2; --l) level(SARA_IDWT, l);
+  js.synth[js.n_synth++] = SaraJob{SARA_FINAL, u, p->sara_rec, out, p->filt, W, g, 1, 0.f, 0.f, nullptr,
+                                   aligned16(u) && aligned16(W) && aligned16(out), g.nx / std::min(SX, g.nx),
+                                   g.ny / SY, 1};
+  return js;
+}
+
+int sara_launch(ppd_plan* p, const SaraJob& j) {
+  const dim3 grid(j.gx, j.gy, j.gz);
+  if (j.kind == SARA_DWT)
+    hipLaunchKernelGGL((k_dwt<A_DUAL, 4>), grid, dim3(DWT_THREADS), 0, p->stream, j.in, j.tmp, j.out, j.filt, j.W, j.g,
+                       j.l, j.alpha, j.lambda, j.active, j.vec);
+  else if (j.kind == SARA_IDWT2)
+    hipLaunchKernelGGL(k_idwt2, grid, dim3(256), 0, p->stream, j.in, j.tmp, j.filt, j.W, j.g);
+  else if (j.kind == SARA_IDWT)
+    hipLaunchKernelGGL(k_idwt, grid, dim3(256), 0, p->stream, j.in, j.tmp, j.filt, j.W, j.g, j.l);
+  else
+    hipLaunchKernelGGL(k_idwt_final, grid, dim3(256), 0, p->stream, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
+  PPD_HIP(hipGetLastError());
+  return PPD_OK;
 }
 
 int sara_synthesis(ppd_plan* p, const float* u, float* out, const float* W) {

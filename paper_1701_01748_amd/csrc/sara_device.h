@@ -556,13 +556,14 @@ __device__ __forceinline__ void sara_dwt_part(const SaraJob& j, int lin) {
   dwt_block<A_DUAL, 4>(sara_tile<true>(lin, j.gx, j.gy, j.gz), j.in, j.tmp, j.out, j.filt, j.W, j.g, j.l, j.alpha,
                        j.lambda, j.active, j.vec);
 }
-__device__ __forceinline__ void sara_idwt2_part(const SaraJob& j, int lin) {
+// One synthesis launch: the two coarsest levels, one level, or the last one.
+template <int KIND>
+__device__ __forceinline__ void sara_synth_part(const SaraJob& j, int lin) {
   if (threadIdx.x >= 256) return;
-  idwt2_block(sara_tile<false>(lin, j.gx, j.gy, j.gz), j.in, j.tmp, j.filt, j.W, j.g);
-}
-__device__ __forceinline__ void sara_final_part(const SaraJob& j, int lin) {
-  if (threadIdx.x >= 256) return;
-  idwt_final_block(sara_tile<false>(lin, j.gx, j.gy, j.gz), j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
+  const TileId tl = sara_tile<false>(lin, j.gx, j.gy, j.gz);
+  if constexpr (KIND == SARA_IDWT2) idwt2_block(tl, j.in, j.tmp, j.filt, j.W, j.g);
+  else if constexpr (KIND == SARA_IDWT) idwt_block(tl, j.in, j.tmp, j.filt, j.W, j.g, j.l);
+  else idwt_final_block(tl, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
 }
 
 }  // namespace
