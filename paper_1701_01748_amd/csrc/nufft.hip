@@ -836,6 +836,52 @@ __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ 
   if (tx * T + b < PW) grid[grid_index(tx * T + b, ty * T + a, Ky)] = make_float2(sx, sy);
 }
 
+// What one cell receives from its four source tiles: the regions i0[q],
+// i0[q] + STRIDE, .. < i1[q] (wave-uniform) at off[q] where ok[q], four at a
+// time and the rest one by one.  All that remains of a source after whole fours
+// is loaded before anything is added: most tiles have one to three regions, and
+// their four sources together then cost one load's latency, not four to twelve.
+// Bound by that latency at small sizes and by the regions' bytes at large ones:
+// 64^2 .. 256^2 5.2 -> 3.9 us; 512^2, 1.3M points 10.7 -> 9.6; 2048^2, 6M points,
+// beside SARA 117 -> 76 (236 MB of regions in, 67 MB out).  Regions stored as
+// four 512-byte quadrants, so that both sides move whole lines, were no faster
+// (10.0 and 78), nor eight loads in flight for the heavy tiles.
+template <int STRIDE>
+__device__ __forceinline__ float2 fold_sources(const float2* __restrict__ scratch, int R2, const int (&off)[4],
+                                               const bool (&ok)[4], const int (&i0)[4], const int (&i1)[4]) {
+  float2 g[4][3];
+  int n[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    n[q] = max(0, (i1[q] - i0[q] + STRIDE - 1) / STRIDE);
+    const int i = i0[q] + STRIDE * (n[q] & ~3);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      g[q][k] = make_float2(0.f, 0.f);
+      if ((n[q] & 3) > k && ok[q]) g[q][k] = scratch[size_t(i + STRIDE * k) * R2 + off[q]];
+    }
+  }
+  float sx = 0.f, sy = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (n[q] >= 4 && ok[q]) {
+      for (int k = 0; k + 4 <= n[q]; k += 4) {
+        const float2* r = scratch + size_t(i0[q] + STRIDE * k) * R2 + off[q];
+        const float2 g0 = r[0], g1 = r[STRIDE * R2], g2 = r[2 * STRIDE * R2], g3 = r[3 * STRIDE * R2];
+        sx += (g0.x + g1.x) + (g2.x + g3.x);
+        sy += (g0.y + g1.y) + (g2.y + g3.y);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if ((n[q] & 3) > k && ok[q]) {
+        sx += g[q][k].x;
+        sy += g[q][k].y;
+      }
+  }
+  return make_float2(sx, sy);
+}
+
 // 8 x 8 tiles, 4-wave workgroups in the plan's fold order (tile rows spread
 // over the XCDs, on each XCD the tiles with the most item regions first).
 // Entry {t0, t1, t2, t3} folds up to four light tiles, one per wave, one
@@ -843,56 +889,33 @@ __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ 
 // FOLD_HEAVY regions to sum: the dense centre of the coverage), wave w
 // summing every fourth item region of each source tile from the w-th, the
 // four partial sums then added in wave order.
-__device__ __forceinline__ void fold_items4(const float2* __restrict__ scratch, int R2, int off, int i0, int i1,
-                                            float& sx, float& sy) {
-  int i = i0;
-  for (; i + 12 < i1; i += 16) {
-    const float2 g0 = scratch[size_t(i) * R2 + off];
-    const float2 g1 = scratch[size_t(i + 4) * R2 + off];
-    const float2 g2 = scratch[size_t(i + 8) * R2 + off];
-    const float2 g3 = scratch[size_t(i + 12) * R2 + off];
-    sx += (g0.x + g1.x) + (g2.x + g3.x);
-    sy += (g0.y + g1.y) + (g2.y + g3.y);
-  }
-  for (; i < i1; i += 4) {
-    const float2 g = scratch[size_t(i) * R2 + off];
-    sx += g.x;
-    sy += g.y;
-  }
-}
-
 __device__ __forceinline__ void fold8_block(int block, int nblocks, const float2* __restrict__ scratch,
                                             const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
                                             int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid) {
   constexpr int T = 8, R = T + 7;
   __shared__ float2 part[4][64];
   const int4 e = wgs[xcd_remap(block, nblocks)];
-  const int w = threadIdx.x >> 6, c = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), c = threadIdx.x & 63;
   const int a = c / T, b = c - a * T;
   const bool heavy = e.y == -2;   // uniform over the workgroup
   const int t = heavy ? e.x : (w == 0 ? e.x : w == 1 ? e.y : w == 2 ? e.z : e.w);
   if (t < 0) return;              // never taken by a heavy workgroup
   const int tx = t % tiles_x, ty = t / tiles_x;
   const int lx = (tx + tiles_x - 1) % tiles_x, uy = (ty + tiles_y - 1) % tiles_y;
-  const int tl = ty * tiles_x + lx, tu = uy * tiles_x + tx, tul = uy * tiles_x + lx;
-  float sx = 0.f, sy = 0.f;
+  const int src[4] = {t, ty * tiles_x + lx, uy * tiles_x + tx, uy * tiles_x + lx};
+  const int off[4] = {a * R + b, a * R + T + b, (T + a) * R + b, (T + a) * R + T + b};
+  const bool ok[4] = {true, b < 7, a < 7, a < 7 && b < 7};
+  int i0[4], i1[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    i0[q] = tio[src[q]] + (heavy ? w : 0);
+    i1[q] = tio[src[q] + 1];
+  }
   if (!heavy) {
-    fold_items(scratch, R * R, a * R + b, tio[t], tio[t + 1], sx, sy);
-    if (b < 7) fold_items(scratch, R * R, a * R + T + b, tio[tl], tio[tl + 1], sx, sy);
-    if (a < 7) {
-      fold_items(scratch, R * R, (T + a) * R + b, tio[tu], tio[tu + 1], sx, sy);
-      if (b < 7) fold_items(scratch, R * R, (T + a) * R + T + b, tio[tul], tio[tul + 1], sx, sy);
-    }
-    grid[grid_index(tx * T + b, ty * T + a, Ky)] = make_float2(sx, sy);
+    grid[grid_index(tx * T + b, ty * T + a, Ky)] = fold_sources<1>(scratch, R * R, off, ok, i0, i1);
     return;
   }
-  fold_items4(scratch, R * R, a * R + b, tio[t] + w, tio[t + 1], sx, sy);
-  if (b < 7) fold_items4(scratch, R * R, a * R + T + b, tio[tl] + w, tio[tl + 1], sx, sy);
-  if (a < 7) {
-    fold_items4(scratch, R * R, (T + a) * R + b, tio[tu] + w, tio[tu + 1], sx, sy);
-    if (b < 7) fold_items4(scratch, R * R, (T + a) * R + T + b, tio[tul] + w, tio[tul + 1], sx, sy);
-  }
-  part[w][c] = make_float2(sx, sy);
+  part[w][c] = fold_sources<4>(scratch, R * R, off, ok, i0, i1);
   __syncthreads();
   if (w == 0) {
     const float2 p0 = part[0][c], p1 = part[1][c], p2 = part[2][c], p3 = part[3][c];
