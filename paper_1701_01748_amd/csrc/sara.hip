@@ -45,22 +45,25 @@ __global__ __launch_bounds__(DWT_THREADS) void k_dwt(const float* __restrict__ x
                       alpha, lambda, active, vec);
 }
 
+template <int WM>
 __global__ __launch_bounds__(256) void k_idwt(const float* __restrict__ u, float* __restrict__ rec,
                                               const float* __restrict__ filt, const float* __restrict__ W,
                                               SaraGeom g, int l) {
-  idwt_block(sara_tile<false>(linear_block(), gridDim.x, gridDim.y, gridDim.z), u, rec, filt, W, g, l);
+  idwt_block<WM>(sara_tile<false>(linear_block(), gridDim.x, gridDim.y, gridDim.z), u, rec, filt, W, g, l);
 }
 
+template <int WM>
 __global__ __launch_bounds__(256) void k_idwt2(const float* __restrict__ u, float* __restrict__ rec,
                                                const float* __restrict__ filt, const float* __restrict__ W,
                                                SaraGeom g) {
-  idwt2_block(sara_tile<false>(linear_block(), gridDim.x, gridDim.y, gridDim.z), u, rec, filt, W, g);
+  idwt2_block<WM>(sara_tile<false>(linear_block(), gridDim.x, gridDim.y, gridDim.z), u, rec, filt, W, g);
 }
 
+template <int WM>
 __global__ __launch_bounds__(256) void k_idwt_final(const float* __restrict__ u, const float* __restrict__ rec,
                                                     const float* __restrict__ filt, const float* __restrict__ W,
                                                     SaraGeom g, float* __restrict__ out, int vec) {
-  idwt_final_block(sara_tile<false>(linear_block(), gridDim.x, gridDim.y, gridDim.z), u, rec, filt, W, g, out, vec);
+  idwt_final_block<WM>(sara_tile<false>(linear_block(), gridDim.x, gridDim.y, gridDim.z), u, rec, filt, W, g, out, vec);
 }
 
 // Algorithm 1 weights (eq. reweighting): W = omega / (omega + |c|), in
@@ -88,6 +91,20 @@ SaraGeom geom(const ppd_plan* p) {
 bool tall_tiles(const SaraGeom& g, int l) {
   const int oh = g.ny >> l, ow = g.nx >> l;
   return int64_t(ow / std::min(TX, ow)) * (oh / std::min(16, oh)) * (l == 1 ? 9 : 8) >= DWT_TALL_MIN;
+}
+
+// Columns of the synthesis tiles of an output of hh x ww: 64, or 32 where that
+// makes fewer than `most` waves.  A wave of 64 columns loads its two bands in
+// two rounds, one of 32 in one: shorter where waves are few, more columns
+// loaded twice where they are many.  A dual step of 3 levels, 64 and 32 columns:
+// 128 x 64 30.3 and 27.3 us, 256^2 32.7 and 29.0, 512^2 38.2 and 34.9.  Last
+// level: 512^2 (2048 waves) 15.0 and 13.9 with the others at 32, 1024 x 512 (4096)
+// 18.8 and 21.3.  The levels before it: 512 x 256 (1024 waves) 20.2 and 18.8
+// for the whole synthesis, 512^2 (2048) 28.7 and 30.1.
+constexpr int64_t NARROW_LAST = 4096, NARROW_LEVEL = 2048;
+int synth_width(int hh, int ww, int64_t most) {
+  const int sx = int64_t(8) * std::max(1, ww / SX) * std::max(1, hh / SY) < most ? SX / 2 : SX;
+  return std::min(sx, ww);
 }
 
 bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
@@ -131,6 +148,32 @@ int sara_dual(ppd_plan* p, const float* x, float* u, float alpha, float lambda, 
   return analysis_launch(p, x, u, W, true, alpha, lambda, active);
 }
 
+// The synthesis launches: the two coarsest levels in one (from three levels
+// on), the others one by one, the last one into out.
+struct SynthJobs {
+  SaraJob job[8];
+  int n = 0;
+};
+static SynthJobs synth_jobs(ppd_plan* p, const float* u, const float* W, float* out) {
+  SynthJobs js;
+  const SaraGeom g = geom(p);
+  auto level = [&](int kind, int l) {
+    const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
+    js.job[js.n++] = SaraJob{kind, u, p->sara_rec, nullptr, p->filt, W, g, l, 0.f, 0.f, nullptr, 0,
+                             ww / synth_width(hh, ww, NARROW_LEVEL), hh / std::min(SY, hh), 2};
+  };
+  int top = g.L;
+  if (g.L >= 3) {
+    level(SARA_IDWT2, g.L - 1);
+    top = g.L - 2;
+  }
+  for (int l = top; l >= 2; --l) level(SARA_IDWT, l);
+  js.job[js.n++] = SaraJob{SARA_FINAL, u, p->sara_rec, out, p->filt, W, g, 1, 0.f, 0.f, nullptr,
+                           aligned16(u) && aligned16(W) && aligned16(out),
+                           g.nx / synth_width(g.ny, g.nx, NARROW_LAST), g.ny / SY, 1};
+  return js;
+}
+
 bool sara_pairs(const ppd_plan* p) { return p->levels <= SARA_PAIR_LEVELS && !tall_tiles(geom(p), 1); }
 
 SaraJobs sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lambda, const float* W,
@@ -143,71 +186,42 @@ SaraJobs sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lam
                                  ow % 4 == 0 && aligned16(u) && aligned16(W) && aligned16(x),
                                  ow / std::min(TX, ow), oh / std::min(8, oh), l == 1 ? 9 : 8};
   }
-  auto level = [&](int kind, int l) {
-    const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-    js.synth[js.n_synth++] = SaraJob{kind, u, p->sara_rec, nullptr, p->filt, W, g, l, 0.f, 0.f, nullptr, 0,
-                                     ww / std::min(SX, ww), hh / std::min(SY, hh), 2};
-  };
-  int top = g.L;
-  if (g.L >= 3) {
-    level(SARA_IDWT2, g.L - 1);
-    top = g.L - 2;
-  }
-  for (int l = top; l >= 2; --l) level(SARA_IDWT, l);
-  js.synth[js.n_synth++] = SaraJob{SARA_FINAL, u, p->sara_rec, out, p->filt, W, g, 1, 0.f, 0.f, nullptr,
-                                   aligned16(u) && aligned16(W) && aligned16(out), g.nx / std::min(SX, g.nx),
-                                   g.ny / SY, 1};
+  const SynthJobs sy = synth_jobs(p, u, W, out);
+  for (; js.n_synth < sy.n; ++js.n_synth) js.synth[js.n_synth] = sy.job[js.n_synth];
   return js;
 }
 
 int sara_launch(ppd_plan* p, const SaraJob& j) {
   const dim3 grid(j.gx, j.gy, j.gz);
+  // the weights ahead of the values where the waves are few: in tiles below 64 columns
+  const int ww = j.g.nx >> (j.l - 1);
+  const bool ahead = ww / j.gx < SX;
+  auto synth = [&](auto none, auto after, auto before, auto... args) {
+    hipLaunchKernelGGL(!j.W ? none : ahead ? before : after, grid, dim3(256), 0, p->stream, args...);
+  };
   if (j.kind == SARA_DWT)
     hipLaunchKernelGGL((k_dwt<A_DUAL, 4>), grid, dim3(DWT_THREADS), 0, p->stream, j.in, j.tmp, j.out, j.filt, j.W, j.g,
                        j.l, j.alpha, j.lambda, j.active, j.vec);
   else if (j.kind == SARA_IDWT2)
-    hipLaunchKernelGGL(k_idwt2, grid, dim3(256), 0, p->stream, j.in, j.tmp, j.filt, j.W, j.g);
+    synth(k_idwt2<W_NONE>, k_idwt2<W_AFTER>, k_idwt2<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g);
   else if (j.kind == SARA_IDWT)
-    hipLaunchKernelGGL(k_idwt, grid, dim3(256), 0, p->stream, j.in, j.tmp, j.filt, j.W, j.g, j.l);
+    synth(k_idwt<W_NONE>, k_idwt<W_AFTER>, k_idwt<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g, j.l);
   else
-    hipLaunchKernelGGL(k_idwt_final, grid, dim3(256), 0, p->stream, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
+    synth(k_idwt_final<W_NONE>, k_idwt_final<W_AFTER>, k_idwt_final<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g, j.out,
+          j.vec);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
 
 int sara_synthesis(ppd_plan* p, const float* u, float* out, const float* W) {
-  const SaraGeom g = geom(p);
-  int top = g.L;
-  if (g.L >= 3) {
-    // levels L and L-1 in one launch
-    const int l = g.L - 1;
-    const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-    const int tsy = std::min(SY, hh), tsx = std::min(SX, ww);
+  const SynthJobs js = synth_jobs(p, u, W, out);
+  for (int k = 0; k < js.n; ++k) {
     int slot;
     PPD_TRY(timer_begin(p, KK_IDWT, &slot));
-    hipLaunchKernelGGL(k_idwt2, dim3(ww / tsx, hh / tsy, 2), dim3(256), 0, p->stream, u, p->sara_rec, p->filt,
-                       W, g);
-    PPD_HIP(hipGetLastError());
-    PPD_TRY(timer_end(p, slot));
-    top = g.L - 2;
-  }
-  for (int l = top; l >= 2; --l) {
-    const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-    const int tsy = std::min(SY, hh), tsx = std::min(SX, ww);
-    int slot;
-    PPD_TRY(timer_begin(p, KK_IDWT, &slot));
-    hipLaunchKernelGGL(k_idwt, dim3(ww / tsx, hh / tsy, 2), dim3(256), 0, p->stream, u, p->sara_rec, p->filt,
-                       W, g, l);
-    PPD_HIP(hipGetLastError());
+    PPD_TRY(sara_launch(p, js.job[k]));
     PPD_TRY(timer_end(p, slot));
   }
-  int slot;
-  PPD_TRY(timer_begin(p, KK_IDWT, &slot));
-  const int vec = aligned16(u) && aligned16(W) && aligned16(out);
-  hipLaunchKernelGGL(k_idwt_final, dim3(g.nx / std::min(SX, g.nx), g.ny / SY), dim3(256), 0, p->stream, u,
-                     p->sara_rec, p->filt, W, g, out, vec);
-  PPD_HIP(hipGetLastError());
-  return timer_end(p, slot);
+  return PPD_OK;
 }
 
 }  // namespace ppd

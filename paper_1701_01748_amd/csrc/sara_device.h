@@ -37,13 +37,14 @@ enum { A_PLAIN = 0, A_DUAL = 1 };
 // of them (level 1 at 2048^2: 97 -> 83 us, at 512^2 11.9 -> 10.5 us).
 struct TileId {
   int x, y, z;
+  int gx;   // tiles in a row, a power of two
 };
 template <bool INNER>
 __device__ inline TileId sara_tile(int lin, int gx, int gy, int gz) {
   const int total = gx * gy * gz;
   if (total % MAX_XCD == 0) lin = xcd_remap(lin, total);
-  if (INNER) return TileId{(lin / gz) % gx, lin / (gz * gx), lin % gz};
-  return TileId{lin % gx, (lin / gx) % gy, lin / (gx * gy)};
+  if (INNER) return TileId{(lin / gz) % gx, lin / (gz * gx), lin % gz, gx};
+  return TileId{lin % gx, (lin / gx) % gy, lin / (gx * gy), gx};
 }
 
 // Filters of db-Q: 2Q taps each, low-pass h and high-pass g, in registers
@@ -110,7 +111,13 @@ __device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstr
   const size_t pos[4] = {size_t(r) * nx + (ow + c), size_t(oh + r) * nx + c, size_t(oh + r) * nx + (ow + c),
                          size_t(r) * nx + c};
   const int nout = llout ? 3 : 4;
-  float uo[4][4];
+  float uo[4][4], wo[4][4];
+  constexpr bool AHEAD = RB == 4;   // low tiles: too few waves to hide the weights' latency
+  if (AHEAD && wb && mine) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if (b < nout) load4(wb + pos[b], vec, nv, wo[b]);
+  }
   if (MODE == A_DUAL && mine) {
 #pragma unroll
     for (int b = 0; b < 4; ++b)
@@ -171,10 +178,9 @@ __device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstr
     if (b >= nout) break;
     float o[4];
     if (wb) {
-      float wv[4];
-      load4(wb + pos[b], vec, nv, wv);
+      if (!AHEAD) load4(wb + pos[b], vec, nv, wo[b]);
 #pragma unroll
-      for (int m = 0; m < 4; ++m) o[m] = cv[b][m] * wv[m];
+      for (int m = 0; m < 4; ++m) o[m] = cv[b][m] * wo[b][m];
     } else {
 #pragma unroll
       for (int m = 0; m < 4; ++m) o[m] = cv[b][m];
@@ -257,6 +263,8 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ __forceinline__ int tile_width(int ww, int gx) { return ww >> (31 - __builtin_clz(gx)); }
+
 // The four sub-bands of one level of one basis in the Mallat layout, periodic,
 // with optional weights, and where the low-pass band is read instead if it is
 // not LL of u (row stride lls, unweighted).
@@ -267,13 +275,18 @@ struct Bands {
   int nx, oh, ow, lls;
 };
 
+// How a synthesis kernel takes the weights: none, loaded after the values, or
+// ahead of them (in flight beside them, for more registers: shorter where waves
+// are few, fewer waves where they are many).
+enum { W_NONE, W_AFTER, W_AHEAD };
+
 // Inverse of one level for basis db-Q on one tile by one wave.  Transposing
 // the analysis gives s[2j + e] = sum_t h[2t + e] a[j - t] + g[2t + e] d[j - t],
 // e in {0, 1}.  Column pass: the axis-1 low band (from LL, HL) and high band
 // (from LH, HH) of 2 SP output rows, at coefficient columns c0 - (Q - 1) + b,
 // b < hx + Q - 1, to s_x[band][row][b].  WIN: the low-pass entry at
 // coefficient row j0 - (Q - 1) + a, column index b is win[a WCOLS + b].
-template <int Q, bool WIN>
+template <int Q, bool WIN, int WM>
 __device__ __forceinline__ void synth_cols(const float (&h)[2 * Q], const float (&g)[2 * Q], const Bands& bd, int j0,
                                            int c0, int hx, const float* win, float* s_x) {
   constexpr int NR = SP + Q - 1;
@@ -289,6 +302,17 @@ __device__ __forceinline__ void synth_cols(const float (&h)[2 * Q], const float 
 #pragma unroll
     for (int a = 0; a < NR; ++a) off[a] = (r0 + a) & (bd.oh - 1);
     const int cd = bd.oh * bd.nx + band * bd.ow + c, ca = band * bd.ow + c;
+    float wd[WM == W_NONE ? 1 : NR], wa[WM == W_NONE ? 1 : NR];
+    auto load_weights = [&]() {
+      if constexpr (WM != W_NONE) {
+#pragma unroll
+        for (int a = 0; a < NR; ++a) {
+          wd[a] = bd.w[off[a] * bd.nx + cd];
+          wa[a] = bd.w[off[a] * bd.nx + ca];
+        }
+      }
+    };
+    if (WM == W_AHEAD) load_weights();
 #pragma unroll
     for (int a = 0; a < NR; ++a) dv[a] = bd.u[off[a] * bd.nx + cd];
     if constexpr (WIN) {
@@ -306,13 +330,8 @@ __device__ __forceinline__ void synth_cols(const float (&h)[2 * Q], const float 
 #pragma unroll
       for (int a = 0; a < NR; ++a) av[a] = pa[off[a] * sa];
     }
-    if (bd.w) {
-      float wd[NR], wa[NR];
-#pragma unroll
-      for (int a = 0; a < NR; ++a) {
-        wd[a] = bd.w[off[a] * bd.nx + cd];
-        wa[a] = bd.w[off[a] * bd.nx + ca];
-      }
+    if (WM == W_AFTER) load_weights();
+    if constexpr (WM != W_NONE) {
       const bool low = (WIN || bd.ll) && !band;   // an unweighted low-pass band
 #pragma unroll
       for (int a = 0; a < NR; ++a) {
@@ -396,12 +415,13 @@ __device__ __forceinline__ int wave_basis(int z) {
 }
 
 // Intermediate synthesis level l >= 2 (output = low-pass band of level l-1).
+template <int WM>
 __device__ __forceinline__ void idwt_block(TileId tl, const float* __restrict__ u, float* __restrict__ rec,
                                            const float* __restrict__ filt, const float* __restrict__ W,
                                            const SaraGeom& g, int l) {
   __shared__ __align__(16) float s_all[4][2 * SY * SS];
   const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-  const int tsy = min(SY, hh), tsx = min(SX, ww), hx = tsx >> 1;
+  const int tsy = min(SY, hh), tsx = tile_width(ww, tl.gx), hx = tsx >> 1;
   const int y0 = tl.y * tsy, x0 = tl.x * tsx;
   const int q = wave_basis(tl.z), lane = threadIdx.x & 63;
   float* s_x = s_all[threadIdx.x >> 6];
@@ -413,7 +433,7 @@ __device__ __forceinline__ void idwt_block(TileId tl, const float* __restrict__ 
     constexpr int Q = decltype(ql)::value;
     float h[2 * Q], gf[2 * Q];
     load_filt<Q>(filt, h, gf);
-    synth_cols<Q, false>(h, gf, bd, y0 >> 1, x0 >> 1, hx, nullptr, s_x);
+    synth_cols<Q, false, WM>(h, gf, bd, y0 >> 1, x0 >> 1, hx, nullptr, s_x);
     wave_sync();
     const int G = (hx + 3) >> 2;
     for (int i = lane; i < tsy * G; i += 64) {
@@ -433,6 +453,7 @@ __device__ __forceinline__ void idwt_block(TileId tl, const float* __restrict__ 
 // SARA's chain of dependent launches.
 static_assert(WROWS <= SY && WCOLS <= SS && WCOLS / 2 + 7 <= SS, "the window is an inner tile of its own");
 
+template <int WM>
 __device__ __forceinline__ void idwt2_block(TileId tl, const float* __restrict__ u, float* __restrict__ rec,
                                             const float* __restrict__ filt, const float* __restrict__ W,
                                             const SaraGeom& g) {
@@ -440,7 +461,7 @@ __device__ __forceinline__ void idwt2_block(TileId tl, const float* __restrict__
   __shared__ __align__(16) float w_all[4][WROWS * WCOLS];
   const int l = g.L - 1;                                      // outer level
   const int hh = g.ny >> (l - 1), ww = g.nx >> (l - 1);
-  const int tsy = min(SY, hh), tsx = min(SX, ww), hx = tsx >> 1;
+  const int tsy = min(SY, hh), tsx = tile_width(ww, tl.gx), hx = tsx >> 1;
   const int y0 = tl.y * tsy, x0 = tl.x * tsx;
   const int q = wave_basis(tl.z), lane = threadIdx.x & 63;
   float* s_x = s_all[threadIdx.x >> 6];
@@ -459,7 +480,7 @@ __device__ __forceinline__ void idwt2_block(TileId tl, const float* __restrict__
     const int offy = wy0 - ya, offx = wx0 - xa;
     const int hxi = (hx + Q - 1 + offx + 1) >> 1;             // inner coefficient columns
     // level L: its low-pass band and details are coefficients (in u, weighted)
-    synth_cols<Q, false>(h, gf, bi, ya >> 1, xa >> 1, hxi, nullptr, s_x);
+    synth_cols<Q, false, WM>(h, gf, bi, ya >> 1, xa >> 1, hxi, nullptr, s_x);
     wave_sync();
     const int Gi = (hxi + 3) >> 2;
     for (int i = lane; i < WROWS * Gi; i += 64) {
@@ -470,7 +491,7 @@ __device__ __forceinline__ void idwt2_block(TileId tl, const float* __restrict__
       *reinterpret_cast<float4*>(s_w + row * WCOLS + 8 * mg + 4) = make_float4(o[4], o[5], o[6], o[7]);
     }
     wave_sync();
-    synth_cols<Q, true>(h, gf, bo, j0, c0, hx, s_w + offy * WCOLS + offx, s_x);
+    synth_cols<Q, true, WM>(h, gf, bo, j0, c0, hx, s_w + offy * WCOLS + offx, s_x);
     wave_sync();
     const int G = (hx + 3) >> 2;
     for (int i = lane; i < tsy * G; i += 64) {
@@ -485,13 +506,14 @@ __device__ __forceinline__ void idwt2_block(TileId tl, const float* __restrict__
 // Level 1 for all 8 wavelet bases, plus the Dirac part, times 1/3.  Wave w of
 // the workgroup takes bases 8 - w and 1 + w (the same number of taps in every
 // wave) on the same tile; their sums are added in wave order.
+template <int WM>
 __device__ __forceinline__ void idwt_final_block(TileId tl, const float* __restrict__ u, const float* __restrict__ rec,
                                                  const float* __restrict__ filt, const float* __restrict__ W,
                                                  const SaraGeom& g, float* __restrict__ out, int vec) {
   __shared__ __align__(16) float s_all[4][2 * SY * SS];
   static_assert(SY * SX <= 2 * SY * SS, "a wave's sums take the place of its columns");
   constexpr int IPL = SY * (SX / 8) / 64;   // runs of 8 outputs per lane
-  const int nx = g.nx, tsx = min(SX, nx), hx = tsx >> 1;   // images are at least 16 x 16
+  const int nx = g.nx, tsx = tile_width(nx, tl.gx), hx = tsx >> 1;   // images are at least 16 x 16
   const int y0 = tl.y * SY, x0 = tl.x * tsx;
   const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = threadIdx.x & 63;
   float* s_x = s_all[w];
@@ -507,7 +529,7 @@ __device__ __forceinline__ void idwt_final_block(TileId tl, const float* __restr
       constexpr int Q = decltype(ql)::value;
       float h[2 * Q], gf[2 * Q];
       load_filt<Q>(filt, h, gf);
-      synth_cols<Q, false>(h, gf, bd, j0, c0, hx, nullptr, s_x);
+      synth_cols<Q, false, WM>(h, gf, bd, j0, c0, hx, nullptr, s_x);
       wave_sync();
 #pragma unroll
       for (int n = 0; n < IPL; ++n) {
@@ -529,7 +551,7 @@ __device__ __forceinline__ void idwt_final_block(TileId tl, const float* __restr
     const size_t P = size_t(y0 + run / G) * nx + (x0 + 8 * (run % G) + k0);
     float d[4], v[4];
     load4(u + P, vec, 4, d);
-    if (W) {
+    if (WM != W_NONE) {
       float wv[4];
       load4(W + P, vec, 4, wv);
 #pragma unroll
@@ -557,13 +579,18 @@ __device__ __forceinline__ void sara_dwt_part(const SaraJob& j, int lin) {
                        j.lambda, j.active, j.vec);
 }
 // One synthesis launch: the two coarsest levels, one level, or the last one.
+template <int KIND, int WM>
+__device__ __forceinline__ void sara_synth_weighted(const SaraJob& j, TileId tl) {
+  if constexpr (KIND == SARA_IDWT2) idwt2_block<WM>(tl, j.in, j.tmp, j.filt, j.W, j.g);
+  else if constexpr (KIND == SARA_IDWT) idwt_block<WM>(tl, j.in, j.tmp, j.filt, j.W, j.g, j.l);
+  else idwt_final_block<WM>(tl, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
+}
 template <int KIND>
 __device__ __forceinline__ void sara_synth_part(const SaraJob& j, int lin) {
   if (threadIdx.x >= 256) return;
   const TileId tl = sara_tile<false>(lin, j.gx, j.gy, j.gz);
-  if constexpr (KIND == SARA_IDWT2) idwt2_block(tl, j.in, j.tmp, j.filt, j.W, j.g);
-  else if constexpr (KIND == SARA_IDWT) idwt_block(tl, j.in, j.tmp, j.filt, j.W, j.g, j.l);
-  else idwt_final_block(tl, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
+  if (j.W) sara_synth_weighted<KIND, W_AHEAD>(j, tl);
+  else sara_synth_weighted<KIND, W_NONE>(j, tl);
 }
 
 }  // namespace
