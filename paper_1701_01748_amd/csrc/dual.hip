@@ -520,12 +520,35 @@ __device__ __forceinline__ bool sec_done(double nu, double nu0) {
   return nu == nu0 || fabs(nu - nu0) <= 0x1p-50 * nu;
 }
 
+// Waits for the two tagged partials of a slot at once; false after a give-up.
+__device__ bool sec_wait(uint64_t* slot, uint64_t tag, uint32_t* flag, int spin_limit, double& v2, double& v3) {
+  int polls = 0;
+  while (true) {
+    const uint64_t b2 = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t b3 = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (b2 != PA_EMPTY && b3 != PA_EMPTY && (b2 & PA_SIGN) == tag && (b3 & PA_SIGN) == tag) {
+      v2 = __longlong_as_double(int64_t(b2 & ~PA_SIGN));
+      v3 = __longlong_as_double(int64_t(b3 & ~PA_SIGN));
+      return true;
+    }
+    if ((polls & 31) == 31 && __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return false;
+    if (++polls > spin_limit) {
+      __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return false;
+    }
+#if PPD_PA_SLEEP > 0
+    __builtin_amdgcn_s_sleep(PPD_PA_SLEEP);
+#endif
+  }
+}
+
 template <int PER>
 __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
   static_assert(PA_THREADS == 256, "partials are summed over exactly 4 waves");
-  __shared__ double red[PA_THREADS / 64][PA_MAXB][2];
-  __shared__ double s_nu[PA_MAXB];
-  __shared__ int done[PA_MAXB], quit, last_out;
+  constexpr int WAVES = PA_THREADS / 64;
+  __shared__ double red[2][WAVES][PA_MAXB][2];   // partials of the even and the odd steps
+  __shared__ double s_nu[WAVES][PA_MAXB];        // every wave takes the Newton steps itself
+  __shared__ int done[WAVES][PA_MAXB], left[2][WAVES], quit[2], last_out, gave_up;
   const int g = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int64_t i0 = int64_t(g) * PER * PA_THREADS;
@@ -549,17 +572,22 @@ __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
       sl[k] = b;
     }
   }
-  if (tid < PA_MAXB) {
-    s_nu[tid] = 0.0;
-    done[tid] = tid >= nb;
+  if (lane < PA_MAXB) {
+    s_nu[wid][lane] = 0.0;
+    done[wid][lane] = lane >= nb;
   }
-  if (tid == 0) quit = 0;
+  if (tid < 2) quit[tid] = 0;
+  if (lane == 0) left[1][wid] = 1;
   __syncthreads();
+  // One barrier a step: behind it the waves know of each other's partials and
+  // of the step before, whether a wave gave up and whether a block is left (in
+  // two copies, as a wave may be a step ahead of another's reading).
   for (int s = 0; s < a.steps; ++s) {
+    const int h = s & 1;
     // the workgroup's partials per block, summed in a fixed order
     for (int b = 0; b < nb; ++b) {
-      if (done[b]) continue;
-      const double nu = s_nu[b];
+      if (done[wid][b]) continue;
+      const double nu = s_nu[wid][b];
       double t2 = 0.0, t3 = 0.0;
 #pragma unroll
       for (int k = 0; k < PER; ++k) {
@@ -571,12 +599,13 @@ __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
       t2 = wave_sum(t2);
       t3 = wave_sum(t3);
       if (lane == 0) {
-        red[wid][b][0] = t2;
-        red[wid][b][1] = t3;
+        red[h][wid][b][0] = t2;
+        red[h][wid][b][1] = t3;
       }
     }
     __syncthreads();
-    uint64_t* part = a.part + size_t(s & 1) * size_t(a.G) * (2 * PA_MAXB);
+    if (quit[h ^ 1] || !(left[h ^ 1][0] | left[h ^ 1][1] | left[h ^ 1][2] | left[h ^ 1][3])) break;   // uniform
+    uint64_t* part = a.part + size_t(h) * size_t(a.G) * (2 * PA_MAXB);
     const uint64_t tag = (s & 2) ? PA_SIGN : 0ull;
     if (wid == 0) {
       // as in k_alg2_persistent: this wave's earlier exchanges are
@@ -584,53 +613,48 @@ __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
       __builtin_amdgcn_s_waitcnt(0);
       __atomic_signal_fence(__ATOMIC_SEQ_CST);
     }
-    if (tid < 2 * nb && !done[tid >> 1]) {
+    if (tid < 2 * nb && !done[0][tid >> 1]) {
       const int b = tid >> 1, q = tid & 1;
-      const double p = ((red[0][b][q] + red[1][b][q]) + red[2][b][q]) + red[3][b][q];
+      const double p = ((red[h][0][b][q] + red[h][1][b][q]) + red[h][2][b][q]) + red[h][3][b][q];
       uint64_t bits = uint64_t(__double_as_longlong(p)) & ~PA_SIGN;
       if (bits == PA_EMPTY) bits |= 1ull;   // a NaN partial must not read as an empty slot
       (void)__hip_atomic_exchange(&part[size_t(g) * (2 * PA_MAXB) + tid], bits | tag, __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_AGENT);
     }
+    // the same in every wave of every workgroup of a block
+    int any = 0;
     for (int b = 0; b < nb; ++b) {
-      if (done[b]) continue;   // uniform: written before a barrier
+      if (done[wid][b]) continue;
       const int j = b0 + b;
       double t2 = 0.0, t3 = 0.0;
       int bad = 0;
-      for (int gg = a.gfirst[j] + tid; gg <= a.glast[j] && !bad; gg += PA_THREADS) {
-        uint64_t* slot = &part[size_t(gg) * (2 * PA_MAXB) + 2 * (j - a.wgb0[gg])];
-        const double v2 = pa_wait(slot, tag, &a.sync[3], a.spin_limit);
-        const double v3 = v2 < 0.0 ? -1.0 : pa_wait(slot + 1, tag, &a.sync[3], a.spin_limit);
-        if (v3 < 0.0) {
-          bad = 1;
-        } else {
+      for (int gg = a.gfirst[j] + lane; gg <= a.glast[j] && !bad; gg += 64) {
+        double v2, v3;
+        if (sec_wait(&part[size_t(gg) * (2 * PA_MAXB) + 2 * (j - a.wgb0[gg])], tag, &a.sync[3], a.spin_limit, v2, v3)) {
           t2 += v2;
           t3 += v3;
+        } else {
+          bad = 1;
         }
       }
       t2 = wave_sum(t2);
       t3 = wave_sum(t3);
-      __syncthreads();   // red[..][0] and done[b] have been read
+      if (bad) quit[h] = 1;
+      const double nu0 = s_nu[wid][b], nu = newton_step(t2, t3, a.eps[j], nu0);
+      const bool end = sec_done(nu, nu0);
+      any |= !end;
+      wave_sync();   // every lane has read the wave's nu
       if (lane == 0) {
-        red[wid][0][0] = t2;
-        red[wid][0][1] = t3;
+        s_nu[wid][b] = nu;
+        done[wid][b] = end;
       }
-      if (bad) quit = 1;
-      __syncthreads();
-      if (tid == 0) {
-        const double nu = newton_step(((red[0][0][0] + red[1][0][0]) + red[2][0][0]) + red[3][0][0],
-                                      ((red[0][0][1] + red[1][0][1]) + red[2][0][1]) + red[3][0][1], a.eps[j], s_nu[b]);
-        done[b] = sec_done(nu, s_nu[b]);
-        s_nu[b] = nu;
-      }
+      wave_sync();
     }
-    __syncthreads();
-    bool left = false;
-    for (int b = 0; b < nb; ++b) left |= !done[b];
-    if (quit || !left) break;   // uniform: read after the barrier
+    if (lane == 0) left[h][wid] = any;
   }
+  __syncthreads();
   // stored by the first workgroup of each block (all others hold the same)
-  if (tid < nb && a.gfirst[b0 + tid] == g && !quit) sec_store(a, b0 + tid, s_nu[tid]);
+  if (tid < nb && a.gfirst[b0 + tid] == g && !(quit[0] | quit[1])) sec_store(a, b0 + tid, s_nu[0][tid]);
   // what each wave stored (partials, results, the flag) is acknowledged before
   // the exit is counted
   __builtin_amdgcn_s_waitcnt(0);
@@ -648,10 +672,10 @@ __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
     __hip_atomic_store(&a.part[e], PA_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (tid == 0) {
     __hip_atomic_store(&a.sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    quit = int(__hip_atomic_exchange(&a.sync[3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    gave_up = int(__hip_atomic_exchange(&a.sync[3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   }
   __syncthreads();
-  if (!quit) return;
+  if (!gave_up) return;
   for (int j = 0; j < a.d; ++j) {
     double nu = 0.0;
     for (int s = 0; s < a.steps; ++s) {
@@ -665,13 +689,13 @@ __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
       t3 = wave_sum(t3);
       __syncthreads();
       if (lane == 0) {
-        red[wid][0][0] = t2;
-        red[wid][0][1] = t3;
+        red[0][wid][0][0] = t2;
+        red[0][wid][0][1] = t3;
       }
       __syncthreads();
       const double nu0 = nu;
-      nu = newton_step(((red[0][0][0] + red[1][0][0]) + red[2][0][0]) + red[3][0][0],
-                       ((red[0][0][1] + red[1][0][1]) + red[2][0][1]) + red[3][0][1], a.eps[j], nu0);
+      nu = newton_step(((red[0][0][0][0] + red[0][1][0][0]) + red[0][2][0][0]) + red[0][3][0][0],
+                       ((red[0][0][0][1] + red[0][1][0][1]) + red[0][2][0][1]) + red[0][3][0][1], a.eps[j], nu0);
       if (sec_done(nu, nu0)) break;   // the same in every thread
     }
     if (tid == 0) sec_store(a, j, nu);
