@@ -77,10 +77,10 @@ def measured_traffic(kind: str, workload: str, tile: int, chunk: int):
     return (fetch + write) * 1024.0
 
 
-# kernel kind -> the kernel's name in a rocprofv3 summary (fused iteration, 8 x 8 tiles)
-KIND_KERNEL = {"degrid": "k_degrid<8, true>", "grid": "k_grid_mfma<true>", "fold": "k_fold8",
-               "fft_rows_fwd": "k_fft_rows_fwd", "fft_cols_fwd": "k_fft_cols_fwd", "fft_cols_inv": "k_fft_cols_inv",
-               "fft_rows_inv": "k_fft_rows_inv<true, true>"}
+# kernel kind -> the kernel's name in a rocprofv3 summary (fused iteration at 512^2, 8 x 8 tiles)
+KIND_KERNEL = {"degrid": "k_degrid<8, 1, 1>", "grid": "k_grid_mfma<true, 1>", "fold": "k_fold8",
+               "fft_rows_fwd": "k_fft_rows_fwd<1024>", "fft_cols_fwd": "k_fft_cols_fwd<1024>",
+               "fft_cols_inv": "k_fft_cols_inv<1024>", "fft_rows_inv": "k_fft_rows_inv<1024, true>"}
 
 
 def rocprof_avg_us(kind: str, workload: str, tile: int, chunk: int):
@@ -109,16 +109,17 @@ def rocprof_avg_us(kind: str, workload: str, tile: int, chunk: int):
 
 
 def algorithmic_bytes(kind: str, M: int, N: int, K: int, ny: int, Kx: int) -> float:
-    """Bytes each kernel kind must move per launch (fused PPD iteration)."""
+    """Bytes each kernel kind must move per launch (fused PPD iteration).  K:
+    cells of the half spectrum that is held; the row pass holds ny Kx / 2."""
     if kind == "degrid":      # omega 8, v 8, U 8, z 16, y 8 in; Theta G a 8 out; grid read once
         return 56.0 * M + 8.0 * K
     if kind == "grid":        # omega 8, Theta G a 8, z 16, U 8, y 8, v 8 in; z 16, v 8 out; grid written once
         return 80.0 * M + 8.0 * K
     if kind == "fft_rows_fwd":
-        return 4.0 * N + 8.0 * ny * Kx
+        return 4.0 * N + 4.0 * ny * Kx
     if kind in ("fft_cols_fwd", "fft_cols_inv"):
-        return 8.0 * ny * Kx + 8.0 * K
-    if kind == "fft_rows_inv":  # half in; x, u~ in; x, x~ out
+        return 4.0 * ny * Kx + 8.0 * K
+    if kind == "fft_rows_inv":  # half in; x, u~ in; x, x~ and the next half out
         return 8.0 * ny * Kx + 16.0 * N
     if kind == "zero":
         return 8.0 * K
@@ -187,7 +188,7 @@ def main():
         (args.tile, args.chunk), tuned = tune.autotune(n, n, wu, wv, off, stream)
     plan = P.Plan(n, n, wu, wv, off, stream=stream, tile=args.tile, chunk=args.chunk)
     info = plan.info
-    K, Kx = info.Kx * info.Ky, info.Kx
+    K, Kx = (info.Kx // 2 + 16) * info.Ky, info.Kx   # cells held: half of the spectrum and its padding columns
     perm = plan.permutation()
 
     # ---- problem setup on the GPU (not timed) --------------------------------
@@ -320,7 +321,7 @@ def main():
         xb = torch.empty((n, n), dtype=torch.float32, device="cuda")
         t_phi = time_calls(lambda: P.ppd_phi(plan, x_true, yb))
         t_phit = time_calls(lambda: P.ppd_phit(plan, y, xb))
-        phi_bytes = 4.0 * N + 16.0 * M + 8.0 * n * Kx + 16.0 * K
+        phi_bytes = 4.0 * N + 16.0 * M + 4.0 * n * Kx + 16.0 * K
         out["phi_vis_per_s"] = round(M / t_phi, 1)
         out["phit_vis_per_s"] = round(M / t_phit, 1)
         out["phi_us"] = round(t_phi * 1e6, 2)
