@@ -281,9 +281,9 @@ typedef struct {
                                       can make a wait give up);
                                       PPD_PERSIST_OFF (1): one launch pair
                                       per step.  PPD_PROX_EXACT: under the
-                                      same conditions (to 3M visibilities) its
-                                      Newton steps run as one launch; a wait of
-                                      it that gives up costs time only       */
+                                      same conditions its Newton steps run as
+                                      one launch; a wait of it that gives up
+                                      costs time only                        */
   int32_t spin_limit;              /* polls of one wait of the persistent
                                       launch before it gives up (0: 2^20);
                                       a give-up

@@ -884,9 +884,9 @@ static int resident_groups(const void* kernel) {
 
 int sec_persistent_capacity(int per) { return resident_groups(reinterpret_cast<const void*>(sec_kernel(per))); }
 
-// Polls of one wait before the last workgroup out solves alone: a poll sleeps
-// 64 clocks, so at least 7 ms, where a step takes 4 us.
-constexpr int SEC_SPIN = 1 << 18;
+// Polls of one wait before the last workgroup out solves alone: tens of
+// milliseconds, where a step takes 4 us.
+constexpr int SEC_SPIN = 1 << 16;
 
 static int secular_persistent(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
                               const double* U, int n_newton, int spin_limit) {
