@@ -36,12 +36,12 @@ __device__ __forceinline__ int linear_block() {
   return int(blockIdx.x) + int(gridDim.x) * (int(blockIdx.y) + int(gridDim.y) * int(blockIdx.z));
 }
 
-template <int MODE, int RB>
+template <int MODE, int RB, bool HW>
 __global__ __launch_bounds__(DWT_THREADS) void k_dwt(const float* __restrict__ x, float* __restrict__ tmp,
                                                      float* __restrict__ out, const float* __restrict__ filt,
                                                      const float* __restrict__ W, SaraGeom g, int l, float alpha,
                                                      float lambda, const uint8_t* __restrict__ active, int vec) {
-  dwt_block<MODE, RB>(sara_tile<true>(linear_block(), gridDim.x, gridDim.y, gridDim.z), x, tmp, out, filt, W, g, l,
+  dwt_block<MODE, RB, HW>(sara_tile<true>(linear_block(), gridDim.x, gridDim.y, gridDim.z), x, tmp, out, filt, W, g, l,
                       alpha, lambda, active, vec);
 }
 
@@ -112,8 +112,9 @@ bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0;
 template <int MODE, int RB>
 void launch_dwt(ppd_plan* p, dim3 grid, const float* x, float* out, const float* W, const SaraGeom& g, int l,
                 float alpha, float lambda, const uint8_t* active, int vec) {
-  hipLaunchKernelGGL((k_dwt<MODE, RB>), grid, dim3(DWT_THREADS), 0, p->stream, x, p->sara_ll, out, p->filt, W, g, l,
-                     alpha, lambda, active, vec);
+  auto kernel = W ? k_dwt<MODE, RB, true> : k_dwt<MODE, RB, false>;
+  hipLaunchKernelGGL(kernel, grid, dim3(DWT_THREADS), 0, p->stream, x, p->sara_ll, out, p->filt, W, g, l, alpha, lambda,
+                     active, vec);
 }
 
 int analysis_launch(ppd_plan* p, const float* x, float* out, const float* W, bool dual, float alpha,
@@ -200,8 +201,7 @@ int sara_launch(ppd_plan* p, const SaraJob& j) {
     hipLaunchKernelGGL(!j.W ? none : ahead ? before : after, grid, dim3(256), 0, p->stream, args...);
   };
   if (j.kind == SARA_DWT)
-    hipLaunchKernelGGL((k_dwt<A_DUAL, 4>), grid, dim3(DWT_THREADS), 0, p->stream, j.in, j.tmp, j.out, j.filt, j.W, j.g,
-                       j.l, j.alpha, j.lambda, j.active, j.vec);
+    launch_dwt<A_DUAL, 4>(p, grid, j.in, j.out, j.W, j.g, j.l, j.alpha, j.lambda, j.active, j.vec);
   else if (j.kind == SARA_IDWT2)
     synth(k_idwt2<W_NONE>, k_idwt2<W_AFTER>, k_idwt2<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g);
   else if (j.kind == SARA_IDWT)

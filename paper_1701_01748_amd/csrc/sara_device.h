@@ -90,8 +90,8 @@ __device__ __forceinline__ void store4(float* __restrict__ p, bool vec, int n, c
 
 // One analysis level of basis db-Q on one output tile: columns (axis 0), then
 // rows (axis 1).  a[k] = sum_n h[n] s[(2k + n) mod L], d[k] likewise with g.
-// A column run makes RB outputs of either filter.
-template <int Q, int MODE, int RB>
+// A column run makes RB outputs of either filter.  HW: there are weights.
+template <int Q, int MODE, int RB, bool HW>
 __device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstride, float scale, int hh, int ww,
                                          int k0y, int k0x, int toy, int tox, const float* __restrict__ filt,
                                          float* s_lo, float* s_hi, float* __restrict__ ub,
@@ -112,8 +112,12 @@ __device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstr
                          size_t(r) * nx + c};
   const int nout = llout ? 3 : 4;
   float uo[4][4], wo[4][4];
-  constexpr bool AHEAD = RB == 4;   // low tiles: too few waves to hide the weights' latency
-  if (AHEAD && wb && mine) {
+  // The weights too, where their latency is not hidden (low tiles are few waves)
+  // or where the registers are there (the dual mode's four waves per SIMD: a
+  // weighted dual step at 2048^2 293 -> 267 us, 1024^2 77.8 -> 75.1; plain
+  // analysis, seven waves before, 115 -> 127).
+  constexpr bool AHEAD = HW && (RB == 4 || MODE == A_DUAL);
+  if (AHEAD && mine) {
 #pragma unroll
     for (int b = 0; b < 4; ++b)
       if (b < nout) load4(wb + pos[b], vec, nv, wo[b]);
@@ -177,7 +181,7 @@ __device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstr
   for (int b = 0; b < 4; ++b) {
     if (b >= nout) break;
     float o[4];
-    if (wb) {
+    if (HW) {
       if (!AHEAD) load4(wb + pos[b], vec, nv, wo[b]);
 #pragma unroll
       for (int m = 0; m < 4; ++m) o[m] = cv[b][m] * wo[b][m];
@@ -199,7 +203,7 @@ __device__ __forceinline__ void dwt_tile(const float* __restrict__ src, int sstr
 // the bases updated this iteration.  Level 1 reads the image scaled by 1/3,
 // deeper levels the low-pass band of the previous level.  vec: every array is
 // 16-byte aligned and a level's rows are whole float4s.
-template <int MODE, int RB>
+template <int MODE, int RB, bool HW>
 __device__ __forceinline__ void dwt_block(TileId tl, const float* __restrict__ x, float* __restrict__ tmp,
                                           float* __restrict__ out, const float* __restrict__ filt,
                                           const float* __restrict__ W, const SaraGeom& g, int l, float alpha,
@@ -226,7 +230,7 @@ __device__ __forceinline__ void dwt_block(TileId tl, const float* __restrict__ x
       const size_t P = size_t(2 * k0y + a) * g.nx + (2 * k0x + 4 * (i - a * F));
       float xv[4], wv[4] = {1.f, 1.f, 1.f, 1.f}, uo[4], o[4];
       load4(x + P, vec, 4, xv);
-      if (W) load4(W + P, vec, 4, wv);
+      if (HW) load4(W + P, vec, 4, wv);
       if (MODE == A_DUAL) load4(out + P, vec, 4, uo);
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
@@ -241,11 +245,11 @@ __device__ __forceinline__ void dwt_block(TileId tl, const float* __restrict__ x
   const int sstride = l == 1 ? g.nx : ww;
   const float scale = l == 1 ? third : 1.0f;
   float* ub = out + size_t(q) * g.N;
-  const float* wb = W ? W + size_t(q) * g.N : nullptr;
+  const float* wb = HW ? W + size_t(q) * g.N : nullptr;
   float* llout = l == g.L ? nullptr : tmp + g.off[l] + size_t(q - 1) * lvl_size(g, l);
 #define PPD_DWT_CASE(Q)                                                                                       \
   case Q:                                                                                                     \
-    dwt_tile<Q, MODE, RB>(src, sstride, scale, hh, ww, k0y, k0x, toy, tox, filt, s_lo, s_hi, ub, wb, g.nx, oh, \
+    dwt_tile<Q, MODE, RB, HW>(src, sstride, scale, hh, ww, k0y, k0x, toy, tox, filt, s_lo, s_hi, ub, wb, g.nx, oh, \
                           ow, llout, alpha, lambda, vec != 0);                                                \
     break;
   switch (q) {
@@ -575,8 +579,11 @@ __device__ __forceinline__ void idwt_final_block(TileId tl, const float* __restr
 // instead.  Waves beyond the workgroup size of their part end at once.
 __device__ __forceinline__ void sara_dwt_part(const SaraJob& j, int lin) {
   if (threadIdx.x >= DWT_THREADS) return;
-  dwt_block<A_DUAL, 4>(sara_tile<true>(lin, j.gx, j.gy, j.gz), j.in, j.tmp, j.out, j.filt, j.W, j.g, j.l, j.alpha,
-                       j.lambda, j.active, j.vec);
+  const TileId tl = sara_tile<true>(lin, j.gx, j.gy, j.gz);
+  if (j.W)
+    dwt_block<A_DUAL, 4, true>(tl, j.in, j.tmp, j.out, j.filt, j.W, j.g, j.l, j.alpha, j.lambda, j.active, j.vec);
+  else
+    dwt_block<A_DUAL, 4, false>(tl, j.in, j.tmp, j.out, j.filt, nullptr, j.g, j.l, j.alpha, j.lambda, j.active, j.vec);
 }
 // One synthesis launch: the two coarsest levels, one level, or the last one.
 template <int KIND, int WM>
