@@ -194,21 +194,19 @@ SaraJobs sara_jobs(ppd_plan* p, const float* x, float* u, float alpha, float lam
 
 int sara_launch(ppd_plan* p, const SaraJob& j) {
   const dim3 grid(j.gx, j.gy, j.gz);
-  // the weights ahead of the values where the waves are few: in tiles below 64 columns
-  const int ww = j.g.nx >> (j.l - 1);
-  const bool ahead = ww / j.gx < SX;
-  auto synth = [&](auto none, auto after, auto before, auto... args) {
-    hipLaunchKernelGGL(!j.W ? none : ahead ? before : after, grid, dim3(256), 0, p->stream, args...);
+  auto synth = [&](auto plain, auto weighted, auto... args) {
+    hipLaunchKernelGGL(j.W ? weighted : plain, grid, dim3(256), 0, p->stream, args...);
   };
   if (j.kind == SARA_DWT)
     launch_dwt<A_DUAL, 4>(p, grid, j.in, j.out, j.W, j.g, j.l, j.alpha, j.lambda, j.active, j.vec);
   else if (j.kind == SARA_IDWT2)
-    synth(k_idwt2<W_NONE>, k_idwt2<W_AFTER>, k_idwt2<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g);
+    synth(k_idwt2<W_NONE>, k_idwt2<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g);
   else if (j.kind == SARA_IDWT)
-    synth(k_idwt<W_NONE>, k_idwt<W_AFTER>, k_idwt<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g, j.l);
+    // a single level's weights ahead cost a wave per SIMD: only where waves are few, in tiles below 64 columns
+    synth(k_idwt<W_NONE>, (j.g.nx >> (j.l - 1)) / j.gx < SX ? k_idwt<W_AHEAD> : k_idwt<W_AFTER>, j.in, j.tmp, j.filt,
+          j.W, j.g, j.l);
   else
-    synth(k_idwt_final<W_NONE>, k_idwt_final<W_AFTER>, k_idwt_final<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g, j.out,
-          j.vec);
+    synth(k_idwt_final<W_NONE>, k_idwt_final<W_AHEAD>, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
