@@ -145,13 +145,14 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factors(const double* __re
 }
 
 // The same after an analysis level of SARA in the first workgroups.
+template <bool HW>
 __global__ __launch_bounds__(BF_THREADS) void k_block_factors_dwt(const double* __restrict__ part,
                                                                   const int32_t* __restrict__ bids,
                                                                   const int32_t* __restrict__ boff,
                                                                   const double* __restrict__ eps,
                                                                   double2* __restrict__ bfac, SaraJob job) {
   const int b = int(blockIdx.x) - job.blocks();
-  if (b < 0) sara_dwt_part(job, blockIdx.x);
+  if (b < 0) sara_dwt_part<HW>(job, blockIdx.x);
   else block_factor(b, part, bids, boff, eps, bfac);
 }
 
@@ -484,9 +485,9 @@ __global__ __launch_bounds__(SEC_THREADS) void k_sec_update(const double* __rest
 // relative step of 2^-50 puts r within that of eps (-g / g' >= (r / eps - 1)
 // nu), and the steps left would only repeat its rounding.  So a solve costs
 // the steps its blocks need, n_newton at most, and none costs a launch: at
-// 512 x 256, 200003 points and 12 steps one launch of 25.5 us instead of 13 of
-// 4.2 and the gaps between them; ten eager iterations 1680 (with the launches
-// of today's other kernels 1291) -> 1065 us.
+// 512 x 256, 200003 points and 12 steps one launch of 24.5 us instead of 13 of
+// 4.2 and the gaps between them; ten eager iterations 1291 -> 1065 us,
+// and with one barrier a step 1008.
 // A wait that gives up costs time, not the result: the workgroups run to the
 // end and the last one out solves all blocks alone, from memory.  So other
 // work on the device, and workgroups that are not resident at once, are no
@@ -975,7 +976,7 @@ int block_factors(ppd_plan* p, const double* part, const SaraJob* with) {
   int slot;
   PPD_TRY(timer_begin(p, KK_MISC, &slot));
   if (with)
-    hipLaunchKernelGGL(k_block_factors_dwt, dim3(p->d + with->blocks()), dim3(BF_THREADS), 0, p->stream, part,
+    hipLaunchKernelGGL((with->W ? k_block_factors_dwt<true> : k_block_factors_dwt<false>), dim3(p->d + with->blocks()), dim3(BF_THREADS), 0, p->stream, part,
                        p->bseg_ids, p->bseg_off_d, p->eps_d, p->bfac, *with);
   else
     hipLaunchKernelGGL(k_block_factors, dim3(p->d), dim3(BF_THREADS), 0, p->stream, part, p->bseg_ids, p->bseg_off_d,

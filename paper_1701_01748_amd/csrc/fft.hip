@@ -379,12 +379,12 @@ __global__ __launch_bounds__(ColCfg<L>::THREADS) void k_fft_cols_fwd(const float
 }
 
 // The same after an analysis level of SARA in the first workgroups.
-template <int L>
+template <int L, bool HW>
 __global__ __launch_bounds__(std::max(ColCfg<L>::THREADS, DWT_THREADS)) void k_fft_cols_fwd_dwt(
     int nblocks, const float2* __restrict__ half, const float2* __restrict__ tw, int Hx, int ngroups,
     float2* __restrict__ grid, SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
-  if (b < 0) sara_dwt_part(j, blockIdx.x);
+  if (b < 0) sara_dwt_part<HW>(j, blockIdx.x);
   else if (threadIdx.x < ColCfg<L>::THREADS) cols_fwd_block<L>(b, nblocks, half, tw, Hx, ngroups, grid);
 }
 
@@ -631,7 +631,8 @@ int fft_cols_forward(ppd_plan* p, const float2* src, const SaraJob* with) {
     const ColLaunch<L> c(p);
     if (with) {
       if constexpr (L <= PAIR_MAX_KY) {
-        hipLaunchKernelGGL(k_fft_cols_fwd_dwt<L>, dim3(c.blocks + with->blocks()),
+        auto kernel = with->W ? k_fft_cols_fwd_dwt<L, true> : k_fft_cols_fwd_dwt<L, false>;
+        hipLaunchKernelGGL(kernel, dim3(c.blocks + with->blocks()),
                            dim3(std::max(ColCfg<L>::THREADS, DWT_THREADS)), 0, p->stream, c.blocks, src, p->twy,
                            p->Kx / 2, c.groups, p->grid_f, *with);
       } else {

@@ -284,7 +284,7 @@ int paired_iteration(ppd_plan* p, const IterCtx& c) {
 // stays on the plan's stream (no queue hand-off at its start); captured
 // into a graph, the data path is forked: replayed graphs put a forked SARA
 // branch's join, and with it the primal update, on the other hardware queue
-// (measured 142.5 against 132.7 us per iteration at 512^2).
+// (142.5 against 132.7 us per iteration at 512^2, when one took that long).
 int one_iteration(ppd_plan* p, const IterCtx& c) {
   if (c.paired) return paired_iteration(p, c);
   PPD_HIP(hipEventRecord(p->ev_fork, p->stream));
@@ -476,9 +476,9 @@ extern "C" int ppd_iterate(ppd_plan* p, ppd_state* st, const ppd_params* prm, in
       // iterations are replayed in captured runs: with periodic statistics,
       // a period of `every` iterations whose last one reduces them (slot 3);
       // otherwise runs of GRAPH_RUN iterations without partials (slot 3);
-      // the rest one at a time (slots 0-2).  Measured at 512^2: 143.9 us per
-      // iteration replayed one at a time, 137.9 in periods of 10, 137.0
-      // eager.
+      // the rest one at a time (slots 0-2).  Measured at 512^2, when an
+      // iteration took 137 us: 143.9 replayed one at a time, 137.9 in
+      // periods of 10.
       int t = 0;
       while (t < n_iter) {
         hipGraphExec_t ex = nullptr;

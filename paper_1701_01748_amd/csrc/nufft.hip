@@ -335,6 +335,7 @@ __global__ __launch_bounds__(64 * NW) void k_degrid(
 
 // The shared 8 x 8 items in the dual mode, after an analysis level of SARA in
 // the first workgroups.
+template <bool HW>
 __global__ __launch_bounds__(DWT_THREADS) void k_degrid_dwt(
     const float2* __restrict__ grid, int PW, int Ky, const Item* __restrict__ items, int n_items,
     const Seg* __restrict__ segs, const float* __restrict__ wu, const float* __restrict__ wv,
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(DWT_THREADS) void k_degrid_dwt(
     SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
   if (b < 0)
-    sara_dwt_part(j, blockIdx.x);
+    sara_dwt_part<HW>(j, blockIdx.x);
   else if (threadIdx.x < 128)
     degrid_block<8, DEGRID_DUAL, 2>(b, grid, PW, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc,
                                     nullptr, nullptr, y, U, v, z, gout, mu, part, rpart, xs);
@@ -773,7 +774,7 @@ __global__ __launch_bounds__(64 * NW) void k_grid_mfma(
 
 // The shared items in the dual mode, after a synthesis launch of SARA in the
 // first workgroups.
-template <int KIND>
+template <int KIND, bool HW>
 __global__ __launch_bounds__(256) void k_grid_synth(
     float2* __restrict__ scratch, int Ky, const Item* __restrict__ items, int n_items, const Seg* __restrict__ segs,
     const float* __restrict__ wu, const float* __restrict__ wv, const float* __restrict__ theta, double su, double sv,
@@ -782,7 +783,7 @@ __global__ __launch_bounds__(256) void k_grid_synth(
     int exact, const uint8_t* __restrict__ active, XcdSplit xs, SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
   if (b < 0)
-    sara_synth_part<KIND>(j, blockIdx.x);
+    sara_synth_part<KIND, HW>(j, blockIdx.x);
   else if (threadIdx.x < 128)
     grid_mfma_block<true, 2>(b, scratch, Ky, items, n_items, segs, wu, wv, theta, su, sv, kbc, nullptr,
                              nullptr, y, U, v, z, ga, mu, lambda, bfac, exact, active, xs);
@@ -931,13 +932,13 @@ __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratc
 }
 
 // The same after a synthesis launch of SARA in the first workgroups.
-template <int KIND>
+template <int KIND, bool HW>
 __global__ __launch_bounds__(256) void k_fold8_synth(int nblocks, const float2* __restrict__ scratch,
                                                      const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
                                                      int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid,
                                                      SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
-  if (b < 0) sara_synth_part<KIND>(j, blockIdx.x);
+  if (b < 0) sara_synth_part<KIND, HW>(j, blockIdx.x);
   else fold8_block(b, nblocks, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
 }
 
@@ -1064,7 +1065,7 @@ int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm) {
 }
 int degrid_dual(ppd_plan* p, const DualArgs& a, double* part_out, const SaraJob* with) {
   if (with) {
-    hipLaunchKernelGGL(k_degrid_dwt, dim3(p->split1.launch + with->blocks()), dim3(DWT_THREADS), 0, p->stream,
+    hipLaunchKernelGGL((with->W ? k_degrid_dwt<true> : k_degrid_dwt<false>), dim3(p->split1.launch + with->blocks()), dim3(DWT_THREADS), 0, p->stream,
                        p->grid_f, p->PW, p->Ky, p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale,
                        p->sv_scale, p->kbc, a.y, a.U, a.v, a.z, p->gabuf, a.mu, part_out, a.rpart, p->split1, *with);
     PPD_HIP(hipGetLastError());
@@ -1097,8 +1098,8 @@ int grid_dual_paired(ppd_plan* p, const DualArgs& a, int exact, const SaraJob* w
                        p->items, p->n_items, p->segs, p->wu, p->wv, p->theta, p->su_scale, p->sv_scale, p->kbc, a.y,
                        a.U, a.v, a.z, p->gabuf, a.mu, a.lambda, p->bfac, exact, a.active, p->split1, *with);
   };
-  if (with->kind == SARA_IDWT2) launch(k_grid_synth<SARA_IDWT2>);
-  else launch(k_grid_synth<SARA_IDWT>);
+  if (with->kind == SARA_IDWT2) launch(with->W ? k_grid_synth<SARA_IDWT2, true> : k_grid_synth<SARA_IDWT2, false>);
+  else launch(with->W ? k_grid_synth<SARA_IDWT, true> : k_grid_synth<SARA_IDWT, false>);
   PPD_HIP(hipGetLastError());
   return fold_grid(p, with_fold);
 }
@@ -1120,8 +1121,8 @@ int fold_grid(ppd_plan* p, const SaraJob* with) {
                          p->gscratch, p->tile_item_off, reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x,
                          p->tiles_y, p->Ky, p->grid_a, *with);
     };
-    if (with->kind == SARA_IDWT) launch(k_fold8_synth<SARA_IDWT>);
-    else launch(k_fold8_synth<SARA_FINAL>);
+    if (with->kind == SARA_IDWT) launch(with->W ? k_fold8_synth<SARA_IDWT, true> : k_fold8_synth<SARA_IDWT, false>);
+    else launch(with->W ? k_fold8_synth<SARA_FINAL, true> : k_fold8_synth<SARA_FINAL, false>);
     PPD_HIP(hipGetLastError());
     return PPD_OK;
   }

@@ -71,15 +71,15 @@ constexpr int FOLD_HEAVY = PPD_FOLD_HEAVY;   // item regions above which a tile'
 constexpr int SHARE_ITEMS = 4096;
 // Item count up to which SARA's launches ride in the data path's (each launch
 // then has the registers and LDS of the larger part).  Per replayed iteration,
-// on two streams and in pairs: 51.7 and 32.9 us at 64^2 (125 items), 51 and 42
-// at 128^2 (1043), 55.6 and 50.7 at 256^2 (1777), 62 and 71 at 256^2 (3118);
-// eager 70 and 38, 70 and 45, 71 and 52, 73 and 72 (512 x 256, 3379).
+// on two streams and in pairs: 50 and 31 us at 64^2 (125 items), 51 and 40 at
+// 128^2 (1043), 51 and 48.5 at 256^2 (1777), 57 and 72 at 256^2 (3118); eager,
+// where the host sets the pace of two streams, 59-74 and 36, 59-74 and 43,
+// 60-74 and 49.5, 63-78 and 75.
 constexpr int PAIR_ITEMS = 2048;
 // The same for replayed iterations with middle Algorithm 2 steps or the exact
 // prox, in which the second stream has SARA run beside those: five steps 54 and
-// 48 us at 64^2 (125 items), 56 and 53 at 128^2 (471), 59 and 59.5 at 128^2
-// (1043), 60 and 66 at 256^2 (1777); exact 59 and 56 at 64^2 (140), 61 and 63 at
-// 128^2 (502).
+// 50 us at 128^2 (471 items), 55.5 and 59 at 128^2 (1043), 58.5 and 68 at 256^2
+// (1777); exact 59 and 56 at 64^2 (140), 61 and 63 at 128^2 (502).
 constexpr int PAIR_ITEMS_MIDDLE = 480;
 // Largest 2 ny of the launches that a SARA level rides in (its kernels exist
 // for the lengths up to there).

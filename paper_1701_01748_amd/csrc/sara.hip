@@ -23,8 +23,8 @@
 // Bound by HBM at large sizes (302 MB of duals in and out per dual step at
 // 2048^2) and by the latency of five dependent launches at small ones.  One
 // dual step alone, against the earlier form that staged a tile's window in
-// LDS and read LDS once per tap and output: 2048^2 332 -> 192 us, 1024^2
-// 108 -> 69 us, 512^2 44 -> 36 us, 64^2 31 -> 26 us.
+// LDS and read LDS once per tap and output: 2048^2 332 -> 183 us, 1024^2
+// 108 -> 65 us, 512^2 44 -> 33 us, 64^2 31 -> 27 us.
 #include <cmath>
 #include "sara_device.h"
 

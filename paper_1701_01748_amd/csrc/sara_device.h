@@ -577,27 +577,22 @@ __device__ __forceinline__ void idwt_final_block(TileId tl, const float* __restr
 // host time per iteration (every node of a forked graph is enqueued by
 // itself; of a chain, 8 us), so the launches of the two chains are paired
 // instead.  Waves beyond the workgroup size of their part end at once.
+// HW: the job has weights.
+template <bool HW>
 __device__ __forceinline__ void sara_dwt_part(const SaraJob& j, int lin) {
   if (threadIdx.x >= DWT_THREADS) return;
-  const TileId tl = sara_tile<true>(lin, j.gx, j.gy, j.gz);
-  if (j.W)
-    dwt_block<A_DUAL, 4, true>(tl, j.in, j.tmp, j.out, j.filt, j.W, j.g, j.l, j.alpha, j.lambda, j.active, j.vec);
-  else
-    dwt_block<A_DUAL, 4, false>(tl, j.in, j.tmp, j.out, j.filt, nullptr, j.g, j.l, j.alpha, j.lambda, j.active, j.vec);
+  dwt_block<A_DUAL, 4, HW>(sara_tile<true>(lin, j.gx, j.gy, j.gz), j.in, j.tmp, j.out, j.filt, j.W, j.g, j.l, j.alpha,
+                           j.lambda, j.active, j.vec);
 }
 // One synthesis launch: the two coarsest levels, one level, or the last one.
-template <int KIND, int WM>
-__device__ __forceinline__ void sara_synth_weighted(const SaraJob& j, TileId tl) {
+template <int KIND, bool HW>
+__device__ __forceinline__ void sara_synth_part(const SaraJob& j, int lin) {
+  if (threadIdx.x >= 256) return;
+  constexpr int WM = HW ? W_AHEAD : W_NONE;
+  const TileId tl = sara_tile<false>(lin, j.gx, j.gy, j.gz);
   if constexpr (KIND == SARA_IDWT2) idwt2_block<WM>(tl, j.in, j.tmp, j.filt, j.W, j.g);
   else if constexpr (KIND == SARA_IDWT) idwt_block<WM>(tl, j.in, j.tmp, j.filt, j.W, j.g, j.l);
   else idwt_final_block<WM>(tl, j.in, j.tmp, j.filt, j.W, j.g, j.out, j.vec);
-}
-template <int KIND>
-__device__ __forceinline__ void sara_synth_part(const SaraJob& j, int lin) {
-  if (threadIdx.x >= 256) return;
-  const TileId tl = sara_tile<false>(lin, j.gx, j.gy, j.gz);
-  if (j.W) sara_synth_weighted<KIND, W_AHEAD>(j, tl);
-  else sara_synth_weighted<KIND, W_NONE>(j, tl);
 }
 
 }  // namespace
