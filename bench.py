@@ -38,7 +38,7 @@ CRITICAL_PATH = ("fft_rows_fwd", "fft_cols_fwd", "degrid", "grid", "fold", "fft_
 # while that file is unchanged since the counters were taken)
 KIND_SOURCE = {"degrid": "nufft.hip", "grid": "nufft.hip", "fold": "nufft.hip",
                "fft_rows_fwd": "fft.hip", "fft_cols_fwd": "fft.hip", "fft_cols_inv": "fft.hip",
-               "fft_rows_inv": "fft.hip", "dwt": "sara.hip", "idwt": "sara.hip", "subiter": "dual.hip"}
+               "fft_rows_inv": "fft.hip", "dwt": "sara_device.h", "idwt": "sara_device.h", "subiter": "dual.hip"}
 
 
 def source_sha(name: str) -> str:

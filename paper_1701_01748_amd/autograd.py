@@ -17,9 +17,10 @@ operators are piecewise smooth).  Each iteration can be checkpointed, so
 memory stays at one iteration's activations.
 
 A whole iteration, and the data fidelity of all channels, are one autograd
-node each: composed of the pieces' nodes and torch operations the calls were
-bound by the host (an iteration at 256^2, 65536 points, forward and backward:
-about 330 us of host work for 28 launches; four channels' fidelity 850 us).
+node each: composed of the pieces' nodes and torch operations the calls are
+bound by the host (an iteration at 256^2, 65536 points, forward and backward
+500 us, as one node 365; the fidelity of four channels of 250000 points at
+512^2 with its gradient 818 us, as one node 231).
 """
 from __future__ import annotations
 
