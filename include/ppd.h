@@ -110,6 +110,18 @@ typedef struct {
 } ppd_plan_info;
 int ppd_plan_get_info(const ppd_plan* plan, ppd_plan_info* info /* HOST */);
 
+/* The forms that the plan's last ppd_iterate call of at least one iteration
+ * took, for tests and tuning.  Synchronous. */
+typedef struct {
+  int32_t paired;             /* 1: SARA's launches rode in the data path's    */
+  int32_t one_launch;         /* 1: the middle Algorithm 2 steps, or the exact
+                                 prox's Newton steps, ran as one launch        */
+  int64_t solved_alone;       /* launches since the plan's creation in which a
+                                 wait gave up and the last workgroup formed the
+                                 result by itself                              */
+} ppd_forms;
+int ppd_plan_get_forms(ppd_plan* plan, ppd_forms* forms /* HOST */);
+
 /* perm[p] = user index of plan position p.  HOST [M] int64.  Synchronous. */
 int ppd_plan_permutation(const ppd_plan* plan, int64_t* perm /* HOST */);
 

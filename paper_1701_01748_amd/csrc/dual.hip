@@ -501,7 +501,7 @@ struct SecArgs {
   const double* eps;
   double2* bfac;
   uint64_t* part;   // [2][G][PA_MAXB][2] tagged partials
-  uint32_t* sync;   // [1] exits, [3] give-up flag
+  uint32_t* sync;   // [1] exits, [3] give-up flag, [4] solves by one workgroup
 };
 
 __device__ __forceinline__ double sec_a2(const SecArgs& a, int64_t i, double Ue) {
@@ -674,6 +674,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_sec_persistent(SecArgs a) {
   if (tid == 0) {
     __hip_atomic_store(&a.sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     gave_up = int(__hip_atomic_exchange(&a.sync[3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if (gave_up) (void)__hip_atomic_fetch_add(&a.sync[4], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __syncthreads();
   if (!gave_up) return;

@@ -452,6 +452,8 @@ extern "C" int ppd_iterate(ppd_plan* p, ppd_state* st, const ppd_params* prm, in
   c.paired = can_pair(p, c, prm->use_graph != 0);
 
   if (n_iter > 0) {
+    p->last_paired = c.paired;
+    p->last_one_launch = c.persistent;
     // the first iteration's forward row pass; each iteration then leaves
     // the next one's
     PPD_TRY(fft_rows_forward(p, st->xt, p->half_f));

@@ -748,6 +748,17 @@ int ppd_plan_get_info(const ppd_plan* p, ppd_plan_info* info) {
   return PPD_OK;
 }
 
+int ppd_plan_get_forms(ppd_plan* p, ppd_forms* forms) {
+  if (!p || !forms) return fail(PPD_EINVAL, "NULL argument");
+  uint32_t alone = 0;
+  PPD_HIP(hipMemcpyAsync(&alone, p->pa_sync + 4, sizeof(alone), hipMemcpyDeviceToHost, p->stream));
+  PPD_HIP(hipStreamSynchronize(p->stream));
+  forms->paired = p->last_paired ? 1 : 0;
+  forms->one_launch = p->last_one_launch ? 1 : 0;
+  forms->solved_alone = alone;
+  return PPD_OK;
+}
+
 int ppd_plan_permutation(const ppd_plan* p, int64_t* perm) {
   if (!p || !perm) return fail(PPD_EINVAL, "NULL argument");
   for (int64_t i = 0; i < p->M; ++i) perm[i] = p->perm_host[i];

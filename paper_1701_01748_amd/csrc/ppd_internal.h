@@ -55,7 +55,7 @@ constexpr int PA_PER_MAX = 12;
 inline int pa_points(int64_t M) { return M <= (1 << 17) ? 2 : M <= (1 << 19) ? 4 : PA_PER_MAX; }
 constexpr int PA_CHUNK_MAX = PA_THREADS * PA_PER_MAX;
 constexpr int PA_MAXB = 4;        // data blocks one workgroup's points may span
-constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag, [3] the Newton steps' flag
+constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag, [3] the Newton steps' flag, [4] solves by one workgroup
 // tagged partial slots of the persistent launch (see k_alg2_persistent)
 constexpr uint64_t PA_SIGN = 0x8000000000000000ull;
 constexpr uint64_t PA_EMPTY = 0x7ff8000000000000ull;   // quiet NaN: no partial yet
@@ -249,7 +249,9 @@ struct ppd_plan {
   int32_t* pa_gfirst = nullptr;            // [d] first workgroup of each block
   int32_t* pa_glast = nullptr;             // [d] last workgroup of each block
   uint64_t* pa_part = nullptr;             // [2][pa_groups][PA_MAXB][2] tagged per-workgroup block partials
-  uint32_t* pa_sync = nullptr;             // [PA_SYNC_WORDS] exit count, give-up flags
+  uint32_t* pa_sync = nullptr;             // [PA_SYNC_WORDS] exit count, give-up flags, solves by one workgroup
+  bool last_paired = false;                // forms of the last ppd_iterate call (ppd_plan_get_forms)
+  bool last_one_launch = false;
   double* part = nullptr;                  // [2][n_segs] block-norm partials
   double* rpart = nullptr;                 // [n_segs] residual partials
   double* eps_d = nullptr;                 // [d]

@@ -64,6 +64,10 @@ class Stats(ctypes.Structure):
                 ("residual_max", c_double)]
 
 
+class Forms(ctypes.Structure):
+    _fields_ = [("paired", c_int32), ("one_launch", c_int32), ("solved_alone", c_int64)]
+
+
 class StepArgs(ctypes.Structure):
     _fields_ = [(k, c_void_p) for k in ("x", "xt", "v", "u", "z", "y", "U")] + [
         ("eps", ctypes.POINTER(c_double))] + [
@@ -87,6 +91,7 @@ _PROTOS = {
     "ppd_plan_destroy": (c_int32, [c_void_p]),
     "ppd_plan_set_stream": (c_int32, [c_void_p, c_void_p]),
     "ppd_plan_get_info": (c_int32, [c_void_p, ctypes.POINTER(PlanInfo)]),
+    "ppd_plan_get_forms": (c_int32, [c_void_p, ctypes.POINTER(Forms)]),
     "ppd_plan_permutation": (c_int32, [c_void_p, ctypes.POINTER(c_int64)]),
     "ppd_plan_permute": (c_int32, [c_void_p, c_int32, c_void_p, c_void_p, c_int32]),
     "ppd_phi": (c_int32, [c_void_p, c_void_p, c_void_p, c_int32]),
@@ -274,6 +279,12 @@ class Plan:
     def set_stream(self, stream):
         _check("ppd_plan_set_stream", lib().ppd_plan_set_stream(self.handle, c_void_p(int(stream.cuda_stream))))
         self.stream = stream
+
+    def forms(self) -> dict:
+        """The forms of the plan's last ppd_iterate call (see ppd_forms)."""
+        f = Forms()
+        _check("ppd_plan_get_forms", lib().ppd_plan_get_forms(self.handle, ctypes.byref(f)))
+        return {"paired": bool(f.paired), "one_launch": bool(f.one_launch), "solved_alone": int(f.solved_alone)}
 
     def permutation(self) -> np.ndarray:
         out = np.empty(self.M, dtype=np.int64)
