@@ -81,3 +81,17 @@ def test_newton_solve_by_one_workgroup(M, d):
     f, _, z = _forms(case, **kw)
     assert f["solved_alone"] == 1   # as the slots and the flag were left
     assert np.linalg.norm(z - zr) <= 1e-11 * np.linalg.norm(zr)
+
+
+def test_timers_leave_replayed_iterations_alone():
+    """Timers do not reach captured launches: a graph captured while they are
+    on is the same one, which later calls with the same arguments replay."""
+    announce("pairing of a graph captured with the timers on")
+    case = _case(4096, 2)
+    P, torch, stream, plan, y, U, eps = case
+    with torch.cuda.stream(stream):
+        it = P.Iteration(plan, P.PPDState(plan, y), y, U, eps, eta=1e-4, use_graph=True)
+        for on in (True, False, True):
+            plan.timing(on)
+            it.run(2)
+            assert plan.forms()["paired"], on
