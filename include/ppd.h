@@ -292,16 +292,20 @@ typedef struct {
                                       as another plan's persistent launch,
                                       can make a wait give up);
                                       PPD_PERSIST_OFF (1): one launch pair
-                                      per step.  PPD_PROX_EXACT: under the
-                                      same conditions its Newton steps run as
-                                      one launch; a wait of it that gives up
-                                      costs time only                        */
+                                      per step.  PPD_PROX_EXACT: its Newton
+                                      steps run as one launch when the points
+                                      fit a quarter of the device (about 0.8M
+                                      visibilities) and span blocks as above,
+                                      or with PPD_PERSIST_OFF one launch each */
   int32_t spin_limit;              /* polls of one wait of the persistent
                                       launch before it gives up (0: 2^20);
                                       a give-up
                                       makes every workgroup finish and the
                                       next call that reads statistics return
-                                      PPD_EDEVICE                            */
+                                      PPD_EDEVICE.  PPD_PROX_EXACT: 0: 2^13
+                                      (2 ms); after a give-up the last
+                                      workgroup solves alone, which costs time
+                                      and is no error                        */
   int32_t stats_every;             /* > 0: the statistics of every
                                       stats_every-th iteration of the call are
                                       also reduced on the device while the

@@ -495,7 +495,6 @@ __global__ __launch_bounds__(SEC_THREADS) void k_sec_update(const double* __rest
 struct SecArgs {
   int steps, G, d, spin_limit;
   int64_t M;
-  const double2* w;   // NULL: from v, ga and U
   const float2* v; const float2* ga; const float2* y; const double* U;
   const int32_t* voff; const int32_t* wgb0; const int32_t* gfirst; const int32_t* glast;
   const double* eps;
@@ -505,7 +504,7 @@ struct SecArgs {
 };
 
 __device__ __forceinline__ double sec_a2(const SecArgs& a, int64_t i, double Ue) {
-  const double2 we = a.w ? a.w[i] : dual_arg(a.v[i], Ue, a.ga[i]);
+  const double2 we = dual_arg(a.v[i], Ue, a.ga[i]);
   const float2 ye = a.y[i];
   const double dx = we.x - double(ye.x), dy = we.y - double(ye.y);
   return Ue * Ue * (dx * dx + dy * dy);
@@ -886,13 +885,14 @@ static int resident_groups(const void* kernel) {
 
 int sec_persistent_capacity(int per) { return resident_groups(reinterpret_cast<const void*>(sec_kernel(per))); }
 
-// Polls of one wait before the last workgroup out solves alone: tens of
-// milliseconds, where a step takes 4 us.
-constexpr int SEC_SPIN = 1 << 16;
+// Polls of one wait before the last workgroup out solves alone: 2 ms at 0.25 us
+// a poll, where a step takes 4 us and the solve by one workgroup 0.9 to 1.4 ms
+// (200003 points, 12 steps).
+constexpr int SEC_SPIN = 1 << 13;
 
-static int secular_persistent(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
-                              const double* U, int n_newton, int spin_limit) {
-  const SecArgs a{n_newton, p->pa_groups, p->d, spin_limit > 0 ? spin_limit : SEC_SPIN, p->M, w, v, ga, y, U,
+static int secular_persistent(ppd_plan* p, const float2* v, const float2* ga, const float2* y, const double* U,
+                              int n_newton, int spin_limit) {
+  const SecArgs a{n_newton, p->pa_groups, p->d, spin_limit > 0 ? spin_limit : SEC_SPIN, p->M, v, ga, y, U,
                   p->voff_d, p->pa_wgb0, p->pa_gfirst, p->pa_glast, p->eps_d, p->bfac, p->pa_part, p->pa_sync};
   int slot;
   PPD_TRY(timer_begin(p, KK_SUBITER, &slot));
@@ -903,7 +903,7 @@ static int secular_persistent(ppd_plan* p, const double2* w, const float2* v, co
 
 int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
                   const double* U, int n_newton, bool persistent, int spin_limit) {
-  if (persistent && p->sec_ok) return secular_persistent(p, w, v, ga, y, U, n_newton, spin_limit);
+  if (persistent && p->sec_ok) return secular_persistent(p, v, ga, y, U, n_newton, spin_limit);
   // pass s writes its partials to buffer s & 1 and (s >= 1) its nu to
   // nu buffer s & 1
   const int nc = p->n_sec_chunks;
@@ -1038,7 +1038,8 @@ extern "C" int ppd_prox_metric(ppd_plan* p, const double* w, const float* y, con
   PPD_TRY(upload_eps(p, eps));
   const double2* w2 = reinterpret_cast<const double2*>(w);
   const float2* y2 = reinterpret_cast<const float2*>(y);
-  PPD_TRY(secular_solve(p, w2, nullptr, nullptr, y2, U, n_newton, true, 0));
+  // step by step: nothing here could turn the waits of the one launch off
+  PPD_TRY(secular_solve(p, w2, nullptr, nullptr, y2, U, n_newton, false, 0));
   int slot;
   PPD_TRY(timer_begin(p, KK_MISC, &slot));
   hipLaunchKernelGGL(k_prox_apply, dim3(int(std::min<int64_t>((p->M + 255) / 256, 4096))), dim3(256), 0, p->stream,

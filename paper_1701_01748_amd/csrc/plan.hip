@@ -666,8 +666,8 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   // the persistent launch needs all its workgroups on the device at once
   if (st == PPD_OK) {
     p->pa_ok = pa_fits && p->pa_groups <= alg2_persistent_capacity(p->pa_per);
-    // half of it for the Newton steps: two plans' solves on two streams fit beside each other
-    p->sec_ok = pa_fits && 2 * p->pa_groups <= sec_persistent_capacity(p->pa_per);
+    // a quarter of it for the Newton steps, which step by step wait for nothing
+    p->sec_ok = pa_fits && PA_BESIDE * p->pa_groups <= sec_persistent_capacity(p->pa_per);
   }
   // mapped pinned host memory the final statistics reduction writes into
   if (st == PPD_OK && (hipHostMalloc(reinterpret_cast<void**>(&p->host_stats), sizeof(double) * (9 + p->d),

@@ -55,6 +55,9 @@ constexpr int PA_PER_MAX = 12;
 inline int pa_points(int64_t M) { return M <= (1 << 17) ? 2 : M <= (1 << 19) ? 4 : PA_PER_MAX; }
 constexpr int PA_CHUNK_MAX = PA_THREADS * PA_PER_MAX;
 constexpr int PA_MAXB = 4;        // data blocks one workgroup's points may span
+// Launches whose workgroups wait for each other that must fit the device beside
+// each other: as many as a process's hardware queues run at once (HIP's default).
+constexpr int PA_BESIDE = 4;
 constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag, [3] the Newton steps' flag, [4] solves by one workgroup
 // tagged partial slots of the persistent launch (see k_alg2_persistent)
 constexpr uint64_t PA_SIGN = 0x8000000000000000ull;
@@ -387,7 +390,7 @@ int alg2_persistent_capacity(int per);
 int sec_persistent_capacity(int per);
 // n_newton Newton steps of the exact prox per block; nu_j in bfac[j].x.
 // The prox argument is w if non-NULL, else U^-1 v + ga (see dual_arg).
-// persistent: as one launch where the plan's points fit the device.
+// persistent (w NULL): as one launch where the plan's points fit a quarter of the device.
 int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* ga, const float2* y,
                   const double* U, int n_newton, bool persistent, int spin_limit);
 int grid_dual_exact(ppd_plan* p, const DualArgs& a);   // dual finish with the exact prox + grid

@@ -95,3 +95,24 @@ def test_timers_leave_replayed_iterations_alone():
             plan.timing(on)
             it.run(2)
             assert plan.forms()["paired"], on
+
+
+def test_newton_steps_leave_room_for_other_launches():
+    """One launch only where four of it fit the device; a plan of a million
+    points takes a launch per step, which waits for nothing."""
+    announce("Newton form at 1000000 points")
+    case = _case(1_000_000, 5)
+    assert _forms(case, prox=case[0].PROX_EXACT)[0]["one_launch"] is False
+
+
+@pytest.mark.parametrize("n_newton", [1, 7])
+def test_prox_metric_waits_for_nothing(n_newton):
+    """ppd_prox_metric has no argument that turns waits off: a launch per step."""
+    announce(f"ppd_prox_metric launches, {n_newton} steps")
+    case = _case(5000, 2)
+    P, torch, stream, plan, y, U, eps = case
+    with torch.cuda.stream(stream):
+        plan.timing(True)
+        P.ppd_prox_metric(plan, y.to(torch.complex128), y, U, eps, n_newton=n_newton)
+        assert plan.timing_read()["subiter"][0] == n_newton
+        plan.timing(False)
