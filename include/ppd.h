@@ -116,6 +116,9 @@ typedef struct {
   int32_t paired;             /* 1: SARA's launches rode in the data path's    */
   int32_t one_launch;         /* 1: the middle Algorithm 2 steps, or the exact
                                  prox's Newton steps, ran as one launch        */
+  int32_t beside;             /* launches of the plan's one-launch Algorithm 2
+                                 steps that the device holds at once           */
+  int32_t pad_;
   int64_t solved_alone;       /* launches since the plan's creation in which a
                                  wait gave up and the last workgroup formed the
                                  result by itself                              */
@@ -298,14 +301,14 @@ typedef struct {
                                       visibilities) and span blocks as above,
                                       or with PPD_PERSIST_OFF one launch each */
   int32_t spin_limit;              /* polls of one wait of the persistent
-                                      launch before it gives up (0: 2^20);
-                                      a give-up
-                                      makes every workgroup finish and the
-                                      next call that reads statistics return
-                                      PPD_EDEVICE.  PPD_PROX_EXACT: 0: 2^13
-                                      (2 ms); after a give-up the last
-                                      workgroup solves alone, which costs time
-                                      and is no error                        */
+                                      launch before it gives up (0: 2^13,
+                                      2 ms): every workgroup then finishes and
+                                      the last one does the launch's work
+                                      alone, which costs time only.  Algorithm
+                                      2: a limit given here (> 0) that a wait
+                                      reaches is reported besides, as
+                                      PPD_EDEVICE by the next call that reads
+                                      statistics                             */
   int32_t stats_every;             /* > 0: the statistics of every
                                       stats_every-th iteration of the call are
                                       also reduced on the device while the

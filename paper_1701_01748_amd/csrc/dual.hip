@@ -177,24 +177,29 @@ __global__ __launch_bounds__(BF_THREADS) void k_block_factors_dwt(const double* 
 // step s + 1 needs the reader's own step s + 1 partial) or a NaN left by the
 // previous launch's reset (step 0 and 1), so the sign tells them apart.  The
 // wait is bounded: a thread that has polled spin_limit times sets a give-up
-// flag that every other waiter checks, all workgroups run to the end, and
-// the host reports the flag.  The last workgroup out puts NaN back into
+// flag that every other waiter checks, all workgroups run to the end, and the
+// last one out forms the steps of all blocks alone, from memory.  So the
+// iterate goes to an array of its own, which the gridding then reads, and z
+// stays what it was: a workgroup that has every factor stores its points (they
+// are what the last one out forms, too), one that gave up stores nothing.  Other
+// work on the device, and workgroups that are not resident at once, thus cost
+// time only.  The last workgroup out puts NaN back into
 // every slot for the next launch (the plan starts them at NaN).
 #ifndef PPD_PA_SLEEP
 #define PPD_PA_SLEEP 1   // s_sleep argument between polls (units of 64 clocks)
 #endif
 struct PaArgs {
-  int steps, G, d, spin_limit;
+  int steps, G, d, spin_limit, report;   // report: a give-up is told to the host
   int64_t M;
   double mu;
   const float2* v; const float2* ga; const float2* y; const double* U;
-  double2* z;
+  const double2* z; double2* zout;
   const uint8_t* active;
   const int32_t* voff; const int32_t* wgb0; const int32_t* gfirst; const int32_t* glast;
   const double* eps;
   double2* bfac;
   uint64_t* part;   // [2][G][PA_MAXB] tagged partials
-  uint32_t* sync;   // [1] exits, [2] give-up flag
+  uint32_t* sync;   // [1] exits, [2] give-up to report, [3] give-up flag, [4] solves by one workgroup
 };
 
 // Waits for the tagged partial in *slot; returns its value, or -1 after a
@@ -213,6 +218,35 @@ __device__ double pa_wait(uint64_t* slot, uint64_t tag, uint32_t* flag, int spin
 #if PPD_PA_SLEEP > 0
     __builtin_amdgcn_s_sleep(PPD_PA_SLEEP);
 #endif
+  }
+}
+
+// All blocks' steps by one workgroup, from memory; red: 4 doubles.
+__device__ __forceinline__ void pa_alone(const PaArgs& a, double* red) {
+  for (int j = 0; j < a.d; ++j) {
+    if (a.active && !a.active[j]) continue;   // keeps z
+    double2 f = make_double2(1.0, 1.0);
+    for (int s = 0; s <= a.steps; ++s) {   // 0: the first step's factor only
+      double acc = 0.0;
+      for (int64_t i = a.voff[j] + threadIdx.x; i < a.voff[j + 1]; i += PA_THREADS) {
+        const double Ue = a.U[i], mU = a.mu * Ue;
+        const double2 we = dual_arg(a.v[i], Ue, a.ga[i]);
+        const float2 ye = a.y[i];
+        double2 ze = s <= 1 ? a.z[i] : a.zout[i];
+        if (s > 0) {
+          const double qx = ze.x - mU * (ze.x - we.x), qy = ze.y - mU * (ze.y - we.y);
+          ze.x = f.y != 0.0 ? qx : double(ye.x) + (qx - double(ye.x)) * f.x;
+          ze.y = f.y != 0.0 ? qy : double(ye.y) + (qy - double(ye.y)) * f.x;
+          a.zout[i] = ze;
+        }
+        const double dx = (ze.x - mU * (ze.x - we.x)) - double(ye.x);
+        const double dy = (ze.y - mU * (ze.y - we.y)) - double(ye.y);
+        acc += dx * dx + dy * dy;
+      }
+      __syncthreads();   // red is free again
+      f = ball_factor(sum256(acc, red), a.eps[j]);
+    }
+    if (threadIdx.x == 0) a.bfac[j] = f;
   }
 }
 
@@ -306,7 +340,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
       double t = 0.0;
       int bad = 0;
       for (int gg = a.gfirst[j] + tid; gg <= a.glast[j]; gg += PA_THREADS) {
-        const double v = pa_wait(&part[size_t(gg) * PA_MAXB + (j - a.wgb0[gg])], tag, &a.sync[2], a.spin_limit);
+        const double v = pa_wait(&part[size_t(gg) * PA_MAXB + (j - a.wgb0[gg])], tag, &a.sync[3], a.spin_limit);
         if (v < 0.0) bad = 1;
         else t += v;
       }
@@ -323,31 +357,42 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
     __syncthreads();
     if (quit) break;   // uniform: read after the barrier
   }
+  const bool whole = !quit;   // every factor came from all workgroups of its block
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int64_t i = i0 + int64_t(k) * PA_THREADS + tid;
-    if (sl[k] >= 0 && act[sl[k]]) a.z[i] = z[k];
+    if (whole && sl[k] >= 0 && act[sl[k]]) a.zout[i] = z[k];
   }
   // the last step's factors, for the final projection in the gridding:
   // stored by the first workgroup of each block (all others hold the same)
-  if (tid < nb && a.gfirst[b0 + tid] == g) a.bfac[b0 + tid] = fac[tid];
-  // the last workgroup out empties every slot for the next launch and clears
-  // the exit count
-  __shared__ int last_out;
+  if (whole && tid < nb && a.gfirst[b0 + tid] == g) a.bfac[b0 + tid] = fac[tid];
+  // what each wave stored (partials, the flag) is acknowledged before the exit
+  // is counted, so that neither the reset nor the reading of the flag can be
+  // overtaken by one of them
+  __shared__ int last_out, gave_up;
+  __builtin_amdgcn_s_waitcnt(0);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __syncthreads();
   if (tid == 0) {
-    // the partials this wave published are acknowledged before the exit
-    // is counted, so that the reset cannot be overtaken by one of them
-    __builtin_amdgcn_s_waitcnt(0);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
     const uint32_t out = __hip_atomic_fetch_add(&a.sync[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     last_out = out == uint32_t(a.G) - 1u;
   }
   __syncthreads();
-  if (last_out) {
-    for (size_t e = tid; e < 2 * size_t(a.G) * PA_MAXB; e += PA_THREADS)
-      __hip_atomic_store(&a.part[e], PA_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0) __hip_atomic_store(&a.sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!last_out) return;
+  // the last workgroup out empties every slot for the next launch and clears
+  // the exit count and the flag
+  for (size_t e = tid; e < 2 * size_t(a.G) * PA_MAXB; e += PA_THREADS)
+    __hip_atomic_store(&a.part[e], PA_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tid == 0) {
+    __hip_atomic_store(&a.sync[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    gave_up = int(__hip_atomic_exchange(&a.sync[3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if (gave_up) {
+      (void)__hip_atomic_fetch_add(&a.sync[4], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (a.report) __hip_atomic_store(&a.sync[2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
+  __syncthreads();
+  if (gave_up) pa_alone(a, &red[0][0]);
 }
 
 // ---- exact prox of eq. elip-proj-1: Newton on the secular equation ------
@@ -885,14 +930,9 @@ static int resident_groups(const void* kernel) {
 
 int sec_persistent_capacity(int per) { return resident_groups(reinterpret_cast<const void*>(sec_kernel(per))); }
 
-// Polls of one wait before the last workgroup out solves alone: 2 ms at 0.25 us
-// a poll, where a step takes 4 us and the solve by one workgroup 0.9 to 1.4 ms
-// (200003 points, 12 steps).
-constexpr int SEC_SPIN = 1 << 13;
-
 static int secular_persistent(ppd_plan* p, const float2* v, const float2* ga, const float2* y, const double* U,
                               int n_newton, int spin_limit) {
-  const SecArgs a{n_newton, p->pa_groups, p->d, spin_limit > 0 ? spin_limit : SEC_SPIN, p->M, v, ga, y, U,
+  const SecArgs a{n_newton, p->pa_groups, p->d, spin_limit > 0 ? spin_limit : PA_SPIN, p->M, v, ga, y, U,
                   p->voff_d, p->pa_wgb0, p->pa_gfirst, p->pa_glast, p->eps_d, p->bfac, p->pa_part, p->pa_sync};
   int slot;
   PPD_TRY(timer_begin(p, KK_SUBITER, &slot));
@@ -949,7 +989,8 @@ int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit) {
   pa.steps = a.n_itr - 1;
   pa.G = p->pa_groups;
   pa.d = p->d;
-  pa.spin_limit = spin_limit > 0 ? spin_limit : (1 << 20);
+  pa.spin_limit = spin_limit > 0 ? spin_limit : PA_SPIN;
+  pa.report = spin_limit > 0;
   pa.M = p->M;
   pa.mu = a.mu;
   pa.v = a.v;
@@ -957,6 +998,7 @@ int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit) {
   pa.y = a.y;
   pa.U = a.U;
   pa.z = a.z;
+  pa.zout = p->qbuf;
   pa.active = a.active;
   pa.voff = p->voff_d;
   pa.wgb0 = p->pa_wgb0;

@@ -194,13 +194,17 @@ struct IterCtx {
 };
 
 // The n_itr - 1 middle Algorithm 2 steps, from the first step's factors to the
-// last one's.
-int middle_steps(ppd_plan* p, const IterCtx& c) {
+// last one's.  `last`: the arguments of the gridding, which then finds the
+// iterate where they left it.
+int middle_steps(ppd_plan* p, const IterCtx& c, DualArgs& last) {
   // one launch, state in registers.  It may run beside the SARA branch:
   // workgroups of it that the SARA launches keep from being resident at first
   // get room as those finish (they never wait on this launch), while the
   // resident ones wait for their partials.
-  if (c.persistent) return alg2_persistent(p, c.dual, c.spin_limit);
+  if (c.persistent) {
+    last.zin = p->qbuf;
+    return alg2_persistent(p, c.dual, c.spin_limit);
+  }
   const BallIn in{nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.dual.mu, c.dual.active};
   double* part[2] = {p->sec_part, p->sec_part + p->n_sec_chunks};
   PPD_TRY(ball_step(p, in, c.dual.z, p->bfac, nullptr, part[0]));
@@ -221,9 +225,10 @@ int data_path(ppd_plan* p, const IterCtx& c) {
   } else if (c.form == PPD_FORM_FUSED) {
     PPD_TRY(degrid_dual(p, c.dual, p->part));               // dual argument, first Alg. 2 step
     if (c.dual.n_itr > 1) {
+      DualArgs last = c.dual;
       PPD_TRY(block_factors(p, p->part));
-      PPD_TRY(middle_steps(p, c));
-      PPD_TRY(grid_dual_factored(p, c.dual));               // last projection, dual finish, gridding
+      PPD_TRY(middle_steps(p, c, last));
+      PPD_TRY(grid_dual_factored(p, last));                 // last projection, dual finish, gridding
     } else {
       PPD_TRY(grid_dual(p, c.dual, p->part));               // projection, dual finish, gridding
     }
@@ -263,15 +268,16 @@ int paired_iteration(ppd_plan* p, const IterCtx& c) {
   PPD_TRY(fft_cols_forward(p, p->half_f, dwt(0)));
   PPD_TRY(degrid_dual(p, c.dual, exact ? nullptr : p->part, dwt(1)));
   int next = 2;
+  DualArgs fin = c.dual;
   if (exact) {
     PPD_TRY(secular_solve(p, nullptr, c.dual.v, p->gabuf, c.dual.y, c.dual.U, c.n_newton, c.persistent, c.spin_limit));
   } else {
     PPD_TRY(block_factors(p, p->part, dwt(next++)));
-    if (c.dual.n_itr > 1) PPD_TRY(middle_steps(p, c));
+    if (c.dual.n_itr > 1) PPD_TRY(middle_steps(p, c, fin));
   }
   for (; next < js.n_dwt; ++next) PPD_TRY(sara_launch(p, js.dwt[next]));
   const SaraJob* last = &js.synth[js.n_synth - 1];
-  PPD_TRY(grid_dual_paired(p, c.dual, exact, js.n_synth > 1 ? &js.synth[0] : nullptr,
+  PPD_TRY(grid_dual_paired(p, fin, exact, js.n_synth > 1 ? &js.synth[0] : nullptr,
                            js.n_synth > 2 ? &js.synth[1] : last));
   if (js.n_synth > 2) PPD_TRY(sara_launch(p, *last));
   PPD_TRY(fft_cols_inverse(p));
@@ -532,12 +538,12 @@ extern "C" int ppd_iterate(ppd_plan* p, ppd_state* st, const ppd_params* prm, in
     const double* h = p->host_stats;
     const bool gave_up = h[8 + p->d] != 0.0;
     if (gave_up) {
-      // a wait of the persistent launch gave up (this call or an earlier
-      // one without statistics): its results are not valid
+      // a wait of the persistent launch reached the given spin limit (in this
+      // call or an earlier one without statistics)
       PPD_HIP(hipMemsetAsync(p->pa_sync + 2, 0, sizeof(uint32_t), p->stream));
       PPD_HIP(hipStreamSynchronize(p->stream));
-      return fail(PPD_EDEVICE, "ppd_iterate: a wait of the persistent Algorithm 2 launch gave up; "
-                               "the iterates of this call are not valid");
+      return fail(PPD_EDEVICE, "ppd_iterate: a wait of the persistent Algorithm 2 launch gave up at the given "
+                               "spin_limit; one workgroup formed its steps");
     }
     if (stats) {
       stats->iter = st->iter;

@@ -755,6 +755,8 @@ int ppd_plan_get_forms(ppd_plan* p, ppd_forms* forms) {
   PPD_HIP(hipStreamSynchronize(p->stream));
   forms->paired = p->last_paired ? 1 : 0;
   forms->one_launch = p->last_one_launch ? 1 : 0;
+  forms->beside = p->pa_ok ? alg2_persistent_capacity(p->pa_per) / p->pa_groups : 0;
+  forms->pad_ = 0;
   forms->solved_alone = alone;
   return PPD_OK;
 }

@@ -46,19 +46,26 @@ constexpr int OWN_SUM_CHUNKS = 4096;
 constexpr int MAX_ITEM_SEGS = 64; // per-block segments of one work item (one wave scans them)
 constexpr int MAX_XCD = 8;
 constexpr int PA_THREADS = 256;   // persistent Algorithm 2: threads per workgroup
-// Points per thread held in registers: 12 (230 VGPRs, 2 waves per SIMD)
-// leaves few workgroups to wait for at each step and still fits the
+// Points per thread held in registers: 12 (2 waves per SIMD: 512 workgroups on
+// the device) leaves few workgroups to wait for at each step and still fits the
 // co-residency limit at 1.3M points.  Fewer points are spread over more
 // compute units: a step's own arithmetic is then short against the exchange
 // (four middle steps at 65536 points: 28.3 us at 12, 18.2 at 4, 16.2 at 2).
+// But then the launch takes a larger share of the device (2048 workgroups at 2
+// points per thread, 1280 at 4), so the shorter chunks end where PA_BESIDE such
+// launches still fit beside each other.
 constexpr int PA_PER_MAX = 12;
-inline int pa_points(int64_t M) { return M <= (1 << 17) ? 2 : M <= (1 << 19) ? 4 : PA_PER_MAX; }
+inline int pa_points(int64_t M) { return M <= (1 << 17) ? 2 : M <= 320 * 1024 ? 4 : PA_PER_MAX; }
 constexpr int PA_CHUNK_MAX = PA_THREADS * PA_PER_MAX;
 constexpr int PA_MAXB = 4;        // data blocks one workgroup's points may span
 // Launches whose workgroups wait for each other that must fit the device beside
 // each other: as many as a process's hardware queues run at once (HIP's default).
 constexpr int PA_BESIDE = 4;
-constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up flag, [3] the Newton steps' flag, [4] solves by one workgroup
+constexpr int PA_SYNC_WORDS = 32;   // [1] exit count, [2] give-up to report, [3] give-up flag, [4] solves by one workgroup
+// Polls of one wait of a persistent launch before it gives up and the last
+// workgroup out does the work alone: 2 ms at 0.25 us a poll, where a step takes 4
+// us and the work of one workgroup, for Newton steps at 200003 points, 0.9 to 1.4 ms.
+constexpr int PA_SPIN = 1 << 13;
 // tagged partial slots of the persistent launch (see k_alg2_persistent)
 constexpr uint64_t PA_SIGN = 0x8000000000000000ull;
 constexpr uint64_t PA_EMPTY = 0x7ff8000000000000ull;   // quiet NaN: no partial yet
@@ -350,6 +357,7 @@ struct DualArgs {
   double mu, lambda;
   int n_itr;
   const uint8_t* active;   // DEVICE [d] block mask of this iteration, NULL = all
+  const double2* zin = nullptr;   // gridding: the iterate before the last projection, NULL = z
   double* rpart = nullptr; // DEVICE [n_segs] residual partials for the statistics, NULL = skip them
 };
 // grid_f -> gabuf; part_out NULL: no Algorithm 2 partials; with: a SARA analysis level
@@ -381,8 +389,8 @@ int ball_factors(ppd_plan* p, const double* pin);   // bfac from chunk partials
 int block_factors(ppd_plan* p, const double* part, const SaraJob* with = nullptr);
 // The n_itr - 1 middle Algorithm 2 steps of the fused form in one persistent
 // launch (needs p->pa_ok and the first step's factors in bfac; leaves the
-// last step's factors in bfac).  spin_limit bounds each wait
-// (0: default).
+// last step's factors in bfac and the iterate in qbuf).  spin_limit bounds each
+// wait (0: PA_SPIN); a given one that runs out is reported.
 int alg2_persistent(ppd_plan* p, const DualArgs& a, int spin_limit);
 // Maximum co-resident workgroups of the persistent launch at `per` points per
 // thread on the current device (0 if it cannot be determined).

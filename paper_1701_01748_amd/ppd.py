@@ -65,7 +65,8 @@ class Stats(ctypes.Structure):
 
 
 class Forms(ctypes.Structure):
-    _fields_ = [("paired", c_int32), ("one_launch", c_int32), ("solved_alone", c_int64)]
+    _fields_ = [("paired", c_int32), ("one_launch", c_int32), ("beside", c_int32), ("pad_", c_int32),
+                ("solved_alone", c_int64)]
 
 
 class StepArgs(ctypes.Structure):
@@ -284,7 +285,8 @@ class Plan:
         """The forms of the plan's last ppd_iterate call (see ppd_forms)."""
         f = Forms()
         _check("ppd_plan_get_forms", lib().ppd_plan_get_forms(self.handle, ctypes.byref(f)))
-        return {"paired": bool(f.paired), "one_launch": bool(f.one_launch), "solved_alone": int(f.solved_alone)}
+        return {"paired": bool(f.paired), "one_launch": bool(f.one_launch), "beside": int(f.beside),
+                "solved_alone": int(f.solved_alone)}
 
     def permutation(self) -> np.ndarray:
         out = np.empty(self.M, dtype=np.int64)
