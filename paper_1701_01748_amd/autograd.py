@@ -224,6 +224,10 @@ class StepFn(torch.autograd.Function):
         x, v, u, z, y = (_dense(t, t.dtype) for t in (x, v, u, z, y))
         outs, mids = P.ppd_step(plan, x, _dense(xt, torch.float32), v, u, z, y, U, eps, **prm)
         ctx.set_materialize_grads(False)
+        # an output that no input with a gradient reaches requires none (x' and x~' are reached by every one)
+        _, nxt, nv, nu, nz, ny = ctx.needs_input_grad[:6]
+        ctx.mark_non_differentiable(*(() if nxt or nv or nz or ny else (outs[2], outs[4])),
+                                    *(() if nxt or nu else (outs[3],)))
         ctx.save_for_backward(x, v, u, z, y, *mids)
         ctx.args = (plan, U, eps, prm)
         return outs
