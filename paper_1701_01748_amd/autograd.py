@@ -118,13 +118,20 @@ class FidelityFn(torch.autograd.Function):
         return img * (2.0 * g.detach()), None, None   # not differentiable again, like the pieces' nodes
 
 
+def _transforms_active():
+    """Whether a function transform (torch.func) is around.  Torch has no public
+    name for it; without this one the answer is the one that is always safe."""
+    query = getattr(torch._C, "_are_functorch_transforms_active", None)
+    return query is None or bool(query())
+
+
 def _one_node(plans, x, ys):
     """Whether FidelityFn gives what the composed operations give: constant
     contiguous complex64 data of the plans' sizes without tangents or pending
     conjugation, a real image, no function transform around, and every plan on
     the stream the tensors are on."""
     if (not plans or len(plans) != len(ys) or not (x.is_cuda and x.is_floating_point()) or
-            torch._C._are_functorch_transforms_active()):
+            _transforms_active()):
         return False
     here = torch.cuda.current_stream(x.device).cuda_stream
     return all(type(y) is torch.Tensor and y.device == x.device and y.dtype == torch.complex64 and
