@@ -111,7 +111,7 @@ class FidelityFn(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, g):
-        rs = ctx.saved_tensors
+        rs = [_dense(r, torch.complex64) for r in ctx.saved_tensors]   # as saved-tensor hooks hand them back
         img = P.ppd_phit(ctx.plans[0], rs[0])
         for p, r in zip(ctx.plans[1:], rs[1:]):
             P.ppd_phit_add(p, r, img)

@@ -39,3 +39,23 @@ def test_iteration_outputs_require_what_the_pieces_require():
         if any(need):   # and backward still runs through what is left
             g = torch.autograd.grad(out[0].sum(), [t for t in (x, xt, v, u, z, y) if t.requires_grad])
             assert all(t is not None for t in g)
+
+
+@pytest.mark.parametrize("unpack", ["strided", "complex128"])
+def test_fidelity_takes_what_saved_tensor_hooks_hand_back(unpack):
+    """Hooks may return a saved tensor in another layout or precision, as an
+    offloading hook does; the residual is taken as the pieces take a gradient."""
+    announce(f"fidelity with saved-tensor hooks, {unpack}")
+    plan = _plan()
+    import torch
+    from paper_1701_01748_amd import autograd as A
+    y = torch.randn(plan.M, device="cuda", dtype=torch.complex64)
+    x = torch.rand(32, 32, device="cuda").requires_grad_(True)
+
+    def back(h):
+        t = torch.stack([h, h], dim=-1).cuda()[..., 0]   # a stride of two
+        return t if unpack == "strided" else t.to(torch.complex128 if t.is_complex() else torch.float64)
+    ref, = torch.autograd.grad(A.multichannel_fidelity([plan, plan], x, [y, 2 * y]), x)
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t.detach().cpu(), back):
+        loss = A.multichannel_fidelity([plan, plan], x, [y, 2 * y])
+    assert torch.equal(torch.autograd.grad(loss, x)[0], ref)
