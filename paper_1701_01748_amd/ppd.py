@@ -585,6 +585,12 @@ def ppd_step_vjp(plan: Plan, x, v, u, z, y, U, eps, mids, grads, needs, *, tau: 
     g, c, a, b, zs = mids
     gx, gxt, gv, gu, gz = grads
     N, M = plan.N, plan.M
+    # the forward pass's tensors, as saved-tensor hooks may have changed them
+    for t, dt, n, name in ((x, torch.float32, N, "x"), (v, torch.complex64, M, "v"), (u, torch.float32, 9 * N, "u"),
+                           (z, torch.complex128, M, "z"), (y, torch.complex64, M, "y"), (U, torch.float64, M, "U"),
+                           (g, torch.complex64, M, "g"), (c, torch.float32, 9 * N, "c"), (a, torch.float32, N, "a"),
+                           (b, torch.float32, N, "b"), (zs, torch.complex128, int(n_itr) * M, "zs")):
+        _need(t, dt, n, name)
     for t, dt, n, name in ((gx, torch.float32, N, "gx"), (gxt, torch.float32, N, "gxt"), (gv, torch.complex64, M, "gv"),
                            (gu, torch.float32, 9 * N, "gu"), (gz, torch.complex128, M, "gz")):
         if t is not None:

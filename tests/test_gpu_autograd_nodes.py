@@ -59,3 +59,40 @@ def test_fidelity_takes_what_saved_tensor_hooks_hand_back(unpack):
     with torch.autograd.graph.saved_tensors_hooks(lambda t: t.detach().cpu(), back):
         loss = A.multichannel_fidelity([plan, plan], x, [y, 2 * y])
     assert torch.equal(torch.autograd.grad(loss, x)[0], ref)
+
+
+def _iteration_grad(plan, hooks):
+    import torch
+    from paper_1701_01748_amd import autograd as A
+    g = torch.Generator(device="cuda").manual_seed(3)
+    M = plan.M
+    y = torch.randn(M, generator=g, device="cuda", dtype=torch.complex64)
+    x = torch.rand(32, 32, generator=g, device="cuda").requires_grad_(True)
+    v = 0.1 * torch.randn(M, generator=g, device="cuda", dtype=torch.complex64)
+    u = 1e-3 * torch.randn(9, 32, 32, generator=g, device="cuda")
+    U = torch.rand(M, generator=g, device="cuda", dtype=torch.float64) + 0.1
+    with hooks:
+        out = A.ppd_iteration(plan, y, U, [5.0, 5.0], x, x, v, u, y.to(torch.complex128), tau=0.3, eta=1e-4, n_itr=2)
+    return torch.autograd.grad(out[0].sum(), x)[0]
+
+
+@pytest.mark.parametrize("unpack", ["strided", "double", "host"])
+def test_iteration_checks_what_saved_tensor_hooks_hand_back(unpack):
+    """The iteration's backward pass reads the saved tensors by address: what is
+    not plain device memory of the saved type is refused, as by the pieces."""
+    announce(f"one-node iteration with saved-tensor hooks, {unpack}")
+    plan = _plan()
+    import contextlib
+
+    import torch
+
+    def back(h):
+        if unpack == "host":
+            return h
+        if unpack == "double":
+            return h.cuda().to(torch.complex128 if h.is_complex() else torch.float64)
+        return torch.stack([h, h], dim=-1).cuda()[..., 0]
+    ref = _iteration_grad(plan, contextlib.nullcontext())
+    assert torch.equal(_iteration_grad(plan, torch.autograd.graph.save_on_cpu()), ref)
+    with pytest.raises(ValueError):
+        _iteration_grad(plan, torch.autograd.graph.saved_tensors_hooks(lambda t: t.detach().cpu(), back))
