@@ -426,6 +426,19 @@ extern "C" int ppd_primal_update_vjp(ppd_plan* p, const float* x, const float* a
   return PPD_OK;
 }
 
+// The scalars of an iteration and, for the data dual, its radii, checked before
+// anything is launched: as the pieces check theirs.
+static int step_check(ppd_plan* p, const ppd_step_args* s, bool dual, const char* fn) {
+  const std::string f(fn);
+  if (s->n_itr < 1) return fail(PPD_EINVAL, f + ": n_itr must be >= 1");
+  if (!(s->mu > 0.0) || !std::isfinite(s->mu) || !(s->lambda <= 1.0 && float(s->lambda) > 0.0f))
+    return fail(PPD_EINVAL, f + ": need mu > 0 and 0 < lambda <= 1");
+  if (!(float(s->alpha) >= 0.0f)) return fail(PPD_EINVAL, f + ": need alpha >= 0");
+  if (!std::isfinite(s->tau) || !std::isfinite(s->eta) || !std::isfinite(s->zeta))
+    return fail(PPD_EINVAL, f + ": non-finite step");
+  return dual ? upload_eps(p, s->eps) : PPD_OK;
+}
+
 // One differentiable iteration as one call, on one stream: at 256^2 with
 // 65536 points its 16 launches (14 in the VJP) take less time on the GPU than
 // on the host, and a fork to the second stream and back cost 40 us of host
@@ -434,6 +447,8 @@ extern "C" int ppd_step(ppd_plan* p, const ppd_step_args* s) {
   if (!p || !s || !s->x || !s->xt || !s->v || !s->u || !s->z || !s->y || !s->U || !s->eps || !s->g || !s->c || !s->a ||
       !s->b || !s->zs || !s->x_out || !s->xt_out || !s->v_out || !s->u_out || !s->z_out)
     return fail(PPD_EINVAL, "ppd_step: NULL argument");
+  if (s->z_out == s->z) return fail(PPD_EINVAL, "ppd_step: z_out must not alias z");
+  PPD_TRY(step_check(p, s, true, "ppd_step"));
   PPD_TRY(ppd_sara_w(p, PPD_SARA_ANALYSIS, s->xt, s->c, nullptr, nullptr, 0.f, 0.f));
   PPD_TRY(ppd_sparsity_update(p, s->u, s->c, float(s->alpha), float(s->lambda), s->u_out));
   PPD_TRY(ppd_sara_w(p, PPD_SARA_SYNTHESIS, s->u_out, s->b, nullptr, nullptr, 0.f, 0.f));
@@ -456,6 +471,8 @@ extern "C" int ppd_step_vjp(ppd_plan* p, const ppd_step_args* s, const ppd_step_
   if (sparse && (prim ? !q->t_u : !q->gu_out)) return fail(PPD_EINVAL, "ppd_step_vjp: t_u (or gu_out) is needed");
   if (q->g_xt && ((!dual && !sparse) || (dual && !q->g_g) || (sparse && !q->g_c)))
     return fail(PPD_EINVAL, "ppd_step_vjp: g_xt needs g_g and g_c");
+  if (dual && q->gz_out == q->g_z) return fail(PPD_EINVAL, "ppd_step_vjp: g_z must not alias gz_out");
+  PPD_TRY(step_check(p, s, dual, "ppd_step_vjp"));
   if (prim)
     PPD_TRY(ppd_primal_update_vjp(p, s->x, s->a, s->b, s->tau, s->eta, s->zeta, s->lambda, q->gx_out, q->gxt_out,
                                   q->g_x, q->g_a, q->g_b));

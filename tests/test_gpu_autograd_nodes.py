@@ -96,3 +96,44 @@ def test_iteration_checks_what_saved_tensor_hooks_hand_back(unpack):
     assert torch.equal(_iteration_grad(plan, torch.autograd.graph.save_on_cpu()), ref)
     with pytest.raises(ValueError):
         _iteration_grad(plan, torch.autograd.graph.saved_tensors_hooks(lambda t: t.detach().cpu(), back))
+
+
+@pytest.mark.parametrize("bad", [dict(mu=0.0), dict(mu=float("nan")), dict(lam=0.0), dict(lam=1.5), dict(lam=1e-60),
+                                 dict(alpha=-1.0), dict(tau=float("inf")), dict(n_itr=0), dict(eps=[5.0, 0.0]),
+                                 "alias"])
+def test_step_refuses_before_it_writes(bad):
+    """A refused ppd_step or ppd_step_vjp leaves every output untouched."""
+    announce(f"ppd_step refuses {bad}")
+    plan = _plan()
+    import ctypes
+
+    import numpy as np
+    import torch
+    from paper_1701_01748_amd import ppd as P
+    M, N, n = plan.M, plan.N, 2
+    f32, c64, c128, f64 = torch.float32, torch.complex64, torch.complex128, torch.float64
+    shape = dict(x=(N, f32), xt=(N, f32), v=(M, c64), u=(9 * N, f32), z=(M, c128), y=(M, c64), U=(M, f64), g=(M, c64),
+                 c=(9 * N, f32), a=(N, f32), b=(N, f32), zs=(n * M, c128), x_out=(N, f32), xt_out=(N, f32),
+                 v_out=(M, c64), u_out=(9 * N, f32), z_out=(M, c128))
+    t = {k: torch.full((m,), 0.5, dtype=dt, device="cuda") for k, (m, dt) in shape.items()}
+    prm = dict(eps=[5.0, 5.0], tau=0.3, eta=1e-4, zeta=1.0, lam=1.0, alpha=1e-4, mu=1.0, n_itr=n)
+    if bad != "alias":
+        prm.update(bad)
+    e = np.asarray(prm["eps"], np.float64)
+    p = {k: P._ptr(v) for k, v in t.items()}
+    if bad == "alias":
+        p["z_out"] = p["z"]
+    args = P.StepArgs(*(p[k] for k in ("x", "xt", "v", "u", "z", "y", "U")),
+                      e.ctypes.data_as(ctypes.POINTER(ctypes.c_double)),
+                      *(prm[k] for k in ("tau", "eta", "zeta", "lam", "alpha", "mu", "n_itr")), 0,
+                      *(p[k] for k in ("g", "c", "a", "b", "zs", "x_out", "xt_out", "v_out", "u_out", "z_out")))
+    assert P.lib().ppd_step(plan.handle, ctypes.byref(args)) == P.PPD_EINVAL
+    want = dict(g_x=(N, f32), g_xt=(N, f32), g_v=(M, c64), g_u=(9 * N, f32), g_z=(M, c128), g_y=(M, c64),
+                g_a=(N, f32), g_b=(N, f32), g_g=(M, c64), g_c=(9 * N, f32), t_v=(M, c64), t_u=(9 * N, f32))
+    q = {k: torch.full((m,), 0.5, dtype=dt, device="cuda") for k, (m, dt) in want.items()}
+    gz = q["g_z"] if bad == "alias" else t["z"]
+    grads = P.StepGrads(*(P._ptr(t[k]) for k in ("x", "xt", "v", "u")), P._ptr(gz), *(P._ptr(v) for v in q.values()))
+    assert P.lib().ppd_step_vjp(plan.handle, ctypes.byref(args), ctypes.byref(grads)) == P.PPD_EINVAL
+    torch.cuda.synchronize()
+    for k, v in {**t, **q}.items():
+        assert bool((v == 0.5).all()), k
