@@ -467,7 +467,6 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
     for (int k = 0; k < MAX_XCD; ++k) longest = std::max(longest, sp.off[k + 1] - sp.off[k]);
     sp.launch = std::max(1, longest) * MAX_XCD;
   }
-  p->n_tile_launch = ((ntiles + MAX_XCD - 1) / MAX_XCD) * MAX_XCD;
   p->items_host = items;
   p->segs_host = segs;
   p->bseg_off.assign(p->d + 1, 0);
@@ -597,7 +596,7 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   A(dalloc(p, &p->pa_glast, p->d));
   A(dalloc(p, &p->pa_part, 4 * size_t(p->pa_groups) * PA_MAXB));
   A(dalloc(p, &p->pa_sync, PA_SYNC_WORDS));
-  A(dalloc(p, &p->part, 2 * size_t(p->n_segs)));
+  A(dalloc(p, &p->part, p->n_segs));
   A(dalloc(p, &p->rpart, p->n_segs));
   A(dalloc(p, &p->eps_d, p->d));
   A(dalloc(p, &p->ppart, size_t(p->ny) * 4));

@@ -206,7 +206,7 @@ struct ppd_plan {
   std::vector<int32_t> bseg_off;           // [d+1] into bseg_ids
   int n_items = 0, n_segs = 0;
   ppd::XcdSplit split1{};
-  int n_tiles = 0, n_tile_launch = 0;
+  int n_tiles = 0;
 
   // device: coverage and plan tables
   float* wu = nullptr;
@@ -262,7 +262,7 @@ struct ppd_plan {
   uint32_t* pa_sync = nullptr;             // [PA_SYNC_WORDS] exit count, give-up flags, solves by one workgroup
   bool last_paired = false;                // forms of the last ppd_iterate call (ppd_plan_get_forms)
   bool last_one_launch = false;
-  double* part = nullptr;                  // [2][n_segs] block-norm partials
+  double* part = nullptr;                  // [n_segs] block-norm partials
   double* rpart = nullptr;                 // [n_segs] residual partials
   double* eps_d = nullptr;                 // [d]
   std::vector<double> eps_cache;
