@@ -78,7 +78,7 @@ def measured_traffic(kind: str, workload: str, tile: int, chunk: int):
 
 
 # kernel kind -> the kernel's name in a rocprofv3 summary (fused iteration at 512^2, 8 x 8 tiles)
-KIND_KERNEL = {"degrid": "k_degrid<8, 1, 1>", "grid": "k_grid_mfma<true, 1>", "fold": "k_fold8",
+KIND_KERNEL = {"degrid": "k_degrid<8, 1, 1>", "grid": "k_grid_mfma<true, 1, false>", "fold": "k_fold8",
                "fft_rows_fwd": "k_fft_rows_fwd<1024>", "fft_cols_fwd": "k_fft_cols_fwd<1024>",
                "fft_cols_inv": "k_fft_cols_inv<1024>", "fft_rows_inv": "k_fft_rows_inv<1024, true>"}
 
