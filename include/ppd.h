@@ -246,7 +246,7 @@ typedef struct {
 
 #define PPD_PROX_FB    0   /* prox^U_h by n_itr Algorithm 2 iterations        */
 #define PPD_PROX_EXACT 1   /* prox^U_h exactly (ppd_prox_metric, n_newton
-                              Newton steps); fused form only                  */
+                              Newton steps at most); fused form only          */
 
 #define PPD_PERSIST_AUTO 0
 #define PPD_PERSIST_OFF  1
@@ -269,7 +269,8 @@ typedef struct {
   const float* W;                  /* optional [9][ny][nx] re-weights (Algorithm 1),
                                       NULL = identity                          */
   int32_t prox;                    /* PPD_PROX_* (0 = Algorithm 2)            */
-  int32_t n_newton;                /* Newton steps for PPD_PROX_EXACT (0 -> 12) */
+  int32_t n_newton;                /* most Newton steps for PPD_PROX_EXACT
+                                      (0 -> 12)                                */
   const uint8_t* block_active;     /* optional DEVICE [d] active set D of the
                                       iterations of this call (randomised
                                       Algorithm 3): block j's v_j and z_j
@@ -294,12 +295,15 @@ typedef struct {
                                       beside it and that waits itself, such
                                       as another plan's persistent launch,
                                       can make a wait give up);
-                                      PPD_PERSIST_OFF (1): one launch pair
-                                      per step.  PPD_PROX_EXACT: its Newton
+                                      PPD_PERSIST_OFF (1): one launch per
+                                      step and one for the last factors.
+                                      PPD_PROX_EXACT: its Newton
                                       steps run as one launch when the points
                                       fit a quarter of the device (about 0.8M
-                                      visibilities) and span blocks as above,
-                                      or with PPD_PERSIST_OFF one launch each */
+                                      visibilities) and span blocks as above
+                                      (a block then ends when a step moves nu
+                                      by 2^-50 of itself or less); else, or
+                                      with PPD_PERSIST_OFF, one launch each    */
   int32_t spin_limit;              /* polls of one wait of the persistent
                                       launch before it gives up (0: 2^13,
                                       2 ms): every workgroup then finishes and

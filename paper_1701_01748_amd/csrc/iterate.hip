@@ -247,9 +247,10 @@ int sara_path(ppd_plan* p, const IterCtx& c) {
 }
 
 // Whether an iteration is one chain of launches, each of the data path's with
-// one of SARA's in its grid where there is one left: for problems so small that a launch of either
-// leaves the chip mostly empty (PAIR_ITEMS).  Eager launches under the per-kernel timers stay
-// separate; captured ones are never timed, so there the timers decide nothing.
+// one of SARA's in its grid where there is one left: for problems so small that
+// a launch of either leaves the chip mostly empty (PAIR_ITEMS).  Eager launches
+// under the per-kernel timers stay separate; captured ones are never timed, so
+// there the timers decide nothing.
 bool can_pair(const ppd_plan* p, const IterCtx& c, bool graph) {
   const bool middle = c.prox == PPD_PROX_EXACT || c.dual.n_itr > 1;
   const int most = graph && middle ? PAIR_ITEMS_MIDDLE : PAIR_ITEMS;
