@@ -133,8 +133,9 @@ __global__ void k_vis_mul_U(float2* __restrict__ y, const double* __restrict__ U
   }
 }
 
-// The segments' squared residual norms added up (one workgroup, fixed order):
-// *acc (+)= their sum, *loss = *acc.
+// The items' squared residual norms added up (one workgroup, fixed order):
+// *acc (+)= their sum, *loss = *acc.  One workgroup reads about 60 GB/s: 2 us
+// for the 13k items at 512^2, 1.3M points, 15 for 112k at 2048^2.
 __global__ __launch_bounds__(STAT_THREADS) void k_fidelity(const double* __restrict__ rpart, int n, int add,
                                                            double* __restrict__ acc, float* __restrict__ loss) {
   __shared__ double red[STAT_THREADS / 64];
@@ -565,7 +566,7 @@ extern "C" int ppd_fidelity(ppd_plan* p, const float* x, const float* y, float* 
   if (!p || !x || !y || !r || !acc || !loss) return fail(PPD_EINVAL, "ppd_fidelity: NULL argument");
   PPD_TRY(fft_forward(p, x));
   PPD_TRY(degrid_residual(p, reinterpret_cast<const float2*>(y), reinterpret_cast<float2*>(r)));
-  hipLaunchKernelGGL(k_fidelity, dim3(1), dim3(STAT_THREADS), 0, p->stream, p->rpart, p->n_segs, add, acc, loss);
+  hipLaunchKernelGGL(k_fidelity, dim3(1), dim3(STAT_THREADS), 0, p->stream, p->rpart, p->n_items, add, acc, loss);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }

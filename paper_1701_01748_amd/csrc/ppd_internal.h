@@ -263,7 +263,7 @@ struct ppd_plan {
   bool last_paired = false;                // forms of the last ppd_iterate call (ppd_plan_get_forms)
   bool last_one_launch = false;
   double* part = nullptr;                  // [n_segs] block-norm partials
-  double* rpart = nullptr;                 // [n_segs] residual partials
+  double* rpart = nullptr;                 // [n_segs] residual partials (per item in the fidelity)
   double* eps_d = nullptr;                 // [d]
   std::vector<double> eps_cache;
   double* ppart = nullptr;                 // [ny][4] primal statistics partials
@@ -350,7 +350,7 @@ int fold_grid(ppd_plan* p, const SaraJob* with = nullptr);     // gscratch -> gr
 
 // grid_f -> out, in plan order, or with uperm (plan -> caller) in the caller's
 int degrid_plain(ppd_plan* p, float2* out, const int32_t* uperm = nullptr);
-// grid_f -> Theta G a - y (plan order), squared norms per segment in rpart
+// grid_f -> Theta G a - y (plan order), squared norms per item in rpart
 int degrid_residual(ppd_plan* p, const float2* y, float2* out);
 struct DualArgs {
   const float2* y; const double* U; float2* v; double2* z;
