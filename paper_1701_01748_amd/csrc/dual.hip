@@ -402,7 +402,7 @@ __global__ __launch_bounds__(PA_THREADS) void k_alg2_persistent(PaArgs a) {
 // nu = 0 climbs to the root without overshooting; g'(nu) = S3 / r^3 with
 // S3 = sum a^2 / (U + nu)^3.  bfac[j].x carries nu between the passes.
 
-// A pass runs over chunks of consecutive plan-order points (sec_chunk) inside
+// A pass runs over chunks of consecutive plan-order points (newton_chunk) inside
 // one block (blocks are contiguous in plan order).  The first pass forms
 // a^2 = U^2 |w - y|^2 and keeps (a^2, U) per point, the later ones read only
 // that (16 bytes per point); each workgroup writes its chunk's S2, S3 at the
@@ -946,7 +946,7 @@ int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* 
   if (persistent && p->sec_ok) return secular_persistent(p, v, ga, y, U, n_newton, spin_limit);
   // pass s writes its partials to buffer s & 1 and (s >= 1) its nu to
   // nu buffer s & 1
-  const int nc = p->n_sec_chunks;
+  const int nc = p->n_nw_chunks;
   double* part[2] = {p->sec_part, p->sec_part + 2 * nc};
   double* nub[2] = {p->sec_nu, p->sec_nu + p->d};
   for (int s = 0; s < n_newton; ++s) {
@@ -958,11 +958,11 @@ int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* 
     int slot;
     PPD_TRY(timer_begin(p, KK_SUBITER, &slot));
     if (s == 0)
-      hipLaunchKernelGGL(k_sec_chunk<true>, dim3(nc), dim3(SEC_THREADS), 0, p->stream, p->sec_cstart, p->sec_cblock,
-                         p->sec_coff, p->eps_d, w, v, ga, y, U, p->qbuf, nullptr, nullptr, nullptr, nullptr, p2, p3);
+      hipLaunchKernelGGL(k_sec_chunk<true>, dim3(nc), dim3(SEC_THREADS), 0, p->stream, p->nw_cstart, p->nw_cblock,
+                         p->nw_coff, p->eps_d, w, v, ga, y, U, p->qbuf, nullptr, nullptr, nullptr, nullptr, p2, p3);
     else
-      hipLaunchKernelGGL(k_sec_chunk<false>, dim3(nc), dim3(SEC_THREADS), 0, p->stream, p->sec_cstart,
-                         p->sec_cblock, p->sec_coff, p->eps_d, w, v, ga, y, U, p->qbuf, q2, q3, pnu, nub[s & 1], p2,
+      hipLaunchKernelGGL(k_sec_chunk<false>, dim3(nc), dim3(SEC_THREADS), 0, p->stream, p->nw_cstart,
+                         p->nw_cblock, p->nw_coff, p->eps_d, w, v, ga, y, U, p->qbuf, q2, q3, pnu, nub[s & 1], p2,
                          p3);
     PPD_HIP(hipGetLastError());
     PPD_TRY(timer_end(p, slot));
@@ -971,7 +971,7 @@ int secular_solve(ppd_plan* p, const double2* w, const float2* v, const float2* 
   int slot;
   PPD_TRY(timer_begin(p, KK_MISC, &slot));
   hipLaunchKernelGGL(k_sec_update, dim3(p->d), dim3(SEC_THREADS), 0, p->stream, part[last & 1],
-                     part[last & 1] + nc, p->sec_coff, p->eps_d, last >= 1 ? nub[last & 1] : nullptr, p->bfac);
+                     part[last & 1] + nc, p->nw_coff, p->eps_d, last >= 1 ? nub[last & 1] : nullptr, p->bfac);
   PPD_HIP(hipGetLastError());
   return timer_end(p, slot);
 }

@@ -509,17 +509,21 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   }
 
   // chunks of the passes over plan-order points, one block each
-  const int64_t chunk_len = sec_chunk(M);
-  std::vector<int32_t> cstart, cblock, coff(p->d + 1, 0);
-  for (int j = 0; j < p->d; ++j) {
-    coff[j] = int32_t(cblock.size());
-    for (int64_t s0 = p->block_off[j]; s0 < p->block_off[j + 1]; s0 += chunk_len) {
-      cstart.push_back(int32_t(s0));
-      cblock.push_back(j);
+  std::vector<int32_t> cstart, cblock, coff, nw_cstart, nw_cblock, nw_coff;
+  auto cut = [&](int64_t len, std::vector<int32_t>& start, std::vector<int32_t>& block, std::vector<int32_t>& off) {
+    for (int j = 0; j < p->d; ++j) {
+      off.push_back(int32_t(block.size()));
+      for (int64_t s0 = p->block_off[j]; s0 < p->block_off[j + 1]; s0 += len) {
+        start.push_back(int32_t(s0));
+        block.push_back(j);
+      }
     }
-  }
-  coff[p->d] = int32_t(cblock.size());
-  cstart.push_back(int32_t(M));
+    off.push_back(int32_t(block.size()));
+    start.push_back(int32_t(M));
+  };
+  cut(sec_chunk(M), cstart, cblock, coff);
+  cut(newton_chunk(M), nw_cstart, nw_cblock, nw_coff);
+  p->n_nw_chunks = int(nw_cblock.size());
   for (int j = 0; j < p->d; ++j) p->own_sums = p->own_sums && coff[j + 1] - coff[j] <= OWN_SUM_CHUNKS;
   p->n_sec_chunks = int(cblock.size());
 
@@ -587,7 +591,10 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   A(dalloc(p, &p->sec_cstart, cstart.size()));
   A(dalloc(p, &p->sec_cblock, cblock.size()));
   A(dalloc(p, &p->sec_coff, coff.size()));
-  A(dalloc(p, &p->sec_part, 4 * cblock.size()));
+  A(dalloc(p, &p->nw_cstart, nw_cstart.size()));
+  A(dalloc(p, &p->nw_cblock, nw_cblock.size()));
+  A(dalloc(p, &p->nw_coff, nw_coff.size()));
+  A(dalloc(p, &p->sec_part, 4 * std::max(cblock.size(), nw_cblock.size())));
   A(dalloc(p, &p->sec_nu, 2 * size_t(p->d)));
   A(dalloc(p, &p->du_blk, p->d));
   A(dalloc(p, &p->voff_d, p->d + 1));
@@ -643,6 +650,9 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   up(p->sec_cstart, cstart.data(), 4 * cstart.size());
   up(p->sec_cblock, cblock.data(), 4 * cblock.size());
   up(p->sec_coff, coff.data(), 4 * coff.size());
+  up(p->nw_cstart, nw_cstart.data(), 4 * nw_cstart.size());
+  up(p->nw_cblock, nw_cblock.data(), 4 * nw_cblock.size());
+  up(p->nw_coff, nw_coff.data(), 4 * nw_coff.size());
   up(p->bseg_ids, bids.data(), 4 * p->n_segs);
   up(p->bseg_off_d, p->bseg_off.data(), 4 * (p->d + 1));
   up(p->vis_block, vblk.data(), 4 * M);

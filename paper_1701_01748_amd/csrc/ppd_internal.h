@@ -35,11 +35,17 @@ constexpr int KB_NC = KB_DEG + 1; // coefficients per tap
 constexpr int N_BASES = 9;        // Dirac + db1..db8
 constexpr int FILT_STRIDE = 16;   // max Daubechies taps (db8)
 // Points per workgroup of the passes over plan-order chunks of one block
-// (Algorithm 2 steps, Newton steps, the differentiable dual update): fewer
+// (Algorithm 2 steps, the differentiable dual update): fewer
 // points where the chip would be left empty, and few enough chunks for every
 // workgroup to add up its block's partials itself.
 inline int64_t sec_chunk(int64_t M) { return M <= (int64_t(1) << 20) ? 512 : M <= (int64_t(1) << 22) ? 1024 : 2048; }
-// Chunks of a block up to which the workgroups do that (each reads all the
+// The same for the launches of a Newton step each, which read 16 bytes a point
+// instead of 40 to 72 and two sums of every chunk, so that with few blocks the
+// reading of the partials weighs more.  A 12-step solve at 512, 1024 and 2048
+// points, us: 250000 points in one block 61, 54, 58; 500000 79, 64, 65; a million
+// 121, 88, 80, in 16 blocks 86, 78, 75; 4 million 773, 336, 236.
+inline int64_t newton_chunk(int64_t M) { return M <= (int64_t(1) << 19) ? 1024 : 2048; }
+// Chunks of a block up to which the workgroups of a step do that (each reads all the
 // block's partials: 32 KB, 16 a thread); beyond it a launch of one workgroup
 // per block forms the block's sum.
 constexpr int OWN_SUM_CHUNKS = 4096;
@@ -238,14 +244,19 @@ struct ppd_plan {
   double2* wbuf = nullptr;                 // [M] complex128 w (plain form)
   float2* gabuf = nullptr;                 // [M] complex64 Theta G a (fused form; w is rebuilt from it)
   double2* qbuf = nullptr;                 // [M] complex128 (plain form; (a^2, U) of the Newton passes)
-  // Newton passes of the exact prox: chunks of consecutive plan-order
-  // visibilities inside one block
+  // Algorithm 2 steps and the differentiable dual update: chunks of consecutive
+  // plan-order visibilities inside one block
   int n_sec_chunks = 0;
   bool own_sums = true;                    // no block has more than OWN_SUM_CHUNKS chunks
   int32_t* sec_cstart = nullptr;           // [n_sec_chunks + 1] first visibility of each chunk
   int32_t* sec_cblock = nullptr;           // [n_sec_chunks] block of each chunk
   int32_t* sec_coff = nullptr;             // [d + 1] chunks of block j: [sec_coff[j], sec_coff[j+1])
-  double* sec_part = nullptr;              // [2][2][n_sec_chunks] S2, S3 partials, two passes
+  double* sec_part = nullptr;              // [2][2][n_sec_chunks] partials: two sums, two passes
+  // the same for the Newton passes, whose chunks are as long or longer
+  int n_nw_chunks = 0;
+  int32_t* nw_cstart = nullptr;
+  int32_t* nw_cblock = nullptr;
+  int32_t* nw_coff = nullptr;
   double* sec_nu = nullptr;                // [2][d] nu of the last two Newton passes
   double4* du_blk = nullptr;               // [d] block terms of the differentiable dual update
   // persistent Algorithm 2 middle steps (one launch, state in registers):
