@@ -1184,10 +1184,26 @@ int permute(ppd_plan* p, int direction, const void* in, void* out, int elem_byte
 
 using namespace ppd;
 
+// Whether the caller's order takes a permutation pass of its own.  A tile's
+// points come from up to d blocks, a cache line of each per-visibility array from
+// each block; neighbouring tiles use the lines again while they are in an XCD's
+// 4 MB of L2.  With more than 8192 blocks the operator's arrays, the permutation
+// and the scattered values no longer fit.  Phi and Phi^H through the permutation
+// and with the pass, us: 512^2, 1.3M points in 8192 blocks 46 and 47, 73 and 74
+// (sorted by radius), in 16384 55 and 50, 81 and 78, interleaved 76 and 63, 106 and
+// 93; 1024^2, 3M in 32768 142 and 111, 198 and 173.  At 600000 points 35 and 36, 53
+// and 53, interleaved 44 and 39, 64 and 59; fewer points than that are so few a
+// block that the lines stay: 250000 in 16384 26 and 28, 40 and 41.
+static bool permutes_apart(const ppd_plan* p) { return p->d > 8192 && p->M > (int64_t(1) << 19); }
+
 extern "C" int ppd_phi(ppd_plan* p, const float* x, float* y, int order) {
   if (!p || !x || !y) return fail(PPD_EINVAL, "ppd_phi: NULL argument");
   if (order != PPD_ORDER_PLAN && order != PPD_ORDER_USER) return fail(PPD_EINVAL, "ppd_phi: bad order");
   PPD_TRY(fft_forward(p, x));
+  if (order == PPD_ORDER_USER && permutes_apart(p)) {
+    PPD_TRY(degrid_plain(p, p->ybuf));
+    return permute(p, PPD_PLAN_TO_USER, p->ybuf, y, sizeof(float2));
+  }
   // in the caller's order the degridding stores through the permutation
   return degrid_plain(p, reinterpret_cast<float2*>(y), order == PPD_ORDER_USER ? p->perm : nullptr);
 }
@@ -1195,6 +1211,11 @@ extern "C" int ppd_phi(ppd_plan* p, const float* x, float* y, int order) {
 extern "C" int ppd_phit(ppd_plan* p, const float* y, float* x, int order) {
   if (!p || !x || !y) return fail(PPD_EINVAL, "ppd_phit: NULL argument");
   if (order != PPD_ORDER_PLAN && order != PPD_ORDER_USER) return fail(PPD_EINVAL, "ppd_phit: bad order");
-  PPD_TRY(grid_plain(p, reinterpret_cast<const float2*>(y), order == PPD_ORDER_USER ? p->perm : nullptr));
+  if (order == PPD_ORDER_USER && permutes_apart(p)) {
+    PPD_TRY(permute(p, PPD_USER_TO_PLAN, y, p->ybuf, sizeof(float2)));
+    PPD_TRY(grid_plain(p, p->ybuf));
+  } else {
+    PPD_TRY(grid_plain(p, reinterpret_cast<const float2*>(y), order == PPD_ORDER_USER ? p->perm : nullptr));
+  }
   return fft_adjoint(p, x);
 }
