@@ -256,8 +256,8 @@ bool can_pair(const ppd_plan* p, const IterCtx& c, bool graph) {
   const bool middle = c.prox == PPD_PROX_EXACT || c.dual.n_itr > 1;
   const int most = graph && middle ? PAIR_ITEMS_MIDDLE : PAIR_ITEMS;
   static_assert(PAIR_ITEMS <= SHARE_ITEMS, "the paired launches share items");
-  return c.form == PPD_FORM_FUSED && p->T == 8 && p->n_items <= most && p->Ky <= PAIR_MAX_KY && sara_pairs(p) &&
-         (graph || !p->timing);
+  return c.form == PPD_FORM_FUSED && p->T == 8 && p->n_items <= most && p->d <= PAIR_BLOCKS && p->Ky <= PAIR_MAX_KY &&
+         sara_pairs(p) && (graph || !p->timing);
 }
 
 // The launches with their riders; analysis and synthesis levels that find no

@@ -97,6 +97,13 @@ constexpr int PAIR_ITEMS = 2048;
 // 50 us at 128^2 (471 items), 55.5 and 59 at 128^2 (1043), 58.5 and 68 at 256^2
 // (1777); exact 59 and 56 at 64^2 (140), 61 and 63 at 128^2 (502).
 constexpr int PAIR_ITEMS_MIDDLE = 480;
+// Block count up to which they do: a block is a workgroup of 1024 threads in the
+// launch of the block factors, and beside an analysis level's registers and LDS
+// few of those are resident.  Per replayed iteration in pairs and on two
+// streams, in 1024 and in 4096 blocks sorted by radius: 65536 points at 256^2 81
+// and 56 us, 119 and 77 (the factors alone, of one block a point, 509 and 266);
+// 20000 at 128^2 51 and 52, 76 and 67; 4096 at 64^2 50 and 53, 73 and 67.
+constexpr int PAIR_BLOCKS = 1024;
 // Largest 2 ny of the launches that a SARA level rides in (its kernels exist
 // for the lengths up to there).
 constexpr int PAIR_MAX_KY = 1024;
