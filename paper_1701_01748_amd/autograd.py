@@ -19,9 +19,9 @@ memory stays at one iteration's activations.
 A whole iteration, and the data fidelity of all channels, are one autograd
 node each: composed of the pieces' nodes and torch operations the calls are
 bound by the host, whose speed differs from process to process.  Medians of
-separate runs: an iteration at 256^2, 65536 points, forward and backward 491 to
-533 us, as one node 377 to 427; the fidelity of four channels of 250000 points
-at 512^2 with its gradient 807 to 855 us, as one node 230 to 269.
+separate runs: an iteration at 256^2, 65536 points, forward and backward 412 to
+533 us, as one node 249 to 427; the fidelity of four channels of 250000 points
+at 512^2 with its gradient 741 to 855 us, as one node 211 to 269.
 """
 from __future__ import annotations
 
