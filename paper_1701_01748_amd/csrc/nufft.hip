@@ -811,25 +811,59 @@ __global__ __launch_bounds__(256) void k_grid_synth(
 // loads overlap.
 constexpr int FOLD_CELLS = 256;
 
+// Sums of the regions of up to FOLD_GROUP consecutive items of a tile, into the
+// first one's: a dense centre puts thousands of items into a few tiles, and a
+// fold's threads would add them up one after the other.  Bound by the loads'
+// latency, all of a thread's at once.  Phi^H at 512^2, 1.3M points normal about
+// the centre, with and without groups, us: standard deviation 0.06 rad (1359
+// items in a tile) 52 and 129, 0.02 rad (5858) 56 and 232; tiles of 16 at 0.06
+// rad (993) 88 and 227, of 32 (1562) 123 and 304, of 64 (1575) 428 and 601.
+// Cells are independent, so the sums take their first region's place.
+template <int T>
+__global__ __launch_bounds__(FOLD_CELLS) void k_fold_groups(float2* __restrict__ scratch,
+                                                            const int2* __restrict__ groups) {
+  constexpr int R2 = (T + 7) * (T + 7), PARTS = (R2 + FOLD_CELLS - 1) / FOLD_CELLS;
+  const int g = blockIdx.x / PARTS, c = (blockIdx.x - g * PARTS) * FOLD_CELLS + threadIdx.x;
+  if (c >= R2) return;
+  const int2 e = groups[g];
+  float2* r = scratch + size_t(e.x) * R2 + c;
+  float2 v[FOLD_GROUP];
+#pragma unroll
+  for (int k = 0; k < FOLD_GROUP; ++k) v[k] = k < e.y ? r[k * R2] : make_float2(0.f, 0.f);
+#pragma unroll
+  for (int w = FOLD_GROUP / 2; w > 0; w >>= 1)
+#pragma unroll
+    for (int k = 0; k < w; ++k) v[k] = make_float2(v[k].x + v[k + w].x, v[k].y + v[k + w].y);
+  r[0] = v[0];
+}
+
+// Items between the regions that a tile of n items is summed from.
+template <bool GROUPED>
+__device__ __forceinline__ int fold_step(int n) {
+  return GROUPED && n > FOLD_GROUP ? FOLD_GROUP : 1;
+}
+
+template <bool GROUPED>
 __device__ __forceinline__ void fold_items(const float2* __restrict__ scratch, int R2, int off, int i0,
                                            int i1, float& sx, float& sy) {
+  const int st = fold_step<GROUPED>(i1 - i0);
   int i = i0;
-  for (; i + 4 <= i1; i += 4) {
+  for (; i + 3 * st < i1; i += 4 * st) {
     const float2 g0 = scratch[size_t(i) * R2 + off];
-    const float2 g1 = scratch[size_t(i + 1) * R2 + off];
-    const float2 g2 = scratch[size_t(i + 2) * R2 + off];
-    const float2 g3 = scratch[size_t(i + 3) * R2 + off];
+    const float2 g1 = scratch[size_t(i + st) * R2 + off];
+    const float2 g2 = scratch[size_t(i + 2 * st) * R2 + off];
+    const float2 g3 = scratch[size_t(i + 3 * st) * R2 + off];
     sx += (g0.x + g1.x) + (g2.x + g3.x);
     sy += (g0.y + g1.y) + (g2.y + g3.y);
   }
-  for (; i < i1; ++i) {
+  for (; i < i1; i += st) {
     const float2 g = scratch[size_t(i) * R2 + off];
     sx += g.x;
     sy += g.y;
   }
 }
 
-template <int T>
+template <int T, bool GROUPED>
 __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ scratch,
                                                      const int32_t* __restrict__ tio, int tiles_x,
                                                      int tiles_y, int PW, int Ky, float2* __restrict__ grid) {
@@ -845,18 +879,18 @@ __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ 
   const int c = part * FOLD_CELLS + threadIdx.x;
   const int a = c / T, b = c - a * T;
   float sx = 0.f, sy = 0.f;
-  fold_items(scratch, R * R, a * R + b, tio[t], tio[t + 1], sx, sy);
-  if (b < 7) fold_items(scratch, R * R, a * R + T + b, tio[tl], tio[tl + 1], sx, sy);
+  fold_items<GROUPED>(scratch, R * R, a * R + b, tio[t], tio[t + 1], sx, sy);
+  if (b < 7) fold_items<GROUPED>(scratch, R * R, a * R + T + b, tio[tl], tio[tl + 1], sx, sy);
   if (a < 7) {
-    fold_items(scratch, R * R, (T + a) * R + b, tio[tu], tio[tu + 1], sx, sy);
-    if (b < 7) fold_items(scratch, R * R, (T + a) * R + T + b, tio[tul], tio[tul + 1], sx, sy);
+    fold_items<GROUPED>(scratch, R * R, (T + a) * R + b, tio[tu], tio[tu + 1], sx, sy);
+    if (b < 7) fold_items<GROUPED>(scratch, R * R, (T + a) * R + T + b, tio[tul], tio[tul + 1], sx, sy);
   }
   if (tx * T + b < PW) grid[grid_index(tx * T + b, ty * T + a, Ky)] = make_float2(sx, sy);
 }
 
 // What one cell receives from its four source tiles: the regions i0[q],
-// i0[q] + STRIDE, .. < i1[q] (wave-uniform) at off[q] where ok[q], four at a
-// time and the rest one by one.  All that remains of a source after whole fours
+// i0[q] + STRIDE st[q], .. < i1[q] (wave-uniform; st: fold_step) at off[q] where
+// ok[q], four at a time and the rest one by one.  All that remains of a source after whole fours
 // is loaded before anything is added: most tiles have one to three regions, and
 // their four sources together then cost one load's latency, not four to twelve.
 // Bound by that latency at small sizes and by the regions' bytes at large ones:
@@ -864,28 +898,31 @@ __global__ __launch_bounds__(FOLD_CELLS) void k_fold(const float2* __restrict__ 
 // beside SARA 117 -> 76 (236 MB of regions in, 67 MB out).  Regions stored as
 // four 512-byte quadrants, so that both sides move whole lines, were no faster
 // (10.0 and 78), nor eight loads in flight for the heavy tiles.
-template <int STRIDE>
+template <int STRIDE, bool GROUPED>
 __device__ __forceinline__ float2 fold_sources(const float2* __restrict__ scratch, int R2, const int (&off)[4],
-                                               const bool (&ok)[4], const int (&i0)[4], const int (&i1)[4]) {
+                                               const bool (&ok)[4], const int (&i0)[4], const int (&i1)[4],
+                                               const int (&st)[4]) {
   float2 g[4][3];
   int n[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    n[q] = max(0, (i1[q] - i0[q] + STRIDE - 1) / STRIDE);
-    const int i = i0[q] + STRIDE * (n[q] & ~3);
+    const int step = GROUPED ? STRIDE * st[q] : STRIDE;
+    n[q] = max(0, (i1[q] - i0[q] + step - 1) / step);
+    const int i = i0[q] + step * (n[q] & ~3);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       g[q][k] = make_float2(0.f, 0.f);
-      if ((n[q] & 3) > k && ok[q]) g[q][k] = scratch[size_t(i + STRIDE * k) * R2 + off[q]];
+      if ((n[q] & 3) > k && ok[q]) g[q][k] = scratch[size_t(i + step * k) * R2 + off[q]];
     }
   }
   float sx = 0.f, sy = 0.f;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     if (n[q] >= 4 && ok[q]) {
+      const int step = GROUPED ? STRIDE * st[q] : STRIDE;
       for (int k = 0; k + 4 <= n[q]; k += 4) {
-        const float2* r = scratch + size_t(i0[q] + STRIDE * k) * R2 + off[q];
-        const float2 g0 = r[0], g1 = r[STRIDE * R2], g2 = r[2 * STRIDE * R2], g3 = r[3 * STRIDE * R2];
+        const float2* r = scratch + size_t(i0[q] + step * k) * R2 + off[q];
+        const float2 g0 = r[0], g1 = r[step * R2], g2 = r[2 * step * R2], g3 = r[3 * step * R2];
         sx += (g0.x + g1.x) + (g2.x + g3.x);
         sy += (g0.y + g1.y) + (g2.y + g3.y);
       }
@@ -907,6 +944,7 @@ __device__ __forceinline__ float2 fold_sources(const float2* __restrict__ scratc
 // FOLD_HEAVY regions to sum: the dense centre of the coverage), wave w
 // summing every fourth item region of each source tile from the w-th, the
 // four partial sums then added in wave order.
+template <bool GROUPED>
 __device__ __forceinline__ void fold8_block(int block, int nblocks, const float2* __restrict__ scratch,
                                             const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
                                             int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid) {
@@ -923,17 +961,19 @@ __device__ __forceinline__ void fold8_block(int block, int nblocks, const float2
   const int src[4] = {t, ty * tiles_x + lx, uy * tiles_x + tx, uy * tiles_x + lx};
   const int off[4] = {a * R + b, a * R + T + b, (T + a) * R + b, (T + a) * R + T + b};
   const bool ok[4] = {true, b < 7, a < 7, a < 7 && b < 7};
-  int i0[4], i1[4];
+  int i0[4], i1[4], st[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    i0[q] = tio[src[q]] + (heavy ? w : 0);
+    i0[q] = tio[src[q]];
     i1[q] = tio[src[q] + 1];
+    st[q] = fold_step<GROUPED>(i1[q] - i0[q]);
+    i0[q] += heavy ? w * st[q] : 0;
   }
   if (!heavy) {
-    grid[grid_index(tx * T + b, ty * T + a, Ky)] = fold_sources<1>(scratch, R * R, off, ok, i0, i1);
+    grid[grid_index(tx * T + b, ty * T + a, Ky)] = fold_sources<1, GROUPED>(scratch, R * R, off, ok, i0, i1, st);
     return;
   }
-  part[w][c] = fold_sources<4>(scratch, R * R, off, ok, i0, i1);
+  part[w][c] = fold_sources<4, GROUPED>(scratch, R * R, off, ok, i0, i1, st);
   __syncthreads();
   if (w == 0) {
     const float2 p0 = part[0][c], p1 = part[1][c], p2 = part[2][c], p3 = part[3][c];
@@ -945,18 +985,24 @@ __device__ __forceinline__ void fold8_block(int block, int nblocks, const float2
 __global__ __launch_bounds__(256) void k_fold8(const float2* __restrict__ scratch, const int32_t* __restrict__ tio,
                                                 const int4* __restrict__ wgs, int tiles_x, int tiles_y, int Ky,
                                                 float2* __restrict__ grid) {
-  fold8_block(blockIdx.x, gridDim.x, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
+  fold8_block<false>(blockIdx.x, gridDim.x, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
+}
+__global__ __launch_bounds__(256) void k_fold8_grouped(const float2* __restrict__ scratch,
+                                                       const int32_t* __restrict__ tio,
+                                                       const int4* __restrict__ wgs, int tiles_x, int tiles_y, int Ky,
+                                                       float2* __restrict__ grid) {
+  fold8_block<true>(blockIdx.x, gridDim.x, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
 }
 
 // The same after a synthesis launch of SARA in the first workgroups.
-template <int KIND, bool HW>
+template <int KIND, bool HW, bool GROUPED>
 __global__ __launch_bounds__(256) void k_fold8_synth(int nblocks, const float2* __restrict__ scratch,
                                                      const int32_t* __restrict__ tio, const int4* __restrict__ wgs,
                                                      int tiles_x, int tiles_y, int Ky, float2* __restrict__ grid,
                                                      SaraJob j) {
   const int b = int(blockIdx.x) - j.blocks();
   if (b < 0) sara_synth_part<KIND, HW>(j, blockIdx.x);
-  else fold8_block(b, nblocks, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
+  else fold8_block<GROUPED>(b, nblocks, scratch, tio, wgs, tiles_x, tiles_y, Ky, grid);
 }
 
 template <typename E>
@@ -1023,18 +1069,36 @@ int launch_grid(ppd_plan* p, bool dual, const float2* vin, const int32_t* uperm,
   return PPD_OK;
 }
 
+// The sums of the groups, where the plan has any.
+int fold_groups(ppd_plan* p) {
+  if (!p->n_fold_groups) return PPD_OK;
+  auto launch = [&](auto kernel, int T) {
+    const int parts = ((T + 7) * (T + 7) + FOLD_CELLS - 1) / FOLD_CELLS;
+    hipLaunchKernelGGL(kernel, dim3(p->n_fold_groups * parts), dim3(FOLD_CELLS), 0, p->stream, p->gscratch,
+                       reinterpret_cast<const int2*>(p->fold_groups));
+  };
+  switch (p->T) {
+    case 8: launch(k_fold_groups<8>, 8); break;
+    case 16: launch(k_fold_groups<16>, 16); break;
+    case 32: launch(k_fold_groups<32>, 32); break;
+    default: launch(k_fold_groups<64>, 64); break;
+  }
+  PPD_HIP(hipGetLastError());
+  return PPD_OK;
+}
+
 template <int T>
 int launch_fold(ppd_plan* p) {
   const int n = p->n_tiles * ((T * T) / FOLD_CELLS);
   const int nl = ((n + MAX_XCD - 1) / MAX_XCD) * MAX_XCD;
-  hipLaunchKernelGGL(k_fold<T>, dim3(nl), dim3(FOLD_CELLS), 0, p->stream, p->gscratch,
+  hipLaunchKernelGGL((p->n_fold_groups ? k_fold<T, true> : k_fold<T, false>), dim3(nl), dim3(FOLD_CELLS), 0, p->stream, p->gscratch,
                      p->tile_item_off, p->tiles_x, p->tiles_y, p->PW, p->Ky, p->grid_a);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
 }
 
 int launch_fold8(ppd_plan* p) {
-  hipLaunchKernelGGL(k_fold8, dim3(p->n_fold_wg), dim3(256), 0, p->stream, p->gscratch, p->tile_item_off,
+  hipLaunchKernelGGL(p->n_fold_groups ? k_fold8_grouped : k_fold8, dim3(p->n_fold_wg), dim3(256), 0, p->stream, p->gscratch, p->tile_item_off,
                      reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x, p->tiles_y, p->Ky, p->grid_a);
   PPD_HIP(hipGetLastError());
   return PPD_OK;
@@ -1134,18 +1198,27 @@ int grid_dual_exact(ppd_plan* p, const DualArgs& a) {
 
 int fold_grid(ppd_plan* p, const SaraJob* with) {
   if (with) {
+    PPD_TRY(fold_groups(p));
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(p->n_fold_wg + with->blocks()), dim3(256), 0, p->stream, p->n_fold_wg,
                          p->gscratch, p->tile_item_off, reinterpret_cast<const int4*>(p->fold_wg), p->tiles_x,
                          p->tiles_y, p->Ky, p->grid_a, *with);
     };
-    if (with->kind == SARA_IDWT) launch(with->W ? k_fold8_synth<SARA_IDWT, true> : k_fold8_synth<SARA_IDWT, false>);
-    else launch(with->W ? k_fold8_synth<SARA_FINAL, true> : k_fold8_synth<SARA_FINAL, false>);
+    auto choose = [&](auto grouped) {
+      constexpr bool G = decltype(grouped)::value;
+      if (with->kind == SARA_IDWT)
+        launch(with->W ? k_fold8_synth<SARA_IDWT, true, G> : k_fold8_synth<SARA_IDWT, false, G>);
+      else
+        launch(with->W ? k_fold8_synth<SARA_FINAL, true, G> : k_fold8_synth<SARA_FINAL, false, G>);
+    };
+    if (p->n_fold_groups) choose(std::true_type());
+    else choose(std::false_type());
     PPD_HIP(hipGetLastError());
     return PPD_OK;
   }
   int slot;
   PPD_TRY(timer_begin(p, KK_FOLD, &slot));
+  PPD_TRY(fold_groups(p));
   int st;
   switch (p->T) {
     case 8: st = launch_fold8(p); break;

@@ -445,6 +445,16 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
       fold_wg.insert(fold_wg.end(), w.begin(), w.end());
     }
   }
+  std::vector<int32_t> fold_groups;
+  {
+    auto n = [&](int t) { return tile_item_off[t + 1] - tile_item_off[t]; };
+    int most = 0;
+    for (int t = 0; t < ntiles; ++t) most = std::max(most, n(t));
+    if (most > fold_group_from(p->T))
+      for (int t = 0; t < ntiles; ++t)
+        for (int k = 0; n(t) > FOLD_GROUP && k < n(t); k += FOLD_GROUP)
+          fold_groups.insert(fold_groups.end(), {tile_item_off[t] + k, std::min(FOLD_GROUP, n(t) - k)});
+  }
   p->n_items = int(items.size());
   p->n_segs = int(segs.size());
   p->n_tiles = ntiles;
@@ -569,6 +579,8 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   A(dalloc(p, &p->tile_item_off, ntiles + 1));
   A(dalloc(p, &p->fold_wg, fold_wg.size()));
   p->n_fold_wg = int(fold_wg.size() / 4);
+  A(dalloc(p, &p->fold_groups, fold_groups.size()));
+  p->n_fold_groups = int(fold_groups.size() / 2);
   A(dalloc(p, &p->bseg_ids, p->n_segs));
   A(dalloc(p, &p->bseg_off_d, p->d + 1));
   A(dalloc(p, &p->bfac, p->d));
@@ -647,6 +659,7 @@ static int create_plan(ppd_plan** out, const ppd_plan_desc* desc, void* stream, 
   up(p->segs, segs.data(), sizeof(Seg) * p->n_segs);
   up(p->tile_item_off, tile_item_off.data(), 4 * (ntiles + 1));
   up(p->fold_wg, fold_wg.data(), 4 * fold_wg.size());
+  if (!fold_groups.empty()) up(p->fold_groups, fold_groups.data(), 4 * fold_groups.size());
   up(p->sec_cstart, cstart.data(), 4 * cstart.size());
   up(p->sec_cblock, cblock.data(), 4 * cblock.size());
   up(p->sec_coff, coff.data(), 4 * coff.size());

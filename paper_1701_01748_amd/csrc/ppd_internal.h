@@ -79,6 +79,14 @@ constexpr uint64_t PA_EMPTY = 0x7ff8000000000000ull;   // quiet NaN: no partial 
 #define PPD_FOLD_HEAVY 16
 #endif
 constexpr int FOLD_HEAVY = PPD_FOLD_HEAVY;   // item regions above which a tile's fold takes a whole workgroup
+// Where a tile has more items than fold_group_from, every FOLD_GROUP regions of
+// the tiles with more than that are added up in a launch before the fold.  Phi^H
+// without and with it, us: 8 x 8 tiles with up to 94 to 117 items (four waves
+// share a tile there) 26 and 25, 22 and 20, 31 and 34, 53 and 53, with 246 and 297
+// 27 and 19, 39 and 25; larger ones with 25 to 30 items 34 and 34, 37 and 38, 93
+// and 92, with 72 and 78 49 and 37, 56 and 42.
+constexpr int FOLD_GROUP = 16;
+inline int fold_group_from(int T) { return T == 8 ? 128 : 32; }
 // Item count up to which two waves share each item in the 8 x 8 kernels: with
 // fewer waves than the chip holds (4096 at 4 per SIMD), the length of one
 // wave's chain is the kernel's time.  Gridding 10.8 -> 5.4 us at 64^2, 4096
@@ -231,6 +239,8 @@ struct ppd_plan {
   int32_t* tile_item_off = nullptr;        // [n_tiles+1] items of each tile
   int32_t* fold_wg = nullptr;              // [n_fold_wg][4] tiles per 4-wave fold workgroup
   int n_fold_wg = 0;                       // multiple of MAX_XCD
+  int32_t* fold_groups = nullptr;          // [n_fold_groups][2] first item and items of each group
+  int n_fold_groups = 0;                   // 0: no tile has so many items
   int32_t* bseg_ids = nullptr;             // segment ids grouped by block
   int32_t* bseg_off_d = nullptr;           // [d+1]
   float2* gscratch = nullptr;              // [n_items][(T+7)^2] gridding partials
